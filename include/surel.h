@@ -96,8 +96,8 @@ extern "C" {
 #define SUREL_DEV_BAD_SIZES     0x80u  /* a seed's d_set_sizes entry (or the offsets given to a
                                           filling call) do not match its number of rows; that
                                           seed's / query's rows are not written              */
-#define SUREL_DEV_STALL         0x100u /* a bounded wait inside surel_sample_walks_rpe ran out
-                                          (see surel_set_spin_limit), or a bounded probe of a
+#define SUREL_DEV_STALL         0x100u /* a bounded wait inside surel_sample_walks_rpe or inside a
+                                          join of few queries ran out (see surel_set_spin_limit), or a bounded probe of a
                                           hash table of surel_bfs_batches; outputs are
                                           incomplete                                         */
 
@@ -405,7 +405,8 @@ int surel_bfs_batches(surel_ctx* ctx, const int32_t* d_queries, int64_t n_querie
                       int32_t* d_counts);
 
 /* Every wait inside the fused kernel of surel_sample_walks_rpe (a wave waiting for an offset,
- * the offset scan waiting for a row count) and inside surel_prune_rpe (a lane waiting for
+ * the offset scan waiting for a row count), inside the joins of few queries (a workgroup waiting
+ * for the row counts of those before it) and inside surel_prune_rpe (a lane waiting for
  * another to finish writing a hash slot) gives up after `spins` polls, raises
  * SUREL_DEV_STALL and lets the kernel end.  The default (2^22 polls, seconds) is never reached
  * by a healthy run; tests set 0 to see the bounded exit.  Errors: SUREL_E_CTX. */

@@ -16,6 +16,7 @@ struct surel_ctx {
     int n_cu = 0;                 // compute units of the device
     uint32_t spin_limit = 1u << 22;  // bound of every wait inside the fused walk + RPE kernel
     uint32_t* d_err = nullptr;    // sticky device error word
+    void* d_small = nullptr;      // words of the launches that lay small outputs out themselves
     int64_t* h_pinned = nullptr;  // 2 x int64 of pinned host memory for small read-backs
     void* d_ws = nullptr;         // grow-only workspace: row counts + scan partials
     size_t ws_bytes = 0;
@@ -225,6 +226,8 @@ int surel_create(surel_ctx** out, int device, void* hip_stream) {
                                      device) == hipSuccess && ctx->n_cu > 0;
     ok = ok && hipMalloc(reinterpret_cast<void**>(&ctx->d_err), 256) == hipSuccess;
     ok = ok && hipMemsetAsync(ctx->d_err, 0, 256, ctx->stream) == hipSuccess;
+    ok = ok && hipMalloc(&ctx->d_small, surel::small_scan_bytes()) == hipSuccess;
+    ok = ok && hipMemsetAsync(ctx->d_small, 0, surel::small_scan_bytes(), ctx->stream) == hipSuccess;
     ok = ok && hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 2 * sizeof(int64_t),
                              hipHostMallocDefault) == hipSuccess;
     ok = ok && hipStreamSynchronize(ctx->stream) == hipSuccess;
@@ -233,6 +236,7 @@ int surel_create(surel_ctx** out, int device, void* hip_stream) {
          ctx->d_scratch != nullptr;
     if (!ok) {
         if (ctx->d_err) (void)hipFree(ctx->d_err);
+        if (ctx->d_small) (void)hipFree(ctx->d_small);
         if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
         delete ctx;
         (void)hipGetLastError();
@@ -257,6 +261,7 @@ void surel_destroy(surel_ctx* ctx) {
     if (ctx->d_prune) (void)hipFree(ctx->d_prune);
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
     if (ctx->d_err) (void)hipFree(ctx->d_err);
+    if (ctx->d_small) (void)hipFree(ctx->d_small);
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
     delete ctx;
 }
@@ -314,12 +319,21 @@ static int check_rpe_args(int32_t n_nodes, int64_t n_seeds, int32_t M, int32_t m
 
 // Waits for the stream and reports the row total that a scan or a scanner wave left at off[n]
 // (-1: the kernel gave up on a bounded wait before it got there).
+static int judge_total(bool has_outputs, int64_t cap_rows, int64_t rows) {
+    if (rows < 0) return SUREL_E_DEVICE;
+    if (has_outputs && rows > cap_rows) return SUREL_E_CAPACITY;
+    return SUREL_OK;
+}
 static int report_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, bool has_outputs,
                         int64_t cap_rows, int64_t* h_rows) {
     if (int rc = read_total(ctx, d_off, n, h_rows)) return rc;
-    if (*h_rows < 0) return SUREL_E_DEVICE;
-    if (has_outputs && *h_rows > cap_rows) return SUREL_E_CAPACITY;
-    return SUREL_OK;
+    return judge_total(has_outputs, cap_rows, *h_rows);
+}
+// The same where the launch has put the total into the pinned word itself.
+static int report_pinned_total(surel_ctx* ctx, bool has_outputs, int64_t cap_rows, int64_t* h_rows) {
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+    *h_rows = ctx->h_pinned[0];
+    return judge_total(has_outputs, cap_rows, *h_rows);
 }
 
 // Phase A of the RPE builder: per-seed set sizes (the caller's, or counted here) -> rpe_off.
@@ -597,6 +611,29 @@ static int join_rows(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d_
     return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
 }
 
+// The whole join of a short query list in one launch (no scratch of its own).
+static bool join_is_small(const surel_ctx* ctx, int32_t max_set, int32_t m, int64_t n_queries,
+                          int32_t k) {
+    return surel::join_is_small(ctx->n_cu, ctx->max_lds_bytes, max_set, m, n_queries, k);
+}
+static int join_small(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d_rpe_ids,
+                      const uint16_t* d_rpe_cnt, int64_t n_blocks, int32_t m, int32_t max_set,
+                      const int32_t* d_queries, int64_t n_queries, int32_t k, int64_t cap_rows,
+                      int64_t* d_join_off, int32_t* d_join_ids, uint16_t* d_join_cnt,
+                      uint16_t absent16, int64_t* h_rows) {
+    {
+        KernelSpan span(ctx, d_join_ids ? SUREL_K_JOIN_FILL : SUREL_K_JOIN_COUNT);
+        hipError_t hrc = surel::launch_join_small(
+            ctx->stream, ctx->n_cu, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set, d_queries,
+            n_queries, k, d_join_off, cap_rows, d_join_ids, d_join_cnt, absent16, ctx->d_small,
+            ctx->spin_limit, h_rows ? ctx->h_pinned : nullptr, ctx->d_err);
+        if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
+        if (hrc != hipSuccess) return SUREL_E_HIP;
+    }
+    if (h_rows) return report_pinned_total(ctx, d_join_ids != nullptr, cap_rows, h_rows);
+    return SUREL_OK;
+}
+
 // The whole join with the scratch given: layout, then (unless the outputs are NULL) the rows.
 static int join_vectors(surel_ctx* ctx, const JoinScratch& ws, const int64_t* d_rpe_off,
                         const int32_t* d_rpe_ids, const uint16_t* d_rpe_cnt, int64_t n_blocks,
@@ -644,6 +681,9 @@ static int join_checked(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t*
         return rc;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
+    if (join_is_small(ctx, max_set, m, n_queries, k))
+        return join_small(ctx, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set, d_queries,
+                          n_queries, k, cap_rows, d_join_off, d_join_ids, d_join_cnt, absent16, h_rows);
     JoinScratch ws;
     if (int rc = ensure_workspace(ctx, n_queries, &ws.counts, &ws.partials)) return rc;
     return join_vectors(ctx, ws, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set, d_queries,
@@ -659,6 +699,9 @@ int surel_join_count(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d_
     if (!ctx) return SUREL_E_CTX;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
+    if (join_is_small(ctx, max_set, 1, n_queries, k))
+        return join_small(ctx, d_rpe_off, d_rpe_ids, nullptr, n_blocks, 1, max_set, d_queries,
+                          n_queries, k, 0, d_join_off, nullptr, nullptr, 0, h_rows);
     JoinScratch ws;
     if (int rc = ensure_workspace(ctx, n_queries, &ws.counts, &ws.partials)) return rc;
     if (int rc = join_layout(ctx, ws, d_rpe_off, d_rpe_ids, n_blocks, max_set, d_queries, n_queries,
@@ -721,7 +764,11 @@ int surel_join_queries_noalloc(surel_ctx* ctx, const int64_t* d_rpe_off, const i
     ws.counts = static_cast<int32_t*>(ctx->d_scratch);
     ws.partials = reinterpret_cast<int64_t*>(static_cast<char*>(ctx->d_scratch) + kScratchCountsBytes);
     ctx->no_spans = true;  // timing a launch would create events
-    const int rc = join_vectors(ctx, ws, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set,
+    const int rc =
+        join_is_small(ctx, max_set, m, n_queries, k)
+            ? join_small(ctx, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set, d_queries,
+                         n_queries, k, cap_rows, d_join_off, d_join_ids, d_join_cnt, 0, h_rows)
+            : join_vectors(ctx, ws, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set,
                                 d_queries, n_queries, k, cap_rows, d_join_off, d_join_ids,
                                 d_join_cnt, 0, h_rows);
     ctx->no_spans = false;

@@ -89,22 +89,22 @@ __device__ __forceinline__ int32_t wave_incl_max(int32_t v) {
     return v;
 }
 
-// Copies n 32-bit words from global memory to LDS with the whole wave.  Loads are issued U
-// at a time before any of them is waited for, so a copy costs ceil(n / (64*U)) memory round
-// trips instead of one per 64 words.
+// Copies n 32-bit words from global memory to LDS with `threads` threads, numbered tid.  Loads
+// are issued U at a time before any of them is waited for, so a copy costs
+// ceil(n / (threads*U)) memory round trips instead of one per `threads` words.
 template <int U>
 __device__ __forceinline__ void stage_words(uint32_t* dst, const uint32_t* __restrict__ src, int n,
-                                            int lane) {
-    for (int t0 = 0; t0 < n; t0 += kWave * U) {
+                                            int tid, int threads = kWave) {
+    for (int t0 = 0; t0 < n; t0 += threads * U) {
         uint32_t v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = t0 + u * kWave + lane;
+            const int t = t0 + u * threads + tid;
             v[u] = t < n ? src[t] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = t0 + u * kWave + lane;
+            const int t = t0 + u * threads + tid;
             if (t < n) dst[t] = v[u];
         }
     }

@@ -73,6 +73,20 @@ hipError_t launch_join_fill(hipStream_t stream, int max_lds_bytes, const int64_t
                             int32_t k, const int64_t* join_off, int64_t cap_rows, int32_t* out_ids,
                             uint16_t* out_cnt, uint16_t absent16, uint32_t* err);
 
+// The whole join in one launch, for query lists of which join_is_small says so: writes
+// join_off[0..n_queries] and (unless out_ids is null) the rows.  small_scan: small_scan_bytes()
+// bytes of device memory, zero before its first use and kept by the launches from then on; only
+// one launch may use it at a time.  h_total (optional): host memory that gets the row total too.
+bool join_is_small(int n_cu, int max_lds_bytes, int32_t max_set, int32_t m, int64_t n_queries,
+                   int32_t k);
+hipError_t launch_join_small(hipStream_t stream, int n_cu, const int64_t* rpe_off,
+                             const int32_t* rpe_ids, const uint16_t* rpe_cnt, int64_t n_blocks,
+                             int32_t m, int32_t max_set, const int32_t* queries, int64_t n_queries,
+                             int32_t k, int64_t* join_off, int64_t cap_rows, int32_t* out_ids,
+                             uint16_t* out_cnt, uint16_t absent16, void* small_scan,
+                             uint32_t spin_limit, int64_t* h_total, uint32_t* err);
+size_t small_scan_bytes();
+
 // query_ids.hip.  out int32[n_queries][k][M][m+1][k]: for every entry of the walk blocks of a
 // query's k table blocks, the table rows that hold its node in each of the k blocks (-1 where
 // a block does not hold it).  walks[b] must be the walk block of table block b.  code

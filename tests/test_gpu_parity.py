@@ -718,6 +718,55 @@ def test_join_of_hand_made_tables_around_64_row_boundaries(ctx, max_set, L):
     assert_table_equal(got3, want3, f"hand-made join of triples, max_set {max_set}, L {L}")
 
 
+@pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("L", [2, 3, 6, 7, 8, 9, 10, 13, 15, 16])
+def test_join_vector_lengths_in_one_and_in_two_launches(ctx, L, k):
+    # every kind of row (whole words, rows that straddle words) of short and long vectors, from
+    # unions that end around multiples of 64 rows; few queries take one launch with several waves
+    # to a query, many take two with one wave each: same rows
+    rng = np.random.default_rng(10 * L + k)
+    n = 96
+    blocks = [np.sort(rng.choice(3 * n, size, replace=False)) for size in (96, 95, 64, 63, 33, 1, 0, 80)]
+    table = hand_made_table(blocks, L, rng)
+    d_table = (dev(table[0]), dev(table[1]), dev(table[2].view(np.int16)).view(torch.uint16))
+    few = rng.integers(0, len(blocks), size=(333, k)).astype(np.int32)
+    many = np.concatenate([few] * 13)
+    assert few.shape[0] < 4096 < many.shape[0]
+    for queries in (few, many):
+        want = oracle.join_queries(*table, queries)
+        got = binding.join_queries(ctx, *d_table, dev(queries), max_set=n)
+        assert ctx.check() == 0
+        assert_table_equal(got, want, f"join of {queries.shape[0]} {k}-tuples, L {L}")
+
+
+@pytest.mark.parametrize("k", [2, 3])
+def test_join_in_one_launch_of_the_largest_blocks_and_with_bounded_waits(ctx, k):
+    # full blocks of 2048 rows; then no wait allowed at all: the launch ends, says so if it gave
+    # up, and the next call is right again
+    rng = np.random.default_rng(k)
+    blocks = [np.sort(rng.choice(9000, 2048, replace=False)) for _ in range(4)]
+    table = hand_made_table(blocks, 5, rng)
+    d_table = (dev(table[0]), dev(table[1]), dev(table[2].view(np.int16)).view(torch.uint16))
+    queries = rng.integers(0, 4, size=(300, k)).astype(np.int32)
+    want = oracle.join_queries(*table, queries)
+    joff = torch.empty(queries.shape[0] + 1, dtype=torch.int64, device="cuda")
+    for spins in (1 << 22, 0, 1 << 22):
+        ctx.set_spin_limit(spins)
+        try:
+            rc, rows = binding.join_queries_raw(ctx, *d_table, dev(queries), 2048, 0, joff, None, None)
+        finally:
+            ctx.set_spin_limit(1 << 22)
+        flags = ctx.check()
+        assert flags == 0 or (spins == 0 and flags == binding.DEV_STALL)
+        if flags == 0:
+            assert rc == binding.OK and np.array_equal(joff.cpu().numpy(), want[0])
+        else:
+            assert rc in (binding.OK, binding.E_DEVICE)
+    got = binding.join_queries(ctx, *d_table, dev(queries), max_set=2048)
+    assert ctx.check() == 0
+    assert_table_equal(got, want, "join of full blocks")
+
+
 def test_largest_node_ids(ctx):
     # a graph with the most nodes the library takes (2^28 - 1): the largest ids make sort keys
     # (id << 4 | position) that use all 32 bits and must still sort in front of the padding
