@@ -352,7 +352,7 @@ int surel_query_rpe_ids(surel_ctx* ctx, const int32_t* d_walks, const int64_t* d
  *   d_T          uint16[cap_T][m+1], d_code int32[n_rows] (device, written).
  *   h_n_T        host int64, required: the number of distinct vectors.  The call always waits
  *                for its own work (the sort is sized by that number).
- * The context's workspace grows by 292 bytes per unit of cap_T (rounded up to a power of two).
+ * The context's workspace grows by 296 bytes per unit of cap_T (rounded up to a power of two).
  * Returns SUREL_E_CAPACITY when there are more than cap_T distinct vectors (*h_n_T says how
  * many; d_T and d_code are then undefined).  Limits: 1 <= m <= SUREL_MAX_STEPS, n_rows >= 0.
  * Device-detected: STALL. */

@@ -26,6 +26,7 @@ struct surel_ctx {
     size_t lb_bytes = 0;
     void* d_prune = nullptr;      // grow-only workspace: hash slots, sort list, counters of prune
     size_t prune_bytes = 0;
+    size_t prune_clean = 0;       // bytes of the hash slots in it that are known to be empty
     void* d_batch = nullptr;      // grow-only workspace: sort arrays of the incidence lists, hash
     size_t batch_bytes = 0;       // tables of the mini-batch search
     void* d_scratch = nullptr;    // this device's copy of the file-scope `scratch` array below
@@ -361,9 +362,8 @@ static int rpe_rows(surel_ctx* ctx, const int32_t* d_walks, int64_t n_seeds, int
                     int32_t n_nodes, const int64_t* d_rpe_off, int64_t cap_rows,
                     int32_t* d_rpe_ids, uint16_t* d_rpe_cnt) {
     KernelSpan span(ctx, SUREL_K_RPE_FILL);
-    hipError_t hrc = surel::launch_rpe_fill(ctx->stream, ctx->max_lds_bytes, d_walks, n_seeds, M, m,
-                                            n_nodes, d_rpe_off, cap_rows, d_rpe_ids, d_rpe_cnt,
-                                            ctx->d_err);
+    hipError_t hrc = surel::launch_rpe_fill(ctx->stream, d_walks, n_seeds, M, m, n_nodes,
+                                            d_rpe_off, cap_rows, d_rpe_ids, d_rpe_cnt, ctx->d_err);
     if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
     return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
 }
@@ -433,24 +433,24 @@ static int check_fused_args(const int32_t* d_row_ptr, const int32_t* d_col_idx, 
 }
 
 // The fused kernel (n_seeds >= 1): edge records if the job wants them, look-back scratch, launch.
-// code / slots / counters: the hash set of distinct count vectors, or null.
+// d_code / ps: the hash set of distinct count vectors that is to be fed, or null.
 static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                         int32_t n_nodes, int64_t n_edges, const int32_t* d_seeds, int64_t n_seeds,
                         int32_t M, int32_t m, uint64_t rng_seed, int32_t* d_walks, int64_t cap_rows,
                         int64_t* d_rpe_off, int32_t* d_rpe_ids, uint16_t* d_rpe_cnt, int32_t* d_code,
-                        uint32_t* slots, int64_t cap_T, unsigned long long* counters) {
+                        const surel::PruneScratch& ps, int64_t* h_total) {
     surel::EdgeRecords records;
     if (int rc = make_edge_records(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, n_seeds, M, m,
                                    &records))
         return rc;
     const size_t lb_need = (size_t)surel::lookback_words(n_seeds) * sizeof(uint64_t);
     if (int rc = grow_buffer(ctx, &ctx->d_lb, &ctx->lb_bytes, lb_need)) return rc;
+    if (h_total) *h_total = -1;
     KernelSpan span(ctx, SUREL_K_WALK_RPE);
     hipError_t hrc = surel::launch_walk_rpe(
         ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds,
         n_seeds, M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, records,
-        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, ctx->d_err, d_code, slots, cap_T,
-        counters);
+        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, h_total, ctx->d_err, d_code, ps);
     if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
     return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
 }
@@ -482,28 +482,63 @@ int surel_sample_walks_rpe(surel_ctx* ctx, const int32_t* d_row_ptr, const int32
         if (int rc = empty_table(ctx, d_rpe_off)) return rc;
     } else if (int rc = fused_launch(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds, n_seeds,
                                      M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids,
-                                     d_rpe_cnt, nullptr, nullptr, 0, nullptr)) {
+                                     d_rpe_cnt, nullptr, surel::PruneScratch{},
+                                     h_rows ? ctx->h_pinned : nullptr)) {
         return rc;
+    } else if (h_rows) {
+        return report_pinned_total(ctx, d_rpe_ids != nullptr, cap_rows, h_rows);
     }
     if (h_rows) return report_total(ctx, d_rpe_off, n_seeds, d_rpe_ids != nullptr, cap_rows, h_rows);
     return SUREL_OK;
 }
 
-// The scratch of the pruning calls inside the context's workspace.
-struct PruneScratch {
-    uint32_t* slots;
-    uint32_t* list;
-    unsigned long long* counters;
-};
-static int prune_scratch(surel_ctx* ctx, int64_t cap_T, PruneScratch* out) {
+// The scratch of the pruning calls inside the context's workspace, its hash set empty.  The calls
+// leave the set empty (ctx->prune_clean says so once they are done); it is cleared here when it is
+// new, larger than before, or a call did not come to its end.
+static int prune_scratch(surel_ctx* ctx, int64_t cap_T, surel::PruneScratch* ps) {
     const size_t slot_bytes = surel::prune_slot_bytes(cap_T);
-    const size_t list_bytes = align_up(surel::prune_list_bytes(cap_T), 256);
-    if (int rc = grow_buffer(ctx, &ctx->d_prune, &ctx->prune_bytes, slot_bytes + list_bytes + 256))
-        return rc;
+    const size_t member_bytes = align_up(surel::prune_member_bytes(cap_T), 256);
+    const size_t need = 256 + slot_bytes + member_bytes + surel::prune_rank_bytes(cap_T);
+    if (need > ctx->prune_bytes) ctx->prune_clean = 0;
+    if (int rc = grow_buffer(ctx, &ctx->d_prune, &ctx->prune_bytes, need)) return rc;
     char* ws = static_cast<char*>(ctx->d_prune);
-    out->slots = reinterpret_cast<uint32_t*>(ws);
-    out->list = reinterpret_cast<uint32_t*>(ws + slot_bytes);
-    out->counters = reinterpret_cast<unsigned long long*>(ws + slot_bytes + list_bytes);
+    ps->counters = reinterpret_cast<unsigned long long*>(ws);
+    ps->slots = reinterpret_cast<uint32_t*>(ws + 256);
+    ps->members = reinterpret_cast<uint32_t*>(ws + 256 + slot_bytes);
+    ps->ranks = reinterpret_cast<uint32_t*>(ws + 256 + slot_bytes + member_bytes);
+    ps->cap_T = cap_T;
+    const bool clean = slot_bytes <= ctx->prune_clean;
+    ctx->prune_clean = 0;  // until the call is done
+    if (!clean && surel::launch_prune_clear(ctx->stream, *ps) != hipSuccess) return SUREL_E_HIP;
+    return SUREL_OK;
+}
+
+// The end of the pruning calls: T and the codes, the number of distinct vectors and (what
+// h_pinned[0] then holds, if the call's kernel put it there) the row total, with one wait.
+// n_rows, d_rows: the number of rows, or where it stands on the device.
+static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m, int64_t n_rows,
+                        const int64_t* d_rows, int64_t cap_rows, uint16_t* d_T, int32_t* d_code,
+                        int64_t* h_rows, int64_t* h_n_T) {
+    KernelSpan span(ctx, SUREL_K_PRUNE);
+    if (surel::launch_prune_order(ctx->stream, ctx->n_cu, ps, m, n_rows, d_rows, cap_rows, d_T, d_code,
+                                  ctx->h_pinned + 1) != hipSuccess)
+        return SUREL_E_HIP;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+    const int64_t n_T = ctx->h_pinned[1];
+    *h_n_T = n_T;
+    // with more than cap_T vectors the set's list is not complete, and its slots are not all empty
+    if (n_T <= ps.cap_T) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
+    if (h_rows) {
+        *h_rows = n_rows = ctx->h_pinned[0];
+        if (int rc = judge_total(true, cap_rows, n_rows)) return rc;  // not all rows have codes
+    }
+    if (n_T > ps.cap_T) return SUREL_E_CAPACITY;
+    if (n_T > surel::prune_rank_most(ps.cap_T)) {
+        if (surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_T, d_code) !=
+            hipSuccess)
+            return SUREL_E_HIP;
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+    }
     return SUREL_OK;
 }
 
@@ -528,31 +563,13 @@ int surel_sample_walks_rpe_ids(surel_ctx* ctx, const int32_t* d_row_ptr, const i
         if (int rc = empty_table(ctx, d_rpe_off)) return rc;
         return report_total(ctx, d_rpe_off, 0, true, cap_rows, h_rows);
     }
-    PruneScratch ps;
+    surel::PruneScratch ps;
     if (int rc = prune_scratch(ctx, cap_T, &ps)) return rc;
-    if (surel::launch_prune_clear(ctx->stream, cap_T, ps.slots, ps.counters) != hipSuccess)
-        return SUREL_E_HIP;
     if (int rc = fused_launch(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds, n_seeds, M, m,
                               rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, d_code,
-                              ps.slots, cap_T, ps.counters))
+                              ps, ctx->h_pinned))
         return rc;
-    // the two totals in one read-back: table rows, distinct vectors
-    if (hipMemcpyAsync(ctx->h_pinned + 1, ps.counters, sizeof(int64_t), hipMemcpyDeviceToHost,
-                       ctx->stream) != hipSuccess)
-        return SUREL_E_HIP;
-    if (int rc = report_total(ctx, d_rpe_off, n_seeds, true, cap_rows, h_rows)) {
-        *h_n_T = ctx->h_pinned[1];
-        return rc;  // rows that did not fit have no codes: nothing to finish
-    }
-    const int64_t n_T = ctx->h_pinned[1];
-    *h_n_T = n_T;
-    if (n_T > cap_T) return SUREL_E_CAPACITY;
-    KernelSpan span(ctx, SUREL_K_PRUNE);
-    if (surel::launch_prune_finish(ctx->stream, ctx->n_cu, *h_rows, m, cap_T, n_T, ps.slots,
-                                   ps.counters, ps.list, d_T, d_code) != hipSuccess)
-        return SUREL_E_HIP;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
-    return SUREL_OK;
+    return prune_finish(ctx, ps, m, 0, d_rpe_off + n_seeds, cap_rows, d_T, d_code, h_rows, h_n_T);
 }
 
 // The join over vectors of m+1 16-bit entries per table row; absent16 fills the vector of a
@@ -621,6 +638,7 @@ static int join_small(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d
                       const int32_t* d_queries, int64_t n_queries, int32_t k, int64_t cap_rows,
                       int64_t* d_join_off, int32_t* d_join_ids, uint16_t* d_join_cnt,
                       uint16_t absent16, int64_t* h_rows) {
+    if (h_rows) ctx->h_pinned[0] = -1;
     {
         KernelSpan span(ctx, d_join_ids ? SUREL_K_JOIN_FILL : SUREL_K_JOIN_COUNT);
         hipError_t hrc = surel::launch_join_small(
@@ -819,27 +837,15 @@ int surel_prune_rpe(surel_ctx* ctx, const uint16_t* d_rpe_cnt, int64_t n_rows, i
     if (!ctx) return SUREL_E_CTX;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
-    PruneScratch ps;
+    surel::PruneScratch ps;
     if (int rc = prune_scratch(ctx, cap_T, &ps)) return rc;
-    uint32_t* slots = ps.slots;
-    uint32_t* list = ps.list;
-    unsigned long long* counters = ps.counters;
-    KernelSpan span(ctx, SUREL_K_PRUNE);
-    if (surel::launch_prune_collect(ctx->stream, ctx->n_cu, d_rpe_cnt, n_rows, m, cap_T, slots,
-                                    counters, d_code, ctx->spin_limit, ctx->d_err) != hipSuccess)
-        return SUREL_E_HIP;
-    if (hipMemcpyAsync(ctx->h_pinned, counters, sizeof(int64_t), hipMemcpyDeviceToHost,
-                       ctx->stream) != hipSuccess)
-        return SUREL_E_HIP;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
-    const int64_t n_T = ctx->h_pinned[0];
-    *h_n_T = n_T;
-    if (n_T > cap_T) return SUREL_E_CAPACITY;
-    if (surel::launch_prune_finish(ctx->stream, ctx->n_cu, n_rows, m, cap_T, n_T, slots, counters,
-                                   list, d_T, d_code) != hipSuccess)
-        return SUREL_E_HIP;
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
-    return SUREL_OK;
+    {
+        KernelSpan span(ctx, SUREL_K_PRUNE);
+        if (surel::launch_prune_collect(ctx->stream, ctx->n_cu, d_rpe_cnt, n_rows, m, ps, d_code,
+                                        ctx->spin_limit, ctx->d_err) != hipSuccess)
+            return SUREL_E_HIP;
+    }
+    return prune_finish(ctx, ps, m, n_rows, nullptr, n_rows, d_T, d_code, nullptr, h_n_T);
 }
 
 int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_queries, int32_t k,

@@ -38,54 +38,60 @@ __device__ __forceinline__ void raise_error(uint32_t* err, bool cond, uint32_t b
     }
 }
 
-// Value of `x` held by lane (lane ^ MASK), MASK a compile-time constant in 1..63.  Uses the
-// cheapest exchange the pattern allows: DPP quad permutes and row mirrors (folded into the
-// consuming VALU instruction), the LDS crossbar's swizzle for other masks below 32, and a
-// general ds_bpermute otherwise.  None of them touches LDS memory.
+// Moves a value between lanes by DPP (part of the vector unit, folded into the consuming
+// instruction where that allows it); lanes without a source get `old`.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t old, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, CTRL, ROWS, 0xF, false);
+}
+// The same for patterns in which every lane has a source.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_permute(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+
+// Value of `x` held by lane (lane ^ MASK), MASK a compile-time constant in 1..31: DPP where the
+// pattern allows it, the LDS crossbar's swizzle (no LDS memory is touched) otherwise.
 template <int MASK>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t x, int lane) {
-    static_assert(MASK >= 1 && MASK < kWave, "mask out of range");
+    static_assert(MASK >= 1 && MASK < 32, "mask out of range");
     if constexpr (MASK == 1) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+        return dpp_permute<0xB1>(x);   // quad_perm [1,0,3,2]
     } else if constexpr (MASK == 2) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+        return dpp_permute<0x4E>(x);   // quad_perm [2,3,0,1]
     } else if constexpr (MASK == 3) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x1B, 0xF, 0xF, false);  // quad_perm [3,2,1,0]
+        return dpp_permute<0x1B>(x);   // quad_perm [3,2,1,0]
     } else if constexpr (MASK == 7) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false);  // row_half_mirror
+        return dpp_permute<0x141>(x);  // row_half_mirror
+    } else if constexpr (MASK == 8) {
+        return dpp_permute<0x128>(x);  // row_ror:8
     } else if constexpr (MASK == 15) {
-        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, false);  // row_mirror
-    } else if constexpr (MASK < 32) {
+        return dpp_permute<0x140>(x);  // row_mirror
+    } else {
         // swizzle, bit mode: new lane = ((lane & and) | or) ^ xor inside each group of 32
         return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (MASK << 10) | 0x1F);
-    } else {
-        return (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ MASK) << 2, (int)x);
     }
 }
 
+// The value of lane `src_lane` (the same in every lane).
 __device__ __forceinline__ uint32_t wave_bcast_u32(uint32_t v, int src_lane) {
-    return (uint32_t)__shfl((int)v, src_lane, kWave);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, src_lane);
 }
 
-// Inclusive prefix sum over the 64 lanes.
+// The value of the lane below (lane 0: its own).
+__device__ __forceinline__ uint32_t wave_from_lane_below(uint32_t v) {
+    return dpp_move<0x138>(v, v);  // wave_shr:1
+}
+
+// Inclusive prefix sum over the 64 lanes: inside rows of 16 lanes by shifts of 1, 2, 4 and 8, then
+// the last lane of a row to the row behind it, then lane 31 to the upper half.
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t t = (uint32_t)__shfl_up((int)v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-// Inclusive prefix maximum (signed) over the 64 lanes.
-__device__ __forceinline__ int32_t wave_incl_max(int32_t v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t t = __shfl_up(v, d, kWave);
-        if (lane >= d) v = max(v, t);
-    }
+    v += dpp_move<0x111>(0u, v);       // row_shr:1
+    v += dpp_move<0x112>(0u, v);
+    v += dpp_move<0x114>(0u, v);
+    v += dpp_move<0x118>(0u, v);
+    v += dpp_move<0x142, 0xA>(0u, v);  // row_bcast:15 to rows 1 and 3
+    v += dpp_move<0x143, 0xC>(0u, v);  // row_bcast:31 to rows 2 and 3
     return v;
 }
 
@@ -115,16 +121,14 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
                                               uint32_t k0, uint32_t k1, uint32_t out[4]) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo0 = 0xD2511F53u * c0;
-        const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2);
-        const uint32_t lo1 = 0xCD9E8D57u * c2;
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0;  // one v_mad_u64_u32 each
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
         c0 = n0;
-        c1 = lo1;
+        c1 = (uint32_t)p1;
         c2 = n2;
-        c3 = lo0;
+        c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -132,6 +136,19 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[1] = c1;
     out[2] = c2;
     out[3] = c3;
+}
+
+// r mod d for d >= 1, exact, in about 13 instructions: the quotient from a reciprocal of d with
+// more than 40 good bits (a single-precision reciprocal and one Newton step in double precision)
+// is below 2^32 and lowered by 2^-10, far more than its error, so it is the true one or one less,
+// which the last step mends.
+__device__ __forceinline__ uint32_t mod_u32(uint32_t r, uint32_t d) {
+    const double dd = (double)d;
+    double y = (double)__builtin_amdgcn_rcpf((float)d);
+    y = __builtin_fma(__builtin_fma(-dd, y, 1.0), y, y);
+    const uint32_t q = (uint32_t)__builtin_fma((double)r, y, -0x1p-10);
+    const uint32_t rest = r - q * d;
+    return min(rest, rest - d);
 }
 
 // floor(x / d) for 0 <= x < 4096 and 1 <= d <= 16 with magic = 65536 / d + 1.

@@ -34,18 +34,23 @@ hipError_t launch_walks(hipStream_t stream, const int32_t* row_ptr, const int32_
 // out; rpe_off[n_seeds] is then -1).  Needs M*(m+1) <= 2048 and n_seeds >= 1.
 // hipErrorInvalidValue = the shape does not fit the device's LDS.
 // With `code` (int32 per table row) the kernel also looks every finished row's count vector up
-// in the hash set of prune.hip (slots of prune_slot_bytes(cap_T) bytes, emptied by
-// launch_prune_clear; counters as for launch_prune_collect) and writes the row's slot number to
-// code[row]; launch_prune_finish then turns slot numbers into indices of the sorted array T.
-// cnt may then be null (rows carry RPE-IDs only).
+// in the hash set of prune.hip and writes the vector's number there to code[row];
+// launch_prune_order then turns numbers into indices of the sorted array T.  cnt may then be null
+// (rows carry RPE-IDs only).
+struct PruneScratch {
+    uint32_t* slots = nullptr;
+    uint32_t* members = nullptr;
+    uint32_t* ranks = nullptr;
+    unsigned long long* counters = nullptr;
+    int64_t cap_T = 0;
+};
 hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, const int32_t* row_ptr,
                            const int32_t* col_idx, int32_t n_nodes, int64_t n_edges,
                            const int32_t* seeds, int64_t n_seeds, int32_t M, int32_t m,
                            uint64_t rng_seed, int32_t* walks, int64_t cap_rows, int64_t* rpe_off,
                            int32_t* ids, uint16_t* cnt, const EdgeRecords& rec, uint64_t* lb,
-                           uint32_t spin_limit, uint32_t* err, int32_t* code = nullptr,
-                           uint32_t* slots = nullptr, int64_t cap_T = 0,
-                           unsigned long long* counters = nullptr);
+                           uint32_t spin_limit, int64_t* h_total, uint32_t* err,
+                           int32_t* code, const PruneScratch& ps);
 
 // rpe.hip.  launch_rpe_count: set_sizes[i] = distinct nodes in walks[i].  launch_rpe_fill:
 // writes the rows of every seed at rpe_off[i] (seeds whose block would pass cap_rows, or whose
@@ -53,10 +58,9 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
 // hipErrorInvalidValue = the shape does not fit the device's LDS.
 hipError_t launch_rpe_count(hipStream_t stream, const int32_t* walks, int64_t n_seeds, int32_t M,
                             int32_t m, int32_t n_nodes, int32_t* set_sizes, uint32_t* err);
-hipError_t launch_rpe_fill(hipStream_t stream, int max_lds_bytes, const int32_t* walks,
-                           int64_t n_seeds, int32_t M, int32_t m, int32_t n_nodes,
-                           const int64_t* rpe_off, int64_t cap_rows, int32_t* ids, uint16_t* cnt,
-                           uint32_t* err);
+hipError_t launch_rpe_fill(hipStream_t stream, const int32_t* walks, int64_t n_seeds, int32_t M,
+                           int32_t m, int32_t n_nodes, const int64_t* rpe_off, int64_t cap_rows,
+                           int32_t* ids, uint16_t* cnt, uint32_t* err);
 
 // join.hip.  launch_join_count: counts[q] = union rows of query q.  launch_join_fill: writes the
 // rows of every query at join_off[q] (a query whose union does not have join_off[q+1]-join_off[q]
@@ -99,24 +103,29 @@ hipError_t launch_query_ids(hipStream_t stream, int max_lds_bytes, const int32_t
                             uint32_t* err);
 
 // prune.hip.  Distinct count vectors of the table, sorted, and every row's index among them.
-// slots: prune_slot_bytes(cap_T) bytes, list: prune_list_bytes(cap_T) bytes, counters: two
-// 64-bit words (all device scratch).  launch_prune_collect fills the hash set and leaves
-// counters[0] = number of distinct vectors; the host reads it and, if it fits cap_T, calls
-// launch_prune_finish with it.
+// PruneScratch: device scratch of prune_slot_bytes, prune_member_bytes and prune_rank_bytes(cap_T)
+// bytes and two 64-bit counters.  slots and counters are zero before a call (launch_prune_clear)
+// and are left zero by launch_prune_order, unless there were more than cap_T distinct vectors.
 size_t prune_slot_bytes(int64_t cap_T);
-size_t prune_list_bytes(int64_t cap_T);
-uint32_t prune_slot_mask(int64_t cap_T);
+size_t prune_member_bytes(int64_t cap_T);
+size_t prune_rank_bytes(int64_t cap_T);
 // empties the hash set and its counters (memsets: not for stream capture)
-hipError_t launch_prune_clear(hipStream_t stream, int64_t cap_T, uint32_t* slots,
-                              unsigned long long* counters);
+hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps);
+// code[row] = number of the row's vector in the set
 hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cnt, int64_t n_rows,
-                                int32_t m, int64_t cap_T, uint32_t* slots,
-                                unsigned long long* counters, int32_t* code, uint32_t spin_limit,
-                                uint32_t* err);
-hipError_t launch_prune_finish(hipStream_t stream, int n_cu, int64_t n_rows, int32_t m,
-                               int64_t cap_T, int64_t n_T, uint32_t* slots,
-                               unsigned long long* counters, uint32_t* list, uint16_t* T,
-                               int32_t* code);
+                                int32_t m, const PruneScratch& ps, int32_t* code,
+                                uint32_t spin_limit, uint32_t* err);
+// T = the set's vectors, sorted; code[row] = place of the row's vector there; *h_n_T (host memory)
+// = their number; then empties the set.  d_rows (optional): where the number of rows stands on
+// the device; with more than cap_rows of them the codes stay as they are.  With more than
+// prune_rank_most(cap_T) distinct vectors T and code stay as they are, and launch_prune_order_many
+// has to be called with the number.
+int64_t prune_rank_most(int64_t cap_T);
+hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
+                              int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
+                              int32_t* code, int64_t* h_n_T);
+hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
+                                   int64_t n_rows, int64_t n_T, uint16_t* T, int32_t* code);
 
 // incidence.hip.  The queries of every node: inc_q[inc_off[x] .. inc_off[x+1]) = indices of the
 // queries that name node x, ascending (a query that names x twice is listed twice).  Entries

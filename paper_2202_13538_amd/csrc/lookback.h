@@ -8,7 +8,7 @@
 //     from one global counter and its waves take them one by one through a word in LDS (one
 //     global atomic per run: atomics on one address are slow).  A worker publishes an item's
 //     row count as soon as it knows it, without waiting for anything;
-//   - the scanner (the wave that drew role 0) runs over the published counts in item order and
+//   - the scanner (the first wave of the workgroup that drew the first run) runs over the published counts in item order and
 //     writes, for every group of 8 items, the rows of all items before the group.  A worker
 //     gets an item's offset from its group's base and the counts of the items before it inside
 //     the group.  (The scanner stays this light on purpose: one 8-byte store per group.  A
@@ -21,7 +21,7 @@
 // there; a worker only ever waits for the offset of an item it has already published, i.e.
 // for counts of smaller items.  So the smallest unpublished item is always being worked on,
 // or about to be taken by a wave that waits only for things that already exist.  The scanner
-// was the first wave to draw a role, so it is running whenever anybody waits for it.  On top
+// belongs to the first workgroup that drew, so it is running whenever anybody waits for it.  On top
 // of that every wait is bounded by a spin limit: a wait that runs out raises kDevStall and
 // the wave leaves (the row total, which the scanner writes last, then stays -1).
 #pragma once
@@ -34,7 +34,7 @@ constexpr int kGroup = 8;              // consecutive items per group base
 constexpr int kScanGroupsPerLane = 4;  // groups a scanner lane takes per round (2048 items a round)
 constexpr unsigned long long kChunkLocked = ~0ull;  // LDS chunk word: a wave is refilling it
 
-// Scratch of one launch, in 64-bit words: [0] item counter, [1] role counter, then the group
+// Scratch of one launch, in 64-bit words: [0] item counter, [1] unused, then the group
 // bases (int64, -1 = not yet; one per group plus the grand total), then the 16-bit counts
 // (rows + 1, 0 = not yet), padded so that the scanner's window never leaves the buffer.
 struct LookbackScratch {
@@ -89,16 +89,9 @@ __device__ __forceinline__ void load_counts(const uint16_t* p, uint4 (&v)[kScanG
 }
 
 __device__ __forceinline__ int64_t wave_bcast_i64(int64_t v, int src_lane) {
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)(uint64_t)v, src_lane, kWave);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)((uint64_t)v >> 32), src_lane, kWave);
+    const uint32_t lo = wave_bcast_u32((uint32_t)(uint64_t)v, src_lane);
+    const uint32_t hi = wave_bcast_u32((uint32_t)((uint64_t)v >> 32), src_lane);
     return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// One draw from a counter for the whole wave.
-__device__ __forceinline__ int64_t wave_draw(uint64_t* counter, int lane) {
-    uint64_t drawn = 0;
-    if (lane == 0) drawn = atomicAdd(reinterpret_cast<unsigned long long*>(counter), 1ull);
-    return wave_bcast_i64((int64_t)drawn, 0);
 }
 
 // Next item for this wave.  `chunk` (LDS, one per workgroup) holds the workgroup's current
@@ -140,11 +133,11 @@ __device__ __forceinline__ int64_t take_item(unsigned long long* chunk, uint64_t
 // The scanner.  status[j] = rows of item j plus one (0 = not published yet; the entries that
 // pad the last group are preset to 1).  Writes base[g] = rows of all items before group g, for
 // g = 0..n_groups, in order, as far as the published counts reach, round after round, and
-// the grand total to *total_out (which the launch's clear kernel has preset to -1, so a scan
+// the grand total to *total_out and, if given, to h_total in host memory (the launch's clear kernel has preset the former to -1, so a scan
 // that gives up leaves a total that nobody takes for a row count).
 __device__ __forceinline__ void scan_counts(const uint16_t* status, int64_t n_groups, int64_t* base,
-                                            int64_t* total_out, uint32_t spin_limit,
-                                            uint32_t* err, int lane) {
+                                            int64_t* total_out, int64_t* h_total,
+                                            uint32_t spin_limit, uint32_t* err, int lane) {
     __builtin_amdgcn_s_setprio(3);  // everybody's offsets depend on this wave
     int64_t pos = 0;  // groups [0, pos) are accounted for; base[0..pos] is written
     int64_t sum = 0;  // rows of the items before group pos
@@ -177,7 +170,10 @@ __device__ __forceinline__ void scan_counts(const uint16_t* status, int64_t n_gr
         }
         if (f == 0) {
             if (++idle > spin_limit) {
-                if (lane == 0) atomicOr(err, kDevStall);
+                if (lane == 0) {
+                    atomicOr(err, kDevStall);
+                    if (h_total) *h_total = -1;
+                }
                 return;
             }
             __builtin_amdgcn_s_sleep(4);
@@ -201,7 +197,10 @@ __device__ __forceinline__ void scan_counts(const uint16_t* status, int64_t n_gr
         sum += (int64_t)wave_bcast_u32(incl, kWave - 1);
         pos += f;
     }
-    if (lane == 0) *total_out = sum;
+    if (lane == 0) {
+        *total_out = sum;
+        if (h_total) *h_total = sum;
+    }
 }
 
 // Offset of `item`'s rows once the scanner has reached its group and the items before it in

@@ -4,17 +4,18 @@
 // insertion order; here T is sorted (count vectors compared entry by entry), which makes the
 // result unique and testable bit for bit.
 //
-// Four steps, all on the device:
-//   collect  every row looks its vector up in a global open-addressing hash set and inserts
-//            it if it is new; the row's slot number goes to code[row].  A slot is 64 bytes
-//            (state, rank, vector), aligned, so one cache line holds all of it.  Almost every
-//            lookup finds its vector already there (a few vectors make up nearly all rows)
-//            and is served by the caches with plain loads; only a slot that does not look
-//            full yet is touched with atomics.
-//   gather   the full slots are listed (their number is the size of T),
-//   sort     the list is sorted with a bitonic network in global memory (it is small),
-//   rank     slot.rank = position in the sorted list, T[position] = vector, and finally
-//            code[row] = rank of the row's slot.
+// Steps, all on the device:
+//   collect  every row looks its vector up in a global open-addressing hash set and inserts it if
+//            it is new (prune_set.h); the vector's number in the set goes to code[row].  A slot is
+//            64 bytes (state, number, vector), aligned, so one cache line holds all of it; only a
+//            slot that does not look full yet is touched with atomics.
+//   rank     every vector's place in the sorted array: up to kRankMost vectors are compared all
+//            with all (a few thousand, usually: one short launch that needs no count on the host),
+//            more are sorted with a bitonic network in global memory.  T[place] = vector.
+//   codes    code[row] = place of the row's vector.
+//   clean    the slots that were used are emptied again, by the list of the set's members (a
+//            memset of the table, and a pass over it that gathers the full slots, were 95 us of a
+//            call with cap_T = 2^20).
 // Waiting.  A lane that finds a slot locked (another lane is writing its vector) polls it
 // again; the writer needs nothing from the poller (inside one wavefront the writer's branch
 // runs to its end before the next poll), so the poll ends; it is bounded by the spin limit
@@ -25,71 +26,145 @@
 
 namespace surel {
 
-// The count vector of a row as NW words, entry 2k in the upper half of word k, so that
-// comparing words in order compares the counts in order.  L = m + 1 entries.
-template <int NW>
-__device__ __forceinline__ void load_vector(const uint16_t* __restrict__ cnt, int64_t row, int L,
-                                            uint32_t (&w)[NW]) {
-    const uint16_t* v = cnt + row * L;
-#pragma unroll
-    for (int k = 0; k < NW; ++k) {
-        const uint32_t hi = v[2 * k];
-        const uint32_t lo = (2 * k + 1 < L) ? v[2 * k + 1] : 0u;
-        w[k] = (hi << 16) | lo;
-    }
-}
+constexpr int kCollectWaves = 8;   // wavefronts of a workgroup, which share the LDS tables
+constexpr int kCollectRows = 256;  // rows of a wave's tile
 
-constexpr int kPruneRows = 4;        // rows a lane works on at once
-// A workgroup takes tiles of 256 * kPruneRows consecutive rows; a lane has kPruneRows of them in
-// flight.  A few vectors make up nearly all rows, and all compute units asking the same few
-// cache lines of the global table for them would queue up at those lines' L2 channels; so every
-// workgroup keeps a small cache of (vector -> slot) in LDS.  An entry is written once, by the
-// lane that wins its state word, and is valid for good after that (state, then vector and slot,
-// then "valid": LDS operations of a wave take effect in order), so readers never see a mix of
-// two vectors.  Vectors that find their entry taken by another go to the global table.
-template <int NW>
-__global__ __launch_bounds__(256) void prune_collect_kernel(
-    const uint16_t* __restrict__ cnt, int64_t n_rows, int L, uint32_t* __restrict__ slots,
-    uint32_t slot_mask, int64_t cap_T, unsigned long long* __restrict__ n_inserted,
-    int32_t* __restrict__ code, uint32_t spin_limit, uint32_t* __restrict__ err) {
-    __shared__ uint32_t cache[kCacheEntries * kCacheWords];
-    prune_cache_clear(cache, (int)threadIdx.x, 256);
+// A wavefront takes tiles of 256 consecutive rows: they come in as contiguous 16-byte pieces (the
+// next tile's are on their way while one is looked up) and are read row by row from LDS.
+// Bound by the stream of counts in and codes out: FIGCOLLECT
+template <int LT, int kQuads>
+__global__ __launch_bounds__(kCollectWaves* kWave) void prune_collect_kernel(
+    const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
+    VectorSet set) {
+    __shared__ __align__(16) uint32_t cache[kSetCacheWords];
+    extern __shared__ __align__(16) uint32_t lds32[];
+    set_cache_clear(cache, (int)threadIdx.x, kCollectWaves * kWave);
     __syncthreads();
-    const int64_t tile_rows = 256 * kPruneRows;
-    const int64_t stride = (int64_t)gridDim.x * tile_rows;
-    for (int64_t tile = (int64_t)blockIdx.x * tile_rows; tile < n_rows; tile += stride) {
-        uint32_t w[kPruneRows][NW];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile_words = kCollectRows * L / 2;
+    uint32_t* tile = lds32 + wave * (tile_words + kCollectRows);
+    uint32_t* misses = tile + tile_words;
+    const int n_quads = tile_words / 4;  // 256 * L counts: whole 16-byte pieces
+    struct __attribute__((packed, aligned(4))) quad_t { uint32_t v[4]; };  // the array is 4-byte aligned
+    const int64_t stride = (int64_t)gridDim.x * kCollectWaves;
+    const int64_t n_whole = n_rows / kCollectRows;
+    int64_t at = (int64_t)blockIdx.x * kCollectWaves + wave;
+    quad_t next[kQuads];
+    auto fetch = [&](int64_t t) {
+        const quad_t* from = reinterpret_cast<const quad_t*>(cnt + t * kCollectRows * L);
 #pragma unroll
-        for (int u = 0; u < kPruneRows; ++u) {
-            const int64_t row = min(tile + u * 256 + (int64_t)threadIdx.x, n_rows - 1);
-            load_vector<NW>(cnt, row, L, w[u]);
+        for (int u = 0; u < kQuads; ++u)
+            if (u * kWave + lane < n_quads) next[u] = from[u * kWave + lane];
+    };
+    auto to_lds = [&]() {
+        uint4* to = reinterpret_cast<uint4*>(tile);
+#pragma unroll
+        for (int u = 0; u < kQuads; ++u)
+            if (u * kWave + lane < n_quads)
+                to[u * kWave + lane] = make_uint4(next[u].v[0], next[u].v[1], next[u].v[2], next[u].v[3]);
+        wave_sync();
+    };
+    if (at < n_whole) fetch(at);
+    // the first wave's first tile on its own: it fills the workgroup's tables with the common
+    // vectors, for which the other waves then need not ask the global table all at once
+    for (int turn = 0; turn < 2; ++turn) {
+        if (turn == 1) __syncthreads();
+        while (at < n_whole && (turn == 1 || wave == 0)) {
+            to_lds();
+            const int64_t now = at;
+            at += stride;
+            if (at < n_whole) fetch(at);
+            rows_numbers<LT>(kCollectRows, lane, L, reinterpret_cast<const uint16_t*>(tile), misses,
+                             cache, set, code + now * kCollectRows);
+            wave_sync();
+            if (turn == 0) break;
         }
+    }
+    // the rows behind the last whole tile
+    const int rest = (int)(n_rows - n_whole * kCollectRows);
+    if (at == n_whole && rest > 0) {
+        uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile);
+        for (int t = lane; t < rest * L; t += kWave) tile16[t] = cnt[n_whole * kCollectRows * L + t];
+        wave_sync();
+        rows_numbers<LT>(rest, lane, L, tile16, misses, cache, set, code + n_whole * kCollectRows);
+    }
+}
+
+// Vectors that are compared all with all; beyond, n log^2 n steps of a sort are fewer.
+constexpr int64_t kRankMost = 65536;
+constexpr int kRankTile = 256;
+constexpr int kRankBlocks = 1024;
+
+// ranks[i] += vectors of one tile that are smaller than vector i of another, for all pairs of
+// tiles.  The number of vectors is read on the device, so that the launch does not wait for the
+// host to learn it; with more of them than this launch is for, it does nothing.
+template <int NW>
+__global__ __launch_bounds__(kRankTile) void prune_rank_pairs_kernel(
+    const uint32_t* __restrict__ members, const unsigned long long* __restrict__ n_inserted,
+    int64_t most, uint32_t* __restrict__ ranks) {
+    __shared__ uint32_t other[NW][kRankTile];
+    const int64_t n = (int64_t)*n_inserted;
+    if (n > most) return;
+    const int64_t tiles = (n + kRankTile - 1) / kRankTile;
+    for (int64_t p = blockIdx.x; p < tiles * tiles; p += gridDim.x) {
+        const int64_t i = (p / tiles) * kRankTile + threadIdx.x;
+        const int64_t j0 = (p % tiles) * kRankTile;
+        uint32_t mine[NW];
 #pragma unroll
-        for (int u = 0; u < kPruneRows; ++u) {
-            const int64_t row = tile + u * 256 + (int64_t)threadIdx.x;
-            if (row >= n_rows) continue;
-            const int32_t found = prune_lookup<NW>(w[u], cache, slots, slot_mask, cap_T, n_inserted,
-                                                   spin_limit, err);
-            code[row] = found;
+        for (int k = 0; k < NW; ++k) mine[k] = i < n ? members[i * kItemWords + k] : 0u;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            other[k][threadIdx.x] = j0 + threadIdx.x < n ? members[(j0 + threadIdx.x) * kItemWords + k] : ~0u;
+        __syncthreads();
+        const int m = (int)min((int64_t)kRankTile, n - j0);
+        uint32_t smaller = 0;
+        for (int j = 0; j < m; ++j) {
+            bool less = false;
+#pragma unroll
+            for (int k = NW - 1; k >= 0; --k)
+                less = other[k][j] < mine[k] || (other[k][j] == mine[k] && less);
+            smaller += less ? 1u : 0u;
+        }
+        if (i < n && smaller != 0u) atomicAdd(&ranks[i], smaller);
+    }
+}
+
+// T[ranks[i]] = vector i; the number of vectors also goes to host memory.
+__global__ __launch_bounds__(256) void prune_place_kernel(
+    const uint32_t* __restrict__ members, const unsigned long long* __restrict__ n_inserted,
+    int64_t most, int L, const uint32_t* __restrict__ ranks, uint16_t* __restrict__ T,
+    int64_t* h_n_T) {
+    const int64_t n = (int64_t)*n_inserted;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *h_n_T = n;
+    if (n > most) return;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t* item = members + i * kItemWords;
+        const int64_t place = ranks[i];
+        for (int e = 0; e < L; ++e) {
+            const uint32_t word = item[e >> 1];
+            T[place * L + e] = (uint16_t)((e & 1) ? (word & 0xFFFFu) : (word >> 16));
         }
     }
 }
 
-// Lists the full slots: list[i] = (vector words, slot number), in any order.
-__global__ __launch_bounds__(256) void prune_gather_kernel(const uint32_t* __restrict__ slots,
-                                                           uint32_t n_slots, int64_t list_len,
-                                                           unsigned long long* __restrict__ n_listed,
-                                                           uint32_t* __restrict__ list) {
-    const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n_slots) return;
-    const uint32_t* slot = slots + (size_t)s * kSlotWords;
-    if (slot[0] != kSlotFull) return;
-    const unsigned long long at = atomicAdd(n_listed, 1ull);
-    if ((int64_t)at >= list_len) return;
-    uint32_t* item = list + at * (kMaxVecWords + 1);
-#pragma unroll
-    for (int k = 0; k < kMaxVecWords; ++k) item[k] = slot[kSlotVector + k];
-    item[kMaxVecWords] = s;
+// Empties the slots of the set's members and its counter.
+__global__ __launch_bounds__(256) void prune_clean_kernel(const uint32_t* __restrict__ members,
+                                                          int64_t cap_T,
+                                                          uint32_t* __restrict__ slots,
+                                                          unsigned long long* __restrict__ counters) {
+    // counters[0]: vectors inserted; counters[1]: workgroups of this launch that have read it
+    const int64_t n = min((int64_t)counters[0], cap_T);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        slots[(size_t)members[i * kItemWords + kMaxVecWords] * kSlotWords] = kSlotEmpty;
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(&counters[1], 1ull) + 1ull == gridDim.x) {
+        counters[0] = 0ull;
+        counters[1] = 0ull;
+    }
 }
 
 // Entries from `first` on become padding that sorts behind every vector.
@@ -98,7 +173,7 @@ __global__ __launch_bounds__(256) void prune_pad_kernel(uint32_t* __restrict__ l
     const int64_t i = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= len) return;
 #pragma unroll
-    for (int k = 0; k <= kMaxVecWords; ++k) list[i * (kMaxVecWords + 1) + k] = 0xFFFFFFFFu;
+    for (int k = 0; k <= kMaxVecWords; ++k) list[i * kItemWords + k] = 0xFFFFFFFFu;
 }
 
 __device__ __forceinline__ bool item_less(const uint32_t (&a)[kMaxVecWords + 1],
@@ -120,44 +195,52 @@ __global__ __launch_bounds__(256) void prune_sort_step_kernel(uint32_t* __restri
     uint32_t a[kMaxVecWords + 1], b[kMaxVecWords + 1];
 #pragma unroll
     for (int t = 0; t <= kMaxVecWords; ++t) {
-        a[t] = list[i * (kMaxVecWords + 1) + t];
-        b[t] = list[p * (kMaxVecWords + 1) + t];
+        a[t] = list[i * kItemWords + t];
+        b[t] = list[p * kItemWords + t];
     }
     const bool ascending = (i & k) == 0;
     if (item_less(b, a) == ascending) {
 #pragma unroll
         for (int t = 0; t <= kMaxVecWords; ++t) {
-            list[i * (kMaxVecWords + 1) + t] = b[t];
-            list[p * (kMaxVecWords + 1) + t] = a[t];
+            list[i * kItemWords + t] = b[t];
+            list[p * kItemWords + t] = a[t];
         }
     }
 }
 
-// T[i] = vector of the i-th item of the sorted list; its slot learns its rank.
+// T[i] = vector of the i-th item of the sorted list, whose number learns its place.
 __global__ __launch_bounds__(256) void prune_rank_kernel(const uint32_t* __restrict__ list,
                                                          int64_t n_T, int L,
-                                                         uint32_t* __restrict__ slots,
+                                                         const uint32_t* __restrict__ slots,
+                                                         uint32_t* __restrict__ ranks,
                                                          uint16_t* __restrict__ T) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_T) return;
-    const uint32_t* item = list + i * (kMaxVecWords + 1);
-    slots[(size_t)item[kMaxVecWords] * kSlotWords + 1] = (uint32_t)i;
+    const uint32_t* item = list + i * kItemWords;
+    ranks[slots[(size_t)item[kMaxVecWords] * kSlotWords + 1]] = (uint32_t)i;
     for (int e = 0; e < L; ++e) {
         const uint32_t word = item[e >> 1];
         T[i * L + e] = (uint16_t)((e & 1) ? (word & 0xFFFFu) : (word >> 16));
     }
 }
 
-// code[row]: slot number -> rank of that slot (-1, or anything that is no slot number, becomes -1).
+// code[row]: number of the row's vector -> its place (what is no number becomes -1).
 // Four rows a lane, moved as 16-byte words where the array's alignment allows (the pass is a
-// plain stream over the codes; the ranks come from a few thousand hot cache lines).
+// plain stream over the codes; the places come from a few thousand words).
+// rows (optional): where the number of rows stands on the device (more than cap_rows of them: the
+// codes are not all there, nothing is done); n_known < 0: the number of vectors stands in
+// *n_inserted, and with more than `most` nothing is done.
 constexpr int kCodesUnroll = 4;
-__global__ __launch_bounds__(256) void prune_codes_kernel(const uint32_t* __restrict__ slots,
-                                                          uint32_t n_slots, int64_t n_rows,
-                                                          int32_t* __restrict__ code) {
+__global__ __launch_bounds__(256) void prune_codes_kernel(
+    const uint32_t* __restrict__ ranks, const unsigned long long* __restrict__ n_inserted,
+    int64_t n_known, int64_t most, int64_t n_rows, const int64_t* __restrict__ rows,
+    int64_t cap_rows, int32_t* __restrict__ code) {
+    const int64_t n = n_known >= 0 ? n_known : (int64_t)*n_inserted;
+    if (n > most) return;
+    if (rows != nullptr) n_rows = *rows;
+    if (n_rows > cap_rows) return;
     auto rank_of = [&](int32_t c) -> int32_t {
-        const uint32_t s = (uint32_t)c;
-        return s < n_slots ? (int32_t)slots[(size_t)s * kSlotWords + 1] : -1;
+        return (uint64_t)(uint32_t)c < (uint64_t)n ? (int32_t)ranks[(uint32_t)c] : -1;
     };
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -202,78 +285,115 @@ int64_t prune_list_len(int64_t cap_T) {
     return s;
 }
 size_t prune_slot_bytes(int64_t cap_T) { return (size_t)prune_slots(cap_T) * kSlotWords * 4; }
-size_t prune_list_bytes(int64_t cap_T) {
-    return (size_t)prune_list_len(cap_T) * (kMaxVecWords + 1) * 4;
+size_t prune_member_bytes(int64_t cap_T) { return (size_t)prune_list_len(cap_T) * kItemWords * 4; }
+size_t prune_rank_bytes(int64_t cap_T) { return (size_t)cap_T * sizeof(uint32_t); }
+
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err) {
+    return VectorSet{ps.slots, (uint32_t)(prune_slots(ps.cap_T) - 1), ps.cap_T, ps.members, ps.ranks,
+                     ps.counters, spin_limit, err};
 }
 
-uint32_t prune_slot_mask(int64_t cap_T) { return (uint32_t)(prune_slots(cap_T) - 1); }
-
-hipError_t launch_prune_clear(hipStream_t stream, int64_t cap_T, uint32_t* slots,
-                              unsigned long long* counters) {
-    // empty table, counters to zero (the calls that use it read a total back on the host in any
-    // case, so they cannot be captured into a graph, and plain memsets do)
-    hipError_t rc = hipMemsetAsync(slots, 0, (size_t)prune_slots(cap_T) * kSlotWords * 4, stream);
+hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
+    // (the calls that use the set wait for the host in any case, so they cannot be captured into a
+    // graph, and plain memsets do)
+    hipError_t rc = hipMemsetAsync(ps.slots, 0, prune_slot_bytes(ps.cap_T), stream);
     if (rc != hipSuccess) return rc;
-    return hipMemsetAsync(counters, 0, 2 * sizeof(unsigned long long), stream);
+    return hipMemsetAsync(ps.counters, 0, 2 * sizeof(unsigned long long), stream);
+}
+
+template <int LT, int kQuads>
+static hipError_t launch_collect(hipStream_t stream, int n_cu, const uint16_t* cnt, int64_t n_rows,
+                                 int L, int32_t* code, const VectorSet& set) {
+    const size_t lds_bytes = (size_t)kCollectWaves * (kCollectRows * L / 2 + kCollectRows) * 4;
+    const void* fn = reinterpret_cast<const void*>(prune_collect_kernel<LT, kQuads>);
+    if (lds_bytes > 48 * 1024) {
+        hipError_t rc = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            (int)lds_bytes);
+        if (rc != hipSuccess) return rc;
+    }
+    // a few workgroups per compute unit: each fills its LDS tables once and keeps them
+    const int64_t tiles = n_rows / kCollectRows + 1;
+    int64_t blocks = (tiles + kCollectWaves - 1) / kCollectWaves;
+    const int per_cu = (int)((160 * 1024) / (lds_bytes + kSetCacheWords * 4));
+    const int64_t most = (int64_t)n_cu * (per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu));
+    if (blocks > most) blocks = most;
+    hipLaunchKernelGGL((prune_collect_kernel<LT, kQuads>), dim3((unsigned)blocks),
+                       dim3(kCollectWaves * kWave), lds_bytes, stream, cnt, n_rows, L, code, set);
+    return hipGetLastError();
 }
 
 hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cnt, int64_t n_rows,
-                                int32_t m, int64_t cap_T, uint32_t* slots,
-                                unsigned long long* counters, int32_t* code, uint32_t spin_limit,
-                                uint32_t* err) {
-    const int64_t n_slots = prune_slots(cap_T);
-    hipError_t rc = launch_prune_clear(stream, cap_T, slots, counters);
-    if (rc != hipSuccess) return rc;
+                                int32_t m, const PruneScratch& ps, int32_t* code,
+                                uint32_t spin_limit, uint32_t* err) {
     if (n_rows == 0) return hipSuccess;
+    const VectorSet set = vector_set(ps, spin_limit, err);
     const int L = m + 1;
-    int64_t blocks = (n_rows + 256 * kPruneRows - 1) / (256 * kPruneRows);
-    // several workgroups per slot of the device, so that the last ones to start have little left
-    if (blocks > (int64_t)n_cu * 32) blocks = (int64_t)n_cu * 32;
-#define SUREL_PRUNE_CASE(NW_)                                                                  \
-    if ((L + 1) / 2 == (NW_)) {                                                                \
-        hipLaunchKernelGGL((prune_collect_kernel<NW_>), dim3((unsigned)blocks), dim3(256), 0,  \
-                           stream, cnt, n_rows, L, slots, (uint32_t)(n_slots - 1), cap_T,      \
-                           counters, code, spin_limit, err);                                   \
-        return hipGetLastError();                                                              \
+    // 16-byte pieces of a tile per lane: 256 * L counts are 32 * L of them
+    switch (L) {
+        case 2: return launch_collect<2, 1>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 3: return launch_collect<3, 2>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 4: return launch_collect<4, 2>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 5: return launch_collect<5, 3>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 6: return launch_collect<6, 3>(stream, n_cu, cnt, n_rows, L, code, set);
+        default: return launch_collect<0, 8>(stream, n_cu, cnt, n_rows, L, code, set);
     }
-    SUREL_PRUNE_CASE(1)
-    SUREL_PRUNE_CASE(2)
-    SUREL_PRUNE_CASE(3)
-    SUREL_PRUNE_CASE(4)
-    SUREL_PRUNE_CASE(5)
-    SUREL_PRUNE_CASE(6)
-    SUREL_PRUNE_CASE(7)
-    SUREL_PRUNE_CASE(8)
-#undef SUREL_PRUNE_CASE
-    return hipErrorInvalidValue;
 }
 
-hipError_t launch_prune_finish(hipStream_t stream, int n_cu, int64_t n_rows, int32_t m,
-                               int64_t cap_T, int64_t n_T, uint32_t* slots,
-                               unsigned long long* counters, uint32_t* list, uint16_t* T,
-                               int32_t* code) {
-    if (n_T > 0) {
-        const int64_t n_slots = prune_slots(cap_T);
-        int64_t len = 1;
-        while (len < n_T) len *= 2;  // <= prune_list_len(cap_T) because n_T <= cap_T
-        hipLaunchKernelGGL(prune_gather_kernel, dim3((unsigned)((n_slots + 255) / 256)), dim3(256), 0,
-                           stream, slots, (uint32_t)n_slots, len, counters + 1, list);
-        if (len > n_T)
-            hipLaunchKernelGGL(prune_pad_kernel, dim3((unsigned)((len - n_T + 255) / 256)),
-                               dim3(256), 0, stream, list, n_T, len);
-        for (int64_t k = 2; k <= len; k *= 2)
-            for (int64_t j = k / 2; j >= 1; j /= 2)
-                hipLaunchKernelGGL(prune_sort_step_kernel, dim3((unsigned)((len + 255) / 256)),
-                                   dim3(256), 0, stream, list, len, j, k);
-        hipLaunchKernelGGL(prune_rank_kernel, dim3((unsigned)((n_T + 255) / 256)), dim3(256), 0,
-                           stream, list, n_T, m + 1, slots, T);
+static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int64_t n_known,
+                         int64_t most, int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
+                         int32_t* code) {
+    int64_t blocks = ((d_rows ? cap_rows : n_rows) / 4 + 256) / 256;
+    if (blocks > (int64_t)n_cu * 32) blocks = (int64_t)n_cu * 32;
+    hipLaunchKernelGGL(prune_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, ps.ranks,
+                       ps.counters, n_known, most, n_rows, d_rows, cap_rows, code);
+}
+
+int64_t prune_rank_most(int64_t cap_T) { return cap_T < kRankMost ? cap_T : kRankMost; }
+
+hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
+                              int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
+                              int32_t* code, int64_t* h_n_T) {
+    const int64_t most = prune_rank_most(ps.cap_T);
+    const int L = m + 1;
+    switch ((L + 1) / 2) {
+#define SUREL_RANK_CASE(NW_)                                                                     \
+    case NW_:                                                                                    \
+        hipLaunchKernelGGL((prune_rank_pairs_kernel<NW_>), dim3(kRankBlocks), dim3(kRankTile), 0, \
+                           stream, ps.members, ps.counters, most, ps.ranks);                     \
+        break;
+        SUREL_RANK_CASE(1)
+        SUREL_RANK_CASE(2)
+        SUREL_RANK_CASE(3)
+        SUREL_RANK_CASE(4)
+        SUREL_RANK_CASE(5)
+        SUREL_RANK_CASE(6)
+        SUREL_RANK_CASE(7)
+        SUREL_RANK_CASE(8)
+#undef SUREL_RANK_CASE
+        default: return hipErrorInvalidValue;
     }
-    if (n_rows > 0) {
-        int64_t blocks = (n_rows / 4 + 256) / 256;
-        if (blocks > (int64_t)n_cu * 32) blocks = (int64_t)n_cu * 32;
-        hipLaunchKernelGGL(prune_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, slots,
-                           (uint32_t)prune_slots(cap_T), n_rows, code);
-    }
+    hipLaunchKernelGGL(prune_place_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.counters,
+                       most, L, ps.ranks, T, h_n_T);
+    launch_codes(stream, n_cu, ps, -1, most, n_rows, d_rows, cap_rows, code);
+    hipLaunchKernelGGL(prune_clean_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.cap_T,
+                       ps.slots, ps.counters);
+    return hipGetLastError();
+}
+
+hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
+                                   int64_t n_rows, int64_t n_T, uint16_t* T, int32_t* code) {
+    int64_t len = 1;
+    while (len < n_T) len *= 2;  // <= prune_list_len(cap_T) because n_T <= cap_T
+    if (len > n_T)
+        hipLaunchKernelGGL(prune_pad_kernel, dim3((unsigned)((len - n_T + 255) / 256)), dim3(256), 0,
+                           stream, ps.members, n_T, len);
+    for (int64_t k = 2; k <= len; k *= 2)
+        for (int64_t j = k / 2; j >= 1; j /= 2)
+            hipLaunchKernelGGL(prune_sort_step_kernel, dim3((unsigned)((len + 255) / 256)),
+                               dim3(256), 0, stream, ps.members, len, j, k);
+    hipLaunchKernelGGL(prune_rank_kernel, dim3((unsigned)((n_T + 255) / 256)), dim3(256), 0, stream,
+                       ps.members, n_T, m + 1, ps.slots, ps.ranks, T);
+    launch_codes(stream, n_cu, ps, n_T, n_T, n_rows, nullptr, n_rows, code);
     return hipGetLastError();
 }
 

@@ -1,19 +1,38 @@
 // The hash set of distinct count vectors behind the pruning of the central RPE array (Sec. 3.3;
 // Algorithm 1, last step), shared by the stand-alone pruning kernels and the fused walk + RPE
-// kernel when it emits RPE-IDs: a global open-addressing table of 64-byte slots (state, rank,
-// vector in one cache line) and a small per-workgroup cache of (vector -> slot) in LDS in front
-// of it.  A vector is NW 32-bit words, entry 2k of the count vector in the upper half of word k,
-// so that comparing words in order compares the counts in order.
+// kernel when it emits RPE-IDs: a global open-addressing table of 64-byte slots (state, number,
+// vector in one cache line) with small per-workgroup tables in LDS in front of it.  A vector is NW
+// 32-bit words, entry 2k of the count vector in the upper half of word k, so that comparing words
+// in order compares the counts in order.  The vectors of the set are numbered in the order in
+// which they are inserted; a vector's number is what a row is given until the numbers become
+// places in the sorted array T.
 #pragma once
 
 #include "device_util.h"
+#include "kernels.h"
 
 namespace surel {
 
 constexpr uint32_t kSlotEmpty = 0u, kSlotLocked = 1u, kSlotFull = 2u;
-constexpr int kSlotWords = 16;    // 64-byte slots: [0] state, [1] rank, [2..3] unused, [4..11] vector
+constexpr int kSlotWords = 16;    // 64-byte slots: [0] state, [1] number, [2..3] unused, [4..11] vector
 constexpr int kSlotVector = 4;    // first word of the vector inside a slot
 constexpr int kMaxVecWords = 8;   // m + 1 <= 16 counts of 16 bits
+constexpr int kItemWords = kMaxVecWords + 1;  // a member of the set: its vector, zeros, its slot
+
+// The set.  members[i] = vector number i and its slot (kItemWords words; i < cap_T), ranks[i] = 0:
+// written by whoever inserts it.  *n_inserted = vectors inserted so far.
+struct VectorSet {
+    uint32_t* slots;
+    uint32_t slot_mask;
+    int64_t cap_T;
+    uint32_t* members;
+    uint32_t* ranks;
+    unsigned long long* n_inserted;
+    uint32_t spin_limit;
+    uint32_t* err;
+};
+
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err);
 
 template <int NW>
 __device__ __forceinline__ uint32_t hash_vector(const uint32_t (&w)[NW]) {
@@ -26,37 +45,42 @@ __device__ __forceinline__ uint32_t hash_vector(const uint32_t (&w)[NW]) {
     return h;
 }
 
-// Finds (or inserts) vector w, first probe at slot h; returns its slot number, or -1 if a wait
-// ran out or the table is full.  *n_inserted counts the vectors inserted so far (the size of T
-// when collect has ended).
+// Finds (or inserts) vector w, first probe at slot h; returns its number, or -1 if a wait ran out
+// or the table is full.
 template <int NW>
 __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint32_t h,
-                                                  uint32_t* __restrict__ slots, uint32_t slot_mask,
-                                                  int64_t cap_T,
-                                                  unsigned long long* __restrict__ n_inserted,
-                                                  uint32_t spin_limit, uint32_t* __restrict__ err) {
+                                                  const VectorSet& set) {
     uint32_t spins = 0;
-    for (uint32_t probe = 0; probe <= slot_mask;) {
-        uint32_t* slot = slots + (size_t)h * kSlotWords;
-        // a slot that reads as full is final, and its vector lies in the same cache line
+    for (uint32_t probe = 0; probe <= set.slot_mask;) {
+        uint32_t* slot = set.slots + (size_t)h * kSlotWords;
+        // a slot that reads as full is final, and all of it lies in the same cache line
         uint32_t st = slot[0];
         if (st != kSlotFull) {
             st = atomicCAS(slot, kSlotEmpty, kSlotLocked);
             if (st == kSlotEmpty) {
                 // this lane owns the slot: is there still room in T?
-                const unsigned long long before = atomicAdd(n_inserted, 1ull);
-                if ((int64_t)before >= cap_T) atomicOr(err, kDevCapacity);
+                const unsigned long long number = atomicAdd(set.n_inserted, 1ull);
+                if ((int64_t)number >= set.cap_T) {
+                    atomicOr(set.err, kDevCapacity);
+                } else {
+                    uint32_t* item = set.members + number * kItemWords;
+#pragma unroll
+                    for (int k = 0; k < kMaxVecWords; ++k) item[k] = k < NW ? w[k < NW ? k : 0] : 0u;
+                    item[kMaxVecWords] = h;
+                    set.ranks[number] = 0u;
+                }
+                __hip_atomic_store(slot + 1, (uint32_t)number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                 for (int k = 0; k < NW; ++k)
                     __hip_atomic_store(slot + kSlotVector + k, w[k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(slot, kSlotFull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                return (int32_t)h;
+                return (int32_t)number;
             }
             if (st == kSlotLocked) {
                 // somebody is writing this slot's vector: look again
-                if (++spins > spin_limit) {
-                    atomicOr(err, kDevStall);
+                if (++spins > set.spin_limit) {
+                    atomicOr(set.err, kDevStall);
                     return -1;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -68,129 +92,97 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
             for (int k = 0; k < NW; ++k)
                 same = same && __hip_atomic_load(slot + kSlotVector + k, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT) == w[k];
-            if (same) return (int32_t)h;
+            if (same)
+                return (int32_t)__hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             bool same = true;
 #pragma unroll
             for (int k = 0; k < NW; ++k) same = same && slot[kSlotVector + k] == w[k];
-            if (same) return (int32_t)h;
+            if (same) return (int32_t)slot[1];
         }
-        h = (h + 1u) & slot_mask;
+        h = (h + 1u) & set.slot_mask;
         probe += 1;
     }
     return -1;
 }
 
-constexpr int kCacheEntries = 256;   // per-workgroup LDS cache of (vector -> slot), direct mapped
-constexpr int kCacheWords = 12;      // [0] state, [1] slot, [2..3] unused, [4..11] vector
+// The LDS tables of a workgroup (kSetCacheWords words, all zero at the start).
+//
+// Vectors of 2 .. 6 counts have two of them.  The first is a plain array: where the first count is
+// zero (every row but the seed's own) and the others are small, the counts themselves, a few bits
+// each, are the index, so nothing is hashed and nothing compared, and an entry (number + 1, 0 =
+// not known yet) may be written by anybody at any time.  Nearly all rows are of that kind: a node
+// that one or a few of a seed's walks met.  The second, for the rest, is a cache of (vector ->
+// number) with entries of one LDS read.  (All rows went through a hashed cache before: 25 against
+// about 60 instructions a row, and a wave took as long as its slowest lane's walk through the
+// global table.)
+// Longer vectors have one cache with entries of as many words as they need.
+constexpr int kDirectWords = 4096;
+constexpr int kHashedWords = 2048;
+constexpr int kSetCacheWords = kDirectWords + kHashedWords;  // 24 KB
 
-
-// Clears a workgroup's cache (every thread of the workgroup calls it, a barrier follows).
-__device__ __forceinline__ void prune_cache_clear(uint32_t* cache, int tid, int n_threads) {
-    for (int t = tid; t < kCacheEntries; t += n_threads) cache[t * kCacheWords] = 0u;
+__device__ __forceinline__ void set_cache_clear(uint32_t* cache, int tid, int n_threads) {
+    for (int t = tid; t < kSetCacheWords; t += n_threads) cache[t] = 0u;
 }
 
-// The slot of vector w: from the workgroup's cache if it is there, else from the global table
-// (inserting it if it is new), remembering it in the cache when its entry is still free.  An
-// entry is written once, by the lane that wins its state word, and is valid for good after that
-// (state, then vector and slot, then "valid": LDS operations of a wave take effect in order), so
-// readers never see a mix of two vectors.  Returns the slot number, or -1 (see find_or_insert).
-template <int NW>
-__device__ __forceinline__ int32_t prune_lookup(const uint32_t (&w)[NW], uint32_t* cache,
-                                                uint32_t* __restrict__ slots, uint32_t slot_mask,
-                                                int64_t cap_T,
-                                                unsigned long long* __restrict__ n_inserted,
-                                                uint32_t spin_limit, uint32_t* __restrict__ err) {
-    const uint32_t hv = hash_vector<NW>(w);
-    uint32_t* entry = cache + ((hv >> 20) & (kCacheEntries - 1)) * kCacheWords;
-    if (entry[0] == 2u) {
-        bool same = true;
+template <int LT>
+struct DirectIndex {
+    static_assert(LT >= 2 && LT <= 6, "direct index of 2 .. 6 counts");
+    static constexpr int NW = (LT + 1) / 2;
+    static constexpr int kBits = LT == 2 ? 12 : LT == 3 ? 6 : LT == 4 ? 4 : LT == 5 ? 3 : 2;
+    static_assert(kBits * (LT - 1) <= 12, "the index must stay inside the table");
+    // pair[k] holds entry 2k in its lower and entry 2k + 1 in its upper half (zero past the last).
+    // Returns whether the vector has an index; *index is below kDirectWords in any case.
+    static __device__ __forceinline__ bool of(const uint32_t (&pair)[NW], uint32_t* index) {
+        constexpr uint32_t kMost = (1u << kBits) - 1u;
+        uint32_t outside = pair[0] & ~(kMost << 16);
+        uint32_t at = 0;
 #pragma unroll
-        for (int k = 0; k < NW; ++k) same = same && entry[4 + k] == w[k];
-        if (same) return (int32_t)entry[1];
-    }
-    const int32_t found = find_or_insert<NW>(w, hv & slot_mask, slots, slot_mask, cap_T, n_inserted,
-                                             spin_limit, err);
-    if (found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
+        for (int k = 1; k < NW; ++k) outside |= pair[k] & ~(kMost << 16 | kMost);
 #pragma unroll
-        for (int k = 0; k < NW; ++k) entry[4 + k] = w[k];
-        entry[1] = (uint32_t)found;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __hip_atomic_store(entry, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    return found;
-}
-
-// The same in front of a kernel that does not know the vector length at compile time: w holds
-// kMaxVecWords words of which the first nw can be non-zero, a cache entry is 2 + nw words (state,
-// slot, vector), so that short vectors get many entries out of a fixed LDS budget:
-// kFusedCacheWords words hold fused_cache_entries(nw) entries (a power of two).
-constexpr int kFusedCacheWords = 6144;  // 24 KB
-__host__ __device__ constexpr int fused_cache_entries(int nw) {
-    int e = 64;
-    while (e * 2 * (2 + nw) <= kFusedCacheWords) e *= 2;
-    return e;
-}
-__device__ __forceinline__ void fused_cache_clear(uint32_t* cache, int nw, int tid, int n_threads) {
-    const int n = fused_cache_entries(nw);
-    for (int t = tid; t < n; t += n_threads) cache[t * (2 + nw)] = 0u;
-}
-__device__ __forceinline__ int32_t prune_lookup_any(const uint32_t (&w)[kMaxVecWords], int nw,
-                                                    uint32_t* cache, uint32_t* __restrict__ slots,
-                                                    uint32_t slot_mask, int64_t cap_T,
-                                                    unsigned long long* __restrict__ n_inserted,
-                                                    uint32_t spin_limit,
-                                                    uint32_t* __restrict__ err) {
-    const uint32_t hv = hash_vector<kMaxVecWords>(w);
-    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(fused_cache_entries(nw) - 1)) * (2 + nw);
-    if (entry[0] == 2u) {
-        bool same = true;
-#pragma unroll
-        for (int k = 0; k < kMaxVecWords; ++k)
-            if (k < nw) same = same && entry[2 + k] == w[k];
-        if (same) return (int32_t)entry[1];
-    }
-    const int32_t found = find_or_insert<kMaxVecWords>(w, hv & slot_mask, slots, slot_mask, cap_T,
-                                                       n_inserted, spin_limit, err);
-    if (found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
-#pragma unroll
-        for (int k = 0; k < kMaxVecWords; ++k)
-            if (k < nw) entry[2 + k] = w[k];
-        entry[1] = (uint32_t)found;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __hip_atomic_store(entry, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    return found;
-}
-
-// For vectors of at most three words (m + 1 <= 6, the usual walk lengths) with the length known
-// at compile time, the cache entries are packed: [0] 0 = free, 1 = being written, 2^31 | slot =
-// valid; [1 .. NW] the vector; 2 words an entry for NW = 1, else 4, so that an entry is one LDS
-// read.  The entry is read as a whole: should the read ever see the valid word next to vector
-// words that are not yet there, the comparison fails and the lane asks the global table, which is
-// slower and right; a valid entry never changes again.
-template <int NW>
-struct PackedCache {
-    static_assert(NW >= 1 && NW <= 3, "packed cache entries hold up to three words");
-    static constexpr int kEntryWords = NW == 1 ? 2 : 4;
-    static constexpr int entries() {
-        int e = 64;
-        while (e * 2 * kEntryWords <= kFusedCacheWords) e *= 2;
-        return e;
+        for (int e = 1; e < LT; ++e)
+            at |= ((pair[e / 2] >> (e % 2 ? 16 : 0)) & kMost) << (kBits * (e - 1));
+        *index = at;
+        return outside == 0u;
     }
 };
-constexpr uint32_t kPackedValid = 0x80000000u;
 
+// find_or_insert for the lanes with `pending` set (all lanes of the wavefront call it together).
+// One lane goes to the global table for all lanes with the same vector: when a kernel starts,
+// nothing is known yet and every row is looked up there, most of them one of a handful of vectors,
+// and additions to one address are served one after the other, 13 ns each (350,000 of them, from
+// all waves' first tiles, were 3 ms of the pruning of 138 M rows).
 template <int NW>
-__device__ __forceinline__ int32_t prune_lookup_packed(const uint32_t (&w)[NW], uint32_t* cache,
-                                                       uint32_t* __restrict__ slots,
-                                                       uint32_t slot_mask, int64_t cap_T,
-                                                       unsigned long long* __restrict__ n_inserted,
-                                                       uint32_t spin_limit,
-                                                       uint32_t* __restrict__ err) {
-    constexpr int EW = PackedCache<NW>::kEntryWords;
+__device__ __forceinline__ int32_t find_or_insert_shared(const uint32_t (&w)[NW], uint32_t h,
+                                                         bool pending, const VectorSet& set, int lane) {
+    int leader = lane;
+    bool open = pending;
+    for (uint64_t left = __ballot(open); left != 0ull; left = __ballot(open)) {
+        const int first = __builtin_ctzll(left);
+        bool same = open;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) same = same && wave_bcast_u32(w[k], first) == w[k];
+        if (same) leader = first, open = false;
+    }
+    int32_t number = -1;
+    if (pending && leader == lane) number = find_or_insert<NW>(w, h, set);
+    return __shfl(number, leader, kWave);
+}
+
+// The number of vector w from the hashed cache or the global table (all lanes call it together,
+// those without `valid` get -1).  Entries of vectors of at most three words: [0] 0 = free, 1 =
+// being written, 2^31 | number = valid; [1 .. NW] the vector; 2 words for NW = 1, else 4, so that
+// an entry is one LDS read.  Should the read ever see the valid word next to vector words that are
+// not yet there, the comparison fails and the lane asks the global table, which is slower and
+// right; a valid entry never changes again.
+constexpr uint32_t kPackedValid = 0x80000000u;
+template <int NW>
+__device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool valid, uint32_t* cache,
+                                                 const VectorSet& set, int lane) {
+    static_assert(NW >= 1 && NW <= 3, "packed cache entries hold up to three words");
+    constexpr int EW = NW == 1 ? 2 : 4;
     const uint32_t hv = hash_vector<NW>(w);
-    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(PackedCache<NW>::entries() - 1)) * EW;
+    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(kHashedWords / EW - 1)) * EW;
     uint32_t e[4] = {0u, 0u, 0u, 0u};
     if constexpr (EW == 2) {
         const uint2 v = *reinterpret_cast<const uint2*>(entry);
@@ -199,27 +191,144 @@ __device__ __forceinline__ int32_t prune_lookup_packed(const uint32_t (&w)[NW], 
         const uint4 v = *reinterpret_cast<const uint4*>(entry);
         e[0] = v.x, e[1] = v.y, e[2] = v.z, e[3] = v.w;
     }
-    if (e[0] & kPackedValid) {
-        bool same = true;
+    bool hit = valid && (e[0] & kPackedValid) != 0u;
 #pragma unroll
-        for (int k = 0; k < NW; ++k) same = same && e[1 + k] == w[k];
-        if (same) return (int32_t)(e[0] & ~kPackedValid);
-    }
-    const int32_t found = find_or_insert<NW>(w, hv & slot_mask, slots, slot_mask, cap_T, n_inserted,
-                                             spin_limit, err);
-    if (found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
+    for (int k = 0; k < NW; ++k) hit = hit && e[1 + k] == w[k];
+    const bool miss = valid && !hit;
+    int32_t number = hit ? (int32_t)(e[0] & ~kPackedValid) : -1;
+    if (__ballot(miss) != 0ull) {
+        const int32_t found = find_or_insert_shared<NW>(w, hv & set.slot_mask, miss, set, lane);
+        if (miss) number = found;
+        if (miss && found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
 #pragma unroll
-        for (int k = 0; k < NW; ++k) entry[1 + k] = w[k];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __hip_atomic_store(entry, kPackedValid | (uint32_t)found, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int k = 0; k < NW; ++k) entry[1 + k] = w[k];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __hip_atomic_store(entry, kPackedValid | (uint32_t)found, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
     }
-    return found;
+    return number;
 }
 
-// Clears the whole cache: all-zero words are free entries in both layouts.
-__device__ __forceinline__ void fused_cache_clear_all(uint32_t* cache, int tid, int n_threads) {
-    for (int t = tid; t < kFusedCacheWords; t += n_threads) cache[t] = 0u;
+// The same for vectors of nw <= kMaxVecWords words (the others zero): entries of 2 + nw words
+// (state, number, vector).  An entry is written once, by the lane that wins its state word, and is
+// valid for good after that (state, then vector and number, then "valid": LDS operations of a wave
+// take effect in order).
+__device__ __forceinline__ int32_t lookup_any(const uint32_t (&w)[kMaxVecWords], bool valid, int nw,
+                                              uint32_t* cache, const VectorSet& set, int lane) {
+    int entries = 64;
+    while (entries * 2 * (2 + nw) <= kSetCacheWords) entries *= 2;
+    const uint32_t hv = hash_vector<kMaxVecWords>(w);
+    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(entries - 1)) * (2 + nw);
+    bool hit = valid && entry[0] == 2u;
+#pragma unroll
+    for (int k = 0; k < kMaxVecWords; ++k)
+        if (k < nw) hit = hit && entry[2 + k] == w[k];
+    const bool miss = valid && !hit;
+    int32_t number = hit ? (int32_t)entry[1] : -1;
+    if (__ballot(miss) != 0ull) {
+        const int32_t found = find_or_insert_shared<kMaxVecWords>(w, hv & set.slot_mask, miss, set, lane);
+        if (miss) number = found;
+        if (miss && found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
+#pragma unroll
+            for (int k = 0; k < kMaxVecWords; ++k)
+                if (k < nw) entry[2 + k] = w[k];
+            entry[1] = (uint32_t)found;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __hip_atomic_store(entry, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    return number;
+}
+
+// The vector of row t among the rows at cnt16 (LDS, densely packed), as the aligned words that
+// cover it, shifted into place: pair[k] holds entry 2k in its lower and 2k + 1 in its upper half.
+// n_words: words that hold rows.
+template <int NW>
+__device__ __forceinline__ void row_pairs(const uint32_t* words, int odd, int n_words, int t, int L,
+                                          uint32_t (&pair)[NW]) {
+    const int first = odd + t * L;
+    const uint32_t shift = (uint32_t)(first & 1) * 2u;
+    uint32_t raw[NW + 1];
+#pragma unroll
+    for (int k = 0; k <= NW; ++k) raw[k] = 2 * k <= L ? words[min((first >> 1) + k, n_words - 1)] : 0u;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        pair[k] = __builtin_amdgcn_alignbyte(raw[k + 1], raw[k], shift);
+        if (2 * k + 1 >= L) pair[k] &= 0xFFFFu;  // the upper half is the next row's
+        if (2 * k >= L) pair[k] = 0u;
+    }
+}
+
+// The numbers of n rows whose counts lie in LDS, to code[0 .. n).  One wavefront; rows that are not
+// in the direct table are put on a list (misses, n words of LDS of the wave's own) and looked up
+// together afterwards, so that few lanes wait for few.  LT = m + 1 at compile time for 2 .. 6, 0 =
+// any.
+template <int LT>
+__device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint16_t* cnt16,
+                                             uint32_t* misses, uint32_t* cache, const VectorSet& set,
+                                             int32_t* __restrict__ code) {
+    const int odd = (int)((reinterpret_cast<uintptr_t>(cnt16) >> 1) & 1u);
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(cnt16 - odd);
+    const int n_words = (odd + n * L + 1) / 2;
+    if constexpr (LT == 0) {
+        for (int t0 = 0; t0 < n; t0 += kWave) {
+            const int t = t0 + lane;
+            uint32_t pair[kMaxVecWords], w[kMaxVecWords];
+            row_pairs<kMaxVecWords>(words, odd, n_words, min(t, n - 1), L, pair);
+#pragma unroll
+            for (int k = 0; k < kMaxVecWords; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
+            const int32_t number = lookup_any(w, t < n, (L + 1) / 2, cache, set, lane);
+            if (t < n) code[t] = number;
+        }
+    } else {
+        constexpr int NW = (LT + 1) / 2;
+        uint32_t* direct = cache;
+        uint32_t* hashed = cache + kDirectWords;
+        int n_miss = 0;
+        for (int t0 = 0; t0 < n; t0 += kWave) {
+            const int t = t0 + lane;
+            uint32_t pair[NW], at;
+            row_pairs<NW>(words, odd, n_words, min(t, n - 1), LT, pair);
+            const bool small = DirectIndex<LT>::of(pair, &at);
+            const uint32_t e = direct[at];
+            const bool hit = small && e != 0u;
+            if (t < n && hit) code[t] = (int32_t)(e - 1u);
+            const uint64_t miss = __ballot(t < n && !hit);
+            if (miss != 0ull) {
+                const int before = (int)__builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(miss >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)miss, 0u));
+                if (t < n && !hit) misses[n_miss + before] = (uint32_t)t;
+                n_miss += __popcll(miss);
+            }
+        }
+        wave_sync();
+        for (int u0 = 0; u0 < n_miss; u0 += kWave) {
+            const bool valid = u0 + lane < n_miss;
+            const int t = (int)misses[valid ? u0 + lane : 0];
+            uint32_t pair[NW], w[NW], at;
+            row_pairs<NW>(words, odd, n_words, t, LT, pair);
+            const bool small = DirectIndex<LT>::of(pair, &at);
+#pragma unroll
+            for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
+            const int32_t number = lookup_hashed<NW>(w, valid, hashed, set, lane);
+            if (valid && small && number >= 0) direct[at] = (uint32_t)number + 1u;
+            if (valid) code[t] = number;
+        }
+        wave_sync();
+    }
+}
+__device__ __forceinline__ void rows_numbers_any(int n, int lane, int L, const uint16_t* cnt16,
+                                                 uint32_t* misses, uint32_t* cache,
+                                                 const VectorSet& set, int32_t* __restrict__ code) {
+    switch (L) {
+        case 2: rows_numbers<2>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 3: rows_numbers<3>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 4: rows_numbers<4>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 5: rows_numbers<5>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 6: rows_numbers<6>(n, lane, L, cnt16, misses, cache, set, code); break;
+        default: rows_numbers<0>(n, lane, L, cnt16, misses, cache, set, code); break;
+    }
 }
 
 }  // namespace surel

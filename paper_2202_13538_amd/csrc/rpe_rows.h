@@ -1,119 +1,143 @@
 // From a wave's sorted walk keys to the rows of one seed's RPE block (Sec. 3.2 "Relative
-// Positional Encoding"): a key is node id << 4 | walk position; id changes start rows,
-// equal-key runs are the landing counts.  Shared by the stand-alone RPE builder and the fused
-// walk + RPE kernel.
+// Positional Encoding"): a key is node id << 4 | walk position; id changes start rows, and every
+// key adds to the count of its (row, position).  Shared by the stand-alone RPE builder and the
+// fused walk + RPE kernels.
 #pragma once
 
 #include "device_util.h"
 
 namespace surel {
 
-constexpr uint32_t kPadKey = 0xFFFFFFFFu;  // sorts last; differs from every valid key in id and position
+// Keys that fill the sort up to 64*E: an id no node has, so they sort last and form one row of
+// their own behind the block's rows.  Their 16 position values keep them from all counting in the
+// same LDS word.
+constexpr uint32_t kPadKeys = 0xFFFFFFF0u;
+__device__ __forceinline__ uint32_t pad_key(int lane) { return kPadKeys | ((uint32_t)lane & 15u); }
+
+// Walk keys of a wave: the sort is compiled for these numbers of keys per lane.
+#define SUREL_FOR_SORT_SIZES(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32)
+
+template <int E>
+__device__ __forceinline__ void copy_keys(uint32_t (&to)[E], const uint32_t (&from)[E]) {
+    to[0] = from[0];
+    if constexpr (E > 1) {
+#pragma unroll
+        for (int r = 1; r < E; ++r) to[r] = from[r];
+    }
+}
 
 // What a lane knows about the rows of the wave's sorted keys (sort position p = lane*E + r).
 struct RpeRowScan {
-    uint32_t before;    // key just before this lane's first (kPadKey for lane 0)
-    uint32_t after;     // key just after this lane's last (kPadKey for lane 63)
-    uint32_t n_head;    // rows that start inside this lane
-    uint32_t incl;      // rows that start in lanes 0..this
-    int32_t n_rows;     // rows of the whole wave (wave-uniform)
-    int32_t run_start;  // sort position where the key run open at this lane's start began
+    uint32_t before;     // key just before this lane's first
+    int32_t first_row;   // row of that key (-1 in lane 0)
+    int32_t n_rows;      // rows of the whole wave (wave-uniform), the padding's not counted
 };
 
 template <int E>
 __device__ __forceinline__ RpeRowScan rpe_scan_rows(const uint32_t (&x)[E], int lane) {
     RpeRowScan sc;
-    sc.before = (uint32_t)__shfl_up((int)x[E - 1], 1, kWave);
-    sc.after = (uint32_t)__shfl_down((int)x[0], 1, kWave);
-    if (lane == 0) sc.before = kPadKey;
-    if (lane == kWave - 1) sc.after = kPadKey;
-    sc.n_head = 0;
-    int32_t last_start = -1;  // sort position of the last key-run start inside this lane
+    sc.before = wave_from_lane_below(x[E - 1]);
+    if (lane == 0) sc.before = ~x[0];  // the first key starts a row
+    uint32_t n_head = 0;
     uint32_t prev = sc.before;
 #pragma unroll
     for (int r = 0; r < E; ++r) {
-        const bool valid = x[r] != kPadKey;
-        sc.n_head += (valid && (x[r] >> 4) != (prev >> 4)) ? 1u : 0u;
-        if (valid && x[r] != prev) last_start = lane * E + r;
+        n_head += (x[r] ^ prev) > 15u ? 1u : 0u;
         prev = x[r];
     }
-    sc.incl = wave_incl_sum(sc.n_head);
-    sc.n_rows = (int32_t)wave_bcast_u32(sc.incl, kWave - 1);
-    sc.run_start = __shfl_up(wave_incl_max(last_start), 1, kWave);
-    if (lane == 0) sc.run_start = -1;
+    const uint32_t incl = wave_incl_sum(n_head);
+    sc.first_row = (int32_t)(incl - n_head) - 1;
+    const bool padded = (uint32_t)__builtin_amdgcn_readlane((int)x[E - 1], kWave - 1) >= kPadKeys;
+    sc.n_rows = (int32_t)wave_bcast_u32(incl, kWave - 1) - (padded ? 1 : 0);
     return sc;
 }
 
-// Assembles the block's rows in LDS: ids_lds gets n_rows words, cnt_lds32 gets n_rows*L uint16
-// (rounded up to whole words).  Ends with the LDS writes ordered before later reads.
+// LDS words that hold up to `rows` rows of a block: ids (behind up to three words that align them
+// like their destination), then counts (behind up to seven counts), each with room for the
+// padding's row.
+__host__ __device__ constexpr int rpe_id_words(int rows) { return (rows + 1 + 3 + 3) & ~3; }
+__host__ __device__ constexpr int rpe_cnt_words(int rows, int L) {
+    return (rows * L + 16 + 7 + 1 + 7) / 8 * 4;
+}
+__host__ __device__ constexpr int rpe_row_words(int rows, int L) {
+    return rpe_id_words(rows) + rpe_cnt_words(rows, L);
+}
+
+// Assembles rows [row0, row0 + n) of the block in LDS: ids[0 .. n) and counts cnt16[0 .. n*L).
+// cnt_words: the 16-byte aligned words that hold cnt16, which starts `head` counts in; they are
+// cleared here.  The key of position 0, if `start_weight` is not 0, stands for that many walks
+// that start at its node.  Ends with the LDS writes ordered before later reads.
+// No lane is ever masked out: every key of a row writes the row's id, a key's count is an
+// addition in LDS (no runs of equal keys to be found), and the rows outside the window, like the
+// padding's, all go to the row behind it.
 template <int E>
 __device__ __forceinline__ void rpe_assemble_rows(const uint32_t (&x)[E], const RpeRowScan& sc,
-                                                  int lane, int L, uint32_t* ids_lds,
-                                                  uint32_t* cnt_lds32) {
-    uint16_t* cnt_lds = reinterpret_cast<uint16_t*>(cnt_lds32);
-    const int n_cnt = sc.n_rows * L;
-    for (int t = lane; t < (n_cnt + 1) / 2; t += kWave) cnt_lds32[t] = 0u;
+                                                  int lane, int L, int row0, int n,
+                                                  uint32_t start_weight, uint32_t* ids,
+                                                  uint32_t* cnt_words, int head) {
+    uint4* clear = reinterpret_cast<uint4*>(cnt_words);
+    for (int t = lane; t * 8 < head + n * L; t += kWave) clear[t] = make_uint4(0u, 0u, 0u, 0u);
     wave_sync();
     uint32_t prev = sc.before;
-    int32_t run_start = sc.run_start;
-    int32_t row = (int32_t)(sc.incl - sc.n_head) - 1;  // row of the last key before this lane
+    int32_t row = sc.first_row - row0;
 #pragma unroll
     for (int r = 0; r < E; ++r) {
         const uint32_t key = x[r];
-        const uint32_t next = (r + 1 < E) ? x[(r + 1 < E) ? r + 1 : r] : sc.after;
-        const bool valid = key != kPadKey;
-        const int32_t e = lane * E + r;
-        if (valid && (key >> 4) != (prev >> 4)) {
-            row += 1;
-            ids_lds[row] = key >> 4;
-        }
-        if (valid && key != prev) run_start = e;
-        if (valid && key != next)
-            cnt_lds[row * L + (int)(key & 15u)] = (uint16_t)(e - run_start + 1);
+        row += (key ^ prev) > 15u ? 1 : 0;
         prev = key;
+        const uint32_t to = min((uint32_t)row, (uint32_t)n);
+        const uint32_t pos = key & 15u;
+        const uint32_t weight = start_weight != 0u && pos == 0u ? start_weight : 1u;
+        const uint32_t at = (uint32_t)head + (uint32_t)__umul24(to, (uint32_t)L) + pos;
+        ids[to] = key >> 4;
+        atomicAdd(cnt_words + (at >> 1), weight << ((at & 1u) * 16u));
     }
     wave_sync();
 }
 
-// Streams an assembled block out to rows [off, off + n_rows) of the table: ids as dwords,
-// counts (unless cnt is null: a table that carries RPE-IDs only) as dwords where the
-// destination's alignment allows.
-__device__ __forceinline__ void rpe_stream_rows(int n_rows, int lane, int L, const uint32_t* ids_lds,
-                                                const uint32_t* cnt_lds32, int64_t off,
-                                                int32_t* __restrict__ ids,
-                                                uint16_t* __restrict__ cnt) {
-    const uint16_t* cnt_lds = reinterpret_cast<const uint16_t*>(cnt_lds32);
-    const int n_cnt = n_rows * L;
-    int32_t* out_ids = ids + off;
-    for (int t = lane; t < n_rows; t += kWave) out_ids[t] = (int32_t)ids_lds[t];
-    if (cnt == nullptr) return;
-
-    const int64_t d0 = off * L;  // first destination element (uint16 units)
-    const int head = (int)(d0 & 1);
-    uint16_t* out_cnt = cnt + d0;
-    if (head && lane == 0) out_cnt[0] = cnt_lds[0];
-    const int n_pair = (n_cnt - head) / 2;
-    uint32_t* out32 = reinterpret_cast<uint32_t*>(out_cnt + head);
-    if (head == 0) {
-        for (int t = lane; t < n_pair; t += kWave) out32[t] = cnt_lds32[t];
-    } else {
-        for (int t = lane; t < n_pair; t += kWave) {
-            const uint32_t a = cnt_lds[1 + 2 * t];
-            const uint32_t b = cnt_lds[2 + 2 * t];
-            out32[t] = a | (b << 16);
-        }
-    }
-    if (((n_cnt - head) & 1) && lane == 0) out_cnt[n_cnt - 1] = cnt_lds[n_cnt - 1];
+// Moves n 32-bit words, or 16-bit counts, from LDS to global memory, 16 bytes per
+// lane where it can: src lies at the same place inside a 16-byte piece as dst.
+template <typename T>
+__device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst, int n, int lane) {
+    constexpr int kPer = 16 / (int)sizeof(T);
+    const int head = (int)((reinterpret_cast<uintptr_t>(dst) / sizeof(T)) & (kPer - 1));
+    const int lead = min((kPer - head) & (kPer - 1), n);
+    const int n_quads = (n - lead) / kPer;
+    const int tail = lead + n_quads * kPer;
+    if (lane < lead) dst[lane] = src[lane];
+    const uint4* s4 = reinterpret_cast<const uint4*>(src + lead);
+    uint4* d4 = reinterpret_cast<uint4*>(dst + lead);
+    for (int t = lane; t < n_quads; t += kWave) d4[t] = s4[t];
+    if (lane < n - tail) dst[tail + lane] = src[tail + lane];
 }
 
-template <int E>
+// Writes the block's rows to rows [off, off + sc.n_rows) of the table, at most lds_rows of them
+// at a time (lds: rpe_row_words(lds_rows, L) words, 16-byte aligned; blocks that need more than
+// one turn are rare, the LDS of a wave decides how many waves a compute unit holds).  cnt may be
+// null: a table that carries RPE-IDs only.  each(row0, n, cnt16, free_words) is called for every
+// turn while its counts lie in LDS (from cnt16 on), with n words of LDS that are free again.
+template <int E, typename Each>
 __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const RpeRowScan& sc,
-                                               int lane, int L, uint32_t* ids_lds,
-                                               uint32_t* cnt_lds32, int64_t off,
+                                               int lane, int L, uint32_t start_weight,
+                                               uint32_t* lds, int lds_rows, int64_t off,
                                                int32_t* __restrict__ ids,
-                                               uint16_t* __restrict__ cnt) {
-    rpe_assemble_rows<E>(x, sc, lane, L, ids_lds, cnt_lds32);
-    rpe_stream_rows(sc.n_rows, lane, L, ids_lds, cnt_lds32, off, ids, cnt);
+                                               uint16_t* __restrict__ cnt, Each&& each) {
+    uint32_t* cnt_words = lds + rpe_id_words(lds_rows);
+    for (int row0 = 0; row0 < sc.n_rows; row0 += lds_rows) {
+        const int n = min(lds_rows, sc.n_rows - row0);
+        int32_t* dst_ids = ids + off + row0;
+        uint16_t* dst_cnt = cnt == nullptr ? nullptr : cnt + (off + row0) * L;
+        uint32_t* lds_ids = lds + (int)((reinterpret_cast<uintptr_t>(dst_ids) >> 2) & 3u);
+        const int head = (int)((reinterpret_cast<uintptr_t>(dst_cnt) >> 1) & 7u);
+        rpe_assemble_rows<E>(x, sc, lane, L, row0, n, start_weight, lds_ids, cnt_words, head);
+        const uint16_t* cnt16 = reinterpret_cast<const uint16_t*>(cnt_words) + head;
+        stream_aligned(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane);
+        wave_sync();
+        each(row0, n, cnt16, lds_ids);
+        if (cnt != nullptr) stream_aligned(cnt16, dst_cnt, n * L, lane);
+        wave_sync();  // the LDS words are free again
+    }
 }
 
 }  // namespace surel

@@ -140,11 +140,12 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
 EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     EdgeRecords plan;
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
-    plan.lo_bits = bits_for((uint64_t)n_edges);
-    // packed records where they matter (an array well beyond the caches) and where ordinary
-    // degrees fit their field; the wide layout otherwise
-    const bool packed = n_edges >= (1ll << 22) && rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12;
-    plan.format = packed ? kRecPacked : kRecWide;
+    plan.lo_bits = bits_for((uint64_t)n_edges);   // 31 at most
+    // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
+    // small graphs the packed array fits more of its lines into the L2s: SMALLFIG)
+    plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
+    // the degree lies in the word's upper half
+    if (plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
     return plan;
 }
 

@@ -9,12 +9,13 @@ namespace surel {
 // Per-edge neighbour records: one record per CSR entry e with the neighbour col_idx[e], the start
 // of that neighbour's row and its degree, so that a step is one gather instead of two dependent
 // ones.  Two layouts:
-//   kRecWide    int4 (id, row start, degree, 0); id -1 for an entry that names no node or whose
-//               row is malformed;
 //   kRecPacked  one 64-bit word, id in the low id_bits, row start in the next lo_bits, degree in
 //               the rest; id = n_nodes marks a bad entry, a degree field of all ones means "does
-//               not fit, it is row_ptr[id + 1] - row start".  Half the bytes: the seed's own row
-//               and the rows of its neighbours take fewer cache lines.
+//               not fit, it is row_ptr[id + 1] - row start".  id_bits + lo_bits >= 32: the degree
+//               lies in the upper half of the word;
+//   kRecWide    int4 (id, row start, degree, 0); id -1 for an entry that names no node or whose
+//               row is malformed: for graphs whose ids and row starts leave the packed degree too
+//               few bits.
 constexpr int kRecNone = 0, kRecWide = 1, kRecPacked = 2;
 
 // Bits of the degree field of a packed record: what the two other fields leave, 31 at most.
@@ -49,23 +50,27 @@ __device__ __forceinline__ bool seed_row(const WalkGraph& g, int32_t u, int32_t*
 // ignores.  Step s uses word (s-1)&3 of Philox(counter (u, w, (s-1)>>2, 0), key).
 // Returns true if a malformed CSR row or a neighbour id outside the graph was met (the
 // walker then stays in place for that step).
-template <int kRec, int C, typename Visit>
+// With records nothing here branches on the lane: a walker that does not move (no neighbours, or
+// inactive, which is the same thing to it) reads record 0 and keeps its state by selects.
+template <int kRec, int C, bool kPeel = true, typename Visit>
 __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t u_lo, int32_t u_deg,
                                           const int (&w)[C], const bool (&active)[C], int m,
                                           uint32_t key0, uint32_t key1, int32_t* const (&row)[C],
                                           Visit&& visit) {
     bool bad_graph = false;
-    int32_t cur[C], cur_lo[C], cur_deg[C];  // cur_lo / cur_deg: row of `cur` (kRec only)
+    int32_t cur[C];
+    uint32_t cur_lo[C], cur_deg[C];  // row of `cur`, of degree 0 if the walker does not move (kRec only)
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         cur[c] = u;
-        cur_lo[c] = u_lo;
-        cur_deg[c] = u_deg;
+        cur_lo[c] = (uint32_t)u_lo;
+        cur_deg[c] = active[c] ? (uint32_t)u_deg : 0u;
         row[c][0] = u;
     }
     // One group of four steps (one Philox call).  The first group is written out on its own:
     // there s0 is the constant 1, so the steps' row offsets and the Philox counter are known
-    // at compile time (walks of up to four steps never leave it).
+    // at compile time (walks of up to four steps never leave it).  kPeel false: not written out,
+    // which is half the code.
     auto group = [&](const int s0) __attribute__((always_inline)) {
         uint32_t r[C][4];
 #pragma unroll
@@ -76,55 +81,54 @@ __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t
         for (int j = 0; j < 4; ++j) {
             const int s = s0 + j;
             if (s <= m) {
-                if (kRec == kRecWide) {
-                    const int4* rec = static_cast<const int4*>(g.rec);
-                    int4 nb[C];
+                if (kRec != kRecNone) {
+                    uint32_t e[C];
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        const bool go = active[c] && cur_deg[c] > 0;
-                        const uint32_t pick = go ? r[c][j] % (uint32_t)cur_deg[c] : 0u;
-                        nb[c] = make_int4(cur[c], cur_lo[c], cur_deg[c], 0);
-                        if (go) nb[c] = rec[(int64_t)cur_lo[c] + (int64_t)pick];
+                        const uint32_t pick = mod_u32(r[c][j], max(cur_deg[c], 1u));
+                        e[c] = cur_deg[c] != 0u ? cur_lo[c] + pick : 0u;
                     }
+                    uint32_t id[C], lo[C], deg[C];
+                    if (kRec == kRecWide) {
+                        const int4* rec = static_cast<const int4*>(g.rec);
+                        int4 nb[C];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        if (nb[c].x < 0) {
-                            bad_graph = true;
-                        } else {
-                            cur[c] = nb[c].x;
-                            cur_lo[c] = nb[c].y;
-                            cur_deg[c] = nb[c].z;
+                        for (int c = 0; c < C; ++c) nb[c] = rec[e[c]];
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            id[c] = (uint32_t)nb[c].x;  // -1: not below n_nodes
+                            lo[c] = (uint32_t)nb[c].y;
+                            deg[c] = (uint32_t)nb[c].z;
                         }
-                    }
-                } else if (kRec == kRecPacked) {
-                    const unsigned long long* rec = static_cast<const unsigned long long*>(g.rec);
-                    const int deg_shift = g.id_bits + g.lo_bits;
-                    const uint32_t deg_big = (1u << rec_degree_bits(g.id_bits, g.lo_bits)) - 1u;
-                    unsigned long long nb[C];
-                    bool go[C];
+                    } else {
+                        const uint2* rec = static_cast<const uint2*>(g.rec);
+                        const uint32_t id_mask = (1u << g.id_bits) - 1u;
+                        const uint32_t lo_mask = (1u << g.lo_bits) - 1u;  // lo_bits <= 31
+                        const uint32_t deg_shift = (uint32_t)(g.id_bits + g.lo_bits - 32);
+                        const uint32_t deg_big = (1u << rec_degree_bits(g.id_bits, g.lo_bits)) - 1u;
+                        uint2 nb[C];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        go[c] = active[c] && cur_deg[c] > 0;
-                        const uint32_t pick = go[c] ? r[c][j] % (uint32_t)cur_deg[c] : 0u;
-                        nb[c] = 0ull;
-                        if (go[c]) nb[c] = rec[(int64_t)cur_lo[c] + (int64_t)pick];
-                    }
+                        for (int c = 0; c < C; ++c) nb[c] = rec[e[c]];
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        if (!go[c]) continue;
-                        const int32_t id = (int32_t)(nb[c] & ((1ull << g.id_bits) - 1ull));
-                        const int32_t lo = (int32_t)((nb[c] >> g.id_bits) & ((1ull << g.lo_bits) - 1ull));
-                        uint32_t deg = (uint32_t)(nb[c] >> deg_shift) & deg_big;
-                        if (id >= g.n_nodes) {
-                            bad_graph = true;
-                        } else {
+                        for (int c = 0; c < C; ++c) {
+                            id[c] = nb[c].x & id_mask;
+                            lo[c] = __builtin_amdgcn_alignbit(nb[c].y, nb[c].x, (uint32_t)g.id_bits) & lo_mask;
+                            deg[c] = (nb[c].y >> deg_shift) & deg_big;
                             // a degree too large for its field: the record's row was validated
                             // when the records were made, so its end can be taken from the CSR
-                            if (deg == deg_big) deg = (uint32_t)(g.row_ptr[id + 1] - lo);
-                            cur[c] = id;
-                            cur_lo[c] = lo;
-                            cur_deg[c] = (int32_t)deg;
+                            if (deg[c] == deg_big && id[c] < (uint32_t)g.n_nodes)
+                                deg[c] = (uint32_t)g.row_ptr[id[c] + 1] - lo[c];
                         }
+                    }
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const bool go = cur_deg[c] != 0u;
+                        const bool ok = id[c] < (uint32_t)g.n_nodes;
+                        bad_graph = bad_graph || (go && !ok);
+                        const bool move = go && ok;
+                        cur[c] = move ? (int32_t)id[c] : cur[c];
+                        cur_lo[c] = move ? lo[c] : cur_lo[c];
+                        cur_deg[c] = move ? deg[c] : cur_deg[c];
                     }
                 } else {
                     int32_t lo[C], hi[C];
@@ -145,7 +149,7 @@ __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t
                             bad_graph = true;
                         } else if (hi[c] > lo[c]) {
                             const uint32_t deg = (uint32_t)(hi[c] - lo[c]);
-                            nxt[c] = g.col_idx[(int64_t)lo[c] + (int64_t)(r[c][j] % deg)];
+                            nxt[c] = g.col_idx[(int64_t)lo[c] + (int64_t)mod_u32(r[c][j], deg)];
                         }
                     }
 #pragma unroll
@@ -165,8 +169,8 @@ __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t
             }
         }
     };
-    group(1);
-    for (int s0 = 5; s0 <= m; s0 += 4) group(s0);
+    if constexpr (kPeel) group(1);
+    for (int s0 = kPeel ? 5 : 1; s0 <= m; s0 += 4) group(s0);
     return bad_graph;
 }
 
