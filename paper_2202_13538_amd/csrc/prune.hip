@@ -26,33 +26,138 @@
 
 namespace surel {
 
-constexpr int kCollectWaves = 8;   // wavefronts of a workgroup, which share the LDS tables
-constexpr int kCollectRows = 256;  // rows of a wave's tile
+constexpr int kTableWords = kDirectWords + kHashedCollect;
+// Rows of a wave's tile, the list of rows that wait for a look-up, and wavefronts of a workgroup,
+// which share the LDS tables (32 KB): as many as its LDS then holds.
+template <int LT>
+struct Collect {
+    static constexpr int kRows = LT == 0 ? 128 : 512;
+    static constexpr int kMaxL = LT == 0 ? 16 : LT;
+    static constexpr int kTileWords = kRows * kMaxL / 2;
+    static constexpr int kQuads = (kTileWords / 4 + kWave - 1) / kWave;  // 16-byte pieces a lane moves
+    static constexpr int kMisses = LT == 0 ? 0 : 3 * kWave;             // of four words each
+    static constexpr int kWaveWords = kTileWords + 4 * kMisses;
+    static constexpr int kFit = (160 * 1024 / 4 - kTableWords) / kWaveWords;
+    static constexpr int kWaves = kFit < 16 ? kFit : 16;
+};
 
-// A wavefront takes tiles of 256 consecutive rows: they come in as contiguous 16-byte pieces (the
-// next tile's are on their way while one is looked up) and are read row by row from LDS.
+// Rows whose vectors were not in the direct table, with their vectors (as pairs of counts, see
+// row_pairs): looked up together once a wavefront is full of them.  (Every workgroup meets every
+// vector of the set for the first time once, which is a trip to memory behind the counts on their
+// way: one trip per tile, 9 us a tile of 512 rows, or one per 64 such rows.)
+template <int LT>
+struct MissList {
+    static constexpr int NW = (LT + 1) / 2;
+    uint4* items;  // pairs 0 .. NW-1, row
+    int n;
+    __device__ __forceinline__ void append(bool miss, const uint32_t (&pair)[NW], uint32_t row) {
+        const uint64_t all = __ballot(miss);
+        if (all == 0ull) return;
+        const int before = (int)__builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
+        if (miss)
+            items[n + before] = make_uint4(pair[0], NW > 1 ? pair[NW > 1 ? 1 : 0] : 0u,
+                                           NW > 2 ? pair[NW > 2 ? 2 : 0] : 0u, row);
+        n += __popcll(all);
+    }
+    // place(row): where the row's code goes
+    template <typename Place>
+    __device__ __forceinline__ void resolve(int lane, uint32_t* cache, const VectorSet& set,
+                                            Place&& place) {
+        wave_sync();
+        for (int u0 = 0; u0 < n; u0 += kWave) {
+            const bool valid = u0 + lane < n;
+            const uint4 item = items[valid ? u0 + lane : 0];
+            const uint32_t all[3] = {item.x, item.y, item.z};
+            uint32_t pair[NW], w[NW], at;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                pair[k] = all[k];
+                w[k] = (all[k] << 16) | (all[k] >> 16);
+            }
+            const bool small = DirectIndex<LT>::of(pair, &at);
+            const int32_t number = lookup_hashed<NW, kHashedCollect>(w, valid, cache + kDirectWords,
+                                                                     set, lane);
+            if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
+            if (valid) *place(item.w) = number;
+        }
+        n = 0;
+        wave_sync();
+    }
+};
+
+// The rows of a whole tile, two neighbouring rows a lane: they are LT whole words, so the places of
+// their counts are known at compile time.  Stored unconditionally; the rows that the direct table
+// does not have are put right when the list is resolved.  first: number of the tile's first row in
+// the list.
+template <int LT, typename Place>
+__device__ __forceinline__ void tile_numbers(const uint32_t* tile, int lane, uint32_t first,
+                                             MissList<LT>& misses, uint32_t* cache,
+                                             const VectorSet& set, Place&& place) {
+    constexpr int NW = (LT + 1) / 2;
+    constexpr int kRows = Collect<LT>::kRows;
+    struct __attribute__((packed, aligned(4))) two_t { int32_t v[2]; };
+    int32_t* code = place(first);
+#pragma unroll 1
+    for (int t0 = 0; t0 < kRows; t0 += 2 * kWave) {
+        const int t = t0 + 2 * lane;
+        const uint32_t* from = tile + (t / 2) * LT;
+        uint32_t raw[LT];
+#pragma unroll
+        for (int k = 0; k < LT; ++k) raw[k] = from[k];
+        uint32_t pair[2][NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            if constexpr (LT % 2 == 0) {
+                pair[0][k] = raw[k];
+                pair[1][k] = raw[NW + k];
+            } else {
+                pair[0][k] = k + 1 < NW ? raw[k] : raw[k] & 0xFFFFu;
+                pair[1][k] = k + 1 < NW ? __builtin_amdgcn_alignbyte(raw[NW + k], raw[NW - 1 + k], 2u)
+                                        : raw[LT - 1] >> 16;
+            }
+        }
+        two_t number;
+        bool hit[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t at;
+            const bool small = DirectIndex<LT>::of(pair[h], &at);
+            const uint32_t e = cache[at];
+            hit[h] = small && e != 0u;
+            number.v[h] = (int32_t)(e - 1u);
+        }
+        *reinterpret_cast<two_t*>(code + t) = number;
+        misses.append(!hit[0], pair[0], first + (uint32_t)t);
+        misses.append(!hit[1], pair[1], first + (uint32_t)t + 1u);
+        if (misses.n > kWave) misses.resolve(lane, cache, set, place);
+    }
+}
+
+// A wavefront takes tiles of consecutive rows: they come in as contiguous 16-byte pieces (the next
+// tile's are on their way while one is looked up) and are read row by row from LDS.
 // Bound by the stream of counts in and codes out: FIGCOLLECT
-template <int LT, int kQuads>
-__global__ __launch_bounds__(kCollectWaves* kWave) void prune_collect_kernel(
+template <int LT>
+__global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(
     const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
     VectorSet set) {
-    __shared__ __align__(16) uint32_t cache[kSetCacheWords];
+    using C = Collect<LT>;
+    constexpr int kRows = C::kRows, kQuads = C::kQuads;
     extern __shared__ __align__(16) uint32_t lds32[];
-    set_cache_clear(cache, (int)threadIdx.x, kCollectWaves * kWave);
+    uint32_t* cache = lds32;
+    set_cache_clear(cache, kTableWords, (int)threadIdx.x, C::kWaves * kWave);
     __syncthreads();
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tile_words = kCollectRows * L / 2;
-    uint32_t* tile = lds32 + wave * (tile_words + kCollectRows);
-    uint32_t* misses = tile + tile_words;
-    const int n_quads = tile_words / 4;  // 256 * L counts: whole 16-byte pieces
+    uint32_t* tile = lds32 + kTableWords + wave * C::kWaveWords;
+    const int n_quads = kRows * L / 8;  // whole 16-byte pieces
     struct __attribute__((packed, aligned(4))) quad_t { uint32_t v[4]; };  // the array is 4-byte aligned
-    const int64_t stride = (int64_t)gridDim.x * kCollectWaves;
-    const int64_t n_whole = n_rows / kCollectRows;
-    int64_t at = (int64_t)blockIdx.x * kCollectWaves + wave;
+    const int64_t stride = (int64_t)gridDim.x * C::kWaves;
+    const int64_t n_whole = n_rows / kRows;
+    int64_t at = (int64_t)blockIdx.x * C::kWaves + wave;
     quad_t next[kQuads];
     auto fetch = [&](int64_t t) {
-        const quad_t* from = reinterpret_cast<const quad_t*>(cnt + t * kCollectRows * L);
+        const quad_t* from = reinterpret_cast<const quad_t*>(cnt + t * kRows * L);
 #pragma unroll
         for (int u = 0; u < kQuads; ++u)
             if (u * kWave + lane < n_quads) next[u] = from[u * kWave + lane];
@@ -65,6 +170,13 @@ __global__ __launch_bounds__(kCollectWaves* kWave) void prune_collect_kernel(
                 to[u * kWave + lane] = make_uint4(next[u].v[0], next[u].v[1], next[u].v[2], next[u].v[3]);
         wave_sync();
     };
+    // a wave's rows are numbered along its own tiles, so that 32 bits do for a table of any size
+    const int64_t at0 = at;
+    uint32_t first = 0;
+    auto place = [&](uint32_t row) -> int32_t* {
+        return code + (at0 + (int64_t)(row / kRows) * stride) * kRows + row % kRows;
+    };
+    MissList<LT == 0 ? 2 : LT> misses{reinterpret_cast<uint4*>(tile + C::kTileWords), 0};
     if (at < n_whole) fetch(at);
     // the first wave's first tile on its own: it fills the workgroup's tables with the common
     // vectors, for which the other waves then need not ask the global table all at once
@@ -72,22 +184,29 @@ __global__ __launch_bounds__(kCollectWaves* kWave) void prune_collect_kernel(
         if (turn == 1) __syncthreads();
         while (at < n_whole && (turn == 1 || wave == 0)) {
             to_lds();
-            const int64_t now = at;
             at += stride;
             if (at < n_whole) fetch(at);
-            rows_numbers<LT>(kCollectRows, lane, L, reinterpret_cast<const uint16_t*>(tile), misses,
-                             cache, set, code + now * kCollectRows);
+            if constexpr (LT > 0) {
+                tile_numbers<LT>(tile, lane, first, misses, cache, set, place);
+            } else {
+                rows_numbers<0, kHashedCollect>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
+                                                nullptr, cache, set, place(first));
+            }
+            first += kRows;
             wave_sync();
             if (turn == 0) break;
         }
+        if constexpr (LT > 0) misses.resolve(lane, cache, set, place);
     }
     // the rows behind the last whole tile
-    const int rest = (int)(n_rows - n_whole * kCollectRows);
+    const int rest = (int)(n_rows - n_whole * kRows);
     if (at == n_whole && rest > 0) {
         uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile);
-        for (int t = lane; t < rest * L; t += kWave) tile16[t] = cnt[n_whole * kCollectRows * L + t];
+        for (int t = lane; t < rest * L; t += kWave) tile16[t] = cnt[n_whole * kRows * L + t];
         wave_sync();
-        rows_numbers<LT>(rest, lane, L, tile16, misses, cache, set, code + n_whole * kCollectRows);
+        rows_numbers<LT, kHashedCollect>(rest, lane, L, tile16,
+                                         reinterpret_cast<uint16_t*>(tile + C::kTileWords), cache, set,
+                                         code + n_whole * kRows);
     }
 }
 
@@ -301,24 +420,19 @@ hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
     return hipMemsetAsync(ps.counters, 0, 2 * sizeof(unsigned long long), stream);
 }
 
-template <int LT, int kQuads>
+template <int LT>
 static hipError_t launch_collect(hipStream_t stream, int n_cu, const uint16_t* cnt, int64_t n_rows,
                                  int L, int32_t* code, const VectorSet& set) {
-    const size_t lds_bytes = (size_t)kCollectWaves * (kCollectRows * L / 2 + kCollectRows) * 4;
-    const void* fn = reinterpret_cast<const void*>(prune_collect_kernel<LT, kQuads>);
-    if (lds_bytes > 48 * 1024) {
-        hipError_t rc = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)lds_bytes);
-        if (rc != hipSuccess) return rc;
-    }
-    // a few workgroups per compute unit: each fills its LDS tables once and keeps them
-    const int64_t tiles = n_rows / kCollectRows + 1;
-    int64_t blocks = (tiles + kCollectWaves - 1) / kCollectWaves;
-    const int per_cu = (int)((160 * 1024) / (lds_bytes + kSetCacheWords * 4));
-    const int64_t most = (int64_t)n_cu * (per_cu < 1 ? 1 : (per_cu > 4 ? 4 : per_cu));
-    if (blocks > most) blocks = most;
-    hipLaunchKernelGGL((prune_collect_kernel<LT, kQuads>), dim3((unsigned)blocks),
-                       dim3(kCollectWaves * kWave), lds_bytes, stream, cnt, n_rows, L, code, set);
+    using C = Collect<LT>;
+    const size_t lds_bytes = (size_t)(kTableWords + C::kWaves * C::kWaveWords) * 4;
+    hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(prune_collect_kernel<LT>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (rc != hipSuccess) return rc;
+    // a workgroup fills its LDS tables once and keeps them
+    int64_t blocks = (n_rows / C::kRows + C::kWaves) / C::kWaves;
+    if (blocks > n_cu) blocks = n_cu;
+    hipLaunchKernelGGL((prune_collect_kernel<LT>), dim3((unsigned)blocks), dim3(C::kWaves * kWave),
+                       lds_bytes, stream, cnt, n_rows, L, code, set);
     return hipGetLastError();
 }
 
@@ -328,14 +442,13 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
     if (n_rows == 0) return hipSuccess;
     const VectorSet set = vector_set(ps, spin_limit, err);
     const int L = m + 1;
-    // 16-byte pieces of a tile per lane: 256 * L counts are 32 * L of them
     switch (L) {
-        case 2: return launch_collect<2, 1>(stream, n_cu, cnt, n_rows, L, code, set);
-        case 3: return launch_collect<3, 2>(stream, n_cu, cnt, n_rows, L, code, set);
-        case 4: return launch_collect<4, 2>(stream, n_cu, cnt, n_rows, L, code, set);
-        case 5: return launch_collect<5, 3>(stream, n_cu, cnt, n_rows, L, code, set);
-        case 6: return launch_collect<6, 3>(stream, n_cu, cnt, n_rows, L, code, set);
-        default: return launch_collect<0, 8>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 2: return launch_collect<2>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 3: return launch_collect<3>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 4: return launch_collect<4>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 5: return launch_collect<5>(stream, n_cu, cnt, n_rows, L, code, set);
+        case 6: return launch_collect<6>(stream, n_cu, cnt, n_rows, L, code, set);
+        default: return launch_collect<0>(stream, n_cu, cnt, n_rows, L, code, set);
     }
 }
 

@@ -106,7 +106,7 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
     return -1;
 }
 
-// The LDS tables of a workgroup (kSetCacheWords words, all zero at the start).
+// The LDS tables of a workgroup (kDirectWords + kHashed words, all zero at the start).
 //
 // Vectors of 2 .. 6 counts have two of them.  The first is a plain array: where the first count is
 // zero (every row but the seed's own) and the others are small, the counts themselves, a few bits
@@ -118,11 +118,13 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
 // global table.)
 // Longer vectors have one cache with entries of as many words as they need.
 constexpr int kDirectWords = 4096;
-constexpr int kHashedWords = 2048;
-constexpr int kSetCacheWords = kDirectWords + kHashedWords;  // 24 KB
+// Words of the hashed cache, a power of two.  (One or two rows in a hundred come here, some 400 to
+// 1,300 different vectors; one that finds its entry taken is a trip to memory every time.)
+constexpr int kHashedFused = 4096;    // 16 KB beside the rows of 16 waves
+constexpr int kHashedCollect = 4096;  // 16 KB beside their tiles and lists
 
-__device__ __forceinline__ void set_cache_clear(uint32_t* cache, int tid, int n_threads) {
-    for (int t = tid; t < kSetCacheWords; t += n_threads) cache[t] = 0u;
+__device__ __forceinline__ void set_cache_clear(uint32_t* cache, int n_words, int tid, int n_threads) {
+    for (int t = tid; t < n_words; t += n_threads) cache[t] = 0u;
 }
 
 template <int LT>
@@ -176,13 +178,13 @@ __device__ __forceinline__ int32_t find_or_insert_shared(const uint32_t (&w)[NW]
 // not yet there, the comparison fails and the lane asks the global table, which is slower and
 // right; a valid entry never changes again.
 constexpr uint32_t kPackedValid = 0x80000000u;
-template <int NW>
+template <int NW, int kHashed>
 __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool valid, uint32_t* cache,
                                                  const VectorSet& set, int lane) {
     static_assert(NW >= 1 && NW <= 3, "packed cache entries hold up to three words");
     constexpr int EW = NW == 1 ? 2 : 4;
     const uint32_t hv = hash_vector<NW>(w);
-    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(kHashedWords / EW - 1)) * EW;
+    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(kHashed / EW - 1)) * EW;
     uint32_t e[4] = {0u, 0u, 0u, 0u};
     if constexpr (EW == 2) {
         const uint2 v = *reinterpret_cast<const uint2*>(entry);
@@ -214,10 +216,11 @@ __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool v
 // (state, number, vector).  An entry is written once, by the lane that wins its state word, and is
 // valid for good after that (state, then vector and number, then "valid": LDS operations of a wave
 // take effect in order).
+template <int kHashed>
 __device__ __forceinline__ int32_t lookup_any(const uint32_t (&w)[kMaxVecWords], bool valid, int nw,
                                               uint32_t* cache, const VectorSet& set, int lane) {
     int entries = 64;
-    while (entries * 2 * (2 + nw) <= kSetCacheWords) entries *= 2;
+    while (entries * 2 * (2 + nw) <= kDirectWords + kHashed) entries *= 2;
     const uint32_t hv = hash_vector<kMaxVecWords>(w);
     uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(entries - 1)) * (2 + nw);
     bool hit = valid && entry[0] == 2u;
@@ -260,13 +263,45 @@ __device__ __forceinline__ void row_pairs(const uint32_t* words, int odd, int n_
     }
 }
 
+// Looks the rows misses[0 .. n_miss) of the rows at cnt16 up (words, odd, n_words as for row_pairs)
+// and enters what belongs there into the direct table.
+template <int LT, int kHashed>
+__device__ __forceinline__ void resolve_misses(const uint16_t* misses, int n_miss, int lane,
+                                               const uint32_t* words, int odd, int n_words,
+                                               uint32_t* cache, const VectorSet& set,
+                                               int32_t* __restrict__ code) {
+    constexpr int NW = (LT + 1) / 2;
+    for (int u0 = 0; u0 < n_miss; u0 += kWave) {
+        const bool valid = u0 + lane < n_miss;
+        const int t = (int)misses[valid ? u0 + lane : 0];
+        uint32_t pair[NW], w[NW], at;
+        row_pairs<NW>(words, odd, n_words, t, LT, pair);
+        const bool small = DirectIndex<LT>::of(pair, &at);
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
+        const int32_t number = lookup_hashed<NW, kHashed>(w, valid, cache + kDirectWords, set, lane);
+        if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
+        if (valid) code[t] = number;
+    }
+}
+
+// The lanes with `miss` set append their row t to the list.
+__device__ __forceinline__ void append_misses(uint16_t* misses, int& n_miss, bool miss, int t) {
+    const uint64_t all = __ballot(miss);
+    if (all == 0ull) return;
+    const int before = (int)__builtin_amdgcn_mbcnt_hi(
+        (uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
+    if (miss) misses[n_miss + before] = (uint16_t)t;
+    n_miss += __popcll(all);
+}
+
 // The numbers of n rows whose counts lie in LDS, to code[0 .. n).  One wavefront; rows that are not
-// in the direct table are put on a list (misses, n words of LDS of the wave's own) and looked up
+// in the direct table are put on a list (misses, n places in LDS of the wave's own) and looked up
 // together afterwards, so that few lanes wait for few.  LT = m + 1 at compile time for 2 .. 6, 0 =
 // any.
-template <int LT>
+template <int LT, int kHashed>
 __device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint16_t* cnt16,
-                                             uint32_t* misses, uint32_t* cache, const VectorSet& set,
+                                             uint16_t* misses, uint32_t* cache, const VectorSet& set,
                                              int32_t* __restrict__ code) {
     const int odd = (int)((reinterpret_cast<uintptr_t>(cnt16) >> 1) & 1u);
     const uint32_t* words = reinterpret_cast<const uint32_t*>(cnt16 - odd);
@@ -278,56 +313,38 @@ __device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint1
             row_pairs<kMaxVecWords>(words, odd, n_words, min(t, n - 1), L, pair);
 #pragma unroll
             for (int k = 0; k < kMaxVecWords; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
-            const int32_t number = lookup_any(w, t < n, (L + 1) / 2, cache, set, lane);
+            const int32_t number = lookup_any<kHashed>(w, t < n, (L + 1) / 2, cache, set, lane);
             if (t < n) code[t] = number;
         }
     } else {
         constexpr int NW = (LT + 1) / 2;
-        uint32_t* direct = cache;
-        uint32_t* hashed = cache + kDirectWords;
         int n_miss = 0;
         for (int t0 = 0; t0 < n; t0 += kWave) {
             const int t = t0 + lane;
             uint32_t pair[NW], at;
             row_pairs<NW>(words, odd, n_words, min(t, n - 1), LT, pair);
             const bool small = DirectIndex<LT>::of(pair, &at);
-            const uint32_t e = direct[at];
+            const uint32_t e = cache[at];
             const bool hit = small && e != 0u;
             if (t < n && hit) code[t] = (int32_t)(e - 1u);
-            const uint64_t miss = __ballot(t < n && !hit);
-            if (miss != 0ull) {
-                const int before = (int)__builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(miss >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)miss, 0u));
-                if (t < n && !hit) misses[n_miss + before] = (uint32_t)t;
-                n_miss += __popcll(miss);
-            }
+            append_misses(misses, n_miss, t < n && !hit, t);
         }
         wave_sync();
-        for (int u0 = 0; u0 < n_miss; u0 += kWave) {
-            const bool valid = u0 + lane < n_miss;
-            const int t = (int)misses[valid ? u0 + lane : 0];
-            uint32_t pair[NW], w[NW], at;
-            row_pairs<NW>(words, odd, n_words, t, LT, pair);
-            const bool small = DirectIndex<LT>::of(pair, &at);
-#pragma unroll
-            for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
-            const int32_t number = lookup_hashed<NW>(w, valid, hashed, set, lane);
-            if (valid && small && number >= 0) direct[at] = (uint32_t)number + 1u;
-            if (valid) code[t] = number;
-        }
+        resolve_misses<LT, kHashed>(misses, n_miss, lane, words, odd, n_words, cache, set, code);
         wave_sync();
     }
 }
+template <int kHashed>
 __device__ __forceinline__ void rows_numbers_any(int n, int lane, int L, const uint16_t* cnt16,
-                                                 uint32_t* misses, uint32_t* cache,
+                                                 uint16_t* misses, uint32_t* cache,
                                                  const VectorSet& set, int32_t* __restrict__ code) {
     switch (L) {
-        case 2: rows_numbers<2>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 3: rows_numbers<3>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 4: rows_numbers<4>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 5: rows_numbers<5>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 6: rows_numbers<6>(n, lane, L, cnt16, misses, cache, set, code); break;
-        default: rows_numbers<0>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 2: rows_numbers<2, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 3: rows_numbers<3, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 4: rows_numbers<4, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 5: rows_numbers<5, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 6: rows_numbers<6, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        default: rows_numbers<0, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
     }
 }
 
