@@ -439,13 +439,22 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
                         int32_t M, int32_t m, uint64_t rng_seed, int32_t* d_walks, int64_t cap_rows,
                         int64_t* d_rpe_off, int32_t* d_rpe_ids, uint16_t* d_rpe_cnt, int32_t* d_code,
                         const surel::PruneScratch& ps, int64_t* h_total) {
+    if (h_total) *h_total = -1;
+    if (d_code == nullptr && surel::walk_rpe_is_small(ctx->n_cu, n_seeds, M, m)) {
+        KernelSpan span(ctx, SUREL_K_WALK_RPE);
+        hipError_t hrc = surel::launch_walk_rpe_small(
+            ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges,
+            d_seeds, n_seeds, M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt,
+            ctx->d_small, ctx->spin_limit, h_total, ctx->d_err);
+        if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
+        return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
+    }
     surel::EdgeRecords records;
     if (int rc = make_edge_records(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, n_seeds, M, m,
                                    &records))
         return rc;
     const size_t lb_need = (size_t)surel::lookback_words(n_seeds) * sizeof(uint64_t);
     if (int rc = grow_buffer(ctx, &ctx->d_lb, &ctx->lb_bytes, lb_need)) return rc;
-    if (h_total) *h_total = -1;
     KernelSpan span(ctx, SUREL_K_WALK_RPE);
     hipError_t hrc = surel::launch_walk_rpe(
         ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds,

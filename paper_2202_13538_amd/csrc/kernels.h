@@ -52,6 +52,16 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
                            uint32_t spin_limit, int64_t* h_total, uint32_t* err,
                            int32_t* code, const PruneScratch& ps);
 
+// walk_rpe_small.hip.  The same for few seeds (walk_rpe_is_small says for how many), in one launch
+// that needs neither records nor look-back scratch.  small_scan, h_total: as for launch_join_small.
+bool walk_rpe_is_small(int n_cu, int64_t n_seeds, int32_t M, int32_t m);
+hipError_t launch_walk_rpe_small(hipStream_t stream, int max_lds_bytes, int n_cu,
+                                 const int32_t* row_ptr, const int32_t* col_idx, int32_t n_nodes,
+                                 int64_t n_edges, const int32_t* seeds, int64_t n_seeds, int32_t M,
+                                 int32_t m, uint64_t rng_seed, int32_t* walks, int64_t cap_rows,
+                                 int64_t* rpe_off, int32_t* ids, uint16_t* cnt, void* small_scan,
+                                 uint32_t spin_limit, int64_t* h_total, uint32_t* err);
+
 // rpe.hip.  launch_rpe_count: set_sizes[i] = distinct nodes in walks[i].  launch_rpe_fill:
 // writes the rows of every seed at rpe_off[i] (seeds whose block would pass cap_rows, or whose
 // row count differs from rpe_off[i+1]-rpe_off[i], are skipped and flagged).

@@ -137,16 +137,9 @@ static hipError_t launch_walk_rpe_erc(hipStream_t stream, int max_lds_bytes, int
     constexpr int kMaxW = E <= 16 ? 16 : 8;
     int W = 4 * (512 / ((regs + 7) / 8 * 8));
     if (W > kMaxW) W = kMaxW;
-    // LDS of a wave: the walk block, or as many rows of a block as the wave's share of the LDS
-    // holds (a block with more rows goes out in turns)
+    // every wave has its share of what the static part leaves of the LDS
     const int lds_words = (160 * 1024 - (int)attr.sharedSizeBytes) / 4;
-    const int share = lds_words / W & ~3;
-    const int block_words = fused_block_words(f.M, f.m);
-    f.lds_rows = 1 + f.M * f.m;  // App. D.4: at most m*M nodes besides the seed
-    while (rpe_row_words(f.lds_rows, f.m + 1) > (share > block_words ? share : block_words))
-        f.lds_rows -= 1;
-    const int row_words = (rpe_row_words(f.lds_rows, f.m + 1) + 3) & ~3;
-    f.lds_words_per_wave = row_words > block_words ? row_words : block_words;
+    fused_lds_plan(&f, lds_words / W & ~3);
     if (W > lds_words / f.lds_words_per_wave) W = lds_words / f.lds_words_per_wave;
     if (W < 1 || f.lds_rows < 1) return hipErrorInvalidValue;
     const size_t lds_bytes = (size_t)W * f.lds_words_per_wave * 4;

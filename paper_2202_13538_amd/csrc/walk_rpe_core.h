@@ -41,6 +41,18 @@ struct FusedJob {
     uint32_t* __restrict__ err;
 };
 
+// Lays out the LDS of a wave that may have `share` words: the walk block, or as many rows of an RPE
+// block as fit (a block with more rows goes out in turns); lds_rows = 0: not even one fits.
+inline void fused_lds_plan(FusedJob* f, int share) {
+    const int L = f->m + 1;
+    const int block_words = fused_block_words(f->M, f->m);
+    const int room = share > block_words ? share : block_words;
+    f->lds_rows = 1 + f->M * f->m;  // App. D.4: at most m*M nodes besides the seed
+    while (f->lds_rows > 0 && rpe_row_words(f->lds_rows, L) > room) f->lds_rows -= 1;
+    const int row_words = (rpe_row_words(f->lds_rows, L) + 3) & ~3;
+    f->lds_words_per_wave = row_words > block_words ? row_words : block_words;
+}
+
 inline FusedJob fused_job(const int32_t* row_ptr, const int32_t* col_idx, int32_t n_nodes,
                           int64_t n_edges, const int32_t* seeds, int64_t n_seeds, int32_t M,
                           int32_t m, uint64_t rng_seed, int32_t* walks, int64_t cap_rows,
