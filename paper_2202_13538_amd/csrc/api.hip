@@ -16,6 +16,7 @@ struct surel_ctx {
     int n_cu = 0;                 // compute units of the device
     uint32_t spin_limit = 1u << 22;  // bound of every wait inside the fused walk + RPE kernel
     uint32_t* d_err = nullptr;    // sticky device error word
+    hipEvent_t done = nullptr;    // completed by the one launch of a call that reports its total
     void* d_small = nullptr;      // words of the launches that lay small outputs out themselves
     int64_t* h_pinned = nullptr;  // 2 x int64 of pinned host memory for small read-backs
     void* d_ws = nullptr;         // grow-only workspace: row counts + scan partials
@@ -229,6 +230,7 @@ int surel_create(surel_ctx** out, int device, void* hip_stream) {
     ok = ok && hipMemsetAsync(ctx->d_err, 0, 256, ctx->stream) == hipSuccess;
     ok = ok && hipMalloc(&ctx->d_small, surel::small_scan_bytes()) == hipSuccess;
     ok = ok && hipMemsetAsync(ctx->d_small, 0, surel::small_scan_bytes(), ctx->stream) == hipSuccess;
+    ok = ok && hipEventCreateWithFlags(&ctx->done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 2 * sizeof(int64_t),
                              hipHostMallocDefault) == hipSuccess;
     ok = ok && hipStreamSynchronize(ctx->stream) == hipSuccess;
@@ -238,6 +240,7 @@ int surel_create(surel_ctx** out, int device, void* hip_stream) {
     if (!ok) {
         if (ctx->d_err) (void)hipFree(ctx->d_err);
         if (ctx->d_small) (void)hipFree(ctx->d_small);
+        if (ctx->done) (void)hipEventDestroy(ctx->done);
         if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
         delete ctx;
         (void)hipGetLastError();
@@ -263,6 +266,7 @@ void surel_destroy(surel_ctx* ctx) {
     if (ctx->d_batch) (void)hipFree(ctx->d_batch);
     if (ctx->d_err) (void)hipFree(ctx->d_err);
     if (ctx->d_small) (void)hipFree(ctx->d_small);
+    if (ctx->done) (void)hipEventDestroy(ctx->done);
     if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
     delete ctx;
 }
@@ -330,9 +334,12 @@ static int report_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, bool ha
     if (int rc = read_total(ctx, d_off, n, h_rows)) return rc;
     return judge_total(has_outputs, cap_rows, *h_rows);
 }
-// The same where the launch has put the total into the pinned word itself.
-static int report_pinned_total(surel_ctx* ctx, bool has_outputs, int64_t cap_rows, int64_t* h_rows) {
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+// The same where the launch has put the total into the pinned word itself; marked: it is one that
+// completes ctx->done.
+static int report_pinned_total(surel_ctx* ctx, bool marked, bool has_outputs, int64_t cap_rows,
+                               int64_t* h_rows) {
+    const hipError_t rc = marked ? hipEventSynchronize(ctx->done) : hipStreamSynchronize(ctx->stream);
+    if (rc != hipSuccess) return SUREL_E_HIP;
     *h_rows = ctx->h_pinned[0];
     return judge_total(has_outputs, cap_rows, *h_rows);
 }
@@ -445,7 +452,7 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
         hipError_t hrc = surel::launch_walk_rpe_small(
             ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges,
             d_seeds, n_seeds, M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt,
-            ctx->d_small, ctx->spin_limit, h_total, ctx->d_err);
+            ctx->d_small, ctx->spin_limit, h_total, h_total ? ctx->done : nullptr, ctx->d_err);
         if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
         return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
     }
@@ -495,7 +502,8 @@ int surel_sample_walks_rpe(surel_ctx* ctx, const int32_t* d_row_ptr, const int32
                                      h_rows ? ctx->h_pinned : nullptr)) {
         return rc;
     } else if (h_rows) {
-        return report_pinned_total(ctx, d_rpe_ids != nullptr, cap_rows, h_rows);
+        return report_pinned_total(ctx, surel::walk_rpe_is_small(ctx->n_cu, n_seeds, M, m),
+                                   d_rpe_ids != nullptr, cap_rows, h_rows);
     }
     if (h_rows) return report_total(ctx, d_rpe_off, n_seeds, d_rpe_ids != nullptr, cap_rows, h_rows);
     return SUREL_OK;
@@ -653,11 +661,12 @@ static int join_small(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d
         hipError_t hrc = surel::launch_join_small(
             ctx->stream, ctx->n_cu, d_rpe_off, d_rpe_ids, d_rpe_cnt, n_blocks, m, max_set, d_queries,
             n_queries, k, d_join_off, cap_rows, d_join_ids, d_join_cnt, absent16, ctx->d_small,
-            ctx->spin_limit, h_rows ? ctx->h_pinned : nullptr, ctx->d_err);
+            ctx->spin_limit, h_rows ? ctx->h_pinned : nullptr, h_rows ? ctx->done : nullptr,
+            ctx->d_err);
         if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
         if (hrc != hipSuccess) return SUREL_E_HIP;
     }
-    if (h_rows) return report_pinned_total(ctx, d_join_ids != nullptr, cap_rows, h_rows);
+    if (h_rows) return report_pinned_total(ctx, true, d_join_ids != nullptr, cap_rows, h_rows);
     return SUREL_OK;
 }
 

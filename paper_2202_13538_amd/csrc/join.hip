@@ -283,6 +283,7 @@ struct JoinJob {
     SmallScan* small_scan;
     uint32_t spin_limit;
     int64_t* h_total;
+    hipEvent_t done;
 };
 
 // Wavefronts of a query in the one-launch join: as many as the device has room for at four waves
@@ -318,10 +319,10 @@ static hipError_t launch_join_small_cfg(const JoinJob& j) {
     const size_t lds_bytes = (size_t)join_lds_layout(K, j.max_set, LT, W).total * 4;
     hipError_t rc = allow_lds(reinterpret_cast<const void*>(join_small_kernel<K, LT>), lds_bytes);
     if (rc != hipSuccess) return rc;
-    hipLaunchKernelGGL((join_small_kernel<K, LT>), dim3((unsigned)j.n_queries), dim3(W * kWave),
-                       lds_bytes, j.stream, j.rpe_off, j.rpe_ids, j.rpe_cnt, j.n_blocks, j.max_set,
-                       j.queries, (int32_t)j.n_queries, j.join_off_out, j.cap_rows, j.out_ids,
-                       j.out_cnt, j.absent16, j.small_scan, j.spin_limit, j.h_total, j.err);
+    launch_and_mark(join_small_kernel<K, LT>, dim3((unsigned)j.n_queries), dim3(W * kWave), lds_bytes,
+                    j.stream, j.done, j.rpe_off, j.rpe_ids, j.rpe_cnt, j.n_blocks, j.max_set,
+                    j.queries, (int32_t)j.n_queries, j.join_off_out, j.cap_rows, j.out_ids,
+                    j.out_cnt, j.absent16, j.small_scan, j.spin_limit, j.h_total, j.err);
     return hipGetLastError();
 }
 
@@ -417,14 +418,14 @@ hipError_t launch_join_small(hipStream_t stream, int n_cu, const int64_t* rpe_of
                              int32_t m, int32_t max_set, const int32_t* queries, int64_t n_queries,
                              int32_t k, int64_t* join_off, int64_t cap_rows, int32_t* out_ids,
                              uint16_t* out_cnt, uint16_t absent16, void* small_scan,
-                             uint32_t spin_limit, int64_t* h_total, uint32_t* err) {
+                             uint32_t spin_limit, int64_t* h_total, hipEvent_t done, uint32_t* err) {
     JoinJob j{};
     j.stream = stream, j.n_cu = n_cu;
     j.rpe_off = rpe_off, j.rpe_ids = rpe_ids, j.rpe_cnt = rpe_cnt, j.n_blocks = n_blocks, j.m = m;
     j.max_set = max_set, j.queries = queries, j.n_queries = n_queries, j.join_off_out = join_off;
     j.cap_rows = cap_rows, j.out_ids = out_ids, j.out_cnt = out_cnt, j.absent16 = absent16;
     j.small_scan = static_cast<SmallScan*>(small_scan), j.spin_limit = spin_limit;
-    j.h_total = h_total, j.err = err;
+    j.h_total = h_total, j.done = done, j.err = err;
     if (k == 2) return launch_join_lt<2, true>(j);
     if (k == 3) return launch_join_lt<3, true>(j);
     return hipErrorInvalidValue;

@@ -92,7 +92,7 @@ bool walk_rpe_is_small(int n_cu, int64_t n_seeds, int32_t M, int32_t m) {
 
 template <int E>
 static hipError_t launch_small_e(hipStream_t stream, int max_lds_bytes, int n_cu, FusedJob f,
-                                 SmallScan* ss) {
+                                 SmallScan* ss, hipEvent_t done) {
     const int W = small_walk_group(n_cu, f.n_seeds);
     const int share = (160 * 1024 - 512) / 4 / W & ~3;
     fused_lds_plan(&f, share);
@@ -103,8 +103,8 @@ static hipError_t launch_small_e(hipStream_t stream, int max_lds_bytes, int n_cu
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (rc != hipSuccess) return rc;
     }
-    hipLaunchKernelGGL((walk_rpe_small_kernel<E>), dim3((unsigned)((f.n_seeds + W - 1) / W)),
-                       dim3(W * kWave), lds_bytes, stream, f, ss);
+    launch_and_mark(walk_rpe_small_kernel<E>, dim3((unsigned)((f.n_seeds + W - 1) / W)),
+                    dim3(W * kWave), lds_bytes, stream, done, f, ss);
     return hipGetLastError();
 }
 
@@ -113,14 +113,16 @@ hipError_t launch_walk_rpe_small(hipStream_t stream, int max_lds_bytes, int n_cu
                                  int64_t n_edges, const int32_t* seeds, int64_t n_seeds, int32_t M,
                                  int32_t m, uint64_t rng_seed, int32_t* walks, int64_t cap_rows,
                                  int64_t* rpe_off, int32_t* ids, uint16_t* cnt, void* small_scan,
-                                 uint32_t spin_limit, int64_t* h_total, uint32_t* err) {
+                                 uint32_t spin_limit, int64_t* h_total, hipEvent_t done,
+                                 uint32_t* err) {
     const FusedJob f = fused_job(row_ptr, col_idx, n_nodes, n_edges, seeds, n_seeds, M, m, rng_seed,
                                  walks, cap_rows, rpe_off, ids, cnt, EdgeRecords{}, spin_limit,
                                  h_total, err);
+    SmallScan* ss = static_cast<SmallScan*>(small_scan);
     const int n_key = fused_keys(M, m);
 #define SUREL_WRS_SIZE(E_)            \
     if (n_key <= kWave * (E_))        \
-        return launch_small_e<E_>(stream, max_lds_bytes, n_cu, f, static_cast<SmallScan*>(small_scan));
+        return launch_small_e<E_>(stream, max_lds_bytes, n_cu, f, ss, done);
     SUREL_FOR_SORT_SIZES(SUREL_WRS_SIZE)
 #undef SUREL_WRS_SIZE
     return hipErrorInvalidValue;
