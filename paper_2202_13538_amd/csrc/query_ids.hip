@@ -2,19 +2,20 @@
 // walks W_u, u in Q, are concatenated and every node occurrence x in them gets
 // RPE-ID_{Q,x} = [RPE-ID_{u,x}]_{u in Q}.  The RPE table is the (unpruned) central array of
 // Sec. 3.3, so RPE-ID_{u,x} is the index of (u, x)'s row in it; -1 stands for "x is not in
-// V_u" (the all-zero vector).  The paper looks x up in the hash dictionary H_u; here the
-// blocks' id lists are sorted, so the lookup is a binary search in LDS.  (Per-query hash
-// dictionaries in LDS were measured too and lost: their probe loops diverge, and their
-// footprint leaves a compute unit too few waves.)
+// V_u" (the all-zero vector).  The paper looks x up in the hash dictionary H_u.
 //
-// A wavefront handles one query (the grid covers the query list; a wave loops only where the
-// grid cannot be that large).  It stages the K id lists in LDS, then runs over the K walk
-// blocks as flat arrays: a lane takes kQiEntries walk entries at a time and searches each in
-// all K lists with a fixed number of branch-free steps, so that the K * kQiEntries searches
-// of a round advance together and their LDS reads overlap; the K row indices of an entry lie
-// next to each other in the output and go out as one store.  The first round of every walk
-// block (the whole block, for up to 512 entries) is loaded before the id lists are staged:
-// a query then costs one wait for memory, not one per block.
+// Here the blocks' id lists are sorted, and a workgroup (one to four wavefronts, by the length of
+// the walk blocks) stages the K lists of a query in LDS with a directory for each: the range of
+// the list's ids cut into twice as many equal parts as the list may have ids (2,048 at most), and
+// for every part the place of the first id in it or behind it.  A look-up reads the directory and
+// then the list from there on: one or two ids, since node ids lie evenly in their range wherever
+// labels carry no order.  The 2K directory entries and first ids of an entry's look-ups are read
+// for all entries of a thread together; only lanes that have to go on read further.  Lists whose
+// ids crowd together (more than kCrowd in one part) are searched by bisection instead, which needs
+// no directory.
+// What bounds it: LDS reads at random places (a wavefront's 64 lanes hit some banks four or five
+// times): FIGQID
+// (Per-query hash dictionaries in LDS were measured too and lost: their probe loops diverge.)
 #include "device_util.h"
 #include "kernels.h"
 
@@ -26,28 +27,44 @@ struct __attribute__((aligned(4))) RowIds {
     int32_t v[K];
 };
 
-// kQiEntries: walk entries a lane looks up at a time (1, 2, 4 or 8: enough for a whole walk block
-// of up to 512 entries in one round).
+constexpr int kCrowd = 8;  // ids in one part of the directory, at most
+
+// LDS of one workgroup, in 32-bit words.
+struct QidLds {
+    int list;     // words from one list's ids to the next one's
+    int codes;    // first list's codes
+    int dir;      // first list's directory (16-bit entries)
+    int parts;    // entries of a directory, a power of two
+    int total;
+};
+__host__ __device__ inline QidLds qid_lds(int K, int max_set, bool code) {
+    QidLds o;
+    o.list = max_set;
+    o.codes = K * o.list;
+    o.dir = o.codes * (code ? 2 : 1);
+    o.parts = 64;
+    while (o.parts < 2 * max_set && o.parts < 2048) o.parts *= 2;
+    o.total = o.dir + K * o.parts / 2;
+    return o;
+}
+
+// kQiEntries: walk entries of a block that a thread looks up at a time.
 // kCode: the rows' codes (their RPE-IDs in the pruned array of Sec. 3.3) are staged next to the
 // ids and go out instead of the row indices.
-template <int K, int WPB, int kQiEntries, bool kCode>
-__global__ __launch_bounds__(WPB* kWave) void query_ids_kernel(
+template <int K, int kQiEntries, bool kCode>
+__global__ __launch_bounds__(256) void query_ids_kernel(
     const int32_t* __restrict__ walks, const int64_t* __restrict__ rpe_off,
     const int32_t* __restrict__ rpe_ids, const int32_t* __restrict__ code, int64_t n_blocks,
-    int32_t n_key, int32_t max_set,
-    int64_t table_rows, const int32_t* __restrict__ queries, int64_t n_queries,
-    int32_t* __restrict__ out, uint32_t* __restrict__ err) {
-    extern __shared__ uint32_t lds32[];
-    const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // list j at [j*(max_set+1) + 1 ...); the word in front of it (index -1 of the list) is
-    // never smaller than a node id, so a search may read it
-    const int list_stride = max_set + 1;
-    uint32_t* ids_lds = lds32 + wave * ((kCode ? 2 : 1) * K * list_stride);
-    uint32_t* code_lds = ids_lds + K * list_stride;  // same places as the ids (kCode only)
-    const int64_t stride = (int64_t)gridDim.x * WPB;
-    for (int64_t q = (int64_t)blockIdx.x * WPB + wave; q < n_queries; q += stride) {
-        // the K blocks of this query (wave-uniform)
+    int32_t n_key, int32_t max_set, int64_t table_rows, const int32_t* __restrict__ queries,
+    int64_t n_queries, int32_t* __restrict__ out, uint32_t* __restrict__ err) {
+    extern __shared__ __align__(16) uint32_t lds32[];
+    __shared__ uint32_t crowded;
+    const int T = (int)blockDim.x;
+    const int tid = (int)threadIdx.x;
+    const QidLds lay = qid_lds(K, max_set, kCode);
+    uint16_t* const dirs = reinterpret_cast<uint16_t*>(lds32 + lay.dir);
+    for (int64_t q = blockIdx.x; q < n_queries; q += gridDim.x) {
+        // the K blocks of this query (the same in every thread)
         int32_t blk[K];
         int64_t lo[K];
         int n[K];
@@ -77,213 +94,222 @@ __global__ __launch_bounds__(WPB* kWave) void query_ids_kernel(
         int32_t* out_q = out + q * (int64_t)K * n_key * K;
         if (problem != 0) {
             // the query gets no RPE-IDs at all
-            if (lane == 0) atomicOr(err, problem);
-            for (int t = lane; t < K * n_key * K; t += kWave) out_q[t] = -1;
+            if (tid == 0) atomicOr(err, problem);
+            for (int t = tid; t < K * n_key * K; t += T) out_q[t] = -1;
             continue;
         }
-        // the first kQiEntries * 64 entries of every walk block (all of it, for the usual sizes)
-        // are asked for before the id lists, so that one wait covers both
+        // the first entries of every walk block (all of them, for the usual sizes) are asked for
+        // before the id lists, so that one wait covers both
         uint32_t x_first[K][kQiEntries];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int32_t* W = walks + (int64_t)blk[j] * n_key;
 #pragma unroll
             for (int e = 0; e < kQiEntries; ++e)
-                x_first[j][e] = (uint32_t)__builtin_nontemporal_load(W + min(e * kWave + lane, n_key - 1));
+                x_first[j][e] = (uint32_t)__builtin_nontemporal_load(W + min(e * T + tid, n_key - 1));
         }
-        int top[K];  // largest power of two <= n[j] (0 for an empty list): the first step
-        if constexpr (!kCode) {
-            // ids only: list after list (asking for all of them together was measured and is
-            // 5 % slower here, though it is what makes the variant with codes fast)
+        __syncthreads();  // the LDS words of the query before are free
+        if (tid == 0) crowded = 0u;
+        // every list's words, ids and codes, are asked for together
+        constexpr int kStageU = 4;
+        constexpr int kLists = kCode ? 2 * K : K;
+        for (int t0 = 0; t0 < max_set; t0 += kStageU * T) {
+            bool any = false;
 #pragma unroll
-            for (int j = 0; j < K; ++j)
-                stage_words<8>(ids_lds + j * list_stride + 1,
-                               reinterpret_cast<const uint32_t*>(rpe_ids + lo[j]), n[j], lane);
-        }
-        // with codes: the lists' first 512 entries (all of them, usually) are asked for together,
-        // ids and codes of all K blocks, before any of them is waited for
-        constexpr int kStageU = 8;
-        constexpr int kLists = kCode ? 2 * K : 0;
-        uint32_t staged[kLists > 0 ? kLists : 1][kStageU];
+            for (int j = 0; j < K; ++j) any = any || t0 < n[j];
+            if (!any) break;
+            uint32_t staged[kLists][kStageU];
 #pragma unroll
-        for (int l = 0; l < kLists; ++l) {
-            const int j = l % K;
-            const int32_t* from = (l < K ? rpe_ids : code) + lo[j];
+            for (int l = 0; l < kLists; ++l) {
+                const int32_t* from = (l < K ? rpe_ids : code) + lo[l % K];
 #pragma unroll
-            for (int u = 0; u < kStageU; ++u) {
-                const int t = u * kWave + lane;
-                staged[l][u] = t < n[j] ? (uint32_t)from[t] : 0u;
+                for (int u = 0; u < kStageU; ++u) {
+                    const int t = t0 + u * T + tid;
+                    staged[l][u] = t < n[l % K] ? (uint32_t)from[t] : 0u;
+                }
+            }
+#pragma unroll
+            for (int l = 0; l < kLists; ++l) {
+                uint32_t* to = lds32 + (l < K ? 0 : lay.codes) + (l % K) * lay.list;
+#pragma unroll
+                for (int u = 0; u < kStageU; ++u) {
+                    const int t = t0 + u * T + tid;
+                    if (t < n[l % K]) to[t] = staged[l][u];
+                }
             }
         }
-#pragma unroll
-        for (int l = 0; l < kLists; ++l) {
-            const int j = l % K;
-            uint32_t* to = (l < K ? ids_lds : code_lds) + j * list_stride + 1;
-#pragma unroll
-            for (int u = 0; u < kStageU; ++u) {
-                const int t = u * kWave + lane;
-                if (t < n[j]) to[t] = staged[l][u];
-            }
-            if (n[j] > kStageU * kWave)  // the rest of a long list
-                stage_words<8>(to + kStageU * kWave,
-                               reinterpret_cast<const uint32_t*>((l < K ? rpe_ids : code) + lo[j]) +
-                                   kStageU * kWave,
-                               n[j] - kStageU * kWave, lane);
-        }
+        __syncthreads();
+        // The directories.  x lies in part mulhi(x - first, scale) of its list's range; part p's
+        // entry is the place of the first id in part p or behind it, so the thread of id t writes
+        // the entries of the parts behind the one of id t - 1, up to its own.
+        uint32_t first[K], range[K], scale[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            if (lane == 0) ids_lds[j * list_stride] = 0xFFFFFFFFu;
-            top[j] = n[j] > 0 ? 1 << (31 - __builtin_clz((unsigned)n[j])) : 0;
+            const uint32_t* ids = lds32 + j * lay.list;
+            first[j] = n[j] > 0 ? ids[0] : 0u;
+            range[j] = n[j] > 0 ? ids[n[j] - 1] - first[j] : 0u;
+            // a little below parts * 2^32 / (range + 1), so that the last id's part is below
+            // `parts`, in single precision (2^-20 covers its errors); ranges below `parts` share
+            // the largest scale that fits 32 bits
+            const float r1 = (float)max(range[j], (uint32_t)lay.parts) + 1.0f;
+            scale[j] = (uint32_t)((float)lay.parts * 4294967296.0f * __builtin_amdgcn_rcpf(r1) *
+                                  (1.0f - 0x1p-20f));
+            uint16_t* dir = dirs + j * lay.parts;
+            bool crowd = false;
+            for (int t = tid; t < n[j]; t += T) {
+                const uint32_t part = __umulhi(ids[t] - first[j], scale[j]);
+                const int before = t > 0 ? (int)__umulhi(ids[t - 1] - first[j], scale[j]) : -1;
+                crowd = crowd || (t >= kCrowd && __umulhi(ids[t - kCrowd] - first[j], scale[j]) == part);
+                for (int p = max(before, -1) + 1; p <= (int)min(part, (uint32_t)lay.parts - 1u); ++p)
+                    dir[p] = (uint16_t)t;
+            }
+            if (__ballot(crowd) != 0ull && (tid & (kWave - 1)) == 0) atomicOr(&crowded, 1u << j);
         }
-        int top_max = 0;
-#pragma unroll
-        for (int j = 0; j < K; ++j) top_max = max(top_max, top[j]);
-        wave_sync();
+        __syncthreads();
+        const uint32_t bisect = crowded;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int32_t* W = walks + (int64_t)blk[j] * n_key;
             int32_t* out_j = out_q + (int64_t)j * n_key * K;
-            for (int t0 = 0; t0 < n_key; t0 += kQiEntries * kWave) {
+            for (int t0 = 0; t0 < n_key; t0 += kQiEntries * T) {
                 uint32_t x[kQiEntries];
-                int pos[kQiEntries][K];  // elements of list j2 that are smaller than x
+                int pos[kQiEntries][K];      // first id of list j2 that is not below x
+                bool found[kQiEntries][K];
 #pragma unroll
                 for (int e = 0; e < kQiEntries; ++e) {
-                    const int t = min(t0 + e * kWave + lane, n_key - 1);
+                    const int t = min(t0 + e * T + tid, n_key - 1);
                     x[e] = t0 == 0 ? x_first[j][e] : (uint32_t)__builtin_nontemporal_load(W + t);
-#pragma unroll
-                    for (int j2 = 0; j2 < K; ++j2) pos[e][j2] = 0;
                 }
-                for (int step = top_max; step > 0; step >>= 1) {
+#pragma unroll
+                for (int j2 = 0; j2 < K; ++j2) {
+                    const uint32_t* ids = lds32 + j2 * lay.list;
+                    const uint16_t* dir = dirs + j2 * lay.parts;
+                    // an id outside the list's range is not in it: it is looked up as the first
 #pragma unroll
                     for (int e = 0; e < kQiEntries; ++e) {
+                        const uint32_t d = x[e] - first[j2];
+                        found[e][j2] = n[j2] > 0 && d <= range[j2];
+                        const uint32_t part = __umulhi(found[e][j2] ? d : 0u, scale[j2]);
+                        pos[e][j2] = (bisect >> j2 & 1u) == 0u && n[j2] > 0 ? min((int)dir[part], n[j2] - 1) : 0;
+                    }
+                    if ((bisect >> j2 & 1u) == 0u) {
+                        bool go[kQiEntries];
+                        bool any = false;
 #pragma unroll
-                        for (int j2 = 0; j2 < K; ++j2) {
-                            // a step past the end of the list reads its last element again
-                            // (or the guard word of an empty list) and is not taken
-                            const int cand = pos[e][j2] + step;
-                            const uint32_t probe =
-                                ids_lds[j2 * list_stride + min(cand, n[j2])];
-                            if (cand <= n[j2] && probe < x[e]) pos[e][j2] = cand;
+                        for (int e = 0; e < kQiEntries; ++e) {
+                            const uint32_t at = n[j2] > 0 ? ids[pos[e][j2]] : 0u;
+                            go[e] = found[e][j2] && at < x[e];
+                            found[e][j2] = found[e][j2] && at >= x[e] ? at == x[e] : found[e][j2];
+                            any = any || go[e];
+                        }
+                        // (x <= the last id: nobody goes past the list's end)
+                        while (any) {
+                            any = false;
+#pragma unroll
+                            for (int e = 0; e < kQiEntries; ++e) {
+                                if (go[e]) {
+                                    pos[e][j2] = min(pos[e][j2] + 1, n[j2] - 1);
+                                    const uint32_t at = ids[pos[e][j2]];
+                                    go[e] = at < x[e] && pos[e][j2] < n[j2] - 1;
+                                    found[e][j2] = at == x[e];
+                                }
+                                any = any || go[e];
+                            }
+                        }
+                    } else {
+                        int step = 1 << (31 - __builtin_clz((unsigned)n[j2]));
+                        for (; step > 0; step >>= 1) {
+#pragma unroll
+                            for (int e = 0; e < kQiEntries; ++e) {
+                                // ids below x among the first pos + step ones?
+                                const int cand = pos[e][j2] + step;
+                                if (cand <= n[j2] && ids[min(cand, n[j2]) - 1] < x[e]) pos[e][j2] = cand;
+                            }
+                        }
+#pragma unroll
+                        for (int e = 0; e < kQiEntries; ++e) {
+                            pos[e][j2] = min(pos[e][j2], n[j2] - 1);
+                            found[e][j2] = found[e][j2] && ids[pos[e][j2]] == x[e];
                         }
                     }
                 }
 #pragma unroll
                 for (int e = 0; e < kQiEntries; ++e) {
-                    const int t = t0 + e * kWave + lane;
-                    int32_t row[K];
+                    const int t = t0 + e * T + tid;
+                    RowIds<K> row;
 #pragma unroll
                     for (int j2 = 0; j2 < K; ++j2) {
-                        const int p = pos[e][j2];
-                        const uint32_t at = ids_lds[j2 * list_stride + 1 + min(p, max(n[j2] - 1, 0))];
-                        const bool found = p < n[j2] && at == x[e];
-                        if constexpr (kCode) {
-                            const uint32_t c = code_lds[j2 * list_stride + 1 + min(p, max(n[j2] - 1, 0))];
-                            row[j2] = found ? (int32_t)c : -1;
-                        } else {
-                            row[j2] = found ? (int32_t)(lo[j2] + p) : -1;
+                        row.v[j2] = -1;
+                        if (found[e][j2]) {
+                            if constexpr (kCode) {
+                                row.v[j2] = (int32_t)lds32[lay.codes + j2 * lay.list + pos[e][j2]];
+                            } else {
+                                row.v[j2] = (int32_t)(lo[j2] + pos[e][j2]);
+                            }
                         }
                     }
-                    if (t < n_key) {
-                        // the K indices of an entry as one 4*K-byte store
-                        RowIds<K> ids;
-#pragma unroll
-                        for (int j2 = 0; j2 < K; ++j2) ids.v[j2] = row[j2];
-                        *reinterpret_cast<RowIds<K>*>(out_j + (int64_t)t * K) = ids;
-                    }
+                    // the K indices of an entry as one 4*K-byte store
+                    if (t < n_key) *reinterpret_cast<RowIds<K>*>(out_j + (int64_t)t * K) = row;
                 }
             }
         }
-        wave_sync();  // the next query reuses the LDS words
     }
 }
 
-template <int K, int WPB, int QE, bool kCode>
-static hipError_t launch_query_ids_kwe(hipStream_t stream, const int32_t* walks,
+template <int K, int QE, bool kCode>
+static hipError_t launch_query_ids_ke(hipStream_t stream, int threads, const int32_t* walks,
                                       const int64_t* rpe_off, const int32_t* rpe_ids,
-                                      const int32_t* code,
-                                      int64_t n_blocks, int32_t M, int32_t m, int32_t max_set,
-                                      int64_t table_rows, const int32_t* queries,
+                                      const int32_t* code, int64_t n_blocks, int32_t n_key,
+                                      int32_t max_set, int64_t table_rows, const int32_t* queries,
                                       int64_t n_queries, int32_t* out, uint32_t* err) {
-    const size_t lds_bytes = (size_t)WPB * (kCode ? 2 : 1) * K * (max_set + 1) * 4;
-    const void* fn = reinterpret_cast<const void*>(query_ids_kernel<K, WPB, QE, kCode>);
+    const size_t lds_bytes = (size_t)qid_lds(K, max_set, kCode).total * 4;
+    const void* fn = reinterpret_cast<const void*>(query_ids_kernel<K, QE, kCode>);
     if (lds_bytes > 48 * 1024) {
         hipError_t rc = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                             (int)lds_bytes);
         if (rc != hipSuccess) return rc;
     }
-    // a wave per query and the hardware hands the workgroups out (a wave loops only where the
-    // grid cannot be that large)
-    int64_t blocks = (n_queries + WPB - 1) / WPB;
-    if (blocks > 0x7FFFFFFFll) blocks = 0x7FFFFFFFll;
-    hipLaunchKernelGGL((query_ids_kernel<K, WPB, QE, kCode>), dim3((unsigned)blocks),
-                       dim3(WPB * kWave), lds_bytes, stream, walks, rpe_off, rpe_ids, code, n_blocks,
-                       M * (m + 1), max_set,
-                       table_rows, queries, n_queries, out, err);
+    // a workgroup per query and the hardware hands them out (a workgroup loops only where the grid
+    // cannot be that large)
+    const int64_t most = 0x7FFFFFFFll / threads;
+    hipLaunchKernelGGL((query_ids_kernel<K, QE, kCode>),
+                       dim3((unsigned)(n_queries < most ? n_queries : most)), dim3(threads), lds_bytes,
+                       stream, walks, rpe_off, rpe_ids, code, n_blocks, n_key, max_set, table_rows,
+                       queries, n_queries, out, err);
     return hipGetLastError();
 }
 
-template <int K, int WPB, bool kCode>
-static hipError_t launch_query_ids_kw(hipStream_t stream, const int32_t* walks,
-                                      const int64_t* rpe_off, const int32_t* rpe_ids,
-                                      const int32_t* code, int64_t n_blocks, int32_t M, int32_t m,
-                                      int32_t max_set, int64_t table_rows, const int32_t* queries,
-                                      int64_t n_queries, int32_t* out, uint32_t* err) {
-    const int64_t n_key = (int64_t)M * (m + 1);
-#define SUREL_QI_ENTRIES(QE_)                                                                  \
-    return launch_query_ids_kwe<K, WPB, QE_, kCode>(stream, walks, rpe_off, rpe_ids, code, \
-                                                    n_blocks, M, m, max_set, table_rows, queries, \
-                                                    n_queries, out, err)
-    if (n_key <= kWave) SUREL_QI_ENTRIES(1);
-    if (n_key <= 2 * kWave) SUREL_QI_ENTRIES(2);
-    if (n_key <= 4 * kWave) SUREL_QI_ENTRIES(4);
-    SUREL_QI_ENTRIES(8);
-#undef SUREL_QI_ENTRIES
-}
-
+// Up to four entries of a walk block a thread at a time, and as many wavefronts as then cover the
+// block, four at most.
 template <int K, bool kCode>
-static hipError_t launch_query_ids_k(hipStream_t stream, int max_lds_bytes,
-                                     const int32_t* walks, const int64_t* rpe_off,
+static hipError_t launch_query_ids_k(hipStream_t stream, const int32_t* walks, const int64_t* rpe_off,
                                      const int32_t* rpe_ids, const int32_t* code, int64_t n_blocks,
-                                     int32_t M, int32_t m,
-                                     int32_t max_set, int64_t table_rows, const int32_t* queries,
-                                     int64_t n_queries, int32_t* out, uint32_t* err) {
-    const size_t per_wave = (size_t)(kCode ? 2 : 1) * K * (max_set + 1) * 4;
-    // waves per workgroup: the choice that lets a compute unit hold the most waves
-    int best = 1, best_waves = 0;
-    for (int w = 4; w >= 1; w /= 2) {
-        const size_t wg = per_wave * w;
-        if (wg > (size_t)max_lds_bytes) continue;
-        int waves = (int)((size_t)max_lds_bytes / wg) * w;
-        if (waves > 32) waves = 32;
-        if (waves > best_waves) {
-            best_waves = waves;
-            best = w;
-        }
-    }
-#define SUREL_QI_CASE(W_)                                                                        \
-    if (best == (W_))                                                                            \
-        return launch_query_ids_kw<K, W_, kCode>(stream, walks, rpe_off, rpe_ids, code,   \
-                                                 n_blocks, M, m, max_set, table_rows, queries,  \
-                                                 n_queries, out, err);
-    SUREL_QI_CASE(4)
-    SUREL_QI_CASE(2)
-    SUREL_QI_CASE(1)
-#undef SUREL_QI_CASE
-    return hipErrorInvalidValue;
+                                     int32_t n_key, int32_t max_set, int64_t table_rows,
+                                     const int32_t* queries, int64_t n_queries, int32_t* out,
+                                     uint32_t* err) {
+#define SUREL_QI_LAUNCH(QE_, THREADS_)                                                          \
+    return launch_query_ids_ke<K, QE_, kCode>(stream, THREADS_, walks, rpe_off, rpe_ids, code, \
+                                              n_blocks, n_key, max_set, table_rows, queries,   \
+                                              n_queries, out, err)
+    if (n_key <= kWave) SUREL_QI_LAUNCH(1, 64);
+    if (n_key <= 2 * kWave) SUREL_QI_LAUNCH(2, 64);
+    if (n_key <= 4 * kWave) SUREL_QI_LAUNCH(4, 64);
+    if (n_key <= 8 * kWave) SUREL_QI_LAUNCH(4, 128);
+    SUREL_QI_LAUNCH(4, 256);
+#undef SUREL_QI_LAUNCH
 }
 
 hipError_t launch_query_ids(hipStream_t stream, int max_lds_bytes, const int32_t* walks,
                             const int64_t* rpe_off, const int32_t* rpe_ids, const int32_t* code,
-                            int64_t n_blocks,
-                            int32_t M, int32_t m, int32_t max_set, int64_t table_rows,
-                            const int32_t* queries, int64_t n_queries, int32_t k, int32_t* out,
-                            uint32_t* err) {
+                            int64_t n_blocks, int32_t M, int32_t m, int32_t max_set,
+                            int64_t table_rows, const int32_t* queries, int64_t n_queries, int32_t k,
+                            int32_t* out, uint32_t* err) {
     if (n_queries == 0) return hipSuccess;
-    if ((size_t)(code ? 2 : 1) * k * (max_set + 1) * 4 > (size_t)max_lds_bytes)
+    if ((size_t)qid_lds(k, max_set, code != nullptr).total * 4 + 64 > (size_t)max_lds_bytes)
         return hipErrorInvalidValue;
+    const int32_t n_key = M * (m + 1);
 #define SUREL_QI_ARGS \
-    stream, max_lds_bytes, walks, rpe_off, rpe_ids, code, n_blocks, M, m, max_set, \
-        table_rows, queries, n_queries, out, err
+    stream, walks, rpe_off, rpe_ids, code, n_blocks, n_key, max_set, table_rows, queries, n_queries, out, err
     if (k == 2 && !code) return launch_query_ids_k<2, false>(SUREL_QI_ARGS);
     if (k == 3 && !code) return launch_query_ids_k<3, false>(SUREL_QI_ARGS);
     if (k == 2) return launch_query_ids_k<2, true>(SUREL_QI_ARGS);
