@@ -6,15 +6,17 @@
 //
 // Here the blocks' id lists are sorted, and a workgroup (one to four wavefronts, by the length of
 // the walk blocks) stages the K lists of a query in LDS with a directory for each: the range of
-// the list's ids cut into twice as many equal parts as the list may have ids (2,048 at most), and
-// for every part the place of the first id in it or behind it.  A look-up reads the directory and
+// the list's ids cut into as many equal parts as the list may have ids (a power of two), and for
+// every part the place of the first id in it or behind it.  A look-up reads the directory and
 // then the list from there on: one or two ids, since node ids lie evenly in their range wherever
 // labels carry no order.  The 2K directory entries and first ids of an entry's look-ups are read
 // for all entries of a thread together; only lanes that have to go on read further.  Lists whose
 // ids crowd together (more than kCrowd in one part) are searched by bisection instead, which needs
 // no directory.
 // What bounds it: LDS reads at random places (a wavefront's 64 lanes hit some banks four or five
-// times): FIGQID
+// times) and the instructions around them, so that waves in flight are what counts: 65,536 pairs of
+// M = 200, m = 4 with codes take 0.44 ms (4.9 TB/s of the bytes in and out) with eight waves per
+// SIMD, 0.50 with five; twice as many parts, 0.55; a wave per query with bisection, 1.22.
 // (Per-query hash dictionaries in LDS were measured too and lost: their probe loops diverge.)
 #include "device_util.h"
 #include "kernels.h"
@@ -28,6 +30,7 @@ struct __attribute__((aligned(4))) RowIds {
 };
 
 constexpr int kCrowd = 8;  // ids in one part of the directory, at most
+constexpr uint32_t kQidEnd = 0xFFFFFFFFu;
 
 // LDS of one workgroup, in 32-bit words.
 struct QidLds {
@@ -39,20 +42,28 @@ struct QidLds {
 };
 __host__ __device__ inline QidLds qid_lds(int K, int max_set, bool code) {
     QidLds o;
-    o.list = max_set;
+    o.list = max_set + 2;  // behind the last id: two that no walk entry reaches
     o.codes = K * o.list;
     o.dir = o.codes * (code ? 2 : 1);
     o.parts = 64;
-    while (o.parts < 2 * max_set && o.parts < 2048) o.parts *= 2;
+    while (o.parts < max_set && o.parts < 2048) o.parts *= 2;
     o.total = o.dir + K * o.parts / 2;
     return o;
+}
+
+template <int K>
+__device__ __forceinline__ int n_of(const int (&n)[K], int j) {
+    int v = n[0];
+#pragma unroll
+    for (int jj = 1; jj < K; ++jj) v = j == jj ? n[jj] : v;
+    return v;
 }
 
 // kQiEntries: walk entries of a block that a thread looks up at a time.
 // kCode: the rows' codes (their RPE-IDs in the pruned array of Sec. 3.3) are staged next to the
 // ids and go out instead of the row indices.
 template <int K, int kQiEntries, bool kCode>
-__global__ __launch_bounds__(256) void query_ids_kernel(
+__global__ __launch_bounds__(256, 8) void query_ids_kernel(
     const int32_t* __restrict__ walks, const int64_t* __restrict__ rpe_off,
     const int32_t* __restrict__ rpe_ids, const int32_t* __restrict__ code, int64_t n_blocks,
     int32_t n_key, int32_t max_set, int64_t table_rows, const int32_t* __restrict__ queries,
@@ -138,6 +149,7 @@ __global__ __launch_bounds__(256) void query_ids_kernel(
                 }
             }
         }
+        if (tid < 2 * K) lds32[(tid >> 1) * lay.list + n_of<K>(n, tid >> 1) + (tid & 1)] = kQidEnd;
         __syncthreads();
         // The directories.  x lies in part mulhi(x - first, scale) of its list's range; part p's
         // entry is the place of the first id in part p or behind it, so the thread of id t writes
@@ -173,64 +185,53 @@ __global__ __launch_bounds__(256) void query_ids_kernel(
             int32_t* out_j = out_q + (int64_t)j * n_key * K;
             for (int t0 = 0; t0 < n_key; t0 += kQiEntries * T) {
                 uint32_t x[kQiEntries];
-                int pos[kQiEntries][K];      // first id of list j2 that is not below x
-                bool found[kQiEntries][K];
+                uint32_t pos[kQiEntries][K];  // place in list j2 where the search ended
+                uint32_t at[kQiEntries][K];   // the id there (kQidEnd behind the list)
 #pragma unroll
                 for (int e = 0; e < kQiEntries; ++e) {
                     const int t = min(t0 + e * T + tid, n_key - 1);
                     x[e] = t0 == 0 ? x_first[j][e] : (uint32_t)__builtin_nontemporal_load(W + t);
+                    x[e] = min(x[e], kQidEnd - 1u);  // an entry of -1 names no node
                 }
 #pragma unroll
                 for (int j2 = 0; j2 < K; ++j2) {
                     const uint32_t* ids = lds32 + j2 * lay.list;
                     const uint16_t* dir = dirs + j2 * lay.parts;
-                    // an id outside the list's range is not in it: it is looked up as the first
-#pragma unroll
-                    for (int e = 0; e < kQiEntries; ++e) {
-                        const uint32_t d = x[e] - first[j2];
-                        found[e][j2] = n[j2] > 0 && d <= range[j2];
-                        const uint32_t part = __umulhi(found[e][j2] ? d : 0u, scale[j2]);
-                        pos[e][j2] = (bisect >> j2 & 1u) == 0u && n[j2] > 0 ? min((int)dir[part], n[j2] - 1) : 0;
-                    }
                     if ((bisect >> j2 & 1u) == 0u) {
-                        bool go[kQiEntries];
-                        bool any = false;
+                        // an id outside the list's range is looked up in the last part
+                        bool more = false;
+#pragma unroll
+                        for (int e = 0; e < kQiEntries; ++e)
+                            pos[e][j2] = dir[__umulhi(min(x[e] - first[j2], range[j2]), scale[j2])];
 #pragma unroll
                         for (int e = 0; e < kQiEntries; ++e) {
-                            const uint32_t at = n[j2] > 0 ? ids[pos[e][j2]] : 0u;
-                            go[e] = found[e][j2] && at < x[e];
-                            found[e][j2] = found[e][j2] && at >= x[e] ? at == x[e] : found[e][j2];
-                            any = any || go[e];
+                            pos[e][j2] = min(pos[e][j2], (uint32_t)n[j2]);
+                            const uint32_t a0 = ids[pos[e][j2]], a1 = ids[pos[e][j2] + 1];
+                            pos[e][j2] += a0 < x[e] ? 1u : 0u;
+                            at[e][j2] = a0 < x[e] ? a1 : a0;
+                            more = more || at[e][j2] < x[e];
                         }
-                        // (x <= the last id: nobody goes past the list's end)
-                        while (any) {
-                            any = false;
+                        while (more) {  // ends at kQidEnd
+                            more = false;
 #pragma unroll
                             for (int e = 0; e < kQiEntries; ++e) {
-                                if (go[e]) {
-                                    pos[e][j2] = min(pos[e][j2] + 1, n[j2] - 1);
-                                    const uint32_t at = ids[pos[e][j2]];
-                                    go[e] = at < x[e] && pos[e][j2] < n[j2] - 1;
-                                    found[e][j2] = at == x[e];
-                                }
-                                any = any || go[e];
+                                if (at[e][j2] < x[e]) at[e][j2] = ids[++pos[e][j2]];
+                                more = more || at[e][j2] < x[e];
                             }
                         }
                     } else {
-                        int step = 1 << (31 - __builtin_clz((unsigned)n[j2]));
-                        for (; step > 0; step >>= 1) {
+                        // pos = number of ids below x
+                        for (int e = 0; e < kQiEntries; ++e) pos[e][j2] = 0u;
+                        for (uint32_t step = 1u << (31 - __builtin_clz((unsigned)n[j2])); step > 0; step >>= 1) {
 #pragma unroll
                             for (int e = 0; e < kQiEntries; ++e) {
-                                // ids below x among the first pos + step ones?
-                                const int cand = pos[e][j2] + step;
-                                if (cand <= n[j2] && ids[min(cand, n[j2]) - 1] < x[e]) pos[e][j2] = cand;
+                                const uint32_t cand = pos[e][j2] + step;
+                                if (cand <= (uint32_t)n[j2] && ids[min(cand, (uint32_t)n[j2]) - 1u] < x[e])
+                                    pos[e][j2] = cand;
                             }
                         }
 #pragma unroll
-                        for (int e = 0; e < kQiEntries; ++e) {
-                            pos[e][j2] = min(pos[e][j2], n[j2] - 1);
-                            found[e][j2] = found[e][j2] && ids[pos[e][j2]] == x[e];
-                        }
+                        for (int e = 0; e < kQiEntries; ++e) at[e][j2] = ids[pos[e][j2]];
                     }
                 }
 #pragma unroll
@@ -239,13 +240,12 @@ __global__ __launch_bounds__(256) void query_ids_kernel(
                     RowIds<K> row;
 #pragma unroll
                     for (int j2 = 0; j2 < K; ++j2) {
-                        row.v[j2] = -1;
-                        if (found[e][j2]) {
-                            if constexpr (kCode) {
-                                row.v[j2] = (int32_t)lds32[lay.codes + j2 * lay.list + pos[e][j2]];
-                            } else {
-                                row.v[j2] = (int32_t)(lo[j2] + pos[e][j2]);
-                            }
+                        const bool found = at[e][j2] == x[e];
+                        if constexpr (kCode) {
+                            row.v[j2] = -1;
+                            if (found) row.v[j2] = (int32_t)lds32[lay.codes + j2 * lay.list + pos[e][j2]];
+                        } else {
+                            row.v[j2] = found ? (int32_t)((uint32_t)lo[j2] + pos[e][j2]) : -1;
                         }
                     }
                     // the K indices of an entry as one 4*K-byte store

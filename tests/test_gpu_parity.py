@@ -510,6 +510,32 @@ def test_query_rpe_ids_problems_are_flagged(ctx):
     assert ctx.check() == binding.DEV_SET_TOO_LARGE and bool((got == -1).all())
 
 
+@pytest.mark.parametrize("k,M,m", [(2, 13, 4), (2, 100, 4), (2, 204, 4), (3, 60, 2), (3, 400, 4)])
+def test_query_rpe_ids_of_crowded_and_even_id_lists(ctx, k, M, m):
+    # hand-made walks whose blocks' ids lie evenly in their range, crowd together at one end with
+    # one id far away, follow one another, are all the same, or lie far above everybody else's:
+    # the look-up's directory and its bisection, walk blocks of one and several rounds
+    rng = np.random.default_rng(M + k)
+    n_nodes = 1 << 27
+    sets = [rng.choice(n_nodes, 300, replace=False), np.r_[np.arange(280), n_nodes - 1],
+            np.arange(5000, 5300), np.array([77]), np.arange(n_nodes - 200, n_nodes),
+            np.r_[np.arange(0, 3000, 30), np.arange(100000, 100009), 70000000], np.array([0, n_nodes - 1])]
+    blocks = [s[rng.integers(0, s.size, size=(M, m + 1))] for s in sets]
+    blocks += [np.concatenate([b[: M // 2], c[M // 2:]]) for b, c in zip(blocks, blocks[1:])]
+    walks = np.stack(blocks).astype(np.int32)
+    off, ids, cnt = oracle.build_rpe(walks)
+    queries = rng.integers(0, len(blocks), size=(200, k)).astype(np.int32)
+    max_set = int(np.diff(off).max())
+    code = rng.integers(0, 1 << 30, size=ids.size).astype(np.int32)
+    want = oracle.query_rpe_ids(walks, off, ids, queries)
+    got = binding.query_rpe_ids(ctx, dev(walks), dev(off), dev(ids), dev(queries), max_set)
+    assert ctx.check() == 0
+    assert np.array_equal(got.cpu().numpy().astype(np.int64), want)
+    got = binding.query_rpe_ids(ctx, dev(walks), dev(off), dev(ids), dev(queries), max_set, code=dev(code))
+    assert ctx.check() == 0
+    assert np.array_equal(got.cpu().numpy(), np.where(want < 0, -1, code[want]))
+
+
 def test_join_problems_are_flagged(ctx):
     wl = synth.Workload("t", "rmat", 256, 900, 0.0, 20, 3, 0, 2, "uniform", graph_seed=3)
     rp, ci = synth.make_graph(wl)
