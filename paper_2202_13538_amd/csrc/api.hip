@@ -165,6 +165,12 @@ int ensure_workspace(surel_ctx* ctx, int64_t n, int32_t** counts, int64_t** part
     return SUREL_OK;
 }
 
+hipError_t exclusive_scan(surel_ctx* ctx, const int32_t* counts, int64_t n, int64_t* off,
+                          int64_t* partials) {
+    return surel::launch_exclusive_scan(ctx->stream, ctx->n_cu, counts, n, off, partials, ctx->d_small,
+                                        ctx->spin_limit, ctx->d_err);
+}
+
 // Wait for the stream and fetch off[n] (the row total) into *h_rows.
 int read_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, int64_t* h_rows) {
     if (hipMemcpyAsync(ctx->h_pinned, d_off + n, sizeof(int64_t), hipMemcpyDeviceToHost,
@@ -359,8 +365,7 @@ static int rpe_layout(surel_ctx* ctx, const int32_t* d_walks, int64_t n_seeds, i
         sizes = counts;
     }
     KernelSpan span(ctx, SUREL_K_SCAN);
-    if (surel::launch_exclusive_scan(ctx->stream, sizes, n_seeds, d_rpe_off, partials) != hipSuccess)
-        return SUREL_E_HIP;
+    if (exclusive_scan(ctx, sizes, n_seeds, d_rpe_off, partials) != hipSuccess) return SUREL_E_HIP;
     return SUREL_OK;
 }
 
@@ -476,8 +481,7 @@ static int empty_table(surel_ctx* ctx, int64_t* d_rpe_off) {
     int32_t* counts = nullptr;
     int64_t* partials = nullptr;
     if (int rc = ensure_workspace(ctx, 0, &counts, &partials)) return rc;
-    if (surel::launch_exclusive_scan(ctx->stream, counts, 0, d_rpe_off, partials) != hipSuccess)
-        return SUREL_E_HIP;
+    if (exclusive_scan(ctx, counts, 0, d_rpe_off, partials) != hipSuccess) return SUREL_E_HIP;
     return SUREL_OK;
 }
 
@@ -624,8 +628,7 @@ static int join_layout(surel_ctx* ctx, const JoinScratch& ws, const int64_t* d_r
     if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
     if (hrc != hipSuccess) return SUREL_E_HIP;
     KernelSpan span(ctx, SUREL_K_SCAN);
-    if (surel::launch_exclusive_scan(ctx->stream, ws.counts, n_queries, d_join_off, ws.partials) !=
-        hipSuccess)
+    if (exclusive_scan(ctx, ws.counts, n_queries, d_join_off, ws.partials) != hipSuccess)
         return SUREL_E_HIP;
     return SUREL_OK;
 }
@@ -879,7 +882,8 @@ int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_qu
         return rc;
     KernelSpan span(ctx, SUREL_K_BATCH);
     if (surel::launch_query_incidence(ctx->stream, d_queries, n_queries, k, n_nodes, d_inc_off,
-                                      d_inc_q, ctx->d_batch, ctx->d_err) != hipSuccess)
+                                      d_inc_q, ctx->d_batch, ctx->d_small, ctx->spin_limit,
+                                      ctx->d_err) != hipSuccess)
         return SUREL_E_HIP;
     return SUREL_OK;
 }

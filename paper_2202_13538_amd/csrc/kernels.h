@@ -155,11 +155,13 @@ hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScra
 
 // incidence.hip.  The queries of every node: inc_q[inc_off[x] .. inc_off[x+1]) = indices of the
 // queries that name node x, ascending (a query that names x twice is listed twice).  Entries
-// outside [0, n_nodes) are flagged and left out.  scratch: incidence_scratch_bytes(n_queries*k).
+// outside [0, n_nodes) are flagged and left out.  scratch: incidence_scratch_bytes(n_queries*k);
+// small_scan: as for launch_join_small.
 size_t incidence_scratch_bytes(int64_t n_entries);
 hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, int64_t n_queries,
                                   int32_t k, int32_t n_nodes, int64_t* inc_off, int32_t* inc_q,
-                                  void* scratch, uint32_t* err);
+                                  void* scratch, void* small_scan, uint32_t spin_limit,
+                                  uint32_t* err);
 
 // bfs.hip.  n_batches mini-batches, each by breadth-first search from its own n_start start
 // nodes over nodes that share queries, until B1 nodes or B2 queries.  vbar int32[n_batches][B1],
@@ -180,10 +182,12 @@ int64_t lookback_words(int64_t n_items);
 hipError_t launch_lookback_clear(hipStream_t stream, uint64_t* lb, int64_t n_items,
                                  int64_t* total_out);
 
-// scan.hip.  off[0..n] = exclusive prefix sums of counts[0..n-1] (off[n] = total).
-// partials: device scratch of scan_partials_len(n) int64.
+// scan.hip.  off[0..n] = exclusive prefix sums of counts[0..n-1] (off[n] = total, -1 if a bounded
+// wait ran out).  partials: device scratch of scan_partials_len(n) int64; small_scan: as for
+// launch_join_small.
 int64_t scan_partials_len(int64_t n);
-hipError_t launch_exclusive_scan(hipStream_t stream, const int32_t* counts, int64_t n,
-                                 int64_t* off, int64_t* partials);
+hipError_t launch_exclusive_scan(hipStream_t stream, int n_cu, const int32_t* counts, int64_t n,
+                                 int64_t* off, int64_t* partials, void* small_scan,
+                                 uint32_t spin_limit, uint32_t* err);
 
 }  // namespace surel

@@ -1,9 +1,12 @@
 // Exclusive prefix sums that turn per-seed / per-query row counts into the offset arrays
-// rpe_off and join_off.  Reduce-then-scan in three small launches: tile sums, a scan of
-// the tile sums by one workgroup, and a tile-local scan that adds the tile's base.
+// rpe_off and join_off.  Up to 8,192 counts per compute unit (two million): one launch, whose
+// workgroups are all on the device and add up what those before them have published
+// (small_scan.h); 5 us instead of 14.  More: reduce-then-scan in three launches, tile sums, a scan
+// of the tile sums by one workgroup, and a tile-local scan that adds the tile's base.
 #include "device_util.h"
 #include "kernels.h"
 #include "lookback.h"
+#include "small_scan.h"
 
 namespace surel {
 
@@ -29,6 +32,57 @@ __device__ __forceinline__ uint32_t block_excl_sum(uint32_t v, uint32_t* total) 
     }
     *total = sum;
     return base + incl - v;
+}
+
+constexpr int kWideThreads = 1024;
+constexpr int kWideItems = 8;
+constexpr int kWideTile = kWideThreads * kWideItems;
+__global__ __launch_bounds__(kWideThreads) void scan_at_once_kernel(
+    const int32_t* __restrict__ counts, int64_t n, int64_t* __restrict__ off, SmallScan* __restrict__ ss,
+    uint32_t spin_limit, uint32_t* __restrict__ err) {
+    __shared__ uint32_t wave_sums[kWideThreads / kWave];
+    __shared__ int64_t s_base;
+    const int lane = lane_id();
+    const int wave = (int)(threadIdx.x >> 6);
+    uint32_t tag = 0;
+    if (wave == 0) tag = small_scan_tag(ss);
+    // thread t owns the kWideItems consecutive entries from `first` on
+    const int64_t first = (int64_t)blockIdx.x * kWideTile + (int64_t)threadIdx.x * kWideItems;
+    uint32_t item[kWideItems];
+    uint32_t v = 0;
+#pragma unroll
+    for (int j = 0; j < kWideItems; ++j) {
+        item[j] = first + j < n ? (uint32_t)counts[first + j] : 0u;
+        v += item[j];
+    }
+    const uint32_t incl = wave_incl_sum(v);
+    if (lane == kWave - 1) wave_sums[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWideThreads / kWave; ++w) {
+        if (w < wave) before += wave_sums[w];
+        total += wave_sums[w];
+    }
+    if (wave == 0) {
+        const int at = (int)blockIdx.x;
+        if (lane == 0) small_scan_publish(ss, at, tag, total);
+        const int64_t base = small_scan_before(ss, at, tag, spin_limit, lane);
+        if (lane == 0) {
+            small_scan_done(ss, at, tag, (int)gridDim.x);
+            s_base = base;
+            if (base < 0) atomicOr(err, kDevStall);
+            if (at == (int)gridDim.x - 1) off[n] = base < 0 ? -1 : base + total;
+        }
+    }
+    __syncthreads();
+    if (s_base < 0) return;
+    int64_t run = s_base + before + (incl - v);
+#pragma unroll
+    for (int j = 0; j < kWideItems; ++j) {
+        if (first + j < n) off[first + j] = run;
+        run += item[j];
+    }
 }
 
 __global__ __launch_bounds__(kScanThreads) void tile_sum_kernel(const int32_t* __restrict__ counts,
@@ -139,8 +193,15 @@ hipError_t launch_lookback_clear(hipStream_t stream, uint64_t* lb, int64_t n_ite
 
 int64_t scan_partials_len(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 
-hipError_t launch_exclusive_scan(hipStream_t stream, const int32_t* counts, int64_t n,
-                                 int64_t* off, int64_t* partials) {
+hipError_t launch_exclusive_scan(hipStream_t stream, int n_cu, const int32_t* counts, int64_t n,
+                                 int64_t* off, int64_t* partials, void* small_scan,
+                                 uint32_t spin_limit, uint32_t* err) {
+    if (n > 0 && n <= (int64_t)n_cu * kWideTile && n <= (int64_t)kSmallScanMax * kWideTile) {
+        hipLaunchKernelGGL(scan_at_once_kernel, dim3((unsigned)((n + kWideTile - 1) / kWideTile)),
+                           dim3(kWideThreads), 0, stream, counts, n, off,
+                           static_cast<SmallScan*>(small_scan), spin_limit, err);
+        return hipGetLastError();
+    }
     const int64_t n_tiles = (n + kScanTile - 1) / kScanTile;
     if (n_tiles > 0) {
         hipLaunchKernelGGL(tile_sum_kernel, dim3((unsigned)n_tiles), dim3(kScanThreads), 0,
