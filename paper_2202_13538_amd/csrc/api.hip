@@ -905,7 +905,7 @@ int surel_bfs_batches(surel_ctx* ctx, const int32_t* d_queries, int64_t n_querie
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
     if (int rc = grow_buffer(ctx, &ctx->d_batch, &ctx->batch_bytes,
-                             surel::bfs_scratch_bytes(ctx->n_cu, n_batches, n_start, B1, B2)))
+                             surel::bfs_scratch_bytes(ctx->n_cu, n_batches, n_start, B1, B2, k)))
         return rc;
     KernelSpan span(ctx, SUREL_K_BATCH);
     if (surel::launch_bfs_batches(ctx->stream, ctx->n_cu, d_queries, n_queries, k, n_nodes, d_inc_off,

@@ -167,7 +167,8 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
 // nodes over nodes that share queries, until B1 nodes or B2 queries.  vbar int32[n_batches][B1],
 // batch int32[n_batches][B2], tuples int32[n_batches][B2][k] (optional), counts
 // int32[n_batches][2] = (nodes, queries) of every batch.  scratch: bfs_scratch_bytes(...).
-size_t bfs_scratch_bytes(int n_cu, int64_t n_batches, int32_t n_start, int32_t B1, int32_t B2);
+size_t bfs_scratch_bytes(int n_cu, int64_t n_batches, int32_t n_start, int32_t B1, int32_t B2,
+                         int32_t k);
 hipError_t launch_bfs_batches(hipStream_t stream, int n_cu, const int32_t* queries,
                               int64_t n_queries, int32_t k, int32_t n_nodes, const int64_t* inc_off,
                               const int32_t* inc_q, const int32_t* start, int64_t n_batches,
