@@ -190,7 +190,7 @@ int make_edge_records(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d
     *records = surel::EdgeRecords{};
     if (!surel::walks_want_records(n_edges, n_seeds, M, m)) return SUREL_OK;
     surel::EdgeRecords plan = surel::edge_record_plan(n_nodes, n_edges);
-    const size_t need = surel::edge_record_bytes(plan, n_edges);
+    const size_t need = surel::edge_record_bytes(plan, n_nodes, n_edges);
     (void)grow_buffer(ctx, &ctx->d_rec, &ctx->rec_bytes, need);
     if (ctx->rec_bytes < need) return SUREL_OK;
     plan.data = ctx->d_rec;

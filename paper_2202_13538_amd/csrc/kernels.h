@@ -22,7 +22,7 @@ inline void launch_and_mark(Kernel kernel, dim3 grid, dim3 block, size_t lds_byt
 
 // walk.hip.  The per-edge neighbour records that launch_edge_records makes of a CSR (layouts in
 // walk_core.h; worth making when walks_want_records says so): edge_record_plan picks the layout
-// for a graph, the caller provides edge_record_bytes(plan, n_edges) bytes in plan.data.
+// for a graph, the caller provides edge_record_bytes(plan, n_nodes, n_edges) bytes in plan.data.
 struct EdgeRecords {
     const void* data = nullptr;  // null: no records, the walk reads the CSR
     int format = 0;
@@ -30,7 +30,7 @@ struct EdgeRecords {
 };
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m);
 EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges);
-size_t edge_record_bytes(const EdgeRecords& plan, int64_t n_edges);
+size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges);
 hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const int32_t* col_idx,
                                int32_t n_nodes, int64_t n_edges, const EdgeRecords& rec);
 

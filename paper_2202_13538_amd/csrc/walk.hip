@@ -29,35 +29,126 @@ namespace surel {
 constexpr int kWalkWavesPerBlock = 4;
 constexpr int kWalkChains = 2;  // walks a lane moves at a time
 
+// Rows of 12 consecutive nodes in 16 bytes: the start of the first row, then the degrees, a byte
+// each.  A byte of 255 says "ask row_ptr": a degree that does not fit, a malformed row, and every
+// row behind such a one in the group (a row starts where the degrees before it in the group end).
+constexpr int kRowsPerGroup = 12;
+constexpr uint32_t kAskRowPtr = 255u;
+static size_t row_group_bytes(int32_t n_nodes) {
+    return ((size_t)n_nodes + kRowsPerGroup - 1) / kRowsPerGroup * sizeof(uint4);
+}
+
+__global__ void row_group_kernel(const int32_t* __restrict__ row_ptr, int32_t n_nodes,
+                                 int64_t n_edges, uint4* __restrict__ groups) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t x0 = g * kRowsPerGroup;
+    if (x0 >= n_nodes) return;
+    int32_t start[kRowsPerGroup + 1];
+#pragma unroll
+    for (int j = 0; j <= kRowsPerGroup; ++j) start[j] = row_ptr[min(x0 + j, (int64_t)n_nodes)];
+    uint32_t w[4] = {(uint32_t)start[0]};
+    bool ask = false;
+#pragma unroll
+    for (int j = 0; j < kRowsPerGroup; ++j) {
+        const int32_t lo = start[j], hi = start[j + 1];
+        ask = ask || lo < 0 || hi < lo || (int64_t)hi > n_edges || (uint32_t)(hi - lo) >= kAskRowPtr;
+        w[1 + j / 4] |= (ask ? kAskRowPtr : (uint32_t)(hi - lo)) << (j % 4 * 8);
+    }
+    groups[g] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Both ends of node t's row in one load.
+__device__ __forceinline__ void row_ends(const int32_t* __restrict__ row_ptr, uint32_t t, int32_t* lo,
+                                         int32_t* hi) {
+    typedef int ends_t __attribute__((ext_vector_type(2), aligned(4)));
+    const ends_t ends = *reinterpret_cast<const ends_t*>(row_ptr + t);
+    *lo = ends.x;
+    *hi = ends.y;
+}
+
 // The record of every CSR entry e (layouts in walk_core.h): the neighbour col_idx[e], the start
 // of its row and its degree; an entry that names no node, or whose row is malformed, gets the
 // layout's "bad entry" id (the walker will stay in place and flag it).
-template <int kRec>
-__global__ void edge_record_kernel(const int32_t* __restrict__ row_ptr,
-                                   const int32_t* __restrict__ col_idx, int32_t n_nodes,
-                                   int64_t n_edges, int id_bits, int lo_bits,
-                                   void* __restrict__ rec) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_edges) return;
-    const int32_t t = col_idx[e];
-    bool ok = false;
-    int32_t lo = 0, hi = 0;
-    if ((uint32_t)t < (uint32_t)n_nodes) {
-        lo = row_ptr[t];
-        hi = row_ptr[t + 1];
-        ok = lo >= 0 && hi >= lo && (int64_t)hi <= n_edges;
+// kGroups: the rows are looked up in groups (above) instead of row_ptr; kStream: entries and records
+// go past the caches.  What bounds this kernel is the random look-up: a 128-byte line each, from
+// memory where it misses the L2 (56 G/s), and from the L2 no more than twice as many as this kernel
+// takes.  The 11.6 MB of row_ptr of a 2.9M-node graph miss a 4 MB L2 most of the time, its groups
+// are 3.9 MB: 60 M entries in 508 us, 693 with two loads from row_ptr an entry (20 M entries on 1M
+// nodes 141, before 166).  Groups of 28 rows in 32 bytes are two requests: 569 and 158 us.
+constexpr int kRecordThreads = 256;
+constexpr int kRecordItems = 4;  // entries of a thread, all their look-ups in flight
+template <int kRec, bool kGroups, bool kStream>
+__global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
+    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n_nodes,
+    int64_t n_edges, int id_bits, int lo_bits, const uint4* __restrict__ groups,
+    void* __restrict__ rec) {
+    const int64_t e0 = (int64_t)blockIdx.x * (kRecordThreads * kRecordItems) + threadIdx.x;
+    uint32_t t[kRecordItems];
+    bool node[kRecordItems];
+#pragma unroll
+    for (int u = 0; u < kRecordItems; ++u) {
+        const int32_t* from = col_idx + min(e0 + u * kRecordThreads, n_edges - 1);
+        t[u] = (uint32_t)(kStream ? __builtin_nontemporal_load(from) : *from);
     }
-    if (kRec == kRecWide) {
-        static_cast<int4*>(rec)[e] = ok ? make_int4(t, lo, hi - lo, 0) : make_int4(-1, 0, 0, 0);
-    } else {
-        const uint32_t deg_big = (1u << rec_degree_bits(id_bits, lo_bits)) - 1u;
-        unsigned long long r = (unsigned long long)(uint32_t)n_nodes;  // bad entry
-        if (ok) {
-            const uint32_t deg = min((uint32_t)(hi - lo), deg_big);
-            r = (unsigned long long)(uint32_t)t | ((unsigned long long)(uint32_t)lo << id_bits) |
-                ((unsigned long long)deg << (id_bits + lo_bits));
+#pragma unroll
+    for (int u = 0; u < kRecordItems; ++u) node[u] = t[u] < (uint32_t)n_nodes;
+    int32_t lo[kRecordItems], hi[kRecordItems];
+    if constexpr (kGroups) {
+        uint4 a[kRecordItems];
+        uint32_t j[kRecordItems];
+#pragma unroll
+        for (int u = 0; u < kRecordItems; ++u) {
+            const uint32_t x = node[u] ? t[u] : 0u;
+            const uint32_t g = x / kRowsPerGroup;
+            j[u] = x - g * kRowsPerGroup;
+            a[u] = groups[g];
         }
-        static_cast<unsigned long long*>(rec)[e] = r;
+#pragma unroll
+        for (int u = 0; u < kRecordItems; ++u) {
+            const uint32_t w[3] = {a[u].y, a[u].z, a[u].w};
+            // the word with the node's degree and what the degrees in front of it add up to
+            uint32_t start = a[u].x, degrees = w[0], sum = a[u].x;
+#pragma unroll
+            for (uint32_t q = 1; q < 3; ++q) {
+                sum = __builtin_amdgcn_sad_u8(w[q - 1], 0u, sum);
+                const bool here = j[u] >= 4u * q;
+                start = here ? sum : start;
+                degrees = here ? w[q] : degrees;
+            }
+            const uint32_t in_front = 8u * (j[u] & 3u);
+            start = __builtin_amdgcn_sad_u8(__builtin_amdgcn_ubfe(degrees, 0u, in_front), 0u, start);
+            const uint32_t degree = __builtin_amdgcn_ubfe(degrees, in_front, 8u);
+            lo[u] = (int32_t)start;
+            hi[u] = (int32_t)(start + degree);
+            if (node[u] && degree == kAskRowPtr) row_ends(row_ptr, t[u], &lo[u], &hi[u]);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < kRecordItems; ++u) row_ends(row_ptr, node[u] ? t[u] : 0u, &lo[u], &hi[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRecordItems; ++u) {
+        const int64_t e = e0 + u * kRecordThreads;
+        if (e >= n_edges) return;
+        const bool ok = node[u] && lo[u] >= 0 && hi[u] >= lo[u] && (int64_t)hi[u] <= n_edges;
+        if (kRec == kRecWide) {
+            static_cast<int4*>(rec)[e] =
+                ok ? make_int4((int)t[u], lo[u], hi[u] - lo[u], 0) : make_int4(-1, 0, 0, 0);
+        } else {
+            const uint32_t deg_big = (1u << rec_degree_bits(id_bits, lo_bits)) - 1u;
+            unsigned long long r = (unsigned long long)(uint32_t)n_nodes;  // bad entry
+            if (ok) {
+                const uint32_t deg = min((uint32_t)(hi[u] - lo[u]), deg_big);
+                r = (unsigned long long)t[u] | ((unsigned long long)(uint32_t)lo[u] << id_bits) |
+                    ((unsigned long long)deg << (id_bits + lo_bits));
+            }
+            unsigned long long* to = static_cast<unsigned long long*>(rec) + e;
+            if (kStream) {
+                __builtin_nontemporal_store(r, to);
+            } else {
+                *to = r;
+            }
+        }
     }
 }
 
@@ -142,15 +233,30 @@ EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
     plan.lo_bits = bits_for((uint64_t)n_edges);   // 31 at most
     // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
-    // small graphs the packed array fits more of its lines into the L2s: SMALLFIG)
+    // small graphs the packed array fits more of its lines into the L2s.)
     plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
     // the degree lies in the word's upper half
     if (plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
     return plan;
 }
 
-size_t edge_record_bytes(const EdgeRecords& plan, int64_t n_edges) {
-    return (size_t)n_edges * (plan.format == kRecPacked ? 8 : 16);
+// Whether the rows are worth grouping: where row_ptr does not stay in an L2 beside the streams, and
+// where most entries name a node whose degree fits a byte.  (On 524,288 nodes with 80 entries each
+// one load of both ends and streams past the caches: 42 M entries in 244 us, 283 with ordinary
+// streams, 300 with two loads.  On 235,000 nodes, 2.6 M entries, everything stays in the caches: 21
+// us either way.)
+constexpr int32_t kManyNodes = 1 << 18;
+static bool rows_in_groups(int32_t n_nodes, int64_t n_edges) {
+    return n_nodes >= kManyNodes && n_edges <= 32 * (int64_t)n_nodes;
+}
+
+static size_t record_array_bytes(const EdgeRecords& plan, int64_t n_edges) {
+    return ((size_t)n_edges * (plan.format == kRecPacked ? 8 : 16) + 15) & ~(size_t)15;
+}
+
+size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges) {
+    return record_array_bytes(plan, n_edges) +
+           (rows_in_groups(n_nodes, n_edges) ? row_group_bytes(n_nodes) : 0);
 }
 
 template <bool kCount, int kRec>
@@ -179,16 +285,24 @@ static hipError_t launch_walks_cfg(hipStream_t stream, const int32_t* row_ptr,
 hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const int32_t* col_idx,
                                int32_t n_nodes, int64_t n_edges, const EdgeRecords& rec) {
     if (n_edges <= 0) return hipSuccess;
-    const int threads = 256;
-    const dim3 grid((unsigned)((n_edges + threads - 1) / threads));
+    const int64_t tile = kRecordThreads * kRecordItems;
+    const dim3 grid((unsigned)((n_edges + tile - 1) / tile)), block(kRecordThreads);
     void* data = const_cast<void*>(rec.data);
-    if (rec.format == kRecPacked) {
-        hipLaunchKernelGGL(edge_record_kernel<kRecPacked>, grid, dim3(threads), 0, stream, row_ptr,
-                           col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits, data);
-    } else {
-        hipLaunchKernelGGL(edge_record_kernel<kRecWide>, grid, dim3(threads), 0, stream, row_ptr,
-                           col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits, data);
+    uint4* groups = nullptr;  // they lie behind the records
+    if (rows_in_groups(n_nodes, n_edges)) {
+        groups = reinterpret_cast<uint4*>(static_cast<char*>(data) + record_array_bytes(rec, n_edges));
+        const int64_t n_groups = (int64_t)(row_group_bytes(n_nodes) / sizeof(uint4));
+        row_group_kernel<<<dim3((unsigned)((n_groups + 63) / 64)), dim3(64), 0, stream>>>(
+            row_ptr, n_nodes, n_edges, groups);
     }
+    const bool big = n_nodes >= kManyNodes;
+    const auto kernel =
+        rec.format == kRecPacked
+            ? (groups ? edge_record_kernel<kRecPacked, true, true>
+                      : big ? edge_record_kernel<kRecPacked, false, true> : edge_record_kernel<kRecPacked, false, false>)
+            : (groups ? edge_record_kernel<kRecWide, true, true> : edge_record_kernel<kRecWide, false, false>);
+    kernel<<<grid, block, 0, stream>>>(row_ptr, col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits,
+                                       groups, data);
     return hipGetLastError();
 }
 

@@ -901,3 +901,42 @@ def test_one_call_rpe_ids_capacity(ctx):
     rc, rows, got_T = binding.sample_walks_rpe_ids_raw(ctx, d_rp, d_ci, d_seeds[:0], M, m, 3,
                                                        walks[:0], 0, off[:1], ids, None, code, n_T, T)
     assert rc == binding.OK and rows == 0 and got_T == 0 and int(off[0]) == 0
+
+
+@pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
+                                           ((1 << 18) + 11, False), (1 << 18, True)])
+def test_edge_records_of_grouped_rows(ctx, n_nodes, malformed):
+    # from 2^18 nodes on rows are looked up in groups of 12: degrees at both sides of a byte's
+    # range, an empty row, a hub, and rows behind them in their group and in the last, short one
+    rng = np.random.default_rng(n_nodes)
+    deg = rng.integers(0, 3, size=n_nodes)
+    special = [0, 1, 253, 254, 255, 256, 0, 70_000]
+    for at in (0, 11, 24, 12 * 2000 + 5, n_nodes - 9):
+        deg[at:at + 8] = special[:min(8, n_nodes - at)]
+    rp = np.zeros(n_nodes + 1, dtype=np.int64)
+    np.cumsum(deg, out=rp[1:])
+    # half of the neighbours are nodes near the special rows
+    near = np.concatenate([np.arange(max(at - 3, 0), min(at + 30, n_nodes))
+                           for at in (0, 11, 24, 12 * 2000 + 5, n_nodes - 9)])
+    ci = rng.integers(0, n_nodes, size=int(rp[-1]))
+    ci[::2] = rng.choice(near, size=ci[::2].size)
+    seeds = rng.integers(0, n_nodes, size=40_000).astype(np.int32)
+    seeds[::4] = rng.choice(near, size=seeds[::4].size)
+    M, m = 60, 3
+    rp, ci = rp.astype(np.int32), ci.astype(np.int32)
+    assert seeds.size * M * (m - 1) >= 4 * ci.size         # enough steps to make the records
+    if malformed:                                               # a malformed row: flagged, never followed
+        rp[12 * 4000 + 3] = -7
+        near_bad = np.arange(12 * 4000, 12 * 4001, dtype=np.int32)
+        ci[1::64] = rng.choice(near_bad, size=ci[1::64].size)
+        walks = binding.sample_walks(ctx, dev(rp), dev(ci), dev(seeds), M, m, 3).cpu().numpy()
+        assert ctx.check() == binding.DEV_BAD_GRAPH
+        assert ((walks >= 0) & (walks < n_nodes)).all()
+        good = rp[:-1][walks[:, :, :-1]], rp[1:][walks[:, :, :-1]]
+        moved = walks[:, :, 1:] != walks[:, :, :-1]
+        bad_row = (good[0] < 0) | (good[1] < good[0])
+        assert not (moved & bad_row).any()
+        return
+    walks = binding.sample_walks(ctx, dev(rp), dev(ci), dev(seeds), M, m, 3)
+    assert ctx.check() == 0
+    assert np.array_equal(walks.cpu().numpy(), oracle.sample_walks(rp, ci, seeds, M, m, 3))
