@@ -18,9 +18,9 @@
 //
 // Writing.  A lane takes one union row: it gathers the row's K vectors of LT = m + 1 counts from
 // the table (zeros where the node is absent) as the aligned words that cover them, packs them into
-// the row's words in registers, and the row goes out either straight from the registers (vectors
-// of whole words) or through an LDS tile that is laid out like the output and streamed out 16
-// bytes per lane (vectors of an odd number of counts, whose rows straddle words).
+// the row's words in registers, and the row goes out either straight from the registers (rows of
+// whole words that one store takes) or through an LDS tile that is laid out like the output and
+// streamed out 16 bytes per lane (join_tiled).
 #pragma once
 
 #include "device_util.h"
@@ -44,10 +44,14 @@ __host__ __device__ constexpr int join_rounds(int K, int LT) {
     return fit < 1 ? 1 : (fit < most ? fit : most);
 }
 
-// Rows of vectors with an odd number of counts go out through an LDS tile: 64 rows, and up to 16
-// bytes in front so that the tile is aligned like the output it goes to.
+// Rows go out through an LDS tile, 64 rows and up to 16 bytes in front so that it is aligned like
+// the output it goes to, where a lane cannot store its row in one instruction: vectors of an odd
+// number of counts, whose rows straddle words, and rows of more than 16 bytes, of which every store
+// instruction would write a piece (each line of the output then takes several requests: 30,011
+// pairs of m = 9 402 us from the tile, 542 from registers; 262,144 triples of m = 3 1.33 and 1.58 ms).
+__host__ __device__ constexpr bool join_tiled(int K, int LT) { return LT % 2 != 0 || K * LT > 8; }
 __host__ __device__ constexpr int join_tile_words(int K, int LT) {
-    return LT % 2 == 0 ? 0 : (kWave * K * LT + 1) / 2 + 4;
+    return join_tiled(K, LT) ? (kWave * K * LT + 1) / 2 + 4 : 0;
 }
 
 // LDS of one query, in 32-bit words.  LT = 0: no rows are written (counting).
@@ -505,18 +509,18 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
             const int r = r0 + g * kWave + lane;
             const bool live = r < n_out;
             if (live) out_ids[off + r] = (int32_t)id[g];
-            if constexpr (LT % 2 == 0) {
-                // count vectors of whole words: a lane's row is stored from its registers (the
-                // rows of neighbouring lanes adjoin, so a wave's stores are contiguous)
+            if constexpr (!join_tiled(K, LT)) {
+                // a lane's row is stored from its registers, in one instruction: the rows of
+                // neighbouring lanes adjoin, so a wave's store is contiguous
                 if (live) {
                     uint32_t* row_words = reinterpret_cast<uint32_t*>(out_cnt) + (off + r) * kWords;
 #pragma unroll
                     for (int d = 0; d < kWords; ++d) row_words[d] = w[d];
                 }
             } else {
-                // An odd number of 16-bit counts per list: the rows are put together in an LDS
-                // tile and go out 16 bytes per lane.  The tile starts `head` counts in, so that
-                // 16-byte pieces of the tile are 16-byte pieces of the output.
+                // The rows are put together in an LDS tile and go out 16 bytes per lane.  The tile
+                // starts `head` counts in, so that 16-byte pieces of the tile are 16-byte pieces of
+                // the output.
                 uint16_t* dst = out_cnt + (off + r0 + g * kWave) * kCounts;
                 const int head = (int)((reinterpret_cast<uintptr_t>(dst) >> 1) & 7u);
                 uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile32);
