@@ -9,7 +9,7 @@
 // tile's pairs in order in LDS first, so that they leave as runs of a digit.  The first pass reads
 // the query list itself.
 // What bounds it: the memory round trips of the launches one after the other, at these sizes.
-// A million two-node queries on 2.9M nodes: 96 us (three passes of 5 + 6 + 14, offsets 22); with
+// A million two-node queries on 2.9M nodes: 86 us (three passes of 5 + 6 + 14, offsets 12); with
 // a wavefront per tile of 1,024 pairs, a bisection per node and five launches a pass it was 290.
 #include "device_util.h"
 #include "kernels.h"
@@ -239,45 +239,98 @@ __device__ __forceinline__ int64_t wave_lower_bound(const uint32_t* __restrict__
 }
 
 // inc_off[x] = number of sorted keys below x, for x = 0..n_nodes.  A workgroup's nodes are
-// consecutive: two waves find where their keys begin and end, and the keys in between are searched
-// in LDS (in place, where they are too many).  2.9M nodes and 2.1M keys: 22 us; with the two
-// searches done by single threads 57.
-constexpr int kOffsetsThreads = 256;
-constexpr int kOffsetsNodes = 1024;
-constexpr int kOffsetsKeys = 4096;
+// consecutive: two waves find where their keys begin and end, the place behind a node's last key is
+// noted in LDS, and a node's offset is the largest such place of the nodes before it.
+// What bounds it: the chain of a workgroup (four trips of the search, the keys, the scan), so all
+// workgroups are to be on the device at once: 512 of them, up to the nodes whose places LDS holds.
+// 2.9M nodes and 2.1M keys: 11.7 us; with 1,024 nodes to a workgroup of four waves, each searched
+// for in the LDS copy of the keys, 22.
+// Where a workgroup has more keys than kOffsetsKeys (a few nodes hold most of the list), its nodes
+// are searched for in the list itself, which takes no longer for a longer list.
+constexpr int kOffsetsThreads = 1024;
+constexpr int kOffsetsItems = 8;      // nodes of a thread, at most
+constexpr int kOffsetsGroups = 512;   // two workgroups per compute unit
+constexpr int64_t kOffsetsKeys = 1 << 16;
+int offsets_items(int32_t n_nodes) {
+    const int64_t want = ((int64_t)n_nodes + 1 + kOffsetsThreads * kOffsetsGroups - 1) /
+                         (kOffsetsThreads * kOffsetsGroups);
+    return want < kOffsetsItems ? (int)want : kOffsetsItems;
+}
 __global__ __launch_bounds__(kOffsetsThreads) void incidence_offsets_kernel(
-    const uint32_t* __restrict__ keys, int64_t n, int32_t n_nodes, int64_t* __restrict__ inc_off) {
-    __shared__ uint32_t near_keys[kOffsetsKeys];
+    const uint32_t* __restrict__ keys, int64_t n, int32_t n_nodes, int items,
+    int64_t* __restrict__ inc_off) {
+    __shared__ int32_t behind[kOffsetsThreads * kOffsetsItems];  // place behind the node's last key
+    __shared__ int32_t wave_most[kOffsetsThreads / kWave];
     __shared__ int64_t ends[2];
     const int tid = (int)threadIdx.x;
+    const int lane = lane_id();
     const int wave = tid >> 6;
-    const int64_t x0 = (int64_t)blockIdx.x * kOffsetsNodes;
+    const int n_here = kOffsetsThreads * items;
+    const int64_t x0 = (int64_t)blockIdx.x * n_here;
     if (wave < 2) {
-        const int64_t at = wave_lower_bound(keys, n, x0 + wave * kOffsetsNodes, lane_id());
-        if (lane_id() == 0) ends[wave] = at;
+        const int64_t at = wave_lower_bound(keys, n, x0 + wave * n_here, lane);
+        if (lane == 0) ends[wave] = at;
     }
+    for (int t = tid; t < n_here; t += kOffsetsThreads) behind[t] = 0;
     __syncthreads();
     const int64_t first = ends[0], n_near = ends[1] - first;
-    const bool in_lds = n_near <= kOffsetsKeys;
-    if (in_lds) {
-        for (int t = tid; t < n_near; t += kOffsetsThreads) near_keys[t] = keys[first + t];
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < kOffsetsNodes / kOffsetsThreads; ++u) {
-        const int64_t x = x0 + u * kOffsetsThreads + tid;
-        int64_t lo = 0, hi = n_near;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            const uint32_t key = in_lds ? near_keys[mid] : keys[first + mid];
-            if ((int64_t)key < x) {
-                lo = mid + 1;
-            } else {
-                hi = mid;
+    if (n_near > kOffsetsKeys) {
+        for (int64_t x = x0 + tid; x < x0 + n_here && x <= n_nodes; x += kOffsetsThreads) {
+            int64_t lo = first, hi = ends[1];
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if ((int64_t)keys[mid] < x) {
+                    lo = mid + 1;
+                } else {
+                    hi = mid;
+                }
             }
+            inc_off[x] = lo;
         }
-        if (x <= n_nodes) inc_off[x] = first + lo;
+        return;
     }
+    const uint32_t* near_keys = keys + first;
+    constexpr int kFlight = 4;  // keys a thread has in flight
+    for (int t0 = 0; t0 < (int)n_near; t0 += kFlight * kOffsetsThreads) {
+        uint32_t key[kFlight], next[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const int t = t0 + u * kOffsetsThreads + tid;
+            key[u] = near_keys[min(t, (int)n_near - 1)];
+            next[u] = near_keys[min(t + 1, (int)n_near - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const int t = t0 + u * kOffsetsThreads + tid;
+            // (a key is one of the workgroup's nodes unless a wait of the sort ran out)
+            const uint32_t at = key[u] - (uint32_t)x0;
+            if (t < (int)n_near && at < (uint32_t)n_here && (key[u] != next[u] || t + 1 == (int)n_near))
+                behind[at] = t + 1;
+        }
+    }
+    __syncthreads();
+    // the largest of the nodes before: of the thread's own, of the lanes before, of the waves before
+    int32_t most = 0;
+    for (int u = 0; u < items; ++u) most = max(most, behind[tid * items + u]);
+    int32_t incl = most;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int32_t other = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl = max(incl, other);
+    }
+    if (lane == kWave - 1) wave_most[wave] = incl;
+    const int32_t below = __shfl_up(incl, 1, kWave);
+    __syncthreads();
+    int32_t before = lane > 0 ? below : 0;
+    for (int w = 0; w < wave; ++w) before = max(before, wave_most[w]);
+    for (int u = 0; u < items; ++u) {
+        const int32_t own = behind[tid * items + u];
+        behind[tid * items + u] = before;
+        before = max(before, own);
+    }
+    __syncthreads();
+    for (int t = tid; t < n_here; t += kOffsetsThreads)
+        if (x0 + t <= n_nodes) inc_off[x0 + t] = first + behind[t];
 }
 
 int sort_items(int64_t n) { return n <= kSortFew ? kSortFewItems : kSortMostItems; }
@@ -300,10 +353,11 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
                                   void* scratch, void* small_scan, uint32_t spin_limit,
                                   uint32_t* err) {
     const int64_t n = n_queries * k;
-    const dim3 offset_grid((unsigned)((int64_t)n_nodes / kOffsetsNodes + 1));
+    const int offset_items = offsets_items(n_nodes);
+    const dim3 offset_grid((unsigned)((int64_t)n_nodes / (kOffsetsThreads * offset_items) + 1));
     if (n == 0) {  // no entries: every part is empty
-        incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(nullptr, 0, n_nodes,
-                                                                                 inc_off);
+        incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(
+            nullptr, 0, n_nodes, offset_items, inc_off);
         return hipGetLastError();
     }
     const int64_t n_tiles = sort_tiles(n);
@@ -344,7 +398,8 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
                 src, n, shift, hist, to, last ? keys : nullptr, inc_q);
         }
     }
-    incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(keys, n, n_nodes, inc_off);
+    incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(
+        keys, n, n_nodes, offset_items, inc_off);
     return hipGetLastError();
 }
 

@@ -56,6 +56,24 @@ def test_query_incidence_equals_a_stable_sort(ctx, n_nodes, n_queries, k):
     assert np.array_equal(inc_q.cpu().numpy(), want_q)
 
 
+@pytest.mark.parametrize("n_nodes", [1023, 1024, 524_287, 524_288, 1_048_575, 4_194_303, 4_300_000])
+@pytest.mark.parametrize("spread", [1.0, 0.002, 0.0])
+def test_query_incidence_offsets_around_group_sizes(ctx, n_nodes, spread):
+    # offsets are laid out 1,024 to 8,192 nodes at a time; lists spread over all nodes, over a few
+    # groups (more keys than a group looks at in LDS) and two nodes that hold nearly all of it
+    rng = np.random.default_rng(n_nodes)
+    n_queries = 100_000
+    width = max(int(n_nodes * spread), 2)
+    start = rng.integers(0, n_nodes - width + 1)
+    queries = rng.integers(start, start + width, size=(n_queries, 2)).astype(np.int32)
+    queries[0], queries[-1] = (0, n_nodes - 1), (n_nodes - 1, 0)
+    inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
+    assert ctx.check() == 0
+    want_off, want_q = numpy_incidence(queries, n_nodes)
+    assert np.array_equal(inc_off.cpu().numpy(), want_off)
+    assert np.array_equal(inc_q.cpu().numpy(), want_q)
+
+
 def test_query_incidence_of_an_empty_list_and_bad_ids(ctx):
     empty = torch.empty((0, 2), dtype=torch.int32, device="cuda")
     inc_off, inc_q = binding.query_incidence(ctx, empty, 17)
