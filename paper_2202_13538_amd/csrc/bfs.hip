@@ -25,7 +25,10 @@ constexpr int kBfsMaxThreads = 256;  // a workgroup has 256 threads, or 64 for s
 constexpr int kBfsMaxChunk = kBfsMaxThreads * kBfsPer;  // candidates settled at a time, at most
 // Searches whose tables fit into this much LDS keep them there (two workgroups per compute unit, or
 // more): an insertion is a few LDS round trips instead of atomics that travel to memory.  8,192
-// searches of 32 queries: 76 us, with the tables in global memory 524.
+// searches of 32 queries: 71 us, with the tables in global memory 524.  Of a chunk's new queries only
+// those that the batch has room for get their nodes entered: the tables and lists of such a search
+// are then 4.9 KB, not 9.5, 32 searches of a compute unit run at a time instead of 16, and with the
+// entries of a chunk spread over all threads (bfs_share) the launch takes 35 us.
 constexpr size_t kBfsLdsMost = 79 * 1024;
 constexpr int kBfsMaxK = 3;
 constexpr uint32_t kBfsEmpty = 0xFFFFFFFFu;
@@ -86,6 +89,13 @@ __device__ __forceinline__ uint32_t bfs_block_scan(uint32_t v, uint32_t* total, 
     return base + incl - v;
 }
 
+// Entries of a thread where n (at most kBfsPer * T) of them are settled: thread t takes the entries
+// from t * share on.
+template <int T>
+__device__ __forceinline__ int bfs_share(int32_t n) {
+    return min((n + T - 1) / T, kBfsPer);
+}
+
 struct BfsArgs {
     const int32_t* __restrict__ queries;
     int64_t n_queries;
@@ -104,6 +114,7 @@ struct BfsArgs {
     uint32_t* tables;                    // per workgroup: query table, node table (unless in LDS)
     uint32_t slots_q, slots_v;           // powers of two
     uint32_t chunk;                      // candidates settled at a time: at most four per thread
+    uint32_t most_new;                   // new queries looked at a time: those of a chunk, B2 at most
     uint32_t queue;                      // nodes a search can reach: entries of the queue in LDS
     uint32_t* err;
 };
@@ -113,13 +124,14 @@ struct BfsArgs {
 struct BfsLds {
     uint32_t cand_q, cand_slot, new_q, node_slot, queue, tables, total;
 };
-__host__ __device__ inline BfsLds bfs_lds(uint32_t chunk, uint32_t queue, uint32_t slots, bool in_lds) {
+__host__ __device__ inline BfsLds bfs_lds(uint32_t chunk, uint32_t most_new, uint32_t queue,
+                                          uint32_t slots, bool in_lds) {
     BfsLds o;
     o.cand_q = 0;                        // query of each candidate
     o.cand_slot = o.cand_q + chunk;      // its slot in the query table
     o.new_q = o.cand_slot + chunk;       // newly reached queries, in order
-    o.node_slot = o.new_q + chunk;       // slots of their nodes
-    o.queue = o.node_slot + chunk * kBfsMaxK;
+    o.node_slot = o.new_q + most_new;      // slots of their nodes
+    o.queue = (o.node_slot + most_new * kBfsMaxK + 3) / 4 * 4;
     o.tables = o.queue + (in_lds ? (queue + 3) / 4 * 4 : 0);
     o.total = o.tables + (in_lds ? 2 * slots : 0);
     return o;
@@ -131,7 +143,7 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
     __shared__ uint32_t pre[T + 1];              // candidates before each node of the stretch
     __shared__ uint32_t s_take;
     extern __shared__ __align__(16) uint32_t lds32[];
-    const BfsLds lay = bfs_lds(a.chunk, a.queue, a.slots_q + a.slots_v, kLds);
+    const BfsLds lay = bfs_lds(a.chunk, a.most_new, a.queue, a.slots_q + a.slots_v, kLds);
     uint32_t* const cand_q = lds32 + lay.cand_q;
     uint32_t* const cand_slot = lds32 + lay.cand_slot;
     uint32_t* const new_q = lds32 + lay.new_q;
@@ -167,14 +179,16 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
         uint32_t n_v = 0, n_b = 0;
         // the seed-set: distinct start nodes in the order given, B1 at most
         for (int32_t s0 = 0; s0 < a.n_start && n_v < (uint32_t)a.B1; s0 += T * kBfsPer) {
+            const int32_t per = bfs_share<T>(a.n_start - s0);
+            const int32_t s1 = min(a.n_start, s0 + per * T);
             uint32_t slot[kBfsPer];
             int32_t node[kBfsPer];
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const int32_t i = s0 + tid * kBfsPer + r;
+                const int32_t i = s0 + tid * per + r;
                 slot[r] = kBfsEmpty;
                 node[r] = -1;
-                if (i < a.n_start) {
+                if (r < per && i < s1) {
                     node[r] = start[i];
                     if ((uint32_t)node[r] < (uint32_t)a.n_nodes) {
                         slot[r] = insert_min(v_tab, v_mask, (uint32_t)node[r], (uint32_t)i);
@@ -188,7 +202,7 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             uint32_t own = 0;
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const int32_t i = s0 + tid * kBfsPer + r;
+                const int32_t i = s0 + tid * per + r;
                 const bool mine = slot[r] != kBfsEmpty && table_load<kLds>(&v_tab[2 * slot[r] + 1]) == (uint32_t)i;
                 own |= mine ? 1u << r : 0u;
             }
@@ -237,12 +251,13 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             const bool partial = take == 0;  // the first node's list alone is longer than a chunk
             const uint32_t n_c = partial ? a.chunk : pre[take];
             const uint32_t n_src = partial ? 1u : take;
+            const int per_c = bfs_share<T>((int32_t)n_c);
 
             // candidates: entry j of node t' of the stretch, numbered cand_base + c
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t c = (uint32_t)tid * kBfsPer + r;
-                if (c < n_c) {
+                const uint32_t c = (uint32_t)(tid * per_c + r);
+                if (r < per_c && c < n_c) {
                     uint32_t lo = 0, hi = n_src;  // last node with pre[node] <= c
                     while (hi - lo > 1) {
                         const uint32_t mid = (lo + hi) >> 1;
@@ -271,23 +286,35 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             uint32_t own = 0;
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t c = (uint32_t)tid * kBfsPer + r;
-                if (c < n_c && cand_slot[c] != kBfsEmpty &&
+                const uint32_t c = (uint32_t)(tid * per_c + r);
+                if (r < per_c && c < n_c && cand_slot[c] != kBfsEmpty &&
                     table_load<kLds>(&q_tab[2 * cand_slot[c] + 1]) == cand_base + c)
                     own |= 1u << r;
             }
             uint32_t n_new;
             uint32_t at = bfs_block_scan<T>((uint32_t)__popc(own), &n_new, wave_sums);
+            // no more of them can be taken than the batch has room for
+            const uint32_t n_look = min(n_new, (uint32_t)a.B2 - n_b);
+            const int per_q = bfs_share<T>((int32_t)n_look);
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r)
-                if (own & (1u << r)) new_q[at++] = cand_q[(uint32_t)tid * kBfsPer + r];
+                if (own & (1u << r)) {
+                    const uint32_t q = cand_q[tid * per_c + r];
+                    if (at < n_look) {
+                        new_q[at] = q;
+                    } else {  // B2 queries come before it: only its node ids are checked
+                        for (int j = 0; j < k; ++j)
+                            bad_id |= (uint32_t)a.queries[(int64_t)q * k + j] >= (uint32_t)a.n_nodes;
+                    }
+                    at += 1;
+                }
             __syncthreads();
 
             // their nodes: node (i, j) is numbered n_start + (n_b + i) * k + j
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t i = (uint32_t)tid * kBfsPer + r;
-                if (i < n_new) {
+                const uint32_t i = (uint32_t)(tid * per_q + r);
+                if (r < per_q && i < n_look) {
                     const int64_t q = new_q[i];
                     for (int j = 0; j < k; ++j) {
                         const int32_t x = a.queries[q * k + j];
@@ -308,9 +335,9 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             uint32_t n_fresh = 0;
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t i = (uint32_t)tid * kBfsPer + r;
+                const uint32_t i = (uint32_t)(tid * per_q + r);
                 fresh[r] = 0;
-                if (i < n_new) {
+                if (r < per_q && i < n_look) {
                     for (int j = 0; j < k; ++j) {
                         const uint32_t slot = node_slot[i * kBfsMaxK + j];
                         if (slot != kBfsEmpty &&
@@ -329,11 +356,11 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             uint32_t first_at[kBfsPer];
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t i = (uint32_t)tid * kBfsPer + r;
+                const uint32_t i = (uint32_t)(tid * per_q + r);
                 const uint32_t mine = (uint32_t)__popc(fresh[r]);
                 first_at[r] = before;
-                const bool ok = i < n_new && before < (uint32_t)a.B1 && before + mine <= (uint32_t)a.B1 &&
-                                n_b + i < (uint32_t)a.B2;
+                const bool ok = r < per_q && i < n_look && before < (uint32_t)a.B1 &&
+                                before + mine <= (uint32_t)a.B1;
                 if (ok) {
                     n_ok += 1;
                     nodes_ok += mine;
@@ -347,7 +374,7 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             (void)bfs_block_scan<T>(nodes_ok, &took_nodes, wave_sums);
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
-                const uint32_t i = (uint32_t)tid * kBfsPer + r;
+                const uint32_t i = (uint32_t)(tid * per_q + r);
                 if (fresh[r] != 0xFFFFFFFFu) {
                     const int64_t q = new_q[i];
                     batch[n_b + i] = (int32_t)q;
@@ -394,8 +421,8 @@ uint32_t pow2_at_least(uint64_t x) {
 
 }  // namespace
 
-// Candidates settled at a time: every one of them may turn out to be a new query whose nodes
-// are entered into the node table before the limits cut, so small batches take small bites.
+// Candidates settled at a time: every one of them is entered into the query table before the limits
+// cut, so small batches take small bites.
 static uint32_t bfs_chunk(int32_t B2) {
     const uint32_t want = pow2_at_least(4ull * (uint64_t)B2);
     return want < 64u ? 64u : (want > (uint32_t)kBfsMaxChunk ? (uint32_t)kBfsMaxChunk : want);
@@ -418,13 +445,17 @@ struct BfsTables {
 };
 static BfsTables bfs_tables(int32_t n_start, int32_t B1, int32_t B2, int32_t k, bool in_lds) {
     const uint64_t q = (uint64_t)B2 + bfs_chunk(B2);
-    const uint64_t v = bfs_nodes(n_start, B1, B2, k) + (uint64_t)bfs_chunk(B2) * (uint64_t)k + (uint64_t)n_start;
+    const uint64_t v = (uint64_t)n_start + (uint64_t)B2 * (uint64_t)k;
     if (in_lds) return BfsTables{pow2_at_least(q + q / 4), pow2_at_least(v + v / 4)};
     return BfsTables{pow2_at_least(2 * q), pow2_at_least(2 * v)};
 }
+static uint32_t bfs_most_new(int32_t B2) {
+    return (uint32_t)B2 < bfs_chunk(B2) ? (uint32_t)B2 : bfs_chunk(B2);
+}
 static size_t bfs_lds_bytes(int32_t n_start, int32_t B1, int32_t B2, int32_t k, bool in_lds) {
     const BfsTables t = bfs_tables(n_start, B1, B2, k, in_lds);
-    return sizeof(uint32_t) * (size_t)bfs_lds(bfs_chunk(B2), (uint32_t)bfs_nodes(n_start, B1, B2, k),
+    return sizeof(uint32_t) * (size_t)bfs_lds(bfs_chunk(B2), bfs_most_new(B2),
+                                              (uint32_t)bfs_nodes(n_start, B1, B2, k),
                                               t.slots_q + t.slots_v, in_lds).total;
 }
 static bool bfs_in_lds(int32_t n_start, int32_t B1, int32_t B2, int32_t k) {
@@ -488,6 +519,7 @@ hipError_t launch_bfs_batches(hipStream_t stream, int n_cu, const int32_t* queri
     a.slots_q = tables.slots_q;
     a.slots_v = tables.slots_v;
     a.chunk = bfs_chunk(B2);
+    a.most_new = bfs_most_new(B2);
     a.queue = in_lds ? (uint32_t)bfs_nodes(n_start, B1, B2, k) : 0u;
     a.err = err;
     const int threads = bfs_threads(B2);

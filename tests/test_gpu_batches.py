@@ -120,6 +120,35 @@ def test_bfs_batches_equal_the_queue_search(ctx, k, B1, B2):
     print(f"k={k} B1={B1} B2={B2}: nodes {counts[:, 0].tolist()[:6]} queries {counts[:, 1].tolist()[:6]}")
 
 
+@pytest.mark.parametrize("n_start", [1, 16, 64, 65, 128, 257, 1025])
+@pytest.mark.parametrize("B2", [1, 16, 31, 32, 63, 64, 65, 256, 257])
+def test_bfs_batches_around_the_sizes_of_a_share(ctx, n_start, B2):
+    # start nodes, candidates and new queries are shared out one to four a thread, and a stretch looks
+    # at no more new queries than the batch has room for: sizes on both sides of each step
+    rng = np.random.default_rng(1000 * n_start + B2)
+    n_nodes, n_queries = 2000, 6000
+    queries = random_queries(rng, n_nodes, n_queries, 2, hubs=3, hub_share=0.1)
+    start = rng.integers(0, n_nodes, size=(6, n_start)).astype(np.int32)
+    start[0, :] = 0                           # a hub: more candidates than a chunk
+    for B1 in (10 ** 6, n_start + B2):
+        compare_batches(ctx, queries, n_nodes, start, B1, B2)
+
+
+def test_bfs_batches_flag_bad_ids_behind_the_last_query_with_room(ctx):
+    # node 0 is named by ten queries, the last one names no node beside it: flagged also where the
+    # batch is full before
+    queries = np.array([[0, i + 1] for i in range(9)] + [[0, 50]], dtype=np.int32)
+    inc_off, inc_q = binding.query_incidence(ctx, dev(queries), 40)
+    assert ctx.check() == binding.DEV_BAD_QUERY
+    start = np.zeros((1, 1), dtype=np.int32)
+    for B2, want in ((4, 4), (9, 9)):
+        _, batch, _, counts = binding.bfs_batches(ctx, dev(queries), 40, inc_off, inc_q, dev(start),
+                                                  100, B2)
+        assert ctx.check() == binding.DEV_BAD_QUERY
+        assert counts.cpu().tolist() == [[want + 1, want]]
+        assert batch.cpu().numpy()[0, :want].tolist() == list(range(want))
+
+
 def test_bfs_batches_with_long_lists_wide_levels_and_many_seeds(ctx):
     rng = np.random.default_rng(5)
     # a node held by 5000 queries (its list is taken in pieces), levels of thousands of nodes
