@@ -70,9 +70,8 @@ __device__ __forceinline__ void row_ends(const int32_t* __restrict__ row_ptr, ui
 // of its row and its degree; an entry that names no node, or whose row is malformed, gets the
 // layout's "bad entry" id (the walker will stay in place and flag it).
 // kGroups: the rows are looked up in groups (above) instead of row_ptr; kStream: entries and records
-// go past the caches.  What bounds this kernel is the random look-up: a 128-byte line each, from
-// memory where it misses the L2 (56 G/s), and from the L2 no more than twice as many as this kernel
-// takes.  The 11.6 MB of row_ptr of a 2.9M-node graph miss a 4 MB L2 most of the time, its groups
+// go past the caches.  What bounds this kernel is the random look-up: a 128-byte line each, 56 G/s
+// from memory where it misses the L2 and 260 G/s from an L2 with nothing else to do.  The 11.6 MB of row_ptr of a 2.9M-node graph miss a 4 MB L2 most of the time, its groups
 // are 3.9 MB: 60 M entries in 508 us, 693 with two loads from row_ptr an entry (20 M entries on 1M
 // nodes 141, before 166).  Groups of 28 rows in 32 bytes are two requests: 569 and 158 us.
 constexpr int kRecordThreads = 256;
