@@ -24,7 +24,8 @@
  *     never frees or keeps a caller pointer beyond the call's work on the stream.
  *   - All work is enqueued on the context's stream.  A call returns without waiting unless
  *     a non-NULL h_rows is passed (then it waits for its own work and reports the row
- *     total).  Calls on one context must not overlap from several host threads.
+ *     total).  Calls on one context must not overlap from several host threads; any number of
+ *     contexts may work at the same time, on streams of their own.
  *   - The context owns grow-only device workspaces (per-seed / per-query row counts, scan
  *     partials, the walk's per-edge neighbour records, the fused kernel's look-back words,
  *     the hash tables and sort arrays of pruning and mini-batching)
@@ -96,10 +97,11 @@ extern "C" {
 #define SUREL_DEV_BAD_SIZES     0x80u  /* a seed's d_set_sizes entry (or the offsets given to a
                                           filling call) do not match its number of rows; that
                                           seed's / query's rows are not written              */
-#define SUREL_DEV_STALL         0x100u /* a bounded wait inside surel_sample_walks_rpe or inside a
-                                          join of few queries ran out (see surel_set_spin_limit), or a bounded probe of a
-                                          hash table of surel_bfs_batches; outputs are
-                                          incomplete                                         */
+#define SUREL_DEV_STALL         0x100u /* a bounded wait inside surel_sample_walks_rpe (of more seeds
+                                          than the device walks at once), surel_sample_walks_rpe_ids
+                                          or surel_prune_rpe ran out (see surel_set_spin_limit), or
+                                          a bounded probe of a hash table of surel_bfs_batches;
+                                          outputs are incomplete                             */
 
 /* limits */
 #define SUREL_MAX_NODES   268435455   /* 2^28 - 1: node id and step share one 32-bit sort key */
@@ -404,12 +406,16 @@ int surel_bfs_batches(surel_ctx* ctx, const int32_t* d_queries, int64_t n_querie
                       int32_t B2, int32_t* d_vbar, int32_t* d_batch, int32_t* d_tuples,
                       int32_t* d_counts);
 
-/* Every wait inside the fused kernel of surel_sample_walks_rpe (a wave waiting for an offset,
- * the offset scan waiting for a row count), inside the joins of few queries (a workgroup waiting
- * for the row counts of those before it) and inside surel_prune_rpe (a lane waiting for
- * another to finish writing a hash slot) gives up after `spins` polls, raises
+/* Every wait inside the fused kernel of surel_sample_walks_rpe and surel_sample_walks_rpe_ids (a
+ * wave waiting for an offset, the offset scan waiting for a row count) and inside the pruning (a
+ * lane waiting for another to finish writing a hash slot) gives up after `spins` polls, raises
  * SUREL_DEV_STALL and lets the kernel end.  The default (2^22 polls, seconds) is never reached
- * by a healthy run; tests set 0 to see the bounded exit.  Errors: SUREL_E_CTX. */
+ * by a healthy run; tests set 0 to see the bounded exit.
+ * Where the workgroups of a launch add up each other's counts (walks + RPE of few seeds, joins of
+ * few queries, the offset scans, the sort of surel_query_incidence), nothing gives up: after
+ * `spins` polls, or a few thousand if that is less, a workgroup works the missing count out itself.
+ * Such a launch ends with all of its outputs whatever else runs on the device.
+ * Errors: SUREL_E_CTX. */
 int surel_set_spin_limit(surel_ctx* ctx, uint32_t spins);
 
 /* Per-kernel timing for benchmarks.  While enabled, every kernel group the context launches

@@ -14,7 +14,7 @@ struct surel_ctx {
     hipStream_t stream = nullptr;
     int max_lds_bytes = 0;
     int n_cu = 0;                 // compute units of the device
-    uint32_t spin_limit = 1u << 22;  // bound of every wait inside the fused walk + RPE kernel
+    uint32_t spin_limit = 1u << 22;  // bound of every wait inside a kernel
     uint32_t* d_err = nullptr;    // sticky device error word
     hipEvent_t done = nullptr;    // completed by the one launch of a call that reports its total
     void* d_small = nullptr;      // words of the launches that lay small outputs out themselves
@@ -168,7 +168,7 @@ int ensure_workspace(surel_ctx* ctx, int64_t n, int32_t** counts, int64_t** part
 hipError_t exclusive_scan(surel_ctx* ctx, const int32_t* counts, int64_t n, int64_t* off,
                           int64_t* partials) {
     return surel::launch_exclusive_scan(ctx->stream, ctx->n_cu, counts, n, off, partials, ctx->d_small,
-                                        ctx->spin_limit, ctx->d_err);
+                                        ctx->spin_limit);
 }
 
 // Wait for the stream and fetch off[n] (the row total) into *h_rows.
@@ -328,13 +328,13 @@ static int check_rpe_args(int32_t n_nodes, int64_t n_seeds, int32_t M, int32_t m
     return SUREL_OK;
 }
 
-// Waits for the stream and reports the row total that a scan or a scanner wave left at off[n]
-// (-1: the kernel gave up on a bounded wait before it got there).
+// rows < 0: the scanner wave of the fused kernel gave up on a bounded wait.
 static int judge_total(bool has_outputs, int64_t cap_rows, int64_t rows) {
     if (rows < 0) return SUREL_E_DEVICE;
     if (has_outputs && rows > cap_rows) return SUREL_E_CAPACITY;
     return SUREL_OK;
 }
+// Waits for the stream and reports the row total that a scan left at off[n].
 static int report_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, bool has_outputs,
                         int64_t cap_rows, int64_t* h_rows) {
     if (int rc = read_total(ctx, d_off, n, h_rows)) return rc;

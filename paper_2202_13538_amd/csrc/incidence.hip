@@ -68,22 +68,23 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortSource src,
     raise_error(src.err, bad, kDevBadQuery);
 }
 
-// hist[tile][d] -> place of the tile's first pair with digit d.  A workgroup takes 64 digits, its
+// places[tile][d] = place of the tile's first pair with digit d.  A workgroup takes 64 digits, its
 // 16 waves a share of the tiles each; the digits of the workgroups before it come in through
-// small_scan.h.
+// small_scan.h (whose helpers read the counts at any time: the places are an array of their own).
 constexpr int kPlaceGroups = kSortBins / kWave;
-__global__ __launch_bounds__(kSortThreads) void sort_places_kernel(uint32_t* __restrict__ hist,
+__global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_t* __restrict__ hist,
                                                                   int64_t n_tiles,
+                                                                  uint32_t* __restrict__ places,
                                                                   SmallScan* __restrict__ ss,
-                                                                  uint32_t spin_limit,
-                                                                  uint32_t* __restrict__ err) {
+                                                                  uint32_t spin_limit) {
     __shared__ uint32_t share[kSortWaves][kWave];
     __shared__ int64_t s_base;
     const int lane = lane_id();
     const int wave = (int)(threadIdx.x >> 6);
     const int64_t per_wave = (n_tiles + kSortWaves - 1) / kSortWaves;
     const int64_t t0 = wave * per_wave, t1 = min(t0 + per_wave, n_tiles);
-    uint32_t* column = hist + (int64_t)blockIdx.x * kWave + lane;
+    const uint32_t* column = hist + (int64_t)blockIdx.x * kWave + lane;
+    uint32_t* to = places + (int64_t)blockIdx.x * kWave + lane;
     uint32_t tag = 0;
     if (wave == 0) tag = small_scan_tag(ss);
     uint32_t sum = 0;
@@ -105,23 +106,27 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(uint32_t* __r
     const uint32_t incl = wave_incl_sum(total);
     if (wave == 0) {
         if (lane == kWave - 1) small_scan_publish(ss, (int)blockIdx.x, tag, incl);
-        const int64_t base = small_scan_before(ss, (int)blockIdx.x, tag, spin_limit, lane);
+        const int64_t base =
+            small_scan_before(ss, (int)blockIdx.x, tag, spin_limit, lane, [&](int j) {
+                uint32_t pairs = 0;  // of another workgroup's digits
+#pragma unroll 1
+                for (int64_t t = 0; t < n_tiles; ++t) pairs += hist[t * kSortBins + j * kWave + lane];
+                return wave_bcast_u32(wave_incl_sum(pairs), kWave - 1);
+            });
         if (lane == 0) {
             small_scan_done(ss, (int)blockIdx.x, tag, (int)gridDim.x);
             s_base = base;
-            if (base < 0) atomicOr(err, kDevStall);
         }
     }
     __syncthreads();
-    // (a wait that ran out: every place stays below n all the same, the lists are not right)
-    uint32_t at = (uint32_t)max(s_base, (int64_t)0) + incl - total + before;
+    uint32_t at = (uint32_t)s_base + incl - total + before;
     for (int64_t t = t0; t < t1; t += 8) {
         uint32_t v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = t + u < t1 ? column[(t + u) * kSortBins] : 0u;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            if (t + u < t1) column[(t + u) * kSortBins] = at;
+            if (t + u < t1) to[(t + u) * kSortBins] = at;
             at += v[u];
         }
     }
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(kOffsetsThreads) void incidence_offsets_kernel(
 #pragma unroll
         for (int u = 0; u < kFlight; ++u) {
             const int t = t0 + u * kOffsetsThreads + tid;
-            // (a key is one of the workgroup's nodes unless a wait of the sort ran out)
+            // (a key is one of the workgroup's nodes unless the list changes while it is sorted)
             const uint32_t at = key[u] - (uint32_t)x0;
             if (t < (int)n_near && at < (uint32_t)n_here && (key[u] != next[u] || t + 1 == (int)n_near))
                 behind[at] = t + 1;
@@ -345,7 +350,7 @@ size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 size_t incidence_scratch_bytes(int64_t n_entries) {
     const int64_t n = n_entries > 0 ? n_entries : 1;
     return 2 * padded((size_t)n * sizeof(uint2)) + padded((size_t)n * sizeof(uint32_t)) +
-           padded((size_t)sort_tiles(n) * kSortBins * sizeof(uint32_t));
+           2 * padded((size_t)sort_tiles(n) * kSortBins * sizeof(uint32_t));
 }
 
 hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, int64_t n_queries,
@@ -368,6 +373,8 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
     uint32_t* keys = reinterpret_cast<uint32_t*>(p);
     p += padded((size_t)n * sizeof(uint32_t));
     uint32_t* hist = reinterpret_cast<uint32_t*>(p);
+    p += padded((size_t)n_tiles * kSortBins * sizeof(uint32_t));
+    uint32_t* places = reinterpret_cast<uint32_t*>(p);
 
     int bits = 1;  // keys are 0..n_nodes
     while (bits < 32 && ((uint32_t)n_nodes >> bits) != 0u) ++bits;
@@ -389,13 +396,13 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
             sort_hist_kernel<kSortFewItems><<<grid, block, 0, stream>>>(src, n, shift, hist);
         }
         sort_places_kernel<<<dim3(kPlaceGroups), block, 0, stream>>>(
-            hist, n_tiles, static_cast<SmallScan*>(small_scan), spin_limit, err);
+            hist, n_tiles, places, static_cast<SmallScan*>(small_scan), spin_limit);
         if (items == kSortMostItems) {
             sort_scatter_kernel<kSortMostItems><<<grid, block, lds_bytes, stream>>>(
-                src, n, shift, hist, to, last ? keys : nullptr, inc_q);
+                src, n, shift, places, to, last ? keys : nullptr, inc_q);
         } else {
             sort_scatter_kernel<kSortFewItems><<<grid, block, lds_bytes, stream>>>(
-                src, n, shift, hist, to, last ? keys : nullptr, inc_q);
+                src, n, shift, places, to, last ? keys : nullptr, inc_q);
         }
     }
     incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(

@@ -13,9 +13,10 @@
 // hide that wait doubles the LDS a wave needs, and the filling launch with that footprint alone
 // takes 8.9 ms.)
 //
-// Short query lists (join_small_kernel) take one launch of one workgroup per query, all of them
-// on the device at once: there a launch's time is the chain of one query, so several wavefronts
-// share a query, and the offsets come from the words that the workgroups publish (small_scan.h).
+// Short query lists (join_small_kernel) take one launch of one workgroup per query, as many as the
+// device has room for at a time: there a launch's time is the chain of one query, so several
+// wavefronts share a query, and the offsets come from the words that the workgroups publish
+// (small_scan.h).
 #include "device_util.h"
 #include "join_core.h"
 #include "kernels.h"
@@ -78,6 +79,41 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
     }
 }
 
+// Union rows of query q, for a workgroup that helps another one (one wavefront, no LDS): the nodes
+// of a list that none of the lists before it holds, by bisection.
+template <int K>
+__device__ __forceinline__ uint32_t join_small_rows(int q, const int64_t* __restrict__ rpe_off,
+                                                    const int32_t* __restrict__ rpe_ids,
+                                                    int64_t n_blocks, int32_t max_set,
+                                                    const int32_t* __restrict__ queries, int lane) {
+    JoinQuery<K> jq;
+    if (join_lookup<K>(q, rpe_off, n_blocks, max_set, queries, jq) != 0) return 0;
+    uint32_t rows = 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+#pragma unroll 1
+        for (int t = lane; t < jq.n[j]; t += kWave) {
+            const int32_t x = rpe_ids[jq.lo[j] + t];
+            bool known = false;
+#pragma unroll
+            for (int i = 0; i < j; ++i) {
+                int lo = 0, hi = jq.n[i];
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (rpe_ids[jq.lo[i] + mid] < x) {
+                        lo = mid + 1;
+                    } else {
+                        hi = mid;
+                    }
+                }
+                known = known || (lo < jq.n[i] && rpe_ids[jq.lo[i] + lo] == x);
+            }
+            rows += known ? 0u : 1u;
+        }
+    }
+    return wave_bcast_u32(wave_incl_sum(rows), kWave - 1);
+}
+
 // One workgroup of n_waves wavefronts per query (see the file's head).  out_ids null: only the
 // offsets are wanted.  h_total (optional): host memory that gets the row total as well.
 // What bounds it: the chain of one query, about six trips to memory and the merge (10.8 us for 32
@@ -117,22 +153,22 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
     }
     if (wave == 0) {
         if (lane == 0) small_scan_publish(ss, q, tag, (uint32_t)rows);
-        const int64_t before = small_scan_before(ss, q, tag, spin_limit, lane);
+        const int64_t before = small_scan_before(ss, q, tag, spin_limit, lane, [&](int j) {
+            return join_small_rows<K>(j, rpe_off, rpe_ids, n_blocks, max_set, queries, lane);
+        });
         if (lane == 0) {
             small_scan_done(ss, q, tag, n_queries);
             s_off = before;
-            if (before < 0) atomicOr(err, kDevStall);
             join_off[q] = before;
             if (q == n_queries - 1) {
-                const int64_t total = before < 0 ? -1 : before + rows;
-                join_off[n_queries] = total;
-                if (h_total) *h_total = total;
+                join_off[n_queries] = before + rows;
+                if (h_total) *h_total = before + rows;
             }
         }
     }
     __syncthreads();
     const int64_t off = s_off;
-    if (out_ids == nullptr || rows == 0 || off < 0) return;
+    if (out_ids == nullptr || rows == 0) return;
     if (off + rows > cap_rows) {
         if (threadIdx.x == 0) atomicOr(err, kDevCapacity);
         return;
@@ -400,8 +436,9 @@ hipError_t launch_join_fill(hipStream_t stream, int max_lds_bytes, const int64_t
 }
 
 // The one-launch join (up to 4,096 queries on 256 compute units; at that size it still takes half
-// the time of the separate launches) is for query lists whose workgroups are all on the device at once: four waves
-// per SIMD (its 88 registers leave room for five) and 160 KB of LDS per compute unit.
+// the time of the separate launches) is for query lists whose workgroups the device can hold all at
+// once, so that hardly one waits for another to start: four waves per SIMD (its 88 registers leave
+// room for five) and 160 KB of LDS per compute unit.
 bool join_is_small(int n_cu, int max_lds_bytes, int32_t max_set, int32_t m, int64_t n_queries,
                    int32_t k) {
     if (n_queries < 1 || n_queries > kSmallScanMax) return false;

@@ -67,7 +67,8 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
                            int32_t* code, const PruneScratch& ps);
 
 // walk_rpe_small.hip.  The same for few seeds (walk_rpe_is_small says for how many), in one launch
-// that needs neither records nor look-back scratch.  small_scan, h_total, done: as for launch_join_small.
+// that needs neither records nor look-back scratch.  small_scan, spin_limit, h_total, done: as for
+// launch_join_small.
 bool walk_rpe_is_small(int n_cu, int64_t n_seeds, int32_t M, int32_t m);
 hipError_t launch_walk_rpe_small(hipStream_t stream, int max_lds_bytes, int n_cu,
                                  const int32_t* row_ptr, const int32_t* col_idx, int32_t n_nodes,
@@ -105,7 +106,8 @@ hipError_t launch_join_fill(hipStream_t stream, int max_lds_bytes, const int64_t
 // The whole join in one launch, for query lists of which join_is_small says so: writes
 // join_off[0..n_queries] and (unless out_ids is null) the rows.  small_scan: small_scan_bytes()
 // bytes of device memory, zero before its first use and kept by the launches from then on; only
-// one launch may use it at a time.  h_total (optional): host memory that gets the row total too.
+// one launch may use it at a time.  spin_limit: polls before a workgroup helps, see small_scan.h.
+// h_total (optional): host memory that gets the row total too.
 // done (optional): an event that the launch completes (launch_and_mark).
 bool join_is_small(int n_cu, int max_lds_bytes, int32_t max_set, int32_t m, int64_t n_queries,
                    int32_t k);
@@ -156,7 +158,7 @@ hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScra
 // incidence.hip.  The queries of every node: inc_q[inc_off[x] .. inc_off[x+1]) = indices of the
 // queries that name node x, ascending (a query that names x twice is listed twice).  Entries
 // outside [0, n_nodes) are flagged and left out.  scratch: incidence_scratch_bytes(n_queries*k);
-// small_scan: as for launch_join_small.
+// small_scan, spin_limit: as for launch_join_small.
 size_t incidence_scratch_bytes(int64_t n_entries);
 hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, int64_t n_queries,
                                   int32_t k, int32_t n_nodes, int64_t* inc_off, int32_t* inc_q,
@@ -183,12 +185,11 @@ int64_t lookback_words(int64_t n_items);
 hipError_t launch_lookback_clear(hipStream_t stream, uint64_t* lb, int64_t n_items,
                                  int64_t* total_out);
 
-// scan.hip.  off[0..n] = exclusive prefix sums of counts[0..n-1] (off[n] = total, -1 if a bounded
-// wait ran out).  partials: device scratch of scan_partials_len(n) int64; small_scan: as for
-// launch_join_small.
+// scan.hip.  off[0..n] = exclusive prefix sums of counts[0..n-1] (off[n] = total).  partials:
+// device scratch of scan_partials_len(n) int64; small_scan, spin_limit: as for launch_join_small.
 int64_t scan_partials_len(int64_t n);
 hipError_t launch_exclusive_scan(hipStream_t stream, int n_cu, const int32_t* counts, int64_t n,
                                  int64_t* off, int64_t* partials, void* small_scan,
-                                 uint32_t spin_limit, uint32_t* err);
+                                 uint32_t spin_limit);
 
 }  // namespace surel

@@ -1,8 +1,8 @@
 // Exclusive prefix sums that turn per-seed / per-query row counts into the offset arrays
 // rpe_off and join_off.  Up to 8,192 counts per compute unit (two million): one launch, whose
-// workgroups are all on the device and add up what those before them have published
-// (small_scan.h); 5 us instead of 14.  More: reduce-then-scan in three launches, tile sums, a scan
-// of the tile sums by one workgroup, and a tile-local scan that adds the tile's base.
+// workgroups add up what those before them have published (small_scan.h); 5 us instead of 14.
+// More: reduce-then-scan in three launches, tile sums, a scan of the tile sums by one workgroup,
+// and a tile-local scan that adds the tile's base.
 #include "device_util.h"
 #include "kernels.h"
 #include "lookback.h"
@@ -39,7 +39,7 @@ constexpr int kWideItems = 8;
 constexpr int kWideTile = kWideThreads * kWideItems;
 __global__ __launch_bounds__(kWideThreads) void scan_at_once_kernel(
     const int32_t* __restrict__ counts, int64_t n, int64_t* __restrict__ off, SmallScan* __restrict__ ss,
-    uint32_t spin_limit, uint32_t* __restrict__ err) {
+    uint32_t spin_limit) {
     __shared__ uint32_t wave_sums[kWideThreads / kWave];
     __shared__ int64_t s_base;
     const int lane = lane_id();
@@ -67,16 +67,22 @@ __global__ __launch_bounds__(kWideThreads) void scan_at_once_kernel(
     if (wave == 0) {
         const int at = (int)blockIdx.x;
         if (lane == 0) small_scan_publish(ss, at, tag, total);
-        const int64_t base = small_scan_before(ss, at, tag, spin_limit, lane);
+        const int64_t base = small_scan_before(ss, at, tag, spin_limit, lane, [&](int j) {
+            uint32_t sum = 0;  // of another workgroup's tile
+#pragma unroll 1
+            for (int t = lane; t < kWideTile; t += kWave) {
+                const int64_t e = (int64_t)j * kWideTile + t;
+                sum += e < n ? (uint32_t)counts[e] : 0u;
+            }
+            return wave_bcast_u32(wave_incl_sum(sum), kWave - 1);
+        });
         if (lane == 0) {
             small_scan_done(ss, at, tag, (int)gridDim.x);
             s_base = base;
-            if (base < 0) atomicOr(err, kDevStall);
-            if (at == (int)gridDim.x - 1) off[n] = base < 0 ? -1 : base + total;
+            if (at == (int)gridDim.x - 1) off[n] = base + total;
         }
     }
     __syncthreads();
-    if (s_base < 0) return;
     int64_t run = s_base + before + (incl - v);
 #pragma unroll
     for (int j = 0; j < kWideItems; ++j) {
@@ -195,11 +201,11 @@ int64_t scan_partials_len(int64_t n) { return (n + kScanTile - 1) / kScanTile + 
 
 hipError_t launch_exclusive_scan(hipStream_t stream, int n_cu, const int32_t* counts, int64_t n,
                                  int64_t* off, int64_t* partials, void* small_scan,
-                                 uint32_t spin_limit, uint32_t* err) {
+                                 uint32_t spin_limit) {
     if (n > 0 && n <= (int64_t)n_cu * kWideTile && n <= (int64_t)kSmallScanMax * kWideTile) {
         hipLaunchKernelGGL(scan_at_once_kernel, dim3((unsigned)((n + kWideTile - 1) / kWideTile)),
                            dim3(kWideThreads), 0, stream, counts, n, off,
-                           static_cast<SmallScan*>(small_scan), spin_limit, err);
+                           static_cast<SmallScan*>(small_scan), spin_limit);
         return hipGetLastError();
     }
     const int64_t n_tiles = (n + kScanTile - 1) / kScanTile;

@@ -1,17 +1,25 @@
-// Offsets of variable-size blocks inside ONE launch for small jobs: every workgroup of the launch
-// is on the device at the same time, publishes its number of rows and adds up the numbers of the
-// workgroups before it.  (Large jobs use a scanner wave, lookback.h, or a counting launch and a
-// scan of its counts: there a workgroup cannot look at everybody before it.)
+// Offsets of variable-size blocks inside ONE launch for small jobs: every workgroup publishes its
+// number of rows and adds up the numbers of the workgroups before it, most of which run at the same
+// time.  (Large jobs use a scanner wave, lookback.h, or a counting launch and a scan of its counts:
+// there a workgroup cannot look at everybody before it.)
 //
 // A word per workgroup holds (tag << 32 | rows).  The tag is the number of the launch, kept on
 // the device and moved on by the launch itself, so nothing has to be cleared before the next
 // launch, and a launch that was captured into a graph finds a new number at every replay.  The
 // number is moved on by the workgroup that is the last to say "done"; a workgroup says so once it
 // has read the number and waits for nobody any more, so no word of an earlier launch is ever
-// taken for one of this launch, also when a wait gave up.
-// Every wait ends: a workgroup waits only for workgroups before it, which publish before they
-// wait; the launch is no larger than what the device holds at once (small_scan_fits), and each
-// wait is bounded by the spin limit besides (kDevStall).
+// taken for one of this launch.
+// No workgroup depends on another one.  Which workgroups the device holds at a time is not in this
+// code's hands: launches of other contexts may fill a die while the workgroups of this launch that
+// the others wait for are still to start there, and those launches may be waiting in the same way.
+// So whoever has polled kHelpAfter times (or as often as the spin limit allows) for a number works
+// it out itself, publishes it in its owner's place (the owner, once it runs, publishes the same
+// number) and looks again.  There are at most as many numbers to work out as workgroups before it,
+// so every workgroup comes to its end, with all of its rows.  Working a number out is written for
+// few instructions and registers, not for speed: it stands in kernels that hardly ever run it.
+// (The workgroup's own work done over for another one, in a loop around it, made everybody pay:
+// what the compiler moved out of that loop took the walks from 47 to 93 registers, and 32 pairs
+// 23.7 us instead of 23.0.)
 #pragma once
 
 #include "device_util.h"
@@ -20,6 +28,8 @@ namespace surel {
 
 constexpr int kSmallScanMax = 4096;  // workgroups of a launch, at most
 constexpr int kDoneParts = 32;
+// Polls before a workgroup helps: milliseconds, a hundred times what a launch of this kind takes.
+constexpr uint32_t kHelpAfter = 4096;
 
 struct SmallScan {
     uint32_t launch;                  // number of the next launch
@@ -42,14 +52,18 @@ __device__ __forceinline__ void small_scan_publish(SmallScan* s, int at, uint32_
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Rows of the workgroups before `at` (one wavefront calls it), or -1 if the spin limit ran out.
-__device__ __forceinline__ int64_t small_scan_before(const SmallScan* s, int at, uint32_t tag,
-                                                     uint32_t spin_limit, int lane) {
+// Rows of the workgroups before `at` (one wavefront calls it).  rows_of(j): works the rows of
+// workgroup j out (the wavefront's lanes together, the same result in each).
+template <typename RowsOf>
+__device__ __forceinline__ int64_t small_scan_before(SmallScan* s, int at, uint32_t tag,
+                                                     uint32_t spin_limit, int lane,
+                                                     RowsOf&& rows_of) {
     constexpr int kWords = 8;  // words a lane has in flight
+    uint32_t polls = min(spin_limit, kHelpAfter);
     uint64_t sum = 0;
     for (int t0 = 0; t0 < at; t0 += kWords * kWave) {
         for (uint32_t spin = 0;; ++spin) {
-            bool missing = false;
+            int missing = -1;
             uint64_t part = 0;
             uint64_t w[kWords];
 #pragma unroll
@@ -61,14 +75,24 @@ __device__ __forceinline__ int64_t small_scan_before(const SmallScan* s, int at,
             }
 #pragma unroll
             for (int u = 0; u < kWords; ++u) {
-                missing = missing || (uint32_t)(w[u] >> 32) != tag;
+                missing = (uint32_t)(w[u] >> 32) != tag ? t0 + u * kWave + lane : missing;
                 part += (uint32_t)w[u];
             }
-            if (__ballot(missing) == 0ull) {
+            const uint64_t lanes = __ballot(missing >= 0);
+            if (lanes == 0ull) {
                 sum += part;
                 break;
             }
-            if (spin >= spin_limit) return -1;
+            if (spin >= polls) {
+                // of several that are missing, one that depends on `at`: helpers share them out
+                const int turn = at & (kWave - 1);
+                const uint64_t turned = (lanes >> turn) | (lanes << ((kWave - turn) & (kWave - 1)));
+                const int from = (__builtin_ctzll(turned) + turn) & (kWave - 1);
+                const int j = (int)wave_bcast_u32((uint32_t)missing, from);
+                const uint32_t rows = rows_of(j);
+                if (lane == 0) small_scan_publish(s, j, tag, rows);
+                polls = 0;
+            }
             __builtin_amdgcn_s_sleep(1);
         }
     }

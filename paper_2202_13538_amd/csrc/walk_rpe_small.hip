@@ -1,5 +1,5 @@
-// Walks and RPE of few seeds (Sec. 3.2) in one launch that holds all of them at once: a wavefront
-// per seed, every workgroup on the device at the same time.
+// Walks and RPE of few seeds (Sec. 3.2) in one launch, a wavefront per seed, as many seeds as the
+// device has room for at a time.
 //
 // The kernel for many seeds (walk_rpe.hip) has waves that draw seeds, a scanner wave, and scratch
 // that a launch of its own clears; on large graphs it reads neighbour records that another launch
@@ -17,6 +17,38 @@
 namespace surel {
 
 constexpr int small_walk_waves(int E) { return E <= 16 ? 16 : 8; }  // of a compute unit, by registers
+
+// Rows of seed number i, for a workgroup that helps another one: its walks once more, and every
+// entry compared with those before it.  block: LDS of the wave, fused_block_words(M, m) words.
+__device__ __forceinline__ uint32_t small_walk_rows(const FusedJob& f, int64_t i, int32_t* block,
+                                                    int lane) {
+    const int32_t u = __builtin_amdgcn_readfirstlane(f.seeds[i]);
+    if (u < 0 || u >= f.g.n_nodes) return 0;
+    const int L = f.m + 1, n = f.M * L;
+    int32_t u_lo, u_deg;
+    seed_row(f.g, u, &u_lo, &u_deg);
+#pragma unroll 1
+    for (int w0 = 0; w0 < f.M; w0 += kWave) {
+        const int w[1] = {w0 + lane};
+        const bool active[1] = {w[0] < f.M};
+        int32_t* const row[1] = {block + (active[0] ? w[0] : f.M) * L};
+        walk_many<kRecNone, 1, false>(f.g, u, u_lo, u_deg, w, active, f.m, f.key0, f.key1, row,
+                                      [](int, int32_t) {});
+    }
+    wave_sync();
+    uint32_t rows = 0;
+#pragma unroll 1
+    for (int t0 = 0; t0 < n; t0 += kWave) {
+        const int t = t0 + lane;
+        const int32_t v = block[min(t, n - 1)];
+        bool first = t < n;
+#pragma unroll 1
+        for (int s = 0; s < min(t0 + kWave, n); ++s) first = first && !(s < t && block[s] == v);
+        rows += (uint32_t)__popcll(__ballot(first));
+    }
+    wave_sync();
+    return rows;
+}
 
 template <int E>
 __global__ __launch_bounds__(small_walk_waves(E) * kWave) void walk_rpe_small_kernel(
@@ -50,20 +82,24 @@ __global__ __launch_bounds__(small_walk_waves(E) * kWave) void walk_rpe_small_ke
         const uint32_t sum = wave_bcast_u32(wave_incl_sum(mine), kWave - 1);
         const int at = (int)blockIdx.x;
         if (lane == 0) small_scan_publish(ss, at, tag, sum);
-        const int64_t before = small_scan_before(ss, at, tag, f.spin_limit, lane);
+        const int64_t before = small_scan_before(ss, at, tag, f.spin_limit, lane, [&](int j) {
+            uint32_t rows = 0;  // (the wave's LDS is free: its keys are in registers)
+            const int64_t last = min((int64_t)(j + 1) * n_waves, f.n_seeds);
+            for (int64_t s = (int64_t)j * n_waves; s < last; ++s)
+                rows += small_walk_rows(f, s, reinterpret_cast<int32_t*>(wave_lds), lane);
+            return rows;
+        });
         if (lane == 0) {
             small_scan_done(ss, at, tag, (int)gridDim.x);
             s_base = before;
-            if (before < 0) atomicOr(f.err, kDevStall);
             if (at == (int)gridDim.x - 1) {
-                const int64_t total = before < 0 ? -1 : before + sum;
-                f.rpe_off[f.n_seeds] = total;
-                if (f.h_total) *f.h_total = total;
+                f.rpe_off[f.n_seeds] = before + sum;
+                if (f.h_total) *f.h_total = before + sum;
             }
         }
     }
     __syncthreads();
-    if (s_base < 0 || i >= f.n_seeds) return;
+    if (i >= f.n_seeds) return;
     int64_t off = s_base;
     for (int w = 0; w < wave; ++w) off += rows_of[w];
     if (lane == 0) f.rpe_off[i] = off;
