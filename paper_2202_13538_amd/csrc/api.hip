@@ -18,7 +18,9 @@ struct surel_ctx {
     uint32_t* d_err = nullptr;    // sticky device error word
     hipEvent_t done = nullptr;    // completed by the one launch of a call that reports its total
     void* d_small = nullptr;      // words of the launches that lay small outputs out themselves
-    int64_t* h_pinned = nullptr;  // 2 x int64 of pinned host memory for small read-backs
+    // pinned host memory for small read-backs: a row total; a number of distinct vectors or the
+    // error word; 1 if a wait inside the fused kernel ran out
+    int64_t* h_pinned = nullptr;
     void* d_ws = nullptr;         // grow-only workspace: row counts + scan partials
     size_t ws_bytes = 0;
     void* d_rec = nullptr;        // grow-only workspace: per-edge neighbour records of the walk
@@ -237,7 +239,7 @@ int surel_create(surel_ctx** out, int device, void* hip_stream) {
     ok = ok && hipMalloc(&ctx->d_small, surel::small_scan_bytes()) == hipSuccess;
     ok = ok && hipMemsetAsync(ctx->d_small, 0, surel::small_scan_bytes(), ctx->stream) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->done, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 2 * sizeof(int64_t),
+    ok = ok && hipHostMalloc(reinterpret_cast<void**>(&ctx->h_pinned), 3 * sizeof(int64_t),
                              hipHostMallocDefault) == hipSuccess;
     ok = ok && hipStreamSynchronize(ctx->stream) == hipSuccess;
     // where THIS device keeps its copy of the static scratch array (the device is current here)
@@ -328,7 +330,7 @@ static int check_rpe_args(int32_t n_nodes, int64_t n_seeds, int32_t M, int32_t m
     return SUREL_OK;
 }
 
-// rows < 0: the scanner wave of the fused kernel gave up on a bounded wait.
+// rows < 0: a bounded wait inside the fused kernel ran out.
 static int judge_total(bool has_outputs, int64_t cap_rows, int64_t rows) {
     if (rows < 0) return SUREL_E_DEVICE;
     if (has_outputs && rows > cap_rows) return SUREL_E_CAPACITY;
@@ -340,13 +342,21 @@ static int report_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, bool ha
     if (int rc = read_total(ctx, d_off, n, h_rows)) return rc;
     return judge_total(has_outputs, cap_rows, *h_rows);
 }
-// The same where the launch has put the total into the pinned word itself; marked: it is one that
-// completes ctx->done.
+// The pinned words of a launch that reports its total there itself: before it, and once it is done.
+// (A total of rows some of which are missing because a wait ran out is none.)
+static void expect_pinned_total(surel_ctx* ctx) {
+    ctx->h_pinned[0] = -1;
+    ctx->h_pinned[2] = 0;
+}
+static int64_t pinned_total(const surel_ctx* ctx) {
+    return ctx->h_pinned[2] != 0 ? -1 : ctx->h_pinned[0];
+}
+// The same for such a launch; marked: it is one that completes ctx->done.
 static int report_pinned_total(surel_ctx* ctx, bool marked, bool has_outputs, int64_t cap_rows,
                                int64_t* h_rows) {
     const hipError_t rc = marked ? hipEventSynchronize(ctx->done) : hipStreamSynchronize(ctx->stream);
     if (rc != hipSuccess) return SUREL_E_HIP;
-    *h_rows = ctx->h_pinned[0];
+    *h_rows = pinned_total(ctx);
     return judge_total(has_outputs, cap_rows, *h_rows);
 }
 
@@ -445,13 +455,16 @@ static int check_fused_args(const int32_t* d_row_ptr, const int32_t* d_col_idx, 
 }
 
 // The fused kernel (n_seeds >= 1): edge records if the job wants them, look-back scratch, launch.
-// d_code / ps: the hash set of distinct count vectors that is to be fed, or null.
+// d_code / ps: the hash set of distinct count vectors that is to be fed, or null.  want_total: the
+// total goes to the pinned words.
 static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                         int32_t n_nodes, int64_t n_edges, const int32_t* d_seeds, int64_t n_seeds,
                         int32_t M, int32_t m, uint64_t rng_seed, int32_t* d_walks, int64_t cap_rows,
                         int64_t* d_rpe_off, int32_t* d_rpe_ids, uint16_t* d_rpe_cnt, int32_t* d_code,
-                        const surel::PruneScratch& ps, int64_t* h_total) {
-    if (h_total) *h_total = -1;
+                        const surel::PruneScratch& ps, bool want_total) {
+    int64_t* h_total = want_total ? ctx->h_pinned : nullptr;
+    int64_t* h_gave_up = want_total ? ctx->h_pinned + 2 : nullptr;
+    if (want_total) expect_pinned_total(ctx);
     if (d_code == nullptr && surel::walk_rpe_is_small(ctx->n_cu, n_seeds, M, m)) {
         KernelSpan span(ctx, SUREL_K_WALK_RPE);
         hipError_t hrc = surel::launch_walk_rpe_small(
@@ -471,7 +484,7 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
     hipError_t hrc = surel::launch_walk_rpe(
         ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds,
         n_seeds, M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, records,
-        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, h_total, ctx->d_err, d_code, ps);
+        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, h_total, h_gave_up, ctx->d_err, d_code, ps);
     if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
     return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
 }
@@ -503,7 +516,7 @@ int surel_sample_walks_rpe(surel_ctx* ctx, const int32_t* d_row_ptr, const int32
     } else if (int rc = fused_launch(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds, n_seeds,
                                      M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids,
                                      d_rpe_cnt, nullptr, surel::PruneScratch{},
-                                     h_rows ? ctx->h_pinned : nullptr)) {
+                                     h_rows != nullptr)) {
         return rc;
     } else if (h_rows) {
         return report_pinned_total(ctx, surel::walk_rpe_is_small(ctx->n_cu, n_seeds, M, m),
@@ -534,8 +547,8 @@ static int prune_scratch(surel_ctx* ctx, int64_t cap_T, surel::PruneScratch* ps)
     return SUREL_OK;
 }
 
-// The end of the pruning calls: T and the codes, the number of distinct vectors and (what
-// h_pinned[0] then holds, if the call's kernel put it there) the row total, with one wait.
+// The end of the pruning calls: T and the codes, the number of distinct vectors and (h_rows, if the
+// call's kernel reports it in the pinned words) the row total, with one wait.
 // n_rows, d_rows: the number of rows, or where it stands on the device.
 static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m, int64_t n_rows,
                         const int64_t* d_rows, int64_t cap_rows, uint16_t* d_T, int32_t* d_code,
@@ -550,7 +563,7 @@ static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m
     // with more than cap_T vectors the set's list is not complete, and its slots are not all empty
     if (n_T <= ps.cap_T) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
     if (h_rows) {
-        *h_rows = n_rows = ctx->h_pinned[0];
+        *h_rows = n_rows = pinned_total(ctx);
         if (int rc = judge_total(true, cap_rows, n_rows)) return rc;  // not all rows have codes
     }
     if (n_T > ps.cap_T) return SUREL_E_CAPACITY;
@@ -588,7 +601,7 @@ int surel_sample_walks_rpe_ids(surel_ctx* ctx, const int32_t* d_row_ptr, const i
     if (int rc = prune_scratch(ctx, cap_T, &ps)) return rc;
     if (int rc = fused_launch(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds, n_seeds, M, m,
                               rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, d_code,
-                              ps, ctx->h_pinned))
+                              ps, true))
         return rc;
     return prune_finish(ctx, ps, m, 0, d_rpe_off + n_seeds, cap_rows, d_T, d_code, h_rows, h_n_T);
 }
@@ -658,7 +671,7 @@ static int join_small(surel_ctx* ctx, const int64_t* d_rpe_off, const int32_t* d
                       const int32_t* d_queries, int64_t n_queries, int32_t k, int64_t cap_rows,
                       int64_t* d_join_off, int32_t* d_join_ids, uint16_t* d_join_cnt,
                       uint16_t absent16, int64_t* h_rows) {
-    if (h_rows) ctx->h_pinned[0] = -1;
+    if (h_rows) expect_pinned_total(ctx);
     {
         KernelSpan span(ctx, d_join_ids ? SUREL_K_JOIN_FILL : SUREL_K_JOIN_COUNT);
         hipError_t hrc = surel::launch_join_small(

@@ -45,7 +45,8 @@ hipError_t launch_walks(hipStream_t stream, const int32_t* row_ptr, const int32_
 // rpe_off[0..n_seeds] and (unless ids is null) the rows.  lb: device scratch of
 // lookback_words(n_seeds) 64-bit words (cleared by the launch itself).  n_cu: compute
 // units of the device.  spin_limit bounds every wait inside the kernel (kDevStall when one runs
-// out; rpe_off[n_seeds] is then -1).  Needs M*(m+1) <= 2048 and n_seeds >= 1.
+// out; *h_gave_up (optional, host memory, zero before) then becomes 1 unless it was the offset
+// scan's, which leaves a total of -1).  Needs M*(m+1) <= 2048 and n_seeds >= 1.
 // hipErrorInvalidValue = the shape does not fit the device's LDS.
 // With `code` (int32 per table row) the kernel also looks every finished row's count vector up
 // in the hash set of prune.hip and writes the vector's number there to code[row];
@@ -63,8 +64,8 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
                            const int32_t* seeds, int64_t n_seeds, int32_t M, int32_t m,
                            uint64_t rng_seed, int32_t* walks, int64_t cap_rows, int64_t* rpe_off,
                            int32_t* ids, uint16_t* cnt, const EdgeRecords& rec, uint64_t* lb,
-                           uint32_t spin_limit, int64_t* h_total, uint32_t* err,
-                           int32_t* code, const PruneScratch& ps);
+                           uint32_t spin_limit, int64_t* h_total, int64_t* h_gave_up,
+                           uint32_t* err, int32_t* code, const PruneScratch& ps);
 
 // walk_rpe_small.hip.  The same for few seeds (walk_rpe_is_small says for how many), in one launch
 // that needs neither records nor look-back scratch.  small_scan, spin_limit, h_total, done: as for

@@ -23,7 +23,9 @@
 // or about to be taken by a wave that waits only for things that already exist.  The scanner
 // belongs to the first workgroup that drew, so it is running whenever anybody waits for it.  On top
 // of that every wait is bounded by a spin limit: a wait that runs out raises kDevStall and
-// the wave leaves (the row total, which the scanner writes last, then stays -1).
+// the wave leaves.  If it is the scanner, the row total, which it writes last, stays -1; a worker
+// that leaves has published its counts, so the scanner may well come to a total although rows are
+// missing, and the worker tells the host by a word of its own.
 #pragma once
 
 #include "device_util.h"

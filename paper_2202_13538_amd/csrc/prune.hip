@@ -407,9 +407,9 @@ size_t prune_slot_bytes(int64_t cap_T) { return (size_t)prune_slots(cap_T) * kSl
 size_t prune_member_bytes(int64_t cap_T) { return (size_t)prune_list_len(cap_T) * kItemWords * 4; }
 size_t prune_rank_bytes(int64_t cap_T) { return (size_t)cap_T * sizeof(uint32_t); }
 
-VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err) {
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, int64_t* h_gave_up, uint32_t* err) {
     return VectorSet{ps.slots, (uint32_t)(prune_slots(ps.cap_T) - 1), ps.cap_T, ps.members, ps.ranks,
-                     ps.counters, spin_limit, err};
+                     ps.counters, spin_limit, h_gave_up, err};
 }
 
 hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
@@ -440,7 +440,7 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
                                 int32_t m, const PruneScratch& ps, int32_t* code,
                                 uint32_t spin_limit, uint32_t* err) {
     if (n_rows == 0) return hipSuccess;
-    const VectorSet set = vector_set(ps, spin_limit, err);
+    const VectorSet set = vector_set(ps, spin_limit, nullptr, err);
     const int L = m + 1;
     switch (L) {
         case 2: return launch_collect<2>(stream, n_cu, cnt, n_rows, L, code, set);

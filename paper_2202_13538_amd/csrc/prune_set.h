@@ -29,10 +29,11 @@ struct VectorSet {
     uint32_t* ranks;
     unsigned long long* n_inserted;
     uint32_t spin_limit;
+    int64_t* h_gave_up;  // host memory that gets a 1 when a wait runs out, or null
     uint32_t* err;
 };
 
-VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err);
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, int64_t* h_gave_up, uint32_t* err);
 
 template <int NW>
 __device__ __forceinline__ uint32_t hash_vector(const uint32_t (&w)[NW]) {
@@ -81,6 +82,7 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                 // somebody is writing this slot's vector: look again
                 if (++spins > set.spin_limit) {
                     atomicOr(set.err, kDevStall);
+                    if (set.h_gave_up) *set.h_gave_up = 1;
                     return -1;
                 }
                 __builtin_amdgcn_s_sleep(1);

@@ -466,6 +466,52 @@ def test_fused_kernel_waits_are_bounded(ctx):
     assert_table_equal((f_off, f_ids, f_cnt), want, "rpe after the limit was restored")
 
 
+@pytest.mark.parametrize("spins", [0, 2, 4, 6, 8, 10, 12, 16, 24])
+def test_a_wait_that_runs_out_in_the_fused_kernel_is_reported(ctx, spins):
+    # more seeds than go into one launch without roles; whichever wave gives up (the scanner, or a
+    # worker whose counts the scanner has), a call that was given h_rows says so
+    wl = synth.Workload("t", "rmat", 16384, 100000, 0.0, 50, 4, 0, 2, "uniform", graph_seed=9)
+    rp, ci = synth.make_graph(wl)
+    seeds = np.arange(wl.n_nodes, dtype=np.int32)
+    d_rp, d_ci, d_seeds = dev(rp), dev(ci), dev(seeds)
+    M, m, L = wl.M, wl.m, wl.m + 1
+    want = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 1)
+    want_T, want_code = binding.prune_rpe(ctx, want[3], cap_T=4096)
+    assert ctx.check() == 0
+    cap = want[2].numel()
+    walks = torch.empty((seeds.size, M, L), dtype=torch.int32, device="cuda")
+    off = torch.empty(seeds.size + 1, dtype=torch.int64, device="cuda")
+    ids, code = (torch.empty(cap, dtype=torch.int32, device="cuda") for _ in range(2))
+    cnt = torch.empty((cap, L), dtype=torch.uint16, device="cuda")
+    T = torch.zeros((4096, L), dtype=torch.int16, device="cuda").view(torch.uint16)
+    for with_ids in (False, True):
+        ids.fill_(-7)
+        ctx.set_spin_limit(spins)
+        try:
+            if with_ids:
+                rc, rows, n_T = binding.sample_walks_rpe_ids_raw(ctx, d_rp, d_ci, d_seeds, M, m, 1, walks,
+                                                                 cap, off, ids, None, code, 4096, T)
+            else:
+                rc, rows = binding.sample_walks_rpe_raw(ctx, d_rp, d_ci, d_seeds, M, m, 1, walks, cap,
+                                                        off, ids, cnt)
+        finally:
+            ctx.set_spin_limit(1 << 22)
+        flags = ctx.check()
+        print(f"spins {spins} ids {with_ids}: status {rc}, flags {flags:#x}", flush=True)
+        if rc == binding.OK:
+            assert flags == 0 and rows == cap
+            assert torch.equal(off, want[1]) and torch.equal(ids, want[2])
+            if with_ids:
+                assert n_T == want_T.shape[0] and torch.equal(code, want_code)
+        else:
+            assert rc == binding.E_DEVICE and flags == binding.DEV_STALL and rows == -1
+    # the next call is right again, its hash set is what it should be
+    rc, rows, n_T = binding.sample_walks_rpe_ids_raw(ctx, d_rp, d_ci, d_seeds, M, m, 1, walks, cap, off,
+                                                     ids, None, code, 4096, T)
+    assert rc == binding.OK and rows == cap and ctx.check() == 0
+    assert torch.equal(ids, want[2]) and torch.equal(code, want_code)
+
+
 def test_prune_capacity_and_degenerate_tables(ctx):
     rng = np.random.default_rng(3)
     cnt = rng.integers(0, 3, size=(5000, 4)).astype(np.uint16)          # at most 81 vectors
