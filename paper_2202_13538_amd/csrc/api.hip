@@ -18,8 +18,8 @@ struct surel_ctx {
     uint32_t* d_err = nullptr;    // sticky device error word
     hipEvent_t done = nullptr;    // completed by the one launch of a call that reports its total
     void* d_small = nullptr;      // words of the launches that lay small outputs out themselves
-    // pinned host memory for small read-backs: a row total; a number of distinct vectors or the
-    // error word; 1 if a wait inside the fused kernel ran out
+    // pinned host memory for small read-backs: a row total; 1 if a bounded wait ran out; a number of
+    // distinct vectors or the error word
     int64_t* h_pinned = nullptr;
     void* d_ws = nullptr;         // grow-only workspace: row counts + scan partials
     size_t ws_bytes = 0;
@@ -346,10 +346,10 @@ static int report_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, bool ha
 // (A total of rows some of which are missing because a wait ran out is none.)
 static void expect_pinned_total(surel_ctx* ctx) {
     ctx->h_pinned[0] = -1;
-    ctx->h_pinned[2] = 0;
+    ctx->h_pinned[1] = 0;
 }
 static int64_t pinned_total(const surel_ctx* ctx) {
-    return ctx->h_pinned[2] != 0 ? -1 : ctx->h_pinned[0];
+    return ctx->h_pinned[1] != 0 ? -1 : ctx->h_pinned[0];
 }
 // The same for such a launch; marked: it is one that completes ctx->done.
 static int report_pinned_total(surel_ctx* ctx, bool marked, bool has_outputs, int64_t cap_rows,
@@ -463,7 +463,6 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
                         int64_t* d_rpe_off, int32_t* d_rpe_ids, uint16_t* d_rpe_cnt, int32_t* d_code,
                         const surel::PruneScratch& ps, bool want_total) {
     int64_t* h_total = want_total ? ctx->h_pinned : nullptr;
-    int64_t* h_gave_up = want_total ? ctx->h_pinned + 2 : nullptr;
     if (want_total) expect_pinned_total(ctx);
     if (d_code == nullptr && surel::walk_rpe_is_small(ctx->n_cu, n_seeds, M, m)) {
         KernelSpan span(ctx, SUREL_K_WALK_RPE);
@@ -484,7 +483,7 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
     hipError_t hrc = surel::launch_walk_rpe(
         ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_row_ptr, d_col_idx, n_nodes, n_edges, d_seeds,
         n_seeds, M, m, rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, records,
-        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, h_total, h_gave_up, ctx->d_err, d_code, ps);
+        static_cast<uint64_t*>(ctx->d_lb), ctx->spin_limit, h_total, ctx->d_err, d_code, ps);
     if (hrc == hipErrorInvalidValue) return SUREL_E_RANGE;
     return hrc == hipSuccess ? SUREL_OK : SUREL_E_HIP;
 }
@@ -555,10 +554,10 @@ static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m
                         int64_t* h_rows, int64_t* h_n_T) {
     KernelSpan span(ctx, SUREL_K_PRUNE);
     if (surel::launch_prune_order(ctx->stream, ctx->n_cu, ps, m, n_rows, d_rows, cap_rows, d_T, d_code,
-                                  ctx->h_pinned + 1) != hipSuccess)
+                                  ctx->h_pinned + 2, ctx->h_pinned + 1) != hipSuccess)
         return SUREL_E_HIP;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
-    const int64_t n_T = ctx->h_pinned[1];
+    const int64_t n_T = ctx->h_pinned[2];
     *h_n_T = n_T;
     // with more than cap_T vectors the set's list is not complete, and its slots are not all empty
     if (n_T <= ps.cap_T) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
@@ -965,7 +964,7 @@ int surel_check(surel_ctx* ctx, uint32_t* h_flags) {
     if (!ctx) return SUREL_E_CTX;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
-    uint32_t* h_word = reinterpret_cast<uint32_t*>(ctx->h_pinned + 1);
+    uint32_t* h_word = reinterpret_cast<uint32_t*>(ctx->h_pinned + 2);
     if (hipMemcpyAsync(h_word, ctx->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost,
                        ctx->stream) != hipSuccess)
         return SUREL_E_HIP;

@@ -45,8 +45,9 @@ hipError_t launch_walks(hipStream_t stream, const int32_t* row_ptr, const int32_
 // rpe_off[0..n_seeds] and (unless ids is null) the rows.  lb: device scratch of
 // lookback_words(n_seeds) 64-bit words (cleared by the launch itself).  n_cu: compute
 // units of the device.  spin_limit bounds every wait inside the kernel (kDevStall when one runs
-// out; *h_gave_up (optional, host memory, zero before) then becomes 1 unless it was the offset
-// scan's, which leaves a total of -1).  Needs M*(m+1) <= 2048 and n_seeds >= 1.
+// out; rpe_off[n_seeds] is then -1 or a total of rows some of which are missing).  h_total
+// (optional): two words of host memory, which get the total and, in the latter case, a 1.  Needs
+// M*(m+1) <= 2048 and n_seeds >= 1.
 // hipErrorInvalidValue = the shape does not fit the device's LDS.
 // With `code` (int32 per table row) the kernel also looks every finished row's count vector up
 // in the hash set of prune.hip and writes the vector's number there to code[row];
@@ -64,8 +65,8 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
                            const int32_t* seeds, int64_t n_seeds, int32_t M, int32_t m,
                            uint64_t rng_seed, int32_t* walks, int64_t cap_rows, int64_t* rpe_off,
                            int32_t* ids, uint16_t* cnt, const EdgeRecords& rec, uint64_t* lb,
-                           uint32_t spin_limit, int64_t* h_total, int64_t* h_gave_up,
-                           uint32_t* err, int32_t* code, const PruneScratch& ps);
+                           uint32_t spin_limit, int64_t* h_total, uint32_t* err,
+                           int32_t* code, const PruneScratch& ps);
 
 // walk_rpe_small.hip.  The same for few seeds (walk_rpe_is_small says for how many), in one launch
 // that needs neither records nor look-back scratch.  small_scan, spin_limit, h_total, done: as for
@@ -133,7 +134,7 @@ hipError_t launch_query_ids(hipStream_t stream, int max_lds_bytes, const int32_t
 
 // prune.hip.  Distinct count vectors of the table, sorted, and every row's index among them.
 // PruneScratch: device scratch of prune_slot_bytes, prune_member_bytes and prune_rank_bytes(cap_T)
-// bytes and two 64-bit counters.  slots and counters are zero before a call (launch_prune_clear)
+// bytes and three 64-bit counters.  slots and counters are zero before a call (launch_prune_clear)
 // and are left zero by launch_prune_order, unless there were more than cap_T distinct vectors.
 size_t prune_slot_bytes(int64_t cap_T);
 size_t prune_member_bytes(int64_t cap_T);
@@ -145,14 +146,15 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
                                 int32_t m, const PruneScratch& ps, int32_t* code,
                                 uint32_t spin_limit, uint32_t* err);
 // T = the set's vectors, sorted; code[row] = place of the row's vector there; *h_n_T (host memory)
-// = their number; then empties the set.  d_rows (optional): where the number of rows stands on
+// = their number; *h_stalled (host memory) = 1 if a wait ran out while they were collected (else it
+// stays); then empties the set.  d_rows (optional): where the number of rows stands on
 // the device; with more than cap_rows of them the codes stay as they are.  With more than
 // prune_rank_most(cap_T) distinct vectors T and code stay as they are, and launch_prune_order_many
 // has to be called with the number.
 int64_t prune_rank_most(int64_t cap_T);
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                               int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
-                              int32_t* code, int64_t* h_n_T);
+                              int32_t* code, int64_t* h_n_T, int64_t* h_stalled);
 hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                                    int64_t n_rows, int64_t n_T, uint16_t* T, int32_t* code);
 

@@ -250,13 +250,16 @@ __global__ __launch_bounds__(kRankTile) void prune_rank_pairs_kernel(
     }
 }
 
-// T[ranks[i]] = vector i; the number of vectors also goes to host memory.
+// T[ranks[i]] = vector i; the number of vectors also goes to host memory, and whether a wait ran out.
 __global__ __launch_bounds__(256) void prune_place_kernel(
-    const uint32_t* __restrict__ members, const unsigned long long* __restrict__ n_inserted,
+    const uint32_t* __restrict__ members, const unsigned long long* __restrict__ counters,
     int64_t most, int L, const uint32_t* __restrict__ ranks, uint16_t* __restrict__ T,
-    int64_t* h_n_T) {
-    const int64_t n = (int64_t)*n_inserted;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *h_n_T = n;
+    int64_t* h_n_T, int64_t* h_stalled) {
+    const int64_t n = (int64_t)counters[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *h_n_T = n;
+        if (counters[2] != 0ull) *h_stalled = 1;
+    }
     if (n > most) return;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -274,7 +277,8 @@ __global__ __launch_bounds__(256) void prune_clean_kernel(const uint32_t* __rest
                                                           int64_t cap_T,
                                                           uint32_t* __restrict__ slots,
                                                           unsigned long long* __restrict__ counters) {
-    // counters[0]: vectors inserted; counters[1]: workgroups of this launch that have read it
+    // counters[0]: vectors inserted; counters[1]: workgroups of this launch that have read it;
+    // counters[2]: whether a wait ran out
     const int64_t n = min((int64_t)counters[0], cap_T);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
@@ -283,6 +287,7 @@ __global__ __launch_bounds__(256) void prune_clean_kernel(const uint32_t* __rest
     if (threadIdx.x == 0 && atomicAdd(&counters[1], 1ull) + 1ull == gridDim.x) {
         counters[0] = 0ull;
         counters[1] = 0ull;
+        counters[2] = 0ull;
     }
 }
 
@@ -407,9 +412,9 @@ size_t prune_slot_bytes(int64_t cap_T) { return (size_t)prune_slots(cap_T) * kSl
 size_t prune_member_bytes(int64_t cap_T) { return (size_t)prune_list_len(cap_T) * kItemWords * 4; }
 size_t prune_rank_bytes(int64_t cap_T) { return (size_t)cap_T * sizeof(uint32_t); }
 
-VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, int64_t* h_gave_up, uint32_t* err) {
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err) {
     return VectorSet{ps.slots, (uint32_t)(prune_slots(ps.cap_T) - 1), ps.cap_T, ps.members, ps.ranks,
-                     ps.counters, spin_limit, h_gave_up, err};
+                     ps.counters, spin_limit, err};
 }
 
 hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
@@ -417,7 +422,7 @@ hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
     // graph, and plain memsets do)
     hipError_t rc = hipMemsetAsync(ps.slots, 0, prune_slot_bytes(ps.cap_T), stream);
     if (rc != hipSuccess) return rc;
-    return hipMemsetAsync(ps.counters, 0, 2 * sizeof(unsigned long long), stream);
+    return hipMemsetAsync(ps.counters, 0, 3 * sizeof(unsigned long long), stream);
 }
 
 template <int LT>
@@ -440,7 +445,7 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
                                 int32_t m, const PruneScratch& ps, int32_t* code,
                                 uint32_t spin_limit, uint32_t* err) {
     if (n_rows == 0) return hipSuccess;
-    const VectorSet set = vector_set(ps, spin_limit, nullptr, err);
+    const VectorSet set = vector_set(ps, spin_limit, err);
     const int L = m + 1;
     switch (L) {
         case 2: return launch_collect<2>(stream, n_cu, cnt, n_rows, L, code, set);
@@ -465,7 +470,7 @@ int64_t prune_rank_most(int64_t cap_T) { return cap_T < kRankMost ? cap_T : kRan
 
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                               int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
-                              int32_t* code, int64_t* h_n_T) {
+                              int32_t* code, int64_t* h_n_T, int64_t* h_stalled) {
     const int64_t most = prune_rank_most(ps.cap_T);
     const int L = m + 1;
     switch ((L + 1) / 2) {
@@ -486,7 +491,7 @@ hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& 
         default: return hipErrorInvalidValue;
     }
     hipLaunchKernelGGL(prune_place_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.counters,
-                       most, L, ps.ranks, T, h_n_T);
+                       most, L, ps.ranks, T, h_n_T, h_stalled);
     launch_codes(stream, n_cu, ps, -1, most, n_rows, d_rows, cap_rows, code);
     hipLaunchKernelGGL(prune_clean_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.cap_T,
                        ps.slots, ps.counters);

@@ -20,20 +20,20 @@ constexpr int kMaxVecWords = 8;   // m + 1 <= 16 counts of 16 bits
 constexpr int kItemWords = kMaxVecWords + 1;  // a member of the set: its vector, zeros, its slot
 
 // The set.  members[i] = vector number i and its slot (kItemWords words; i < cap_T), ranks[i] = 0:
-// written by whoever inserts it.  *n_inserted = vectors inserted so far.
+// written by whoever inserts it.  counters[0] = vectors inserted so far; counters[2] becomes 1 if a
+// wait runs out.
 struct VectorSet {
     uint32_t* slots;
     uint32_t slot_mask;
     int64_t cap_T;
     uint32_t* members;
     uint32_t* ranks;
-    unsigned long long* n_inserted;
+    unsigned long long* counters;
     uint32_t spin_limit;
-    int64_t* h_gave_up;  // host memory that gets a 1 when a wait runs out, or null
     uint32_t* err;
 };
 
-VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, int64_t* h_gave_up, uint32_t* err);
+VectorSet vector_set(const PruneScratch& ps, uint32_t spin_limit, uint32_t* err);
 
 template <int NW>
 __device__ __forceinline__ uint32_t hash_vector(const uint32_t (&w)[NW]) {
@@ -60,7 +60,7 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
             st = atomicCAS(slot, kSlotEmpty, kSlotLocked);
             if (st == kSlotEmpty) {
                 // this lane owns the slot: is there still room in T?
-                const unsigned long long number = atomicAdd(set.n_inserted, 1ull);
+                const unsigned long long number = atomicAdd(set.counters, 1ull);
                 if ((int64_t)number >= set.cap_T) {
                     atomicOr(set.err, kDevCapacity);
                 } else {
@@ -82,7 +82,7 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                 // somebody is writing this slot's vector: look again
                 if (++spins > set.spin_limit) {
                     atomicOr(set.err, kDevStall);
-                    if (set.h_gave_up) *set.h_gave_up = 1;
+                    __hip_atomic_store(set.counters + 2, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     return -1;
                 }
                 __builtin_amdgcn_s_sleep(1);

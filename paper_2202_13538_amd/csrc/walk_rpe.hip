@@ -92,7 +92,7 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
             if (off < 0) {
                 if (lane == 0) {
                     atomicOr(f.err, kDevStall);
-                    if (f.h_gave_up) *f.h_gave_up = 1;
+                    if (f.h_total) f.h_total[1] = 1;
                 }
                 return;
             }
@@ -187,12 +187,11 @@ hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, cons
                            const int32_t* seeds, int64_t n_seeds, int32_t M, int32_t m,
                            uint64_t rng_seed, int32_t* walks, int64_t cap_rows, int64_t* rpe_off,
                            int32_t* ids, uint16_t* cnt, const EdgeRecords& rec, uint64_t* lb,
-                           uint32_t spin_limit, int64_t* h_total, int64_t* h_gave_up,
-                           uint32_t* err, int32_t* code, const PruneScratch& ps) {
-    const VectorSet set = code != nullptr ? vector_set(ps, spin_limit, h_gave_up, err) : VectorSet{};
+                           uint32_t spin_limit, int64_t* h_total, uint32_t* err, int32_t* code,
+                           const PruneScratch& ps) {
+    const VectorSet set = code != nullptr ? vector_set(ps, spin_limit, err) : VectorSet{};
     const FusedJob f = fused_job(row_ptr, col_idx, n_nodes, n_edges, seeds, n_seeds, M, m, rng_seed,
-                                 walks, cap_rows, rpe_off, ids, cnt, rec, spin_limit, h_total,
-                                 h_gave_up, err);
+                                 walks, cap_rows, rpe_off, ids, cnt, rec, spin_limit, h_total, err);
     const int n_key = fused_keys(M, m);
 #define SUREL_WR_SIZE(E_) \
     if (n_key <= kWave * (E_)) return launch_walk_rpe_e<E_>(stream, max_lds_bytes, n_cu, f, rec.format, lb, code, set);

@@ -37,8 +37,7 @@ struct FusedJob {
     int32_t lds_words_per_wave;
     int32_t lds_rows;     // rows of a block that fit there at a time
     uint32_t spin_limit;
-    int64_t* h_total;     // host memory that gets the row total too, or null
-    int64_t* h_gave_up;   // host memory that gets a 1 when a wait runs out, or null
+    int64_t* h_total;     // host memory, or null: the row total; a 1 behind it if a worker gives up
     uint32_t* __restrict__ err;
 };
 
@@ -58,12 +57,11 @@ inline FusedJob fused_job(const int32_t* row_ptr, const int32_t* col_idx, int32_
                           int64_t n_edges, const int32_t* seeds, int64_t n_seeds, int32_t M,
                           int32_t m, uint64_t rng_seed, int32_t* walks, int64_t cap_rows,
                           int64_t* rpe_off, int32_t* ids, uint16_t* cnt, const EdgeRecords& rec,
-                          uint32_t spin_limit, int64_t* h_total, int64_t* h_gave_up,
-                          uint32_t* err) {
+                          uint32_t spin_limit, int64_t* h_total, uint32_t* err) {
     return FusedJob{{row_ptr, col_idx, rec.data, rec.id_bits, rec.lo_bits, n_nodes, n_edges},
                     seeds, n_seeds, M, m, (uint32_t)(rng_seed & 0xFFFFFFFFull),
                     (uint32_t)(rng_seed >> 32), 65536u / (uint32_t)m + 1u, walks, cap_rows, rpe_off,
-                    ids, cnt, 0, 0, spin_limit, h_total, h_gave_up, err};
+                    ids, cnt, 0, 0, spin_limit, h_total, err};
 }
 
 // Writes -1 for all walks of seed number i, which is not a node.

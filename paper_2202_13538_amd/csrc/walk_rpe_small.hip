@@ -154,7 +154,7 @@ hipError_t launch_walk_rpe_small(hipStream_t stream, int max_lds_bytes, int n_cu
                                  uint32_t* err) {
     const FusedJob f = fused_job(row_ptr, col_idx, n_nodes, n_edges, seeds, n_seeds, M, m, rng_seed,
                                  walks, cap_rows, rpe_off, ids, cnt, EdgeRecords{}, spin_limit,
-                                 h_total, nullptr, err);
+                                 h_total, err);
     SmallScan* ss = static_cast<SmallScan*>(small_scan);
     const int n_key = fused_keys(M, m);
 #define SUREL_WRS_SIZE(E_)            \
