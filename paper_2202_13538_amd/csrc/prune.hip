@@ -26,7 +26,7 @@
 
 namespace surel {
 
-constexpr int kTableWords = kDirectWords + kHashedCollect;
+constexpr int kTableWords = kDirectWords + CollectTables::kHashed;
 // Rows of a wave's tile, the list of rows that wait for a look-up, and wavefronts of a workgroup,
 // which share the LDS tables (32 KB): as many as its LDS then holds.
 template <int LT>
@@ -76,7 +76,7 @@ struct MissList {
                 w[k] = (all[k] << 16) | (all[k] >> 16);
             }
             const bool small = DirectIndex<LT>::of(pair, &at);
-            const int32_t number = lookup_hashed<NW, kHashedCollect>(w, valid, cache + kDirectWords,
+            const int32_t number = lookup_hashed<NW, CollectTables>(w, valid, cache + kDirectWords,
                                                                      set, lane);
             if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
             if (valid) *place(item.w) = number;
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
             if constexpr (LT > 0) {
                 tile_numbers<LT>(tile, lane, first, misses, cache, set, place);
             } else {
-                rows_numbers<0, kHashedCollect>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
+                rows_numbers<0, CollectTables>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
                                                 nullptr, cache, set, place(first));
             }
             first += kRows;
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
         uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile);
         for (int t = lane; t < rest * L; t += kWave) tile16[t] = cnt[n_whole * kRows * L + t];
         wave_sync();
-        rows_numbers<LT, kHashedCollect>(rest, lane, L, tile16,
+        rows_numbers<LT, CollectTables>(rest, lane, L, tile16,
                                          reinterpret_cast<uint16_t*>(tile + C::kTileWords), cache, set,
                                          code + n_whole * kRows);
     }

@@ -120,10 +120,22 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
 // global table.)
 // Longer vectors have one cache with entries of as many words as they need.
 constexpr int kDirectWords = 4096;
-// Words of the hashed cache, a power of two.  (One or two rows in a hundred come here, some 400 to
-// 1,300 different vectors; one that finds its entry taken is a trip to memory every time.)
-constexpr int kHashedFused = 4096;    // 16 KB beside the rows of 16 waves
-constexpr int kHashedCollect = 4096;  // 16 KB beside their tiles and lists
+// kHashed: words of the hashed cache, a power of two.  (One or two rows in a hundred come here, some
+// 400 to 1,300 different vectors; one that finds its entry taken is a trip to memory every time.)
+// kLonely: see find_or_insert_shared.  Pruning 4 M rows of a table of 4,096 vectors that occur equally
+// often took 0.56 ms at m = 15 and 0.32 at m = 4 with a turn for every vector of a wave, 0.24 and 0.14
+// with 4 lonely ones (of 1,024 vectors 0.43 and 0.23 against 0.19 and 0.11); a walk's own table, 138 M
+// rows with some 3,500 vectors, takes 0.78 ms with both, and 0.82 if the loop ends after two turns
+// whatever they find.  The fused kernel has its waves at different places and little to gain: 31.6 M
+// rows of m = 9 with 28,498 vectors 2.18 ms with a turn for every vector, 2.21 with 4 lonely ones.
+struct FusedTables {
+    static constexpr int kHashed = 4096;  // 16 KB beside the rows of 16 waves
+    static constexpr int kLonely = kWave;
+};
+struct CollectTables {
+    static constexpr int kHashed = 4096;  // 16 KB beside their tiles and lists
+    static constexpr int kLonely = 4;
+};
 
 __device__ __forceinline__ void set_cache_clear(uint32_t* cache, int n_words, int tid, int n_threads) {
     for (int t = tid; t < n_words; t += n_threads) cache[t] = 0u;
@@ -156,16 +168,20 @@ struct DirectIndex {
 // nothing is known yet and every row is looked up there, most of them one of a handful of vectors,
 // and additions to one address are served one after the other, 13 ns each (350,000 of them, from
 // all waves' first tiles, were 3 ms of the pruning of 138 M rows).
-template <int NW>
+// A turn of the loop finds the lanes that share one vector; it ends after Tables::kLonely vectors
+// that no other lane shares, for then the rest are mostly such, and every lane left goes for itself.
+template <int NW, typename Tables>
 __device__ __forceinline__ int32_t find_or_insert_shared(const uint32_t (&w)[NW], uint32_t h,
                                                          bool pending, const VectorSet& set, int lane) {
     int leader = lane;
     bool open = pending;
-    for (uint64_t left = __ballot(open); left != 0ull; left = __ballot(open)) {
+    int lonely = 0;
+    for (uint64_t left = __ballot(open); left != 0ull && lonely < Tables::kLonely; left = __ballot(open)) {
         const int first = __builtin_ctzll(left);
         bool same = open;
 #pragma unroll
         for (int k = 0; k < NW; ++k) same = same && wave_bcast_u32(w[k], first) == w[k];
+        if constexpr (Tables::kLonely < kWave) lonely += __popcll(__ballot(same)) == 1 ? 1 : 0;
         if (same) leader = first, open = false;
     }
     int32_t number = -1;
@@ -180,13 +196,13 @@ __device__ __forceinline__ int32_t find_or_insert_shared(const uint32_t (&w)[NW]
 // not yet there, the comparison fails and the lane asks the global table, which is slower and
 // right; a valid entry never changes again.
 constexpr uint32_t kPackedValid = 0x80000000u;
-template <int NW, int kHashed>
+template <int NW, typename Tables>
 __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool valid, uint32_t* cache,
                                                  const VectorSet& set, int lane) {
     static_assert(NW >= 1 && NW <= 3, "packed cache entries hold up to three words");
     constexpr int EW = NW == 1 ? 2 : 4;
     const uint32_t hv = hash_vector<NW>(w);
-    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(kHashed / EW - 1)) * EW;
+    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(Tables::kHashed / EW - 1)) * EW;
     uint32_t e[4] = {0u, 0u, 0u, 0u};
     if constexpr (EW == 2) {
         const uint2 v = *reinterpret_cast<const uint2*>(entry);
@@ -201,7 +217,7 @@ __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool v
     const bool miss = valid && !hit;
     int32_t number = hit ? (int32_t)(e[0] & ~kPackedValid) : -1;
     if (__ballot(miss) != 0ull) {
-        const int32_t found = find_or_insert_shared<NW>(w, hv & set.slot_mask, miss, set, lane);
+        const int32_t found = find_or_insert_shared<NW, Tables>(w, hv & set.slot_mask, miss, set, lane);
         if (miss) number = found;
         if (miss && found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
 #pragma unroll
@@ -218,11 +234,11 @@ __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool v
 // (state, number, vector).  An entry is written once, by the lane that wins its state word, and is
 // valid for good after that (state, then vector and number, then "valid": LDS operations of a wave
 // take effect in order).
-template <int kHashed>
+template <typename Tables>
 __device__ __forceinline__ int32_t lookup_any(const uint32_t (&w)[kMaxVecWords], bool valid, int nw,
                                               uint32_t* cache, const VectorSet& set, int lane) {
     int entries = 64;
-    while (entries * 2 * (2 + nw) <= kDirectWords + kHashed) entries *= 2;
+    while (entries * 2 * (2 + nw) <= kDirectWords + Tables::kHashed) entries *= 2;
     const uint32_t hv = hash_vector<kMaxVecWords>(w);
     uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(entries - 1)) * (2 + nw);
     bool hit = valid && entry[0] == 2u;
@@ -232,7 +248,7 @@ __device__ __forceinline__ int32_t lookup_any(const uint32_t (&w)[kMaxVecWords],
     const bool miss = valid && !hit;
     int32_t number = hit ? (int32_t)entry[1] : -1;
     if (__ballot(miss) != 0ull) {
-        const int32_t found = find_or_insert_shared<kMaxVecWords>(w, hv & set.slot_mask, miss, set, lane);
+        const int32_t found = find_or_insert_shared<kMaxVecWords, Tables>(w, hv & set.slot_mask, miss, set, lane);
         if (miss) number = found;
         if (miss && found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
 #pragma unroll
@@ -267,7 +283,7 @@ __device__ __forceinline__ void row_pairs(const uint32_t* words, int odd, int n_
 
 // Looks the rows misses[0 .. n_miss) of the rows at cnt16 up (words, odd, n_words as for row_pairs)
 // and enters what belongs there into the direct table.
-template <int LT, int kHashed>
+template <int LT, typename Tables>
 __device__ __forceinline__ void resolve_misses(const uint16_t* misses, int n_miss, int lane,
                                                const uint32_t* words, int odd, int n_words,
                                                uint32_t* cache, const VectorSet& set,
@@ -281,7 +297,7 @@ __device__ __forceinline__ void resolve_misses(const uint16_t* misses, int n_mis
         const bool small = DirectIndex<LT>::of(pair, &at);
 #pragma unroll
         for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
-        const int32_t number = lookup_hashed<NW, kHashed>(w, valid, cache + kDirectWords, set, lane);
+        const int32_t number = lookup_hashed<NW, Tables>(w, valid, cache + kDirectWords, set, lane);
         if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
         if (valid) code[t] = number;
     }
@@ -301,7 +317,7 @@ __device__ __forceinline__ void append_misses(uint16_t* misses, int& n_miss, boo
 // in the direct table are put on a list (misses, n places in LDS of the wave's own) and looked up
 // together afterwards, so that few lanes wait for few.  LT = m + 1 at compile time for 2 .. 6, 0 =
 // any.
-template <int LT, int kHashed>
+template <int LT, typename Tables>
 __device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint16_t* cnt16,
                                              uint16_t* misses, uint32_t* cache, const VectorSet& set,
                                              int32_t* __restrict__ code) {
@@ -315,7 +331,7 @@ __device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint1
             row_pairs<kMaxVecWords>(words, odd, n_words, min(t, n - 1), L, pair);
 #pragma unroll
             for (int k = 0; k < kMaxVecWords; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
-            const int32_t number = lookup_any<kHashed>(w, t < n, (L + 1) / 2, cache, set, lane);
+            const int32_t number = lookup_any<Tables>(w, t < n, (L + 1) / 2, cache, set, lane);
             if (t < n) code[t] = number;
         }
     } else {
@@ -332,21 +348,21 @@ __device__ __forceinline__ void rows_numbers(int n, int lane, int L, const uint1
             append_misses(misses, n_miss, t < n && !hit, t);
         }
         wave_sync();
-        resolve_misses<LT, kHashed>(misses, n_miss, lane, words, odd, n_words, cache, set, code);
+        resolve_misses<LT, Tables>(misses, n_miss, lane, words, odd, n_words, cache, set, code);
         wave_sync();
     }
 }
-template <int kHashed>
+template <typename Tables>
 __device__ __forceinline__ void rows_numbers_any(int n, int lane, int L, const uint16_t* cnt16,
                                                  uint16_t* misses, uint32_t* cache,
                                                  const VectorSet& set, int32_t* __restrict__ code) {
     switch (L) {
-        case 2: rows_numbers<2, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 3: rows_numbers<3, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 4: rows_numbers<4, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 5: rows_numbers<5, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
-        case 6: rows_numbers<6, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
-        default: rows_numbers<0, kHashed>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 2: rows_numbers<2, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 3: rows_numbers<3, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 4: rows_numbers<4, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 5: rows_numbers<5, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
+        case 6: rows_numbers<6, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
+        default: rows_numbers<0, Tables>(n, lane, L, cnt16, misses, cache, set, code); break;
     }
 }
 

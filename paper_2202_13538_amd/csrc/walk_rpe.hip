@@ -35,7 +35,7 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
     extern __shared__ __align__(16) uint32_t lds32[];
     __shared__ unsigned long long chunk;
     __shared__ bool scans;
-    __shared__ __align__(16) uint32_t set_cache[kCodes ? kDirectWords + kHashedFused : 1];
+    __shared__ __align__(16) uint32_t set_cache[kCodes ? kDirectWords + FusedTables::kHashed : 1];
 
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
         scans = first == 0;
         chunk = (first + n_waves) << 32 | first;
     }
-    if constexpr (kCodes) set_cache_clear(set_cache, kDirectWords + kHashedFused, (int)threadIdx.x, (int)blockDim.x);
+    if constexpr (kCodes) set_cache_clear(set_cache, kDirectWords + FusedTables::kHashed, (int)threadIdx.x, (int)blockDim.x);
     __syncthreads();                     // the only workgroup-wide barrier of the kernel
     const LookbackScratch scr = lookback_scratch(f.n_seeds);
     int64_t* base = lookback_base(lb);
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
                         [&](int row0, int n, const uint16_t* cnt16, uint32_t* free_words) {
                             // every row's number in the set of distinct vectors
                             if constexpr (kCodes)
-                                rows_numbers_any<kHashedFused>(n, lane, L, cnt16,
+                                rows_numbers_any<FusedTables>(n, lane, L, cnt16,
                                                  reinterpret_cast<uint16_t*>(free_words), set_cache, set,
                                                  code + off + row0);
                         });
