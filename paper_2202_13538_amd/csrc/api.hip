@@ -566,7 +566,7 @@ static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m
         if (int rc = judge_total(true, cap_rows, n_rows)) return rc;  // not all rows have codes
     }
     if (n_T > ps.cap_T) return SUREL_E_CAPACITY;
-    if (n_T > surel::prune_rank_most(ps.cap_T)) {
+    if (n_T > surel::prune_rank_most(ps.cap_T, m)) {
         if (surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_T, d_code) !=
             hipSuccess)
             return SUREL_E_HIP;

@@ -149,9 +149,9 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
 // = their number; *h_stalled (host memory) = 1 if a wait ran out while they were collected (else it
 // stays); then empties the set.  d_rows (optional): where the number of rows stands on
 // the device; with more than cap_rows of them the codes stay as they are.  With more than
-// prune_rank_most(cap_T) distinct vectors T and code stay as they are, and launch_prune_order_many
+// prune_rank_most(cap_T, m) distinct vectors T and code stay as they are, and launch_prune_order_many
 // has to be called with the number.
-int64_t prune_rank_most(int64_t cap_T);
+int64_t prune_rank_most(int64_t cap_T, int32_t m);
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                               int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
                               int32_t* code, int64_t* h_n_T, int64_t* h_stalled);

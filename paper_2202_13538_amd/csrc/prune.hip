@@ -9,9 +9,9 @@
 //            it is new (prune_set.h); the vector's number in the set goes to code[row].  A slot is
 //            64 bytes (state, number, vector), aligned, so one cache line holds all of it; only a
 //            slot that does not look full yet is touched with atomics.
-//   rank     every vector's place in the sorted array: up to kRankMost vectors are compared all
-//            with all (a few thousand, usually: one short launch that needs no count on the host),
-//            more are sorted with a bitonic network in global memory.  T[place] = vector.
+//   rank     every vector's place in the sorted array: up to prune_rank_most vectors are compared
+//            all with all (a few thousand, usually: one short launch that needs no count on the
+//            host), more are sorted with a bitonic network in global memory.  T[place] = vector.
 //   codes    code[row] = place of the row's vector.
 //   clean    the slots that were used are emptied again, by the list of the set's members (a
 //            memset of the table, and a pass over it that gathers the full slots, were 95 us of a
@@ -20,6 +20,8 @@
 // again; the writer needs nothing from the poller (inside one wavefront the writer's branch
 // runs to its end before the next poll), so the poll ends; it is bounded by the spin limit
 // all the same.
+#include <cmath>
+
 #include "device_util.h"
 #include "kernels.h"
 #include "prune_set.h"
@@ -210,8 +212,16 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
     }
 }
 
-// Vectors that are compared all with all; beyond, n log^2 n steps of a sort are fewer.
-constexpr int64_t kRankMost = 65536;
+// Vectors are compared all with all up to so many word comparisons (n^2 times the words of a
+// vector): about 0.09 ns a thousand, so 0.45 ms, which is what the sort's launches take for this many
+// vectors (one compare-exchange launch of 3 to 4 us for every step, 105 to 136 of them).  The whole
+// pruning of 4 M rows, all pairs against the sort, in us (differences are the ranking's):
+//   vectors          16,384        32,768         65,536
+//   1 word         256 / 586     357 / 654      662 /   813
+//   3 words        426 / 712     649 / 789    1,463 /   933
+//   8 words        779 / 954   1,353 / 1,046  3,528 / 1,178
+// so the line lies at 70,710, 40,824 and 25,000 vectors of 1, 3 and 8 words.
+constexpr int64_t kRankWords = 5'000'000'000;
 constexpr int kRankTile = 256;
 constexpr int kRankBlocks = 1024;
 
@@ -466,12 +476,17 @@ static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, i
                        ps.counters, n_known, most, n_rows, d_rows, cap_rows, code);
 }
 
-int64_t prune_rank_most(int64_t cap_T) { return cap_T < kRankMost ? cap_T : kRankMost; }
+int64_t prune_rank_most(int64_t cap_T, int32_t m) {
+    const int64_t words = (m + 2) / 2;
+    int64_t n = (int64_t)std::sqrt((double)kRankWords / (double)words);
+    while (n * n * words > kRankWords) --n;
+    return cap_T < n ? cap_T : n;
+}
 
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                               int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
                               int32_t* code, int64_t* h_n_T, int64_t* h_stalled) {
-    const int64_t most = prune_rank_most(ps.cap_T);
+    const int64_t most = prune_rank_most(ps.cap_T, m);
     const int L = m + 1;
     switch ((L + 1) / 2) {
 #define SUREL_RANK_CASE(NW_)                                                                     \

@@ -537,6 +537,45 @@ def test_prune_capacity_and_degenerate_tables(ctx):
         assert np.array_equal(code.cpu().numpy(), w_code)
 
 
+@pytest.mark.parametrize("L,n_T", [(2, 70_710), (2, 70_711), (5, 40_824), (5, 40_825), (16, 25_000),
+                                   (16, 25_001), (16, 1 << 15), (9, 100_003)])
+def test_prune_of_many_distinct_vectors(ctx, L, n_T):
+    # on both sides of the line from which the vectors are sorted instead of compared all with all,
+    # a list that needs no padding, and more than the codes of 16 bits could tell apart; vectors
+    # occur once, twice or often, neighbours in a wave are mostly different
+    rng = np.random.default_rng(n_T)
+    vectors = rng.integers(0, 4, size=(n_T, L)).astype(np.uint16)
+    number = rng.permutation(n_T)
+    vectors[:, 0], vectors[:, -1] = number % 400, number // 400
+    rows = np.concatenate([np.arange(n_T), rng.integers(0, n_T, size=n_T // 2),
+                           rng.integers(0, 50, size=3001)])
+    cnt = vectors[rng.permutation(rows)]
+    want_T, want_code = oracle.prune_rpe(cnt)
+    assert want_T.shape[0] == n_T
+    d_cnt = dev(cnt.view(np.int16)).view(torch.uint16)
+    for cap_T in (n_T, 1 << 18):
+        T, code = binding.prune_rpe(ctx, d_cnt, cap_T=cap_T)
+        assert ctx.check() == 0
+        assert np.array_equal(host_u16(T), want_T) and np.array_equal(code.cpu().numpy(), want_code)
+
+
+def test_one_call_rpe_ids_of_many_distinct_vectors(ctx):
+    # every node is visited several times at every step, so hardly two rows are the same
+    wl = synth.Workload("t", "rmat", 256, 5000, 0.0, 128, 15, 0, 2, "uniform", graph_seed=3)
+    rp, ci = synth.make_graph(wl)
+    seeds = np.arange(wl.n_nodes, dtype=np.int32)
+    w = oracle.sample_walks(rp, ci, seeds, wl.M, wl.m, 6)
+    t_off, t_ids, t_cnt = oracle.build_rpe(w)
+    want_T, want_code = oracle.prune_rpe(t_cnt)
+    assert want_T.shape[0] > 25_000
+    _, off, ids, cnt, code, T = binding.sample_walks_rpe_ids(ctx, dev(rp), dev(ci), dev(seeds), wl.M,
+                                                             wl.m, 6, cap_T=1 << 17)
+    assert ctx.check() == 0
+    assert np.array_equal(ids.cpu().numpy(), t_ids) and np.array_equal(off.cpu().numpy(), t_off)
+    assert np.array_equal(host_u16(T).reshape(want_T.shape), want_T)
+    assert np.array_equal(code.cpu().numpy(), want_code)
+
+
 def test_query_rpe_ids_problems_are_flagged(ctx):
     wl = synth.Workload("t", "rmat", 256, 900, 0.0, 20, 3, 0, 2, "uniform", graph_seed=3)
     rp, ci = synth.make_graph(wl)
