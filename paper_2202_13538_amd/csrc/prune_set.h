@@ -123,7 +123,7 @@ constexpr int kDirectWords = 4096;
 // kHashed: words of the hashed cache, a power of two.  (One or two rows in a hundred come here, some
 // 400 to 1,300 different vectors; one that finds its entry taken is a trip to memory every time.)
 // kLonely: see find_or_insert_shared.  Pruning 4 M rows of a table of 4,096 vectors that occur equally
-// often took 0.56 ms at m = 15 and 0.32 at m = 4 with a turn for every vector of a wave, 0.24 and 0.14
+// often took 0.56 ms at m = 14 and 0.32 at m = 4 with a turn for every vector of a wave, 0.24 and 0.14
 // with 4 lonely ones (of 1,024 vectors 0.43 and 0.23 against 0.19 and 0.11); a walk's own table, 138 M
 // rows with some 3,500 vectors, takes 0.78 ms with both, and 0.82 if the loop ends after two turns
 // whatever they find.  The fused kernel has its waves at different places and little to gain: 31.6 M

@@ -12,8 +12,8 @@
 // pull a whole cache line for a few bytes, which is what bounds this kernel.  When the job
 // is large next to the graph, a small kernel first expands the CSR into one record per edge
 // entry, (neighbour id, its row start, its degree), so that every step after the first is a
-// single gather: one 64-bit word for large graphs, 16 bytes otherwise (walk_core.h).  All
-// forms make exactly the same walks.
+// single gather: one 64-bit word, or 16 bytes where ids and row starts leave the degree too few of
+// its bits (walk_core.h).  All forms make exactly the same walks.
 //
 // Optionally the kernel also reports |V_u|, the number of distinct nodes of each seed's
 // walks (Algorithm 1: V_u = set(W_u)), through an LDS hash set fed while the walkers move.
@@ -69,14 +69,18 @@ __device__ __forceinline__ void row_ends(const int32_t* __restrict__ row_ptr, ui
 // The record of every CSR entry e (layouts in walk_core.h): the neighbour col_idx[e], the start
 // of its row and its degree; an entry that names no node, or whose row is malformed, gets the
 // layout's "bad entry" id (the walker will stay in place and flag it).
-// kGroups: the rows are looked up in groups (above) instead of row_ptr; kStream: entries and records
-// go past the caches.  What bounds this kernel is the random look-up: a 128-byte line each, 56 G/s
-// from memory where it misses the L2 and 260 G/s from an L2 with nothing else to do.  The 11.6 MB of row_ptr of a 2.9M-node graph miss a 4 MB L2 most of the time, its groups
-// are 3.9 MB: 60 M entries in 508 us, 693 with two loads from row_ptr an entry (20 M entries on 1M
-// nodes 141, before 166).  Groups of 28 rows in 32 bytes are two requests: 569 and 158 us.
+// kGroups: the rows are looked up in groups (above) instead of row_ptr, see rows_in_groups.  Entries
+// and records go past the caches, which a pass's outputs have filled by then: 20 M entries on 1M
+// nodes 137 us, 161 through the caches, 2.6 M on 235,000 22 and 24, 42 M on 524,288 249 and 286.
+// (Only where nothing else had been written since the launch before were they faster through the
+// caches, up to 24 M entries.)
+// What bounds this kernel is the random look-up: a 128-byte line each, 56 G/s from memory where it
+// misses the L2 and 260 G/s from an L2 with nothing else to do.  The 11.6 MB of row_ptr of a
+// 2.9M-node graph miss a 4 MB L2 most of the time, its groups are 3.9 MB: 60 M entries in 508 us,
+// 693 with two loads from row_ptr an entry.  Groups of 28 rows in 32 bytes are two requests: 569 us.
 constexpr int kRecordThreads = 256;
 constexpr int kRecordItems = 4;  // entries of a thread, all their look-ups in flight
-template <int kRec, bool kGroups, bool kStream>
+template <int kRec, bool kGroups>
 __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n_nodes,
     int64_t n_edges, int id_bits, int lo_bits, const uint4* __restrict__ groups,
@@ -86,8 +90,7 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
     bool node[kRecordItems];
 #pragma unroll
     for (int u = 0; u < kRecordItems; ++u) {
-        const int32_t* from = col_idx + min(e0 + u * kRecordThreads, n_edges - 1);
-        t[u] = (uint32_t)(kStream ? __builtin_nontemporal_load(from) : *from);
+        t[u] = (uint32_t)__builtin_nontemporal_load(col_idx + min(e0 + u * kRecordThreads, n_edges - 1));
     }
 #pragma unroll
     for (int u = 0; u < kRecordItems; ++u) node[u] = t[u] < (uint32_t)n_nodes;
@@ -141,12 +144,7 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
                 r = (unsigned long long)t[u] | ((unsigned long long)(uint32_t)lo[u] << id_bits) |
                     ((unsigned long long)deg << (id_bits + lo_bits));
             }
-            unsigned long long* to = static_cast<unsigned long long*>(rec) + e;
-            if (kStream) {
-                __builtin_nontemporal_store(r, to);
-            } else {
-                *to = r;
-            }
+            __builtin_nontemporal_store(r, static_cast<unsigned long long*>(rec) + e);
         }
     }
 }
@@ -239,14 +237,21 @@ EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     return plan;
 }
 
-// Whether the rows are worth grouping: where row_ptr does not stay in an L2 beside the streams, and
-// where most entries name a node whose degree fits a byte.  (On 524,288 nodes with 80 entries each
-// one load of both ends and streams past the caches: 42 M entries in 244 us, 283 with ordinary
-// streams, 300 with two loads.  On 235,000 nodes, 2.6 M entries, everything stays in the caches: 21
-// us either way.)
-constexpr int32_t kManyNodes = 1 << 18;
+// Whether the rows are worth grouping: where row_ptr outgrows a 4 MB L2 so far (5 MB and more) that
+// the hot rows of a graph with uneven degrees do not stay there either, and where most entries name
+// a node whose degree fits a byte.  Measured with cold caches, as the pass before leaves them, us,
+// rows from row_ptr / grouped (the launch that groups them among it):
+//                               entries a node, exponent of the degrees
+//   nodes          4, 2.3        20, 2.1        20, 2.5        28, 2.3       20, even
+//     700,000     23 /  28       90 / 108       90 / 100      123 / 145       90 /  95
+//   1,000,000     31 /  36      135 / 153      136 / 142      188 / 205      136 / 132
+//   1,200,000     39 /  41      172 / 184      175 / 168      240 / 248
+//   1,500,000     50 /  49      222 / 238      228 / 209      312 / 321      235 / 197
+//   2,000,000     75 /  63      327 / 342      369 / 291      491 / 459
+//   2,900,000    133 /  94      596 / 540      682 / 465      916 / 730      717 / 392
+constexpr int32_t kGroupNodes = 5 << 18;
 static bool rows_in_groups(int32_t n_nodes, int64_t n_edges) {
-    return n_nodes >= kManyNodes && n_edges <= 32 * (int64_t)n_nodes;
+    return n_nodes >= kGroupNodes && n_edges <= 32 * (int64_t)n_nodes;
 }
 
 static size_t record_array_bytes(const EdgeRecords& plan, int64_t n_edges) {
@@ -294,12 +299,9 @@ hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const
         row_group_kernel<<<dim3((unsigned)((n_groups + 63) / 64)), dim3(64), 0, stream>>>(
             row_ptr, n_nodes, n_edges, groups);
     }
-    const bool big = n_nodes >= kManyNodes;
-    const auto kernel =
-        rec.format == kRecPacked
-            ? (groups ? edge_record_kernel<kRecPacked, true, true>
-                      : big ? edge_record_kernel<kRecPacked, false, true> : edge_record_kernel<kRecPacked, false, false>)
-            : (groups ? edge_record_kernel<kRecWide, true, true> : edge_record_kernel<kRecWide, false, false>);
+    const auto kernel = rec.format == kRecPacked
+                            ? (groups ? edge_record_kernel<kRecPacked, true> : edge_record_kernel<kRecPacked, false>)
+                            : (groups ? edge_record_kernel<kRecWide, true> : edge_record_kernel<kRecWide, false>);
     kernel<<<grid, block, 0, stream>>>(row_ptr, col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits,
                                        groups, data);
     return hipGetLastError();

@@ -1036,9 +1036,11 @@ def test_one_call_rpe_ids_capacity(ctx):
 
 
 @pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
-                                           ((1 << 18) + 11, False), (1 << 18, True)])
+                                           ((1 << 18) + 11, False), (1 << 18, True),
+                                           ((5 << 18) - 1, False), (5 << 18, False),
+                                           ((5 << 18) + 11, False), (5 << 18, True)])
 def test_edge_records_of_grouped_rows(ctx, n_nodes, malformed):
-    # from 2^18 nodes on rows are looked up in groups of 12: degrees at both sides of a byte's
+    # from 5 * 2^18 nodes on rows are looked up in groups of 12: degrees at both sides of a byte's
     # range, an empty row, a hub, and rows behind them in their group and in the last, short one
     rng = np.random.default_rng(n_nodes)
     deg = rng.integers(0, 3, size=n_nodes)
@@ -1052,7 +1054,7 @@ def test_edge_records_of_grouped_rows(ctx, n_nodes, malformed):
                            for at in (0, 11, 24, 12 * 2000 + 5, n_nodes - 9)])
     ci = rng.integers(0, n_nodes, size=int(rp[-1]))
     ci[::2] = rng.choice(near, size=ci[::2].size)
-    seeds = rng.integers(0, n_nodes, size=40_000).astype(np.int32)
+    seeds = rng.integers(0, n_nodes, size=40_000 if n_nodes < 1 << 19 else 60_000).astype(np.int32)
     seeds[::4] = rng.choice(near, size=seeds[::4].size)
     M, m = 60, 3
     rp, ci = rp.astype(np.int32), ci.astype(np.int32)
