@@ -310,24 +310,26 @@ def test_rpe_capacity_overflow_is_reported_and_nothing_is_written_past_it(ctx):
     assert np.array_equal(cnt_h[:last], want_cnt[:last])
 
 
-def test_fused_bad_seed_capacity_and_count_only(ctx):
+@pytest.mark.parametrize("n_seeds", [64, 6000])
+def test_fused_bad_seed_capacity_and_count_only(ctx, n_seeds):
+    # 64 seeds take one launch without roles, 6,000 the persistent kernel
     wl = synth.Workload("t", "rmat", 256, 900, 0.0, 20, 3, 0, 2, "uniform", graph_seed=3)
     rp, ci = synth.make_graph(wl)
     M, m, L = wl.M, wl.m, wl.m + 1
-    seeds = np.arange(64, dtype=np.int32)
-    seeds[7] = 1000                                          # not a node
-    seeds[20] = -1
-    good = np.ones(64, dtype=bool)
-    good[[7, 20]] = False
+    seeds = np.arange(n_seeds, dtype=np.int32) % wl.n_nodes
+    bad = [7, 20] + ([4500, n_seeds - 1] if n_seeds > 4500 else [])
+    seeds[bad] = ([1000, -1] * 2)[:len(bad)]                 # not nodes
+    good = np.ones(n_seeds, dtype=bool)
+    good[bad] = False
     w = oracle.sample_walks(rp, ci, seeds[good], M, m, 3)
     want_off, want_ids, want_cnt = oracle.build_rpe(w)
-    sizes = np.zeros(64, dtype=np.int64)
+    sizes = np.zeros(n_seeds, dtype=np.int64)
     sizes[good] = np.diff(want_off)
     full_off = np.concatenate([[0], np.cumsum(sizes)])
     total = int(full_off[-1])
     d_rp, d_ci, d_seeds = dev(rp), dev(ci), dev(seeds)
-    walks = torch.empty((64, M, L), dtype=torch.int32, device="cuda")
-    off = torch.empty(65, dtype=torch.int64, device="cuda")
+    walks = torch.empty((n_seeds, M, L), dtype=torch.int32, device="cuda")
+    off = torch.empty(n_seeds + 1, dtype=torch.int64, device="cuda")
     # offsets and total only
     rc, rows = binding.sample_walks_rpe_raw(ctx, d_rp, d_ci, d_seeds, M, m, 3, walks, 0, off,
                                             None, None)
@@ -335,7 +337,7 @@ def test_fused_bad_seed_capacity_and_count_only(ctx):
     assert ctx.check() == binding.DEV_BAD_SEED
     assert np.array_equal(off.cpu().numpy(), full_off)
     wh = walks.cpu().numpy()
-    assert (wh[7] == -1).all() and (wh[20] == -1).all() and np.array_equal(wh[good], w)
+    assert (wh[bad] == -1).all() and np.array_equal(wh[good], w)
     # a table that is too small: complete offsets, nothing written at or past cap_rows
     cap = total // 2
     ids = torch.full((total,), -7, dtype=torch.int32, device="cuda")
@@ -378,14 +380,16 @@ def test_fused_kernel_seed_counts_around_its_group_and_window_sizes(ctx, M, m):
         assert torch.equal(f_cnt.view(torch.int16), cnt.view(torch.int16)), f"counts differ at {n}"
 
 
-def test_one_pass_captured_in_a_graph_replays_to_the_same_bytes():
+@pytest.mark.parametrize("n_seeds,n_queries", [(1500, 700), (6000, 5000)])
+def test_one_pass_captured_in_a_graph_replays_to_the_same_bytes(n_seeds, n_queries):
     # with no row totals asked for, the calls only enqueue kernels: a pass can be captured once
-    # and replayed; every replay (with other work on the stream in between) gives the eager bytes
+    # and replayed; every replay (with other work on the stream in between) gives the eager bytes.
+    # Few seeds and queries take one launch each, more take the persistent kernel and two launches
     wl = synth.Workload("t", "rmat", 4096, 30000, 0.0, 50, 4, 0, 2, "uniform", graph_seed=9)
     rp, ci = synth.make_graph(wl)
     rng = np.random.default_rng(4)
-    seeds = rng.integers(0, wl.n_nodes, size=1500).astype(np.int32)
-    queries = rng.integers(0, seeds.size, size=(700, 2)).astype(np.int32)
+    seeds = rng.integers(0, wl.n_nodes, size=n_seeds).astype(np.int32)
+    queries = rng.integers(0, seeds.size, size=(n_queries, 2)).astype(np.int32)
     M, m, L, S = wl.M, wl.m, wl.m + 1, seeds.size
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
@@ -740,19 +744,20 @@ def test_fill_calls_with_offsets_of_something_else_are_flagged(ctx):
     assert np.array_equal(got[:lo], table[1][:lo]) and np.array_equal(got[hi:], table[1][int(table[0][6]):])
 
 
-def test_bad_seeds_give_the_same_table_on_both_paths(ctx):
+@pytest.mark.parametrize("n_seeds", [50, 5000])
+def test_bad_seeds_give_the_same_table_on_both_paths(ctx, n_seeds):
     # a seed that is not a node gets walks of -1 and no rows, whether the table is built by the
     # fused kernel or by surel_build_rpe over those walks
     wl = synth.Workload("t", "rmat", 256, 900, 0.0, 20, 3, 0, 2, "uniform", graph_seed=3)
     rp, ci = synth.make_graph(wl)
-    seeds = np.arange(50, dtype=np.int32)
-    seeds[[0, 17, 49]] = [-1, 256, 1 << 30]
-    good = np.ones(50, dtype=bool)
-    good[[0, 17, 49]] = False
+    seeds = np.arange(n_seeds, dtype=np.int32) % wl.n_nodes
+    seeds[[0, 17, n_seeds - 1]] = [-1, 256, 1 << 30]
+    good = np.ones(n_seeds, dtype=bool)
+    good[[0, 17, n_seeds - 1]] = False
     d_rp, d_ci, d_seeds = dev(rp), dev(ci), dev(seeds)
     f_walks, f_off, f_ids, f_cnt = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, wl.M, wl.m, 2)
     assert ctx.check() == binding.DEV_BAD_SEED
-    for sizes in (None, torch.empty(50, dtype=torch.int32, device="cuda")):
+    for sizes in (None, torch.empty(n_seeds, dtype=torch.int32, device="cuda")):
         walks = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, wl.M, wl.m, 2, set_sizes=sizes)
         assert ctx.check() == binding.DEV_BAD_SEED
         off, ids, cnt = binding.build_rpe(ctx, walks, wl.n_nodes, set_sizes=sizes)
@@ -761,7 +766,7 @@ def test_bad_seeds_give_the_same_table_on_both_paths(ctx):
         assert torch.equal(cnt.view(torch.int16), f_cnt.view(torch.int16))
     w = oracle.sample_walks(rp, ci, seeds[good], wl.M, wl.m, 2)
     t_off, t_ids, t_cnt = oracle.build_rpe(w)
-    sizes_h = np.zeros(50, dtype=np.int64)
+    sizes_h = np.zeros(n_seeds, dtype=np.int64)
     sizes_h[good] = np.diff(t_off)
     assert np.array_equal(f_off.cpu().numpy(), np.concatenate([[0], np.cumsum(sizes_h)]))
     assert np.array_equal(f_ids.cpu().numpy(), t_ids) and np.array_equal(host_u16(f_cnt), t_cnt)
@@ -955,8 +960,8 @@ def hub_and_ring(n_leaves):
 
 
 def test_packed_edge_records_and_a_degree_beyond_their_field(ctx):
-    # from 2^22 edge entries on, the walks read 8-byte neighbour records; the hub's degree
-    # (1.2 M) does not fit the 20 bits the record leaves for it and is taken from the CSR
+    # the walks read 8-byte neighbour records; the hub's degree (1.2 M) does not fit the 20 bits
+    # the record leaves for it and is taken from the CSR
     n_leaves = 1_200_000
     rp, ci = hub_and_ring(n_leaves)
     assert ci.size >= 1 << 22 and np.all(np.diff(rp) > 0)
@@ -987,6 +992,86 @@ def test_packed_edge_records_and_a_degree_beyond_their_field(ctx):
     assert ((got >= 0) & (got <= n_leaves)).all()
     stay = (got[:, :, 1] == 7)
     assert 0.2 < stay.mean() < 0.5                         # one of node 7's three entries
+
+
+def random_graph_on_the_gpu(n_nodes, n_edges, active, seed):
+    """CSR (row_ptr, col_idx) on the GPU: n_edges entries over `active` nodes spread over all ids."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    nodes = torch.randint(0, n_nodes, (active,), device="cuda", generator=g).unique()
+    nodes[-1] = n_nodes - 1
+    nodes = nodes.unique()
+    deg = torch.zeros(n_nodes, dtype=torch.int64, device="cuda")
+    deg[nodes] = n_edges // nodes.numel()
+    deg[nodes[0]] += n_edges - int(deg.sum())
+    rp = torch.zeros(n_nodes + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(deg, 0, out=rp[1:])
+    ci = nodes[torch.randint(0, nodes.numel(), (n_edges,), device="cuda", generator=g)]
+    return rp.int(), ci.int(), nodes.int()
+
+
+@pytest.mark.parametrize("n_nodes,n_edges", [(1 << 27, 1 << 24), (1 << 23, (1 << 28) + 4321)])
+def test_wide_edge_records(ctx, n_nodes, n_edges):
+    # ids and row starts of 53 bits leave a packed record 11 bits for the degree, so the 16-byte
+    # layout is used: few entries a node (rows looked up in groups), then many (from row_ptr)
+    d_rp, d_ci, nodes = random_graph_on_the_gpu(n_nodes, n_edges, 1 << 18, n_nodes)
+    rng = np.random.default_rng(1)
+    M, m = 128, 15
+    S = 4 * n_edges // (M * (m - 1)) + 5                   # enough steps to make the records
+    d_seeds = nodes[torch.randint(0, nodes.numel(), (S,), device="cuda")].contiguous()
+    lonely = S // 3
+    d_seeds[lonely] = 12345 if int(d_rp[12346]) == int(d_rp[12345]) else 12346    # a node without neighbours
+    walks = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 7)
+    assert ctx.check() == 0
+    # the walks of the same seeds without records (too few steps for them), and the oracle's
+    part = S // 2
+    for at in (0, S - part):
+        assert torch.equal(binding.sample_walks(ctx, d_rp, d_ci, d_seeds[at:at + part].contiguous(), M,
+                                                m, 7), walks[at:at + part])
+    some = np.unique(np.r_[rng.integers(0, S, size=200), lonely, S - 1])
+    rp, ci = d_rp.cpu().numpy(), d_ci.cpu().numpy()
+    pick = torch.from_numpy(some).cuda()
+    assert np.array_equal(walks[pick].cpu().numpy(),
+                          oracle.sample_walks(rp, ci, d_seeds[pick].cpu().numpy(), M, m, 7))
+    del rp, ci, walks
+    # entries that name no node: flagged on both paths, the same walks
+    d_bad = d_ci.clone()
+    d_bad[::1001] = n_nodes
+    a = binding.sample_walks(ctx, d_rp, d_bad, d_seeds, M, m, 7)
+    assert ctx.check() == binding.DEV_BAD_GRAPH
+    b = binding.sample_walks(ctx, d_rp, d_bad, d_seeds[:part].contiguous(), M, m, 7)
+    assert ctx.check() == binding.DEV_BAD_GRAPH
+    assert torch.equal(a[:part], b)
+
+
+@pytest.mark.parametrize("M,m", [(128, 15), (100, 4), (50, 4), (200, 3)])
+def test_fused_kernels_over_wide_edge_records(ctx, M, m):
+    # the table (with counts, and with RPE-IDs) of the fused kernel against the two calls
+    n_nodes, n_edges, L = 1 << 27, 1 << 24, m + 1
+    d_rp, d_ci, nodes = random_graph_on_the_gpu(n_nodes, n_edges, 1 << 14, 3)
+    S = 4 * n_edges // (M * (m - 1)) + 5
+    d_seeds = nodes[torch.randint(0, nodes.numel(), (S,), device="cuda")].contiguous()
+    d_seeds[S // 2] = n_nodes                              # not a node
+    walks = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 7)
+    assert ctx.check() == binding.DEV_BAD_SEED
+    off, ids, cnt = binding.build_rpe(ctx, walks, n_nodes)
+    assert ctx.check() == binding.DEV_BAD_WALK
+    f_walks, f_off, f_ids, f_cnt = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 7)
+    assert ctx.check() == binding.DEV_BAD_SEED
+    assert torch.equal(f_walks, walks) and torch.equal(f_off, off) and torch.equal(f_ids, ids)
+    assert torch.equal(f_cnt.view(torch.int16), cnt.view(torch.int16))
+    del f_ids, f_cnt
+    T, code = binding.prune_rpe(ctx, cnt, cap_T=1 << 22)
+    assert ctx.check() == 0
+    total = ids.numel()
+    i_ids, i_code = (torch.empty(total, dtype=torch.int32, device="cuda") for _ in range(2))
+    i_T = torch.zeros((1 << 22, L), dtype=torch.int16, device="cuda").view(torch.uint16)
+    rc, rows, n_T = binding.sample_walks_rpe_ids_raw(ctx, d_rp, d_ci, d_seeds, M, m, 7, f_walks, total,
+                                                     off, i_ids, None, i_code, 1 << 22, i_T)
+    assert rc == binding.OK and rows == total and n_T == T.shape[0]
+    assert ctx.check() == binding.DEV_BAD_SEED
+    assert torch.equal(f_walks, walks) and torch.equal(i_ids, ids) and torch.equal(i_code, code)
+    assert torch.equal(i_T[:n_T].view(torch.int16), T.view(torch.int16))
 
 
 def test_one_call_rpe_ids_capacity(ctx):

@@ -115,13 +115,15 @@ def test_noalloc_join_at_its_largest_size_and_device_memory_stays_as_it_was():
     ctx.close()
 
 
-def test_noalloc_join_under_graph_capture():
+@pytest.mark.parametrize("n_queries", [3001, 5003])
+def test_noalloc_join_under_graph_capture(n_queries):
     # what the entry point is for: captured once (no allocation, no memset, no wait inside),
-    # replayed with other work on the stream in between, every replay against the eager bytes
+    # replayed with other work on the stream in between, every replay against the eager bytes; few
+    # queries take one launch, more take counting, scan and filling
     wl = synth.Workload("t", "rmat", 4096, 30000, 0.0, 50, 4, 0, 2, "uniform", graph_seed=9)
     rp, ci = synth.make_graph(wl)
     rng = np.random.default_rng(4)
-    queries = rng.integers(0, wl.n_nodes, size=(3001, 2)).astype(np.int32)
+    queries = rng.integers(0, wl.n_nodes, size=(n_queries, 2)).astype(np.int32)
     max_set = 1 + wl.M * wl.m
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
