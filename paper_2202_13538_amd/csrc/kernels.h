@@ -183,10 +183,10 @@ hipError_t launch_bfs_batches(hipStream_t stream, int n_cu, const int32_t* queri
 // scan.hip.  Scratch of the kernels that lay their output out themselves (lookback.h): its
 // size in 64-bit words for n_items seeds or queries, and the small kernel that resets it before
 // such a launch (counters and counts to zero, group bases to "not yet") and presets *total_out,
-// where the scanner will leave the row total, to -1.
+// where the scanner will leave the row total, to -1; h_total: see lookback.h.
 int64_t lookback_words(int64_t n_items);
 hipError_t launch_lookback_clear(hipStream_t stream, uint64_t* lb, int64_t n_items,
-                                 int64_t* total_out);
+                                 int64_t* total_out, int64_t* h_total);
 
 // scan.hip.  off[0..n] = exclusive prefix sums of counts[0..n-1] (off[n] = total).  partials:
 // device scratch of scan_partials_len(n) int64; small_scan, spin_limit: as for launch_join_small.

@@ -36,8 +36,9 @@ constexpr int kGroup = 8;              // consecutive items per group base
 constexpr int kScanGroupsPerLane = 4;  // groups a scanner lane takes per round (2048 items a round)
 constexpr unsigned long long kChunkLocked = ~0ull;  // LDS chunk word: a wave is refilling it
 
-// Scratch of one launch, in 64-bit words: [0] item counter, [1] unused, then the group
-// bases (int64, -1 = not yet; one per group plus the grand total), then the 16-bit counts
+// Scratch of one launch, in 64-bit words: [0] item counter, [1] address of the host's words for the
+// total or null (for whoever gives up: workers that had it as an argument lost registers to it), then
+// the group bases (int64, -1 = not yet; one per group plus the grand total), then the 16-bit counts
 // (rows + 1, 0 = not yet), padded so that the scanner's window never leaves the buffer.
 struct LookbackScratch {
     int64_t n_groups;
@@ -54,6 +55,9 @@ __host__ __device__ inline LookbackScratch lookback_scratch(int64_t n_items) {
     s.status_words = (s.n_groups + window) * kGroup * 2 / 8;
     s.total_words = 2 + s.base_words + s.status_words;
     return s;
+}
+__device__ __forceinline__ int64_t* lookback_host(const uint64_t* lb) {
+    return reinterpret_cast<int64_t*>(lb[1]);
 }
 __device__ __forceinline__ int64_t* lookback_base(uint64_t* lb) {
     return reinterpret_cast<int64_t*>(lb + 2);

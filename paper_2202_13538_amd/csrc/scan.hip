@@ -166,12 +166,12 @@ __global__ __launch_bounds__(kScanThreads) void tile_scan_kernel(const int32_t* 
 // pad the last group to "no rows"), every group base to "not yet", the total to -1.  (A kernel,
 // not a memset, so that the call stays valid under stream capture.)
 __global__ void lookback_clear_kernel(uint64_t* __restrict__ lb, int64_t n_items,
-                                      int64_t* __restrict__ total_out) {
+                                      int64_t* __restrict__ total_out, int64_t* h_total) {
     const LookbackScratch sc = lookback_scratch(n_items);
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t == 0) *total_out = -1;
     if (t >= sc.total_words) return;
-    uint64_t v = 0ull;
+    uint64_t v = t == 1 ? reinterpret_cast<uint64_t>(h_total) : 0ull;
     if (t >= 2 && t < 2 + sc.base_words) {
         v = ~0ull;  // -1
     } else if (t >= 2 + sc.base_words) {
@@ -190,10 +190,10 @@ int64_t lookback_words(int64_t n_items) {
 }
 
 hipError_t launch_lookback_clear(hipStream_t stream, uint64_t* lb, int64_t n_items,
-                                 int64_t* total_out) {
+                                 int64_t* total_out, int64_t* h_total) {
     const int64_t n_clear = lookback_scratch(n_items).total_words;
     hipLaunchKernelGGL(lookback_clear_kernel, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0,
-                       stream, lb, n_items, total_out);
+                       stream, lb, n_items, total_out, h_total);
     return hipGetLastError();
 }
 

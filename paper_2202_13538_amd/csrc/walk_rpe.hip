@@ -92,7 +92,8 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
             if (off < 0) {
                 if (lane == 0) {
                     atomicOr(f.err, kDevStall);
-                    if (f.h_total) f.h_total[1] = 1;
+                    int64_t* h_total = lookback_host(lb);
+                    if (h_total) h_total[1] = 1;
                 }
                 return;
             }
@@ -161,7 +162,7 @@ static hipError_t launch_walk_rpe_erc(hipStream_t stream, int max_lds_bytes, int
     if (blocks > (int64_t)per_cu * n_cu) blocks = (int64_t)per_cu * n_cu;
     if (blocks * W < 2) blocks = 2;  // the scanner and at least one worker
 
-    rc = launch_lookback_clear(stream, lb, f.n_seeds, f.rpe_off + f.n_seeds);
+    rc = launch_lookback_clear(stream, lb, f.n_seeds, f.rpe_off + f.n_seeds, f.h_total);
     if (rc != hipSuccess) return rc;
     hipLaunchKernelGGL((walk_rpe_kernel<E, kRec, kCodes>), dim3((unsigned)blocks), dim3(W * kWave),
                        lds_bytes, stream, f, lb, code, set);

@@ -37,7 +37,7 @@ struct FusedJob {
     int32_t lds_words_per_wave;
     int32_t lds_rows;     // rows of a block that fit there at a time
     uint32_t spin_limit;
-    int64_t* h_total;     // host memory, or null: the row total; a 1 behind it if a worker gives up
+    int64_t* h_total;     // host memory that gets the row total too, or null
     uint32_t* __restrict__ err;
 };
 
