@@ -120,7 +120,8 @@ extern "C" {
 #define SUREL_K_RPE_FILL    2   /* RPE builder: sort-and-write kernel                 */
 #define SUREL_K_JOIN_COUNT  3   /* join: counting launch                              */
 #define SUREL_K_JOIN_FILL   4   /* join: writing launch                               */
-#define SUREL_K_SCAN        5   /* the offset scans (three small launches each)       */
+#define SUREL_K_SCAN        5   /* the offset scans (one small launch up to two million
+                                   counts, three beyond)                              */
 #define SUREL_K_WALK_RPE    6   /* fused walk + RPE kernel (surel_sample_walks_rpe)   */
 #define SUREL_K_EDGE_RECORDS 7  /* expansion of the CSR into per-edge neighbour records
                                    (both walk calls, large jobs only)                 */
@@ -217,7 +218,7 @@ int surel_build_rpe_fill(surel_ctx* ctx, const int32_t* d_walks, int64_t n_seeds
  * Limits: those of both calls (M*(m+1) <= SUREL_MAX_WALK_ENTRIES).  n_seeds = 0 writes
  * d_rpe_off[0] = 0.
  * Device-detected: BAD_SEED (that seed's walks are filled with -1 and it gets no rows),
- * BAD_GRAPH (the walker stays in place for that step), CAPACITY, STALL (the offsets are then
+ * BAD_GRAPH (the walker stays in place for that step), CAPACITY, STALL (offsets and rows are then
  * incomplete; a call that was given h_rows returns SUREL_E_DEVICE instead of a total). */
 int surel_sample_walks_rpe(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                            int32_t n_nodes, int64_t n_edges, const int32_t* d_seeds,
@@ -370,6 +371,7 @@ int surel_prune_rpe(surel_ctx* ctx, const uint16_t* d_rpe_cnt, int64_t n_rows, i
  *                [d_inc_off[x], d_inc_off[x+1]).
  *   d_inc_q      int32[n_queries * k] (device, written); a query that names x twice is listed
  *                twice in x's part.
+ * The context's workspace grows to 20.25 bytes per entry of d_queries (21 for short lists).
  * Asynchronous.  Device-detected: BAD_QUERY (an id outside [0, n_nodes); that entry is left out
  * of every part, d_inc_off[n_nodes] is the number of entries kept). */
 int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_queries, int32_t k,
@@ -394,10 +396,11 @@ int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_qu
  *                tuples, ready to be a query list of the join calls when node x's RPE block is
  *                block x.
  *   d_counts     int32[n_batches][2] (device, written): (nodes in V̄, queries in the batch).
- * Limits: 1 <= n_start, B1, B2 <= SUREL_MAX_BATCH.  The context's workspace grows by 16 bytes
- * times (B1 + B2 + n_start + 4 c), c = 4 B2 rounded up to a power of two within [64, 1024],
- * both tables rounded up to powers of two, for each search in flight (4 per compute unit, 16
- * where B2 <= 64; fewer where that would pass 4 GiB).  Asynchronous.
+ * Limits: 1 <= n_start, B1, B2 <= SUREL_MAX_BATCH.  Searches whose tables and queue fit 79 KB of
+ * LDS (the default limits among them) need no workspace.  For others the context's workspace grows
+ * by 8 bytes times (2 (B2 + c) + 2 (n_start + k B2)), c = 4 B2 rounded up to a power of two within
+ * [64, 1024], both terms rounded up to powers of two, for each search in flight (4 per compute
+ * unit, 16 where B2 <= 64; fewer where that would pass 4 GiB).  Asynchronous.
  * Device-detected: BAD_QUERY (a start node or query entry outside [0, n_nodes): skipped),
  * BAD_TABLE (d_inc_off / d_inc_q are not lists of this query list: those entries are skipped). */
 int surel_bfs_batches(surel_ctx* ctx, const int32_t* d_queries, int64_t n_queries, int32_t k,

@@ -138,7 +138,11 @@ __device__ __forceinline__ void tile_numbers(const uint32_t* tile, int lane, uin
 
 // A wavefront takes tiles of consecutive rows: they come in as contiguous 16-byte pieces (the next
 // tile's are on their way while one is looked up) and are read row by row from LDS.
-// Bound by the stream of counts in and codes out: FIGCOLLECT
+// What bounds it: waiting.  The waves wait 85 to 93 % of their cycles (four waves to a SIMD), vector
+// instructions take 9 to 22 % of the time and LDS 7 to 16 %: a wave's tile goes from memory to
+// registers, LDS, a look-up and out in one chain, and rows that the LDS tables do not know wait for
+// the global table besides.  138 M rows of 1M seeds with some 3,500 vectors 0.54 ms = 3.6 TB/s of
+// counts in and codes out; 97 M rows with 15,586 vectors 0.88 ms.
 template <int LT>
 __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(
     const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
