@@ -80,7 +80,8 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
 }
 
 // Union rows of query q, for a workgroup that helps another one (one wavefront, no LDS): the nodes
-// of a list that none of the lists before it holds, by bisection.
+// of a list that none of the lists before it holds, by bisection.  (Of lists that are not ascending,
+// which no table has, it may count other rows than the merge; nothing is written past cap_rows.)
 template <int K>
 __device__ __forceinline__ uint32_t join_small_rows(int q, const int64_t* __restrict__ rpe_off,
                                                     const int32_t* __restrict__ rpe_ids,

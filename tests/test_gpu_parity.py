@@ -930,6 +930,81 @@ def test_launches_that_add_up_each_others_counts_depend_on_no_wait(ctx, spins):
         ctx.set_spin_limit(1 << 22)
 
 
+@pytest.mark.parametrize("M,m", [(1, 1), (65, 3), (128, 15), (200, 9)])
+def test_helpers_count_what_the_owners_count(ctx, M, m):
+    # no poll allowed: walk blocks of every size, seeds that are no nodes, blocks that are empty,
+    # queries that name none, in the places that helpers work out
+    wl = synth.Workload("t", "rmat", 512, 3000, 0.0, M, m, 0, 2, "uniform", graph_seed=4)
+    rp, ci = synth.make_graph(wl)
+    rng = np.random.default_rng(M)
+    seeds = rng.integers(0, wl.n_nodes, size=1000).astype(np.int32)
+    seeds[::7] = [-1, wl.n_nodes, 1 << 30][M % 3]
+    queries = rng.integers(0, seeds.size, size=(700, 3)).astype(np.int32)
+    queries[::5, 1] = queries[::5, 0]
+    queries[3::11, 2] = seeds.size
+    d_rp, d_ci, d_seeds, d_q = dev(rp), dev(ci), dev(seeds), dev(queries)
+    got = []
+    for spins in (1 << 22, 0):
+        ctx.set_spin_limit(spins)
+        try:
+            walks, off, ids, cnt = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 2)
+            assert ctx.check() == binding.DEV_BAD_SEED
+            joff, jids, jcnt = binding.join_queries(ctx, off, ids, cnt, d_q, max_set=1 + M * m)
+            assert ctx.check() == binding.DEV_BAD_QUERY
+        finally:
+            ctx.set_spin_limit(1 << 22)
+        got.append([walks, off, ids, cnt.view(torch.int16), joff, jids, jcnt.view(torch.int16)])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    w = oracle.sample_walks(rp, ci, seeds[seeds != seeds[0]], M, m, 2)
+    assert int(got[0][1][-1]) == oracle.build_rpe(w)[1].size
+
+
+def test_small_calls_of_three_contexts_at_a_time():
+    # three contexts on streams of their own, each with launches that would fill the device alone,
+    # enqueued in turn without waiting: every call's rows are complete
+    wl = synth.Workload("t", "rmat", 4096, 30000, 0.0, 50, 4, 0, 2, "uniform", graph_seed=9)
+    rp, ci = synth.make_graph(wl)
+    M, m, L, S, rounds = wl.M, wl.m, wl.m + 1, wl.n_nodes, 8
+    rng = np.random.default_rng(2)
+    queries = rng.integers(0, S, size=(4096, 2)).astype(np.int32)
+    jobs = []
+    for i in range(3):
+        w = oracle.sample_walks(rp, ci, np.arange(S, dtype=np.int32), M, m, i)
+        table = oracle.build_rpe(w)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            c = binding.Context(stream=stream)
+            cap = table[1].size
+            joined = oracle.join_queries(*table, queries)
+            J = joined[1].size
+            outs = [(torch.empty((S, M, L), dtype=torch.int32, device="cuda"),
+                     torch.empty(S + 1, dtype=torch.int64, device="cuda"),
+                     torch.full((cap,), -7, dtype=torch.int32, device="cuda"),
+                     torch.empty((cap, L), dtype=torch.uint16, device="cuda"),
+                     torch.empty(4097, dtype=torch.int64, device="cuda"),
+                     torch.full((J,), -7, dtype=torch.int32, device="cuda"),
+                     torch.empty((J, 2, L), dtype=torch.uint16, device="cuda")) for _ in range(rounds)]
+            jobs.append((i, c, stream, dev(rp), dev(ci), torch.arange(S, dtype=torch.int32, device="cuda"),
+                         dev(queries), outs, table, joined))
+    torch.cuda.synchronize()
+    for r in range(rounds):
+        for i, c, stream, d_rp, d_ci, d_seeds, d_q, outs, table, joined in jobs:
+            walks, off, ids, cnt, joff, jids, jcnt = outs[r]
+            rc, _ = binding.sample_walks_rpe_raw(c, d_rp, d_ci, d_seeds, M, m, i, walks, ids.numel(), off,
+                                                 ids, cnt, want_rows=False)
+            assert rc == binding.OK
+            rc, _ = binding.join_queries_raw(c, off, ids, cnt, d_q, 1 + M * m, jids.numel(), joff, jids,
+                                             jcnt, want_rows=False)
+            assert rc == binding.OK
+    for i, c, stream, _, _, _, _, outs, table, joined in jobs:
+        assert c.check() == 0
+        for walks, off, ids, cnt, joff, jids, jcnt in outs:
+            assert_table_equal((off, ids, cnt), table, f"context {i}")
+            assert_table_equal((joff, jids, jcnt), joined, f"join of context {i}")
+        c.close()
+
+
 def test_largest_node_ids(ctx):
     # a graph with the most nodes the library takes (2^28 - 1): the largest ids make sort keys
     # (id << 4 | position) that use all 32 bits and must still sort in front of the padding
