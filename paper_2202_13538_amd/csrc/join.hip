@@ -53,26 +53,27 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
     for (int64_t q = q_first; q < min(q_first + kPerWave, n_queries); ++q) {
         JoinQuery<K> jq;
         const uint32_t problem = join_lookup<K>(q, rpe_off, n_blocks, max_set, queries, jq);
+        const int64_t off = join_off[q];
+        const int first_bit = (int)(off & (kRowsAlign - 1));
         int rows = 0;  // an unusable query yields no rows
         if (problem != 0) {
             if (lane == 0) atomicOr(err, problem);
         } else {
             // the same in every lane; said so, the loops over the rows are scalar loops
             rows = __builtin_amdgcn_readfirstlane(join_unite<K, true, false>(
-                base, lay, max_set, jq, team, [&](uint32_t* dst, int j) {
+                base, lay, max_set, jq, team, first_bit, [&](uint32_t* dst, int j) {
                     stage_words<8>(dst, reinterpret_cast<const uint32_t*>(rpe_ids + jq.lo[j]),
                                    jq.n[j], lane);
                 }));
             if constexpr (K == 3) jq.n01 = __builtin_amdgcn_readfirstlane(jq.n01);
             wave_sync();
         }
-        const int64_t off = join_off[q];
         if (join_off[q + 1] - off != (int64_t)rows) {
             if (lane == 0) atomicOr(err, kDevBadSizes);
         } else if (rows > 0 && off + rows > cap_rows) {
             if (lane == 0) atomicOr(err, kDevCapacity);
         } else if (rows > 0) {
-            join_write<K, LT, false>(base, lay, jq, rows, off, rpe_cnt, max_set, out_ids, out_cnt,
+            join_write<K, LT, false>(base, lay, jq, first_bit, rows, off, rpe_cnt, max_set, out_ids, out_cnt,
                                      absent16, team);
         }
         wave_sync();
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
         if (threadIdx.x == 0) atomicOr(err, problem);
     } else {
         rows = __builtin_amdgcn_readfirstlane(join_unite<K, true, true>(
-            base, lay, max_set, jq, team, [&](uint32_t* dst, int j) {
+            base, lay, max_set, jq, team, 0, [&](uint32_t* dst, int j) {
                 const uint32_t* src = reinterpret_cast<const uint32_t*>(rpe_ids + jq.lo[j]);
                 stage_words<4>(dst, src, jq.n[j], team.tid(), team.threads());
             }));
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
         if (threadIdx.x == 0) atomicOr(err, kDevCapacity);
         return;
     }
-    join_write<K, LT, true>(base, lay, jq, rows, off, rpe_cnt, max_set, out_ids, out_cnt, absent16,
+    join_write<K, LT, true>(base, lay, jq, 0, rows, off, rpe_cnt, max_set, out_ids, out_cnt, absent16,
                             team);
 }
 
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
                 fetch(lo, n);
             }
         };
-        const int n_out = join_unite<K, false, false>(base, lay, max_set, jq, team, stage);
+        const int n_out = join_unite<K, false, false>(base, lay, max_set, jq, team, 0, stage);
         if (lane == 0) counts[q] = n_out;
         wave_sync();  // the next query reuses the LDS words
     }

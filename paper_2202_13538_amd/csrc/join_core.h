@@ -20,7 +20,12 @@
 // the table (zeros where the node is absent) as the aligned words that cover them, packs them into
 // the row's words in registers, and the row goes out either straight from the registers (rows of
 // whole words that one store takes) or through an LDS tile that is laid out like the output and
-// streamed out 16 bytes per lane (join_tiled).
+// streamed out 16 bytes per lane (join_tiled).  In the filling launch a query's rounds of 64 rows
+// lie like the output's groups of 32 (the masks start that many bits in), so that all lines of the
+// output but a query's first and last are written whole by one instruction, and the stores go past
+// the caches: the 1,048,576 pairs of the 2.9M-node graph 5.11 ms, 4.98 with the rounds in place, 4.46
+// past the caches as well; 262,144 triples 1.33 -> 1.18, 262,144 pairs of codes 0.80 -> 0.64.  (Rounds
+// that are not in place lose past the caches, 6.04 ms: pieces of a line go to memory one by one.)
 #pragma once
 
 #include "device_util.h"
@@ -33,14 +38,13 @@ constexpr uint32_t kNoId = 0xFFFFFFFFu;  // no node id reaches 2^28
 __host__ __device__ constexpr int join_cover(int LT) { return LT % 2 == 0 ? LT / 2 : LT / 2 + 1; }
 
 // Rounds of 64 union rows whose gathers a wave has in flight together.  More rounds shorten a
-// wave's chain of memory round trips but cost registers, i.e. waves per compute unit: of 2 to
-// 10 rounds, six made the fastest filling launch on the 2.9M-node workload (5.30 ms with two,
-// 5.09 with six, 5.55 with eight); for the triples of the 1M-node workload four (1.80 ms with
-// three, 1.77 with four, 1.96 with six, 2.26 with eight).  Both hold about 36 and 24 words a
-// lane, which is the measure for longer vectors.
+// wave's chain of memory round trips but cost registers, i.e. waves per compute unit; the measure is
+// the words a lane holds.  Pairs of m = 4: 4.59 ms with four rounds (24 words), 4.46 with six, 4.44
+// with eight; triples of m = 3: 1.22 ms with three (18 words), 1.21 with four, 1.18 with five, 1.21
+// with six; pairs of codes: 0.65 ms with four (8 words), 0.64 with eight and ten.
 __host__ __device__ constexpr int join_rounds(int K, int LT) {
-    const int most = K == 2 ? 6 : 4;
-    const int fit = (K == 2 ? 36 : 27) / (K * join_cover(LT));
+    const int most = 8;
+    const int fit = (K == 2 ? 36 : 33) / (K * join_cover(LT));
     return fit < 1 ? 1 : (fit < most ? fit : most);
 }
 
@@ -55,6 +59,10 @@ __host__ __device__ constexpr int join_tile_words(int K, int LT) {
 }
 
 // LDS of one query, in 32-bit words.  LT = 0: no rows are written (counting).
+// The filling launch puts a row at the place inside kRowsAlign rows that it has in the output: 32 ids
+// are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
+constexpr int kRowsAlign = 32;
+
 struct JoinLds {
     int ids;         // pairs: lists 0 and 1, max_set words each; triples: the same, later list 2
     int u01;         // triples: the union of lists 0 and 1, [2 * max_set]
@@ -83,7 +91,7 @@ __host__ __device__ constexpr JoinLds join_lds_layout(int K, int max_set, int LT
         at += 2 * o.mask01_words;
     }
     o.mask = at;  // even: the masks are read as 64-bit words
-    o.mask_words = LT > 0 ? join_mask_words(K * max_set) : 0;
+    o.mask_words = LT > 0 ? join_mask_words(kRowsAlign - 1 + K * max_set) : 0;
     at += 2 * o.mask_words;
     o.tile_words = LT > 0 ? join_tile_words(K, LT) : 0;
     if (o.tile_words > 0) {
@@ -132,13 +140,13 @@ struct JoinTeam {
 };
 
 // Union size of two lists by merge path and, with kFlags, the two bit masks of the union rows
-// (bit r of amask: list A holds the node of row r; bmask likewise).  The masks must be zero on
+// (bit first_bit + r of amask: list A holds the node of row r; bmask likewise).  The masks must be zero on
 // entry; they are complete after the next team sync.  kLong: a thread may have more than 64 rows
 // (the longest triples on one wavefront).
 template <bool kFlags, bool kMulti, bool kLong = false>
 __device__ __forceinline__ int merge_path_union(const uint32_t* A, int nA, const uint32_t* B, int nB,
                                                 uint32_t* amask, uint32_t* bmask,
-                                                const JoinTeam<kMulti>& team) {
+                                                const JoinTeam<kMulti>& team, int first_bit = 0) {
     const int T = nA + nB;
     const int VT = (T + team.threads() - 1) / team.threads();  // at most 64; kLong: 96
     const int d0 = min(team.tid() * VT, T);
@@ -205,7 +213,7 @@ __device__ __forceinline__ int merge_path_union(const uint32_t* A, int nA, const
         vb = take_a ? vb : next;
     }
     int n_out;
-    const int row0 = team.excl_sum(n_emit, &n_out);
+    const int row0 = first_bit + team.excl_sum(n_emit, &n_out);
     if (kFlags) {
         // the thread's rows start at row0: its bits go in there, as up to three 32-bit words
         auto put = [&](uint32_t* mask, uint64_t bits, int first) {
@@ -333,7 +341,7 @@ __device__ __forceinline__ void materialize_union(const uint32_t* ids, int max_s
 template <int K, bool kFlags, bool kMulti, typename Stage>
 __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, int max_set,
                                           JoinQuery<K>& jq, const JoinTeam<kMulti>& team,
-                                          Stage&& stage) {
+                                          int first_bit, Stage&& stage) {
     uint32_t* ids = base + lay.ids;
     uint32_t* mask = base + lay.mask;
     const int (&n)[K] = jq.n;
@@ -344,7 +352,7 @@ __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, in
     if constexpr (K == 2) {
         team.sync();
         return merge_path_union<kFlags, kMulti>(ids, n[0], ids + max_set, n[1], mask,
-                                                mask + lay.mask_words, team);
+                                                mask + lay.mask_words, team, first_bit);
     } else {
         uint32_t* mask01 = base + lay.mask01;
         uint32_t* u01 = base + lay.u01;
@@ -360,18 +368,30 @@ __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, in
         team.sync();
         if (kFlags && jq.n01 + n[2] > 64 * team.threads())
             return merge_path_union<kFlags, kMulti, true>(u01, jq.n01, ids, n[2], mask,
-                                                          mask + lay.mask_words, team);
+                                                          mask + lay.mask_words, team, first_bit);
         return merge_path_union<kFlags, kMulti>(u01, jq.n01, ids, n[2], mask,
-                                                mask + lay.mask_words, team);
+                                                mask + lay.mask_words, team, first_bit);
     }
 }
 
-// Writes the n_out > 0 union rows of a query that join_unite<K, true> left in LDS to rows
-// [off, off + n_out) of the output; wave w of the team takes a contiguous share of the rounds.
+// Stores rows of a long query list past the caches (see the file's head); a short list's may be
+// wanted there by whoever reads them next, and their lines come in pieces from several waves.
+template <bool kMulti, typename T>
+__device__ __forceinline__ void join_store(T* to, T value) {
+    if constexpr (kMulti) {
+        *to = value;
+    } else {
+        __builtin_nontemporal_store(value, to);
+    }
+}
+
+// Writes the n_out > 0 union rows of a query that join_unite<K, true> left in LDS (first_bit as
+// there) to rows [off, off + n_out) of the output; wave w of the team takes a contiguous share of
+// the rounds.
 template <int K, int LT, bool kMulti>
 __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
-                                           const JoinQuery<K>& jq, int n_out, int64_t off,
-                                           const uint16_t* __restrict__ rpe_cnt, int max_set,
+                                           const JoinQuery<K>& jq, int first_bit, int n_out,
+                                           int64_t off, const uint16_t* __restrict__ rpe_cnt, int max_set,
                                            int32_t* __restrict__ out_ids,
                                            uint16_t* __restrict__ out_cnt, uint16_t absent16,
                                            const JoinTeam<kMulti>& team) {
@@ -406,14 +426,17 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
         vec_words[j] = reinterpret_cast<const uint32_t*>(first - odd[j]);
     }
 
-    int r_first = 0, r_last = n_out;
+    // Rows are counted from the first bit of the masks on.
+    out_ids += off - first_bit;
+    out_cnt += (off - first_bit) * kCounts;
+    int r_first = 0, r_last = first_bit + n_out;
     int before[2] = {0, 0};     // rows of the two merged lists below the present round
     int before01[2] = {0, 0};   // triples: rows of lists 0 and 1 below it
     if constexpr (kMulti) {
-        const int rounds = (n_out + kWave - 1) / kWave;
+        const int rounds = (r_last + kWave - 1) / kWave;
         const int per_wave = (rounds + team.n_waves - 1) / team.n_waves;
         r_first = team.wave * per_wave * kWave;
-        r_last = min(r_first + per_wave * kWave, n_out);
+        r_last = min(r_first + per_wave * kWave, r_last);
         if (r_first >= r_last) return;
         if (r_first > 0) {
             before[0] = mask_bits_below(mask, r_first, lane);
@@ -477,6 +500,14 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                 raw[g][j][kCover] = 0u;
             }
         }
+        // all of them are waited for here: in the middle of the stores, every wait for a load would
+        // wait for stores as well (pairs of codes 0.80 -> 0.72 ms)
+#pragma unroll
+        for (int g = 0; g < kRounds; ++g)
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+#pragma unroll
+                for (int t = 0; t < kCover; ++t) asm volatile("" : "+v"(raw[g][j][t]));
 #pragma unroll
         for (int g = 0; g < kRounds; ++g) {
             if (r0 + g * kWave >= r_last) break;
@@ -506,22 +537,31 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                         w[(start + 1) / 2 + t] = __builtin_amdgcn_alignbyte(vec[t + 1], vec[t], 2u);
                 }
             }
-            const int r = r0 + g * kWave + lane;
-            const bool live = r < n_out;
-            if (live) out_ids[off + r] = (int32_t)id[g];
+            const int r1 = r0 + g * kWave;
+            const int r = r1 + lane;
+            const bool live = r >= first_bit && r < r_last;
+            if (live) join_store<kMulti>(out_ids + r, (int32_t)id[g]);
             if constexpr (!join_tiled(K, LT)) {
                 // a lane's row is stored from its registers, in one instruction: the rows of
                 // neighbouring lanes adjoin, so a wave's store is contiguous
                 if (live) {
-                    uint32_t* row_words = reinterpret_cast<uint32_t*>(out_cnt) + (off + r) * kWords;
+                    typedef uint32_t row_t __attribute__((ext_vector_type(kWords), aligned(4)));
+                    row_t row;
 #pragma unroll
-                    for (int d = 0; d < kWords; ++d) row_words[d] = w[d];
+                    for (int d = 0; d < kWords; ++d) row[d] = w[d];
+                    uint32_t* row_words = reinterpret_cast<uint32_t*>(out_cnt) + (int64_t)r * kWords;
+                    row_t* to = reinterpret_cast<row_t*>(row_words);
+                    if constexpr (kMulti) {
+                        *to = row;
+                    } else {
+                        __builtin_nontemporal_store(row, to);
+                    }
                 }
             } else {
                 // The rows are put together in an LDS tile and go out 16 bytes per lane.  The tile
                 // starts `head` counts in, so that 16-byte pieces of the tile are 16-byte pieces of
                 // the output.
-                uint16_t* dst = out_cnt + (off + r0 + g * kWave) * kCounts;
+                uint16_t* dst = out_cnt + (int64_t)r1 * kCounts;
                 const int head = (int)((reinterpret_cast<uintptr_t>(dst) >> 1) & 7u);
                 uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile32);
                 if constexpr (kCounts % 2 == 0) {  // pairs: rows of whole words (head is even)
@@ -540,22 +580,28 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                 }
                 wave_sync();
                 constexpr int kUnit = kCounts % 2 == 0 ? 2 : 1;  // counts moved at a time at the ends
-                const int n_counts = min(kWave, r_last - (r0 + g * kWave)) * kCounts;
-                const int lead = min((8 - head) & 7, n_counts);  // counts before the first piece
-                const int n_quads = (n_counts - lead) >> 3;
-                const int tail = lead + 8 * n_quads;             // counts before the last ones
-                const uint4* tile_quads = reinterpret_cast<const uint4*>(tile16 + head + lead);
-                uint4* dst_quads = reinterpret_cast<uint4*>(dst + lead);
+                // counts [first, last) of the tile are rows; the 16-byte pieces that lie in there
+                // are [lead, tail)
+                const int first = max(first_bit - r1, 0) * kCounts;
+                const int last = min(r_last - r1, kWave) * kCounts;
+                const int lead = min(((head + first + 7) & ~7) - head, last);
+                const int n_quads = (last - lead) >> 3;
+                const int tail = lead + 8 * n_quads;
+                typedef uint32_t quad_t __attribute__((ext_vector_type(4)));
+                const quad_t* tile_quads = reinterpret_cast<const quad_t*>(tile16 + head + lead);
+                quad_t* dst_quads = reinterpret_cast<quad_t*>(dst + lead);
                 if constexpr (kUnit == 2) {
                     const uint32_t* t32 = tile32 + (head >> 1);
                     uint32_t* d32 = reinterpret_cast<uint32_t*>(dst);
-                    if (lane < lead / 2) d32[lane] = t32[lane];
-                    for (int t = lane; t < n_quads; t += kWave) dst_quads[t] = tile_quads[t];
-                    if (lane < (n_counts - tail) / 2) d32[tail / 2 + lane] = t32[tail / 2 + lane];
+                    if (lane < (lead - first) / 2) d32[first / 2 + lane] = t32[first / 2 + lane];
+                    for (int t = lane; t < n_quads; t += kWave)
+                        join_store<kMulti>(dst_quads + t, tile_quads[t]);
+                    if (lane < (last - tail) / 2) d32[tail / 2 + lane] = t32[tail / 2 + lane];
                 } else {
-                    if (lane < lead) dst[lane] = tile16[head + lane];
-                    for (int t = lane; t < n_quads; t += kWave) dst_quads[t] = tile_quads[t];
-                    if (lane < n_counts - tail) dst[tail + lane] = tile16[head + tail + lane];
+                    if (lane < lead - first) dst[first + lane] = tile16[head + first + lane];
+                    for (int t = lane; t < n_quads; t += kWave)
+                        join_store<kMulti>(dst_quads + t, tile_quads[t]);
+                    if (lane < last - tail) dst[tail + lane] = tile16[head + tail + lane];
                 }
                 wave_sync();
             }

@@ -856,6 +856,31 @@ def test_join_vector_lengths_in_one_and_in_two_launches(ctx, L, k):
 
 
 @pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("L", [2, 4, 5, 10])
+def test_join_fill_at_every_place_of_a_line(ctx, L, k):
+    # the filling launch counts a query's rows from their place inside 32 rows of the output: blocks
+    # of sizes that put queries at every such place, and outputs that start anywhere in a line
+    rng = np.random.default_rng(100 * L + k)
+    sizes = [0, 1, 2, 15, 16, 31, 32, 33, 47, 63, 64, 65, 95, 96]
+    blocks = [np.sort(rng.choice(300, size, replace=False)) for size in sizes]
+    table = hand_made_table(blocks, L, rng)
+    d_table = (dev(table[0]), dev(table[1]), dev(table[2].view(np.int16)).view(torch.uint16))
+    queries = rng.integers(0, len(blocks), size=(2500, k)).astype(np.int32)
+    want = oracle.join_queries(*table, queries)
+    J, d_q, d_off = want[1].size, dev(queries), dev(want[0])
+    assert set(np.unique(want[0] % 32)) == set(range(32))
+    for skip in (0, 1, 5, 32) if k * L % 2 == 0 else (0, 2, 6, 32):  # outputs are aligned words
+        ids = torch.full((J + 64,), -7, dtype=torch.int32, device="cuda")
+        cnt = torch.full((J + 64, k, L), 9, dtype=torch.int16, device="cuda").view(torch.uint16)
+        part = slice(skip, skip + J)
+        assert binding.join_fill(ctx, *d_table, d_q, 96, d_off, J, ids[part], cnt[part]) == binding.OK
+        assert ctx.check() == 0
+        assert_table_equal((d_off, ids[part], cnt[part]), want, f"rows from place {skip} on")
+        for rest in (slice(0, skip), slice(skip + J, None)):
+            assert (ids[rest] == -7).all() and (cnt.view(torch.int16)[rest] == 9).all()
+
+
+@pytest.mark.parametrize("k", [2, 3])
 def test_join_in_one_launch_of_the_largest_blocks_and_with_bounded_waits(ctx, k):
     # full blocks of 2048 rows; with no wait allowed at all a workgroup unites the lists that it
     # would have waited for itself: the offsets are right all the same
