@@ -539,7 +539,7 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
             }
             const int r1 = r0 + g * kWave;
             const int r = r1 + lane;
-            const bool live = r >= first_bit && r < r_last;
+            const bool live = (kMulti || r >= first_bit) && r < r_last;
             if (live) join_store<kMulti>(out_ids + r, (int32_t)id[g]);
             if constexpr (!join_tiled(K, LT)) {
                 // a lane's row is stored from its registers, in one instruction: the rows of
@@ -582,7 +582,7 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                 constexpr int kUnit = kCounts % 2 == 0 ? 2 : 1;  // counts moved at a time at the ends
                 // counts [first, last) of the tile are rows; the 16-byte pieces that lie in there
                 // are [lead, tail)
-                const int first = max(first_bit - r1, 0) * kCounts;
+                const int first = kMulti ? 0 : max(first_bit - r1, 0) * kCounts;
                 const int last = min(r_last - r1, kWave) * kCounts;
                 const int lead = min(((head + first + 7) & ~7) - head, last);
                 const int n_quads = (last - lead) >> 3;

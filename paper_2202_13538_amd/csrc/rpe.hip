@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kWaves* kWave) void rpe_fill_kernel(
         if (lane == 0) atomicOr(err, kDevCapacity);
         return;
     }
-    rpe_write_rows<E>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt,
+    rpe_write_rows<E, true>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt,
                       [](int, int, const uint16_t*, uint32_t*) {});
 }
 

@@ -97,8 +97,12 @@ __device__ __forceinline__ void rpe_assemble_rows(const uint32_t (&x)[E], const 
 }
 
 // Moves n 32-bit words, or 16-bit counts, from LDS to global memory, 16 bytes per
-// lane where it can: src lies at the same place inside a 16-byte piece as dst.
-template <typename T>
+// lane where it can: src lies at the same place inside a 16-byte piece as dst.  Large jobs write
+// past the caches, which walks keep their records in (walks + table of 235,000 seeds of M = 200, m = 4:
+// 1.58 -> 1.55 ms; 500,009 tables of M = 50, m = 4 from finished walks: 423 -> 403 us; through the
+// caches at the lines that a block shares with its neighbours: 1.55 ms and 427 us).  What a small job writes
+// is read from there by the next call (join of 1,024 pairs behind it: 12.4 us, 13.1 past the caches).
+template <bool kPastCaches, typename T>
 __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst, int n, int lane) {
     constexpr int kPer = 16 / (int)sizeof(T);
     const int head = (int)((reinterpret_cast<uintptr_t>(dst) / sizeof(T)) & (kPer - 1));
@@ -106,9 +110,16 @@ __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst
     const int n_quads = (n - lead) / kPer;
     const int tail = lead + n_quads * kPer;
     if (lane < lead) dst[lane] = src[lane];
-    const uint4* s4 = reinterpret_cast<const uint4*>(src + lead);
-    uint4* d4 = reinterpret_cast<uint4*>(dst + lead);
-    for (int t = lane; t < n_quads; t += kWave) d4[t] = s4[t];
+    typedef uint32_t quad_t __attribute__((ext_vector_type(4)));
+    const quad_t* s4 = reinterpret_cast<const quad_t*>(src + lead);
+    quad_t* d4 = reinterpret_cast<quad_t*>(dst + lead);
+    for (int t = lane; t < n_quads; t += kWave) {
+        if constexpr (kPastCaches) {
+            __builtin_nontemporal_store(s4[t], d4 + t);
+        } else {
+            d4[t] = s4[t];
+        }
+    }
     if (lane < n - tail) dst[tail + lane] = src[tail + lane];
 }
 
@@ -117,7 +128,7 @@ __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst
 // one turn are rare, the LDS of a wave decides how many waves a compute unit holds).  cnt may be
 // null: a table that carries RPE-IDs only.  each(row0, n, cnt16, free_words) is called for every
 // turn while its counts lie in LDS (from cnt16 on), with n words of LDS that are free again.
-template <int E, typename Each>
+template <int E, bool kPastCaches, typename Each>
 __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const RpeRowScan& sc,
                                                int lane, int L, uint32_t start_weight,
                                                uint32_t* lds, int lds_rows, int64_t off,
@@ -132,10 +143,10 @@ __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const Rpe
         const int head = (int)((reinterpret_cast<uintptr_t>(dst_cnt) >> 1) & 7u);
         rpe_assemble_rows<E>(x, sc, lane, L, row0, n, start_weight, lds_ids, cnt_words, head);
         const uint16_t* cnt16 = reinterpret_cast<const uint16_t*>(cnt_words) + head;
-        stream_aligned(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane);
+        stream_aligned<kPastCaches>(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane);
         wave_sync();
         each(row0, n, cnt16, lds_ids);
-        if (cnt != nullptr) stream_aligned(cnt16, dst_cnt, n * L, lane);
+        if (cnt != nullptr) stream_aligned<kPastCaches>(cnt16, dst_cnt, n * L, lane);
         wave_sync();  // the LDS words are free again
     }
 }

@@ -16,10 +16,10 @@ constexpr int kFusedChains = 2;  // walks a lane moves at a time
 // Sort keys of a seed: every step of every walk, and ONE key for the M walks' common start
 // (sorting M equal keys would be work for nothing: 1,000 keys instead of 801 at M = 200, m = 4).
 __host__ __device__ constexpr int fused_keys(int M, int m) { return M * m + 1; }
-// LDS words of the walk block: M rows of m + 1 positions and a scratch row for the idle lanes of
-// the last pass.
+// LDS words of the walk block: M rows of m + 1 positions, a scratch row for the idle lanes of the last
+// pass, and up to three words in front.
 __host__ __device__ constexpr int fused_block_words(int M, int m) {
-    return ((M + 1) * (m + 1) + 3) & ~3;
+    return ((M + 1) * (m + 1) + 3 + 3) & ~3;
 }
 
 struct FusedJob {
@@ -78,6 +78,9 @@ template <int E, int kRec>
 __device__ __forceinline__ void fused_walk_and_sort(const FusedJob& f, int64_t i, int32_t u,
                                                     int32_t* block, int lane, uint32_t (&y)[E]) {
     const int M = f.M, m = f.m, L = m + 1;
+    // it lies in LDS at the same place inside a 16-byte piece as in its output
+    int32_t* out = f.walks + i * (int64_t)(M * L);
+    block += (reinterpret_cast<uintptr_t>(out) >> 2) & 3u;
     int32_t u_lo, u_deg;
     bool bad_graph = seed_row(f.g, u, &u_lo, &u_deg);
     for (int w0 = 0; w0 < M; w0 += kFusedChains * kWave) {
@@ -104,18 +107,8 @@ __device__ __forceinline__ void fused_walk_and_sort(const FusedJob& f, int64_t i
     }
     raise_error(f.err, bad_graph, kDevBadGraph);
     wave_sync();
-    // the block goes out as it lies in LDS, 16 bytes a lane where the seed's block starts on such
-    // a boundary
-    const int n_out = M * L;
-    int32_t* out = f.walks + i * (int64_t)n_out;
-    if ((n_out & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
-        typedef int quad_t __attribute__((ext_vector_type(4)));
-        const quad_t* b4 = reinterpret_cast<const quad_t*>(block);
-        quad_t* o4 = reinterpret_cast<quad_t*>(out);
-        for (int t = lane; t < n_out / 4; t += kWave) __builtin_nontemporal_store(b4[t], o4 + t);
-    } else {
-        for (int t = lane; t < n_out; t += kWave) __builtin_nontemporal_store(block[t], out + t);
-    }
+    // the block goes out as it lies in LDS
+    stream_aligned<true>(block, out, M * L, lane);
     // Keys: entry idx of the steps is step 1 + idx mod m of walk idx / m.  A register's entries lie
     // 64 behind those of the register before it.  (Worked out anew for every seed, which the asm
     // makes the compiler believe: kept over the seeds, the places of all E registers are 2E
