@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
             if (lane == 0) atomicOr(err, problem);
         } else {
             // the same in every lane; said so, the loops over the rows are scalar loops
-            rows = __builtin_amdgcn_readfirstlane(join_unite<K, true, false>(
+            rows = __builtin_amdgcn_readfirstlane(join_unite<K, false>(
                 base, lay, max_set, jq, team, first_bit, [&](uint32_t* dst, int j) {
                     stage_words<8>(dst, reinterpret_cast<const uint32_t*>(rpe_ids + jq.lo[j]),
                                    jq.n[j], lane);
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
     if (problem != 0) {
         if (threadIdx.x == 0) atomicOr(err, problem);
     } else {
-        rows = __builtin_amdgcn_readfirstlane(join_unite<K, true, true>(
+        rows = __builtin_amdgcn_readfirstlane(join_unite<K, true>(
             base, lay, max_set, jq, team, 0, [&](uint32_t* dst, int j) {
                 const uint32_t* src = reinterpret_cast<const uint32_t*>(rpe_ids + jq.lo[j]);
                 stage_words<4>(dst, src, jq.n[j], team.tid(), team.threads());
@@ -179,17 +179,51 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
                             team);
 }
 
-// Counting.  A wavefront takes join_count_queries(K) consecutive queries.  Their
+// Counting.  A wavefront takes kCountQueries consecutive queries.  Their
 // blocks are looked up by one lane each (block numbers, then the blocks' offsets: two round
-// trips to memory for all of them), and while the id lists of one query are united in LDS the
-// lists of the next one are already on their way into registers: a query's time is then the
-// longer of its merge and one round trip, where looking up, staging and uniting one query
-// after the other took three round trips and the merge.
-// (Measured on the 2.9M-node workload, pairs: 0.77 ms one query after the other, four to a
-// wave; 0.71 / 0.66 / 0.64 / 0.64 ms this way with 2 / 4 / 8 / 16 to a wave.  Triples of the
-// 1M-node workload: 0.42, and 0.41 / 0.41 / 0.42 / 0.47.)
-__host__ __device__ constexpr int join_count_queries(int K) { return K == 2 ? 8 : 4; }
+// trips to memory for all of them), and while one query is counted in LDS the lists of the next one
+// are already on their way into registers.
+//
+// Nothing is merged: the union has the rows of all lists less those of nodes that an earlier list
+// holds.  A list's nodes set their bits in a hashed bit map; of the next list's nodes only those that
+// find their bit set, true repetitions and a false one or two in a hundred, are put on a list and
+// looked up in the earlier ones by bisection, 64 at a time.
+// What bounds it: the lists' way from memory.  1,048,576 pairs of the 2.9M-node graph move 6.2 TB/s
+// (23.7 M lines of 128 bytes, a tenth of them for the blocks' offsets) with 222 vector instructions
+// a pair; triples of 181 nodes a list the vector instructions (400 a triple, 0.7 of the time).
+// By merge path, where every lane bisects and then merges its share node after node, it took 446
+// instructions a pair and 0.63 ms, now 0.49; 262,144 triples of m = 3 0.36 -> 0.23; 65,536 pairs of
+// 561 nodes a list 0.105 -> 0.075.
+// Queries to a wave: 4 / 8 / 16 pairs take 0.52 / 0.50 / 0.58 ms, 4 / 8 triples 0.239 / 0.234.
+constexpr int kCountQueries = 8;
 constexpr int kCountStage = 8;  // words of a list a lane holds for the next query (512 ids)
+
+// LDS of a counting wave, in 32-bit words: the bit map, the lists that are looked up in, and the
+// nodes that wait for their look-up.
+struct CountLds {
+    int map_bits;  // log2 of the words of the bit map: max_set ids set one bit in eight at most
+    int lists, waiting;
+    int total;
+};
+__host__ __device__ constexpr CountLds count_lds_layout(int K, int max_set) {
+    CountLds o{};
+    o.map_bits = 8;  // cleared 16 bytes a lane
+    while ((4 << o.map_bits) < max_set) o.map_bits += 1;
+    o.lists = 1 << o.map_bits;
+    o.waiting = o.lists + (K - 1) * max_set;
+    o.total = o.waiting + max_set;
+    return o;
+}
+
+// Whether the ascending list[0 .. n) holds x; steps: 2^steps > n.
+__device__ __forceinline__ bool list_holds(const uint32_t* list, int n, int steps, uint32_t x) {
+    int below = 0;  // ids of the list that are known to be smaller than x
+    for (int half = 1 << (steps - 1); half > 0; half >>= 1) {
+        const int at = below + half;
+        if (at <= n && list[at - 1] < x) below = at;
+    }
+    return below < n && list[below] == x;
+}
 
 template <int K>
 __global__ __launch_bounds__(kWave) void join_count_kernel(
@@ -197,10 +231,8 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
     int32_t max_set, const int32_t* __restrict__ queries, int64_t n_queries,
     int32_t* __restrict__ counts, uint32_t* __restrict__ err) {
     extern __shared__ __align__(16) uint32_t base[];
-    const JoinLds lay = join_lds_layout(K, max_set, 0, 1);
-    const JoinTeam<false> team{lane_id(), 0, 1, nullptr};
-    const int lane = team.lane;
-    constexpr int kCountQueries = join_count_queries(K);
+    const CountLds lay = count_lds_layout(K, max_set);
+    const int lane = lane_id();
     const int64_t q_first = (int64_t)blockIdx.x * kCountQueries;
 
     // lane l < kCountQueries looks up the blocks of query q_first + l
@@ -249,50 +281,117 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
             n[j] = __builtin_amdgcn_readlane(my_n[j], i);
         }
     };
-    uint32_t staged[K][kCountStage];
-    auto fetch = [&](const int64_t (&lo)[K], const int (&n)[K]) {
+    // ids t0 .. t0 + 511 of a list
+    auto fetch = [&](uint32_t (&x)[kCountStage], int64_t lo, int t0, int n) {
+        const int32_t* list = rpe_ids + lo;
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
+        for (int u = 0; u < kCountStage; ++u) {
+            const int first = t0 + u * kWave;
+            if (first >= n) break;
+            x[u] = (uint32_t)list[(uint32_t)min(first + lane, n - 1)];
+        }
+    };
+    // an id's bit in the map.  (The product of 24 bits takes a quarter of a full one's time; ids that
+    // differ above them share a bit.)
+    const uint32_t bit_shift = 27u - (uint32_t)lay.map_bits;
+    auto bit_of = [&](uint32_t x) { return (uint32_t)__umul24(x, 0x9E3779u) >> bit_shift; };
+    uint32_t* map = base;
+    auto insert = [&](const uint32_t (&x)[kCountStage], int t0, int n, uint32_t* list) {
 #pragma unroll
-            for (int u = 0; u < kCountStage; ++u) {
-                const int t = u * kWave + lane;
-                staged[j][u] = t < n[j] ? (uint32_t)rpe_ids[lo[j] + t] : 0u;
+        for (int u = 0; u < kCountStage; ++u) {
+            if (t0 + u * kWave >= n) break;
+            const int t = t0 + u * kWave + lane;
+            if (t < n) {
+                const uint32_t b = bit_of(x[u]);
+                list[t] = x[u];
+                atomicOr(map + (b >> 5), 1u << (b & 31u));
             }
         }
     };
+    uint32_t* waiting = base + lay.waiting;
+    auto probe = [&](const uint32_t (&x)[kCountStage], int t0, int n, int& n_waiting) {
+        // (registers that hold no ids read some word of the map)
+        uint32_t word[kCountStage];
+        const int n_words = n - t0;
+#pragma unroll
+        for (int h = 0; h < kCountStage; h += kCountStage / 2) {
+            if (h * kWave >= n_words) break;
+#pragma unroll
+            for (int u = h; u < h + kCountStage / 2; ++u) word[u] = map[bit_of(x[u]) >> 5];
+#pragma unroll
+            for (int u = h; u < h + kCountStage / 2; ++u) {
+                if (u * kWave >= n_words) break;
+                const uint32_t set = (word[u] >> (bit_of(x[u]) & 31u)) & 1u;
+                const uint64_t hits = __ballot(set != 0u) & __ballot(lane < n_words - u * kWave);
+                if (hits != 0ull) {
+                    const int rank = (int)__builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+                    if (__builtin_amdgcn_inverse_ballot_w64(hits)) waiting[n_waiting + rank] = x[u];
+                    n_waiting += __popcll(hits);
+                }
+            }
+        }
+    };
+    const int steps = 32 - __builtin_clz((uint32_t)max_set);
+
+    uint32_t staged[K][kCountStage];
     int64_t lo[K];
     int n[K];
     blocks_of(0, lo, n);
-    fetch(lo, n);
 #pragma unroll
+    for (int j = 0; j < K; ++j) fetch(staged[j], lo[j], 0, n[j]);
+#pragma unroll 1
     for (int i = 0; i < kCountQueries; ++i) {
         const int64_t q = q_first + i;
         if (q >= n_queries) break;
-        // the lists of query i: from the registers, and what is longer than they hold from memory
-        JoinQuery<K> jq;
         int64_t lo_now[K];
+        int n_now[K];
 #pragma unroll
-        for (int j = 0; j < K; ++j) lo_now[j] = lo[j], jq.n[j] = n[j];
-        auto stage = [&](uint32_t* dst, int j) {
+        for (int j = 0; j < K; ++j) lo_now[j] = lo[j], n_now[j] = n[j];
+        uint4* clear = reinterpret_cast<uint4*>(map);
+        for (int t = lane; t < (1 << lay.map_bits) / 4; t += kWave) clear[t] = make_uint4(0u, 0u, 0u, 0u);
+        wave_sync();
+        int rows = n_now[0];
 #pragma unroll
-            for (int u = 0; u < kCountStage; ++u) {
-                const int t = u * kWave + lane;
-                if (t < jq.n[j]) dst[t] = staged[j][u];
+        for (int j = 0; j < K; ++j) {
+            // the ids that the registers do not hold come from memory
+            if (j > 0) {
+                int n_waiting = 0;
+                probe(staged[j], 0, n_now[j], n_waiting);
+                for (int t0 = kCountStage * kWave; t0 < n_now[j]; t0 += kCountStage * kWave) {
+                    uint32_t x[kCountStage];
+                    fetch(x, lo_now[j], t0, n_now[j]);
+                    probe(x, t0, n_now[j], n_waiting);
+                }
+                wave_sync();
+                rows += n_now[j];
+                for (int t0 = 0; t0 < n_waiting; t0 += kWave) {
+                    const int t = t0 + lane;
+                    const uint32_t x = waiting[min(t, n_waiting - 1)];
+                    bool known = false;
+#pragma unroll
+                    for (int e = 0; e < j; ++e)
+                        known = known || list_holds(base + lay.lists + e * max_set, n_now[e], steps, x);
+                    rows -= __popcll(__ballot(known && t < n_waiting));
+                }
             }
-            if (jq.n[j] > kCountStage * kWave)
-                stage_words<8>(dst + kCountStage * kWave,
-                               reinterpret_cast<const uint32_t*>(rpe_ids + lo_now[j]) + kCountStage * kWave,
-                               jq.n[j] - kCountStage * kWave, lane);
-            // list j's registers are free: the next query's list is on its way while this
-            // query is united
-            if (j == K - 1 && i + 1 < kCountQueries && q + 1 < n_queries) {
+            if (j < K - 1) {
+                uint32_t* list = base + lay.lists + j * max_set;
+                insert(staged[j], 0, n_now[j], list);
+                for (int t0 = kCountStage * kWave; t0 < n_now[j]; t0 += kCountStage * kWave) {
+                    uint32_t x[kCountStage];
+                    fetch(x, lo_now[j], t0, n_now[j]);
+                    insert(x, t0, n_now[j], list);
+                }
+            } else if (i + 1 < kCountQueries && q + 1 < n_queries) {
+                // the registers are free: the next query's lists
                 blocks_of(i + 1, lo, n);
-                fetch(lo, n);
+#pragma unroll
+                for (int e = 0; e < K; ++e) fetch(staged[e], lo[e], 0, n[e]);
             }
-        };
-        const int n_out = join_unite<K, false, false>(base, lay, max_set, jq, team, 0, stage);
-        if (lane == 0) counts[q] = n_out;
-        wave_sync();  // the next query reuses the LDS words
+            wave_sync();
+        }
+        if (lane == 0) counts[q] = rows;
     }
 }
 
@@ -394,8 +493,7 @@ static hipError_t launch_join_lt(const JoinJob& j) {
 
 template <int K>
 static hipError_t launch_join_count_k(const JoinJob& j) {
-    constexpr int kCountQueries = join_count_queries(K);
-    const size_t lds_bytes = (size_t)join_lds_layout(K, j.max_set, 0, 1).total * 4;
+    const size_t lds_bytes = (size_t)count_lds_layout(K, j.max_set).total * 4;
     if (lds_bytes > (size_t)j.max_lds_bytes) return hipErrorInvalidValue;
     hipError_t rc = allow_lds(reinterpret_cast<const void*>(join_count_kernel<K>), lds_bytes);
     if (rc != hipSuccess) return rc;

@@ -58,7 +58,7 @@ __host__ __device__ constexpr int join_tile_words(int K, int LT) {
     return join_tiled(K, LT) ? (kWave * K * LT + 1) / 2 + 4 : 0;
 }
 
-// LDS of one query, in 32-bit words.  LT = 0: no rows are written (counting).
+// LDS of one query, in 32-bit words.
 // The filling launch puts a row at the place inside kRowsAlign rows that it has in the output: 32 ids
 // are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
 constexpr int kRowsAlign = 32;
@@ -91,9 +91,9 @@ __host__ __device__ constexpr JoinLds join_lds_layout(int K, int max_set, int LT
         at += 2 * o.mask01_words;
     }
     o.mask = at;  // even: the masks are read as 64-bit words
-    o.mask_words = LT > 0 ? join_mask_words(kRowsAlign - 1 + K * max_set) : 0;
+    o.mask_words = join_mask_words(kRowsAlign - 1 + K * max_set);
     at += 2 * o.mask_words;
-    o.tile_words = LT > 0 ? join_tile_words(K, LT) : 0;
+    o.tile_words = join_tile_words(K, LT);
     if (o.tile_words > 0) {
         at = (at + 3) & ~3;
         o.tile_words = (o.tile_words + 3) & ~3;
@@ -139,11 +139,11 @@ struct JoinTeam {
     }
 };
 
-// Union size of two lists by merge path and, with kFlags, the two bit masks of the union rows
+// Union size of two lists by merge path, and the two bit masks of the union rows
 // (bit first_bit + r of amask: list A holds the node of row r; bmask likewise).  The masks must be zero on
 // entry; they are complete after the next team sync.  kLong: a thread may have more than 64 rows
 // (the longest triples on one wavefront).
-template <bool kFlags, bool kMulti, bool kLong = false>
+template <bool kMulti, bool kLong = false>
 __device__ __forceinline__ int merge_path_union(const uint32_t* A, int nA, const uint32_t* B, int nB,
                                                 uint32_t* amask, uint32_t* bmask,
                                                 const JoinTeam<kMulti>& team, int first_bit = 0) {
@@ -177,29 +177,25 @@ __device__ __forceinline__ int merge_path_union(const uint32_t* A, int nA, const
     for (int d = d0; d < d1; ++d) {
         const bool take_a = (b >= nB) || (a < nA && va <= vb);
         if (take_a) {
-            if (kFlags) {
-                const uint64_t bit = 1ull << (n_emit & 63);
-                const bool both = b < nB && vb == va;
-                if (!kLong || n_emit < 64) {
-                    fa |= bit;
-                    if (both) fb |= bit;
-                } else {
-                    fa2 |= bit;
-                    if (both) fb2 |= bit;
-                }
+            const uint64_t bit = 1ull << (n_emit & 63);
+            const bool both = b < nB && vb == va;
+            if (!kLong || n_emit < 64) {
+                fa |= bit;
+                if (both) fb |= bit;
+            } else {
+                fa2 |= bit;
+                if (both) fb2 |= bit;
             }
             n_emit += 1;
             last_a = va;
             a += 1;
         } else {
             if (vb != last_a) {
-                if (kFlags) {
-                    const uint64_t bit = 1ull << (n_emit & 63);
-                    if (!kLong || n_emit < 64) {
-                        fb |= bit;
-                    } else {
-                        fb2 |= bit;
-                    }
+                const uint64_t bit = 1ull << (n_emit & 63);
+                if (!kLong || n_emit < 64) {
+                    fb |= bit;
+                } else {
+                    fb2 |= bit;
                 }
                 n_emit += 1;
             }
@@ -214,26 +210,24 @@ __device__ __forceinline__ int merge_path_union(const uint32_t* A, int nA, const
     }
     int n_out;
     const int row0 = first_bit + team.excl_sum(n_emit, &n_out);
-    if (kFlags) {
-        // the thread's rows start at row0: its bits go in there, as up to three 32-bit words
-        auto put = [&](uint32_t* mask, uint64_t bits, int first) {
-            if (bits == 0ull) return;
-            const int w = first >> 5;
-            const int sh = first & 31;
-            const uint64_t low = bits << sh;
-            const uint32_t w0 = (uint32_t)low;
-            const uint32_t w1 = (uint32_t)(low >> 32);
-            const uint32_t w2 = sh ? (uint32_t)(bits >> (64 - sh)) : 0u;
-            if (w0) atomicOr(mask + w, w0);
-            if (w1) atomicOr(mask + w + 1, w1);
-            if (w2) atomicOr(mask + w + 2, w2);
-        };
-        put(amask, fa, row0);
-        put(bmask, fb, row0);
-        if (kLong) {
-            put(amask, fa2, row0 + 64);
-            put(bmask, fb2, row0 + 64);
-        }
+    // the thread's rows start at row0: its bits go in there, as up to three 32-bit words
+    auto put = [&](uint32_t* mask, uint64_t bits, int first) {
+        if (bits == 0ull) return;
+        const int w = first >> 5;
+        const int sh = first & 31;
+        const uint64_t low = bits << sh;
+        const uint32_t w0 = (uint32_t)low;
+        const uint32_t w1 = (uint32_t)(low >> 32);
+        const uint32_t w2 = sh ? (uint32_t)(bits >> (64 - sh)) : 0u;
+        if (w0) atomicOr(mask + w, w0);
+        if (w1) atomicOr(mask + w + 1, w1);
+        if (w2) atomicOr(mask + w + 2, w2);
+    };
+    put(amask, fa, row0);
+    put(bmask, fb, row0);
+    if (kLong) {
+        put(amask, fa2, row0 + 64);
+        put(bmask, fb2, row0 + 64);
     }
     return n_out;
 }
@@ -335,10 +329,10 @@ __device__ __forceinline__ void materialize_union(const uint32_t* ids, int max_s
 }
 
 // Unites a query's lists.  `stage(dst, j)` puts list j into LDS at dst (the team's threads
-// together; no sync).  With kFlags the masks that join_write needs are left in LDS.  Returns the
+// together; no sync).  The masks that join_write needs are left in LDS.  Returns the
 // number of union rows (the same in every thread); the LDS contents are complete after the next
 // team sync.
-template <int K, bool kFlags, bool kMulti, typename Stage>
+template <int K, bool kMulti, typename Stage>
 __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, int max_set,
                                           JoinQuery<K>& jq, const JoinTeam<kMulti>& team,
                                           int first_bit, Stage&& stage) {
@@ -347,18 +341,17 @@ __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, in
     const int (&n)[K] = jq.n;
     stage(ids, 0);
     stage(ids + max_set, 1);
-    if constexpr (kFlags)
-        for (int t = team.tid(); t < 2 * lay.mask_words; t += team.threads()) mask[t] = 0u;
+    for (int t = team.tid(); t < 2 * lay.mask_words; t += team.threads()) mask[t] = 0u;
     if constexpr (K == 2) {
         team.sync();
-        return merge_path_union<kFlags, kMulti>(ids, n[0], ids + max_set, n[1], mask,
+        return merge_path_union<kMulti>(ids, n[0], ids + max_set, n[1], mask,
                                                 mask + lay.mask_words, team, first_bit);
     } else {
         uint32_t* mask01 = base + lay.mask01;
         uint32_t* u01 = base + lay.u01;
         for (int t = team.tid(); t < 2 * lay.mask01_words; t += team.threads()) mask01[t] = 0u;
         team.sync();
-        jq.n01 = merge_path_union<true, kMulti>(ids, n[0], ids + max_set, n[1], mask01,
+        jq.n01 = merge_path_union<kMulti>(ids, n[0], ids + max_set, n[1], mask01,
                                                 mask01 + lay.mask01_words, team);
         team.sync();
         materialize_union<kMulti>(ids, max_set, n[0], n[1], mask01, lay.mask01_words, jq.n01, u01,
@@ -366,10 +359,10 @@ __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, in
         team.sync();  // lists 0 and 1 are dead
         stage(ids, 2);
         team.sync();
-        if (kFlags && jq.n01 + n[2] > 64 * team.threads())
-            return merge_path_union<kFlags, kMulti, true>(u01, jq.n01, ids, n[2], mask,
+        if (jq.n01 + n[2] > 64 * team.threads())
+            return merge_path_union<kMulti, true>(u01, jq.n01, ids, n[2], mask,
                                                           mask + lay.mask_words, team, first_bit);
-        return merge_path_union<kFlags, kMulti>(u01, jq.n01, ids, n[2], mask,
+        return merge_path_union<kMulti>(u01, jq.n01, ids, n[2], mask,
                                                 mask + lay.mask_words, team, first_bit);
     }
 }
@@ -385,7 +378,7 @@ __device__ __forceinline__ void join_store(T* to, T value) {
     }
 }
 
-// Writes the n_out > 0 union rows of a query that join_unite<K, true> left in LDS (first_bit as
+// Writes the n_out > 0 union rows of a query that join_unite left in LDS (first_bit as
 // there) to rows [off, off + n_out) of the output; wave w of the team takes a contiguous share of
 // the rounds.
 template <int K, int LT, bool kMulti>

@@ -881,6 +881,32 @@ def test_join_fill_at_every_place_of_a_line(ctx, L, k):
 
 
 @pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("stride", [1, 3, 1 << 13, 1 << 17])
+def test_join_counts_of_lists_whose_ids_share_bits(ctx, stride, k):
+    # the counting launch looks ids up in a bit map of hashed ids first: ids next to each other, in
+    # even steps, and 2^24 apart (which share a bit), in lists around the 64 ids of a register, the
+    # 512 ids that the registers hold, and the largest
+    rng = np.random.default_rng(stride + k)
+    limit = (1 << 28) // stride - 1
+    far = (1 << 24) // stride
+    blocks = []
+    for size in (0, 1, 63, 64, 65, 200, 511, 512, 513, 1024, 2047, 2048):
+        span = min(4096, limit)
+        near = rng.choice(span, min(size, span), replace=False)
+        blocks.append(np.sort(near) * stride)
+        if far and size <= 512:  # every other id 2^24 further on
+            near = near + np.where(np.arange(near.size) % 2 == 1, far, 0)
+            blocks.append(np.unique(near) * stride)
+    table = hand_made_table(blocks, 2, rng)
+    queries = rng.integers(0, len(blocks), size=(4500, k)).astype(np.int32)
+    want = oracle.join_queries(*table, queries)
+    off = torch.empty(queries.shape[0] + 1, dtype=torch.int64, device="cuda")
+    rc, J = binding.join_count(ctx, dev(table[0]), dev(table[1]), dev(queries), 2048, off)
+    assert rc == binding.OK and ctx.check() == 0 and J == want[1].size
+    assert np.array_equal(off.cpu().numpy(), want[0])
+
+
+@pytest.mark.parametrize("k", [2, 3])
 def test_join_in_one_launch_of_the_largest_blocks_and_with_bounded_waits(ctx, k):
     # full blocks of 2048 rows; with no wait allowed at all a workgroup unites the lists that it
     # would have waited for itself: the offsets are right all the same
