@@ -29,6 +29,7 @@
 namespace surel {
 
 constexpr int kTableWords = kDirectWords + CollectTables::kHashed;
+constexpr int kWarmRows = 2 * kWave;
 // Rows of a wave's tile, the list of rows that wait for a look-up, and wavefronts of a workgroup,
 // which share the LDS tables (32 KB): as many as its LDS then holds.
 template <int LT>
@@ -37,27 +38,26 @@ struct Collect {
     static constexpr int kMaxL = LT == 0 ? 16 : LT;
     static constexpr int kTileWords = kRows * kMaxL / 2;
     static constexpr int kQuads = (kTileWords / 4 + kWave - 1) / kWave;  // 16-byte pieces a lane moves
-    static constexpr int kMisses = LT == 0 ? 0 : 3 * kWave;             // of four words each
-    static constexpr int kWaveWords = kTileWords + 4 * kMisses;
+    static constexpr int kMisses = LT == 0 ? 0 : kRows;         // of half a word each
+    static constexpr int kLate = LT == 0 ? 0 : 2 * kWave;       // of four words each
+    static constexpr int kWaveWords = kTileWords + kMisses / 2 + 4 * kLate;
     static constexpr int kFit = (160 * 1024 / 4 - kTableWords) / kWaveWords;
     static constexpr int kWaves = kFit < 16 ? kFit : 16;
 };
 
-// Rows whose vectors were not in the direct table, with their vectors (as pairs of counts, see
-// row_pairs): looked up together once a wavefront is full of them.  (Every workgroup meets every
-// vector of the set for the first time once, which is a trip to memory behind the counts on their
-// way: one trip per tile, 9 us a tile of 512 rows, or one per 64 such rows.)
+// Rows whose vectors no LDS table has, with their vectors (as pairs of counts, see row_pairs): looked
+// up in the global table together once there are 64 of them, for the look-up is a chain of trips to
+// memory behind the counts on their way.
 template <int LT>
-struct MissList {
+struct LateList {
     static constexpr int NW = (LT + 1) / 2;
+    static constexpr int kRoom = Collect<LT>::kLate;
     uint4* items;  // pairs 0 .. NW-1, row
     int n;
-    __device__ __forceinline__ void append(bool miss, const uint32_t (&pair)[NW], uint32_t row) {
-        const uint64_t all = __ballot(miss);
-        if (all == 0ull) return;
+    __device__ __forceinline__ void append(uint64_t all, bool mine, const uint32_t (&pair)[NW], uint32_t row) {
         const int before = (int)__builtin_amdgcn_mbcnt_hi(
             (uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
-        if (miss)
+        if (mine)
             items[n + before] = make_uint4(pair[0], NW > 1 ? pair[NW > 1 ? 1 : 0] : 0u,
                                            NW > 2 ? pair[NW > 2 ? 2 : 0] : 0u, row);
         n += __popcll(all);
@@ -78,8 +78,8 @@ struct MissList {
                 w[k] = (all[k] << 16) | (all[k] >> 16);
             }
             const bool small = DirectIndex<LT>::of(pair, &at);
-            const int32_t number = lookup_hashed<NW, CollectTables>(w, valid, cache + kDirectWords,
-                                                                     set, lane);
+            const int32_t number = lookup_hashed<NW, CollectTables>(w, hash_vector<NW>(w), valid,
+                                                                     cache + kDirectWords, set, lane);
             if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
             if (valid) *place(item.w) = number;
         }
@@ -88,21 +88,28 @@ struct MissList {
     }
 };
 
-// The rows of a whole tile, two neighbouring rows a lane: they are LT whole words, so the places of
-// their counts are known at compile time.  Stored unconditionally; the rows that the direct table
-// does not have are put right when the list is resolved.  first: number of the tile's first row in
-// the list.
-template <int LT, typename Place>
-__device__ __forceinline__ void tile_numbers(const uint32_t* tile, int lane, uint32_t first,
-                                             MissList<LT>& misses, uint32_t* cache,
-                                             const VectorSet& set, Place&& place) {
+// The numbers of the rows of a whole tile, two neighbouring rows a lane: they are LT whole words, so
+// the places of their counts are known at compile time.  Rows that the direct table does not have are
+// put on a list (misses) and looked up in the hashed cache; their numbers come back through the tile,
+// whose rows are dead then, so that the codes go out in whole lines.  Only rows that the cache does not
+// have either go on the list `late`, and out a second time when that is resolved (while it has room;
+// else the global table is asked at once).  first: number of the tile's first row there.
+// (With all rows that the direct table does not have on the late list, two in a hundred went out a
+// second time to a line that had left the caches: 2.6 M more writes beside 9.1 M, a fifth of the time.
+// With none on it, tables with many vectors waited for the global table in every tile.)
+template <int LT>
+__device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t first, uint16_t* misses,
+                                             LateList<LT>& late, uint32_t* cache, const VectorSet& set,
+                                             int32_t* __restrict__ code) {
     constexpr int NW = (LT + 1) / 2;
     constexpr int kRows = Collect<LT>::kRows;
-    struct __attribute__((packed, aligned(4))) two_t { int32_t v[2]; };
-    int32_t* code = place(first);
-#pragma unroll 1
-    for (int t0 = 0; t0 < kRows; t0 += 2 * kWave) {
-        const int t = t0 + 2 * lane;
+    constexpr int kTurns = kRows / (2 * kWave);
+    int32_t number[kTurns][2];
+    uint64_t missed[kTurns][2];
+    int n_miss = 0;
+#pragma unroll
+    for (int g = 0; g < kTurns; ++g) {
+        const int t = (g * kWave + lane) * 2;
         const uint32_t* from = tile + (t / 2) * LT;
         uint32_t raw[LT];
 #pragma unroll
@@ -119,30 +126,71 @@ __device__ __forceinline__ void tile_numbers(const uint32_t* tile, int lane, uin
                                         : raw[LT - 1] >> 16;
             }
         }
-        two_t number;
-        bool hit[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             uint32_t at;
             const bool small = DirectIndex<LT>::of(pair[h], &at);
             const uint32_t e = cache[at];
-            hit[h] = small && e != 0u;
-            number.v[h] = (int32_t)(e - 1u);
+            number[g][h] = (int32_t)(e - 1u);
+            missed[g][h] = __ballot(!(small && e != 0u));
+            append_misses(misses, n_miss, !(small && e != 0u), t + h);
         }
-        *reinterpret_cast<two_t*>(code + t) = number;
-        misses.append(!hit[0], pair[0], first + (uint32_t)t);
-        misses.append(!hit[1], pair[1], first + (uint32_t)t + 1u);
-        if (misses.n > kWave) misses.resolve(lane, cache, set, place);
+    }
+    uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile);
+    if (n_miss > 0) {
+        wave_sync();
+        for (int u0 = 0; u0 < n_miss; u0 += kWave) {
+            const bool valid = u0 + lane < n_miss;
+            const int t = (int)misses[valid ? u0 + lane : 0];
+            uint32_t pair[NW], w[NW], at;
+            row_pairs<NW>(tile, 0, kRows * LT / 2, t, LT, pair);
+            const bool small = DirectIndex<LT>::of(pair, &at);
+#pragma unroll
+            for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
+            const uint32_t hv = hash_vector<NW>(w);
+            int32_t found = cached_number<NW, CollectTables>(w, hv, cache + kDirectWords);
+            const bool unknown = valid && found < 0;
+            const uint64_t all = __ballot(unknown);
+            if (all != 0ull) {
+                if (late.n + __popcll(all) <= LateList<LT>::kRoom) {
+                    late.append(all, unknown, pair, first + (uint32_t)t);
+                } else {
+                    found = lookup_hashed<NW, CollectTables>(w, hv, valid, cache + kDirectWords, set, lane);
+                }
+            }
+            if (valid && small && found >= 0) cache[at] = (uint32_t)found + 1u;
+            if (valid) {
+                tile16[t * LT] = (uint16_t)(uint32_t)found;
+                tile16[t * LT + 1] = (uint16_t)((uint32_t)found >> 16);
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int g = 0; g < kTurns; ++g) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (missed[g][h] == 0ull) continue;
+                const uint16_t* row = tile16 + ((g * kWave + lane) * 2 + h) * LT;
+                const uint32_t found = (uint32_t)row[0] | (uint32_t)row[1] << 16;
+                number[g][h] = ((missed[g][h] >> lane) & 1ull) != 0ull ? (int32_t)found : number[g][h];
+            }
+        }
+    }
+    typedef int32_t two_t __attribute__((ext_vector_type(2), aligned(4)));
+#pragma unroll
+    for (int g = 0; g < kTurns; ++g) {
+        two_t* to = reinterpret_cast<two_t*>(code + (g * kWave + lane) * 2);
+        const two_t both = {number[g][0], number[g][1]};
+        __builtin_nontemporal_store(both, to);
     }
 }
 
 // A wavefront takes tiles of consecutive rows: they come in as contiguous 16-byte pieces (the next
 // tile's are on their way while one is looked up) and are read row by row from LDS.
-// What bounds it: waiting.  The waves wait 85 to 93 % of their cycles (four waves to a SIMD), vector
-// instructions take 9 to 22 % of the time and LDS 7 to 16 %: a wave's tile goes from memory to
-// registers, LDS, a look-up and out in one chain, and rows that the LDS tables do not know wait for
-// the global table besides.  138 M rows of 1M seeds with some 3,500 vectors 0.54 ms = 3.6 TB/s of
-// counts in and codes out; 97 M rows with 15,586 vectors 0.88 ms.
+// What bounds it: the stream of counts in and codes out.  146 M rows of 1M seeds with some 1,500
+// vectors 0.45 ms = 4.5 TB/s (0.53 with fix-ups in place of whole lines), 0.38 with no row looked up
+// anywhere but in the direct table; 97 M rows with 15,609 vectors 0.35 ms (0.81).  The tile's loads and
+// the codes' stores are in one straight line, so that a wait for the next tile is not one for the codes.
 template <int LT>
 __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(
     const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
@@ -166,43 +214,54 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
         const quad_t* from = reinterpret_cast<const quad_t*>(cnt + t * kRows * L);
 #pragma unroll
         for (int u = 0; u < kQuads; ++u)
-            if (u * kWave + lane < n_quads) next[u] = from[u * kWave + lane];
+            if (LT > 0 || u * kWave + lane < n_quads) next[u] = from[u * kWave + lane];
     };
     auto to_lds = [&]() {
         uint4* to = reinterpret_cast<uint4*>(tile);
 #pragma unroll
         for (int u = 0; u < kQuads; ++u)
-            if (u * kWave + lane < n_quads)
+            if (LT > 0 || u * kWave + lane < n_quads)
                 to[u * kWave + lane] = make_uint4(next[u].v[0], next[u].v[1], next[u].v[2], next[u].v[3]);
         wave_sync();
     };
+    uint16_t* misses = reinterpret_cast<uint16_t*>(tile + C::kTileWords);
+    LateList<LT == 0 ? 2 : LT> late{reinterpret_cast<uint4*>(tile + C::kTileWords + C::kMisses / 2), 0};
     // a wave's rows are numbered along its own tiles, so that 32 bits do for a table of any size
     const int64_t at0 = at;
     uint32_t first = 0;
     auto place = [&](uint32_t row) -> int32_t* {
         return code + (at0 + (int64_t)(row / kRows) * stride) * kRows + row % kRows;
     };
-    MissList<LT == 0 ? 2 : LT> misses{reinterpret_cast<uint4*>(tile + C::kTileWords), 0};
-    if (at < n_whole) fetch(at);
+    if (at < n_whole) {
+        fetch(at);
+        to_lds();
+    }
     // the first wave's first tile on its own: it fills the workgroup's tables with the common
     // vectors, for which the other waves then need not ask the global table all at once
     for (int turn = 0; turn < 2; ++turn) {
         if (turn == 1) __syncthreads();
         while (at < n_whole && (turn == 1 || wave == 0)) {
-            to_lds();
+            int32_t* out = code + at * kRows;
             at += stride;
             if (at < n_whole) fetch(at);
             if constexpr (LT > 0) {
-                tile_numbers<LT>(tile, lane, first, misses, cache, set, place);
+                // before anything is known all rows of a tile would go on the list: a few make most
+                // of the others known
+                if (turn == 0)
+                    rows_numbers<LT, CollectTables>(kWarmRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
+                                                     misses, cache, set, out);
+                tile_numbers<LT>(tile, lane, first, misses, late, cache, set, out);
+                if (late.n >= kWave) late.resolve(lane, cache, set, place);
             } else {
                 rows_numbers<0, CollectTables>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
-                                                nullptr, cache, set, place(first));
+                                                nullptr, cache, set, out);
             }
             first += kRows;
             wave_sync();
+            if (at < n_whole) to_lds();
             if (turn == 0) break;
         }
-        if constexpr (LT > 0) misses.resolve(lane, cache, set, place);
+        if constexpr (LT > 0) late.resolve(lane, cache, set, place);
     }
     // the rows behind the last whole tile
     const int rest = (int)(n_rows - n_whole * kRows);
@@ -210,9 +269,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
         uint16_t* tile16 = reinterpret_cast<uint16_t*>(tile);
         for (int t = lane; t < rest * L; t += kWave) tile16[t] = cnt[n_whole * kRows * L + t];
         wave_sync();
-        rows_numbers<LT, CollectTables>(rest, lane, L, tile16,
-                                         reinterpret_cast<uint16_t*>(tile + C::kTileWords), cache, set,
-                                         code + n_whole * kRows);
+        rows_numbers<LT, CollectTables>(rest, lane, L, tile16, misses, cache, set, code + n_whole * kRows);
     }
 }
 
@@ -355,7 +412,7 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const uint32_t* __restr
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_T) return;
     const uint32_t* item = list + i * kItemWords;
-    ranks[slots[(size_t)item[kMaxVecWords] * kSlotWords + 1]] = (uint32_t)i;
+    ranks[slots[(size_t)item[kMaxVecWords] * kSlotWords + kSlotNumber]] = (uint32_t)i;
     for (int e = 0; e < L; ++e) {
         const uint32_t word = item[e >> 1];
         T[i * L + e] = (uint16_t)((e & 1) ? (word & 0xFFFFu) : (word >> 16));

@@ -1,6 +1,6 @@
 // The hash set of distinct count vectors behind the pruning of the central RPE array (Sec. 3.3;
 // Algorithm 1, last step), shared by the stand-alone pruning kernels and the fused walk + RPE
-// kernel when it emits RPE-IDs: a global open-addressing table of 64-byte slots (state, number,
+// kernel when it emits RPE-IDs: a global open-addressing table of 64-byte slots (state with number,
 // vector in one cache line) with small per-workgroup tables in LDS in front of it.  A vector is NW
 // 32-bit words, entry 2k of the count vector in the upper half of word k, so that comparing words
 // in order compares the counts in order.  The vectors of the set are numbered in the order in
@@ -13,9 +13,13 @@
 
 namespace surel {
 
-constexpr uint32_t kSlotEmpty = 0u, kSlotLocked = 1u, kSlotFull = 2u;
-constexpr int kSlotWords = 16;    // 64-byte slots: [0] state, [1] number, [2..3] unused, [4..11] vector
-constexpr int kSlotVector = 4;    // first word of the vector inside a slot
+// 64-byte slots: [0] state (empty, locked, or full with the vector's number), [1..8] vector, [9] the
+// number once more, which stays when the slot is emptied.  A vector of up to three words is found with
+// ONE load of 16 bytes: a look-up is one trip to memory, not three (state, vector, number).
+constexpr uint32_t kSlotEmpty = 0u, kSlotLocked = 1u, kSlotFull = 0x80000000u;
+constexpr int kSlotWords = 16;
+constexpr int kSlotVector = 1;
+constexpr int kSlotNumber = kSlotVector + 8;
 constexpr int kMaxVecWords = 8;   // m + 1 <= 16 counts of 16 bits
 constexpr int kItemWords = kMaxVecWords + 1;  // a member of the set: its vector, zeros, its slot
 
@@ -55,10 +59,19 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
     for (uint32_t probe = 0; probe <= set.slot_mask;) {
         uint32_t* slot = set.slots + (size_t)h * kSlotWords;
         // a slot that reads as full is final, and all of it lies in the same cache line
-        uint32_t st = slot[0];
-        if (st != kSlotFull) {
-            st = atomicCAS(slot, kSlotEmpty, kSlotLocked);
-            if (st == kSlotEmpty) {
+        const uint4 head = *reinterpret_cast<const uint4*>(slot);
+        uint32_t st = head.x;
+        uint32_t first[3] = {head.y, head.z, head.w};
+        const bool plain = (st & kSlotFull) != 0u;
+        if (!plain) {
+            // empty, locked, or a stale line (a die's L2 keeps a slot as it was when its neighbour was
+            // asked for): it is read past the caches, and locked only if it is free (additions to one
+            // address are served one after the other)
+            const uint64_t* words = reinterpret_cast<const uint64_t*>(slot);
+            const uint64_t a = __hip_atomic_load(words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t b = __hip_atomic_load(words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            st = (uint32_t)a;
+            if (st == kSlotEmpty && atomicCAS(slot, kSlotEmpty, kSlotLocked) == kSlotEmpty) {
                 // this lane owns the slot: is there still room in T?
                 const unsigned long long number = atomicAdd(set.counters, 1ull);
                 if ((int64_t)number >= set.cap_T) {
@@ -70,15 +83,20 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                     item[kMaxVecWords] = h;
                     set.ranks[number] = 0u;
                 }
-                __hip_atomic_store(slot + 1, (uint32_t)number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                slot[kSlotNumber] = (uint32_t)number;
 #pragma unroll
                 for (int k = 0; k < NW; ++k)
                     __hip_atomic_store(slot + kSlotVector + k, w[k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(slot, kSlotFull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                // The vector is written past the caches, so "full" may follow as soon as that is
+                // done.  (A release here writes back what the die's L2 holds, for every new vector:
+                // 97 M rows with 15,609 vectors took 0.79 ms, 0.37 without it.)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __hip_atomic_store(slot, kSlotFull | (uint32_t)number, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
                 return (int32_t)number;
             }
-            if (st == kSlotLocked) {
+            if ((st & kSlotFull) == 0u) {
                 // somebody is writing this slot's vector: look again
                 if (++spins > set.spin_limit) {
                     atomicOr(set.err, kDevStall);
@@ -88,20 +106,23 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                 __builtin_amdgcn_s_sleep(1);
                 continue;
             }
-            // full, but the plain load may have come from a stale line: read past it
-            bool same = true;
-#pragma unroll
-            for (int k = 0; k < NW; ++k)
-                same = same && __hip_atomic_load(slot + kSlotVector + k, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT) == w[k];
-            if (same)
-                return (int32_t)__hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            bool same = true;
-#pragma unroll
-            for (int k = 0; k < NW; ++k) same = same && slot[kSlotVector + k] == w[k];
-            if (same) return (int32_t)slot[1];
+            first[0] = (uint32_t)(a >> 32), first[1] = (uint32_t)b, first[2] = (uint32_t)(b >> 32);
         }
+        auto word_past_caches = [&](int k) {
+            return __hip_atomic_load(slot + kSlotVector + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        bool same = true;
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            same = same && (k < 3 ? first[k < 3 ? k : 0] : plain ? slot[kSlotVector + k] : word_past_caches(k)) == w[k];
+        // Another vector, or words that were read before they were written: only what is read after the
+        // slot was seen to be full decides.  (Hardly a vector meets another one's slot.)
+        if (!same) {
+            same = true;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) same = same && word_past_caches(k) == w[k];
+        }
+        if (same) return (int32_t)(st & ~kSlotFull);
         h = (h + 1u) & set.slot_mask;
         probe += 1;
     }
@@ -121,13 +142,13 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
 // Longer vectors have one cache with entries of as many words as they need.
 constexpr int kDirectWords = 4096;
 // kHashed: words of the hashed cache, a power of two.  (One or two rows in a hundred come here, some
-// 400 to 1,300 different vectors; one that finds its entry taken is a trip to memory every time.)
+// 400 to 15,000 different vectors; one that finds both its entries taken is a trip to memory every time.)
 // kLonely: see find_or_insert_shared.  Pruning 4 M rows of a table of 4,096 vectors that occur equally
-// often took 0.56 ms at m = 14 and 0.32 at m = 4 with a turn for every vector of a wave, 0.24 and 0.14
-// with 4 lonely ones (of 1,024 vectors 0.43 and 0.23 against 0.19 and 0.11); a walk's own table, 138 M
-// rows with some 3,500 vectors, takes 0.78 ms with both, and 0.82 if the loop ends after two turns
-// whatever they find.  The fused kernel has its waves at different places and little to gain: 31.6 M
-// rows of m = 9 with 28,498 vectors 2.18 ms with a turn for every vector, 2.21 with 4 lonely ones.
+// often took 0.56 ms at m = 14 and 0.32 at m = 4 with a turn for every vector of a wave, 0.18 and 0.13
+// with 4 lonely ones (of 1,024 vectors 0.43 and 0.22 against 0.17 and 0.12); a walk's own table, 146 M
+// rows with some 1,500 vectors, takes 0.69 ms with both.  The fused kernel has its waves at different
+// places and little to gain: 99,991 seeds of M = 61, m = 9 take 0.93 ms with a
+// turn for every vector, 0.94 with 4 lonely ones (1.27 when every new vector wrote an L2 back).
 struct FusedTables {
     static constexpr int kHashed = 4096;  // 16 KB beside the rows of 16 waves
     static constexpr int kLonely = kWave;
@@ -196,30 +217,54 @@ __device__ __forceinline__ int32_t find_or_insert_shared(const uint32_t (&w)[NW]
 // not yet there, the comparison fails and the lane asks the global table, which is slower and
 // right; a valid entry never changes again.
 constexpr uint32_t kPackedValid = 0x80000000u;
+template <int NW>
+__host__ __device__ constexpr int packed_words() { return NW == 1 ? 2 : 4; }
 template <int NW, typename Tables>
-__device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool valid, uint32_t* cache,
-                                                 const VectorSet& set, int lane) {
+__device__ __forceinline__ uint32_t* packed_pair(uint32_t hv, uint32_t* cache) {
     static_assert(NW >= 1 && NW <= 3, "packed cache entries hold up to three words");
-    constexpr int EW = NW == 1 ? 2 : 4;
-    const uint32_t hv = hash_vector<NW>(w);
-    uint32_t* entry = cache + ((hv >> 18) & (uint32_t)(Tables::kHashed / EW - 1)) * EW;
-    uint32_t e[4] = {0u, 0u, 0u, 0u};
-    if constexpr (EW == 2) {
-        const uint2 v = *reinterpret_cast<const uint2*>(entry);
-        e[0] = v.x, e[1] = v.y;
-    } else {
-        const uint4 v = *reinterpret_cast<const uint4*>(entry);
-        e[0] = v.x, e[1] = v.y, e[2] = v.z, e[3] = v.w;
-    }
-    bool hit = valid && (e[0] & kPackedValid) != 0u;
+    constexpr int EW = packed_words<NW>();
+    return cache + ((hv >> 18) & (uint32_t)(Tables::kHashed / EW / 2 - 1)) * (2 * EW);
+}
+
+// The number of vector w from the cache alone, -1 if it is not there.
+template <int NW, typename Tables>
+__device__ __forceinline__ int32_t cached_number(const uint32_t (&w)[NW], uint32_t hv, uint32_t* cache) {
+    constexpr int EW = packed_words<NW>();
+    const uint32_t* pair = packed_pair<NW, Tables>(hv, cache);
+    int32_t number = -1;
 #pragma unroll
-    for (int k = 0; k < NW; ++k) hit = hit && e[1 + k] == w[k];
-    const bool miss = valid && !hit;
-    int32_t number = hit ? (int32_t)(e[0] & ~kPackedValid) : -1;
+    for (int place = 0; place < 2; ++place) {
+        uint32_t e[4] = {0u, 0u, 0u, 0u};
+        if constexpr (EW == 2) {
+            const uint2 v = reinterpret_cast<const uint2*>(pair)[place];
+            e[0] = v.x, e[1] = v.y;
+        } else {
+            const uint4 v = reinterpret_cast<const uint4*>(pair)[place];
+            e[0] = v.x, e[1] = v.y, e[2] = v.z, e[3] = v.w;
+        }
+        bool same = (e[0] & kPackedValid) != 0u;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) same = same && e[1 + k] == w[k];
+        number = same ? (int32_t)(e[0] & ~kPackedValid) : number;
+    }
+    return number;
+}
+
+template <int NW, typename Tables>
+__device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], uint32_t hv, bool valid,
+                                                 uint32_t* cache, const VectorSet& set, int lane) {
+    int32_t number = cached_number<NW, Tables>(w, hv, cache);
+    const bool miss = valid && number < 0;
     if (__ballot(miss) != 0ull) {
         const int32_t found = find_or_insert_shared<NW, Tables>(w, hv & set.slot_mask, miss, set, lane);
         if (miss) number = found;
-        if (miss && found >= 0 && atomicCAS(entry, 0u, 1u) == 0u) {
+        uint32_t* entry = packed_pair<NW, Tables>(hv, cache);
+        bool taken = miss && found >= 0;
+        if (taken && atomicCAS(entry, 0u, 1u) != 0u) {
+            entry += packed_words<NW>();
+            taken = atomicCAS(entry, 0u, 1u) == 0u;
+        }
+        if (taken) {
 #pragma unroll
             for (int k = 0; k < NW; ++k) entry[1 + k] = w[k];
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -227,7 +272,7 @@ __device__ __forceinline__ int32_t lookup_hashed(const uint32_t (&w)[NW], bool v
                                __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
-    return number;
+    return valid ? number : -1;
 }
 
 // The same for vectors of nw <= kMaxVecWords words (the others zero): entries of 2 + nw words
@@ -297,7 +342,8 @@ __device__ __forceinline__ void resolve_misses(const uint16_t* misses, int n_mis
         const bool small = DirectIndex<LT>::of(pair, &at);
 #pragma unroll
         for (int k = 0; k < NW; ++k) w[k] = (pair[k] << 16) | (pair[k] >> 16);
-        const int32_t number = lookup_hashed<NW, Tables>(w, valid, cache + kDirectWords, set, lane);
+        const int32_t number =
+            lookup_hashed<NW, Tables>(w, hash_vector<NW>(w), valid, cache + kDirectWords, set, lane);
         if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
         if (valid) code[t] = number;
     }

@@ -563,6 +563,29 @@ def test_prune_of_many_distinct_vectors(ctx, L, n_T):
         assert np.array_equal(host_u16(T), want_T) and np.array_equal(code.cpu().numpy(), want_code)
 
 
+@pytest.mark.parametrize("L", [2, 3, 5, 6, 10])
+@pytest.mark.parametrize("n_rows,n_T,most", [(1, 1, 3), (127, 9, 3), (512, 512, 200), (513, 40, 3),
+                                             (3_000_003, 300, 7), (3_000_003, 1500, 90),
+                                             (2_200_000, 40_000, 300)])
+def test_prune_lists_of_rows_that_wait_for_a_look_up(ctx, L, n_rows, n_T, most):
+    # around a tile of 512 rows and the rows looked up first; tables whose rows the direct table knows,
+    # the hashed cache knows, or neither, so that the list of late rows fills, is emptied over several
+    # tiles, and has no room: T is sorted and distinct, and every row's code names its vector
+    g = torch.Generator(device="cuda").manual_seed(n_rows + L)
+    vectors = torch.randint(0, most + 1, (4 * n_T, L), device="cuda", generator=g)
+    vectors[::2, 0] = 0
+    vectors = torch.unique(vectors, dim=0)
+    vectors = vectors[torch.randperm(vectors.shape[0], device="cuda", generator=g)[:n_T]]
+    # common ones and rare ones
+    pick = (torch.rand(n_rows, device="cuda", generator=g) ** 3 * vectors.shape[0]).long()
+    cnt = vectors[pick].to(torch.int16).contiguous().view(torch.uint16)
+    T, code = binding.prune_rpe(ctx, cnt, cap_T=1 << 18)
+    assert ctx.check() == 0
+    want = torch.unique(vectors[torch.unique(pick)], dim=0)  # sorted entry by entry
+    assert torch.equal(T.view(torch.int16).long(), want)
+    assert torch.equal(T.view(torch.int16)[code.long()], cnt.view(torch.int16))
+
+
 def test_one_call_rpe_ids_of_many_distinct_vectors(ctx):
     # every node is visited several times at every step, so hardly two rows are the same
     wl = synth.Workload("t", "rmat", 256, 5000, 0.0, 128, 15, 0, 2, "uniform", graph_seed=3)
