@@ -27,6 +27,7 @@ struct EdgeRecords {
     const void* data = nullptr;  // null: no records, the walk reads the CSR
     int format = 0;
     int id_bits = 0, lo_bits = 0;  // field widths of the packed layout
+    int id_bytes = 0;              // of the short layout
 };
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m);
 EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges);

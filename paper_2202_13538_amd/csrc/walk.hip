@@ -57,15 +57,6 @@ __global__ void row_group_kernel(const int32_t* __restrict__ row_ptr, int32_t n_
     groups[g] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Both ends of node t's row in one load.
-__device__ __forceinline__ void row_ends(const int32_t* __restrict__ row_ptr, uint32_t t, int32_t* lo,
-                                         int32_t* hi) {
-    typedef int ends_t __attribute__((ext_vector_type(2), aligned(4)));
-    const ends_t ends = *reinterpret_cast<const ends_t*>(row_ptr + t);
-    *lo = ends.x;
-    *hi = ends.y;
-}
-
 // The record of every CSR entry e (layouts in walk_core.h): the neighbour col_idx[e], the start
 // of its row and its degree; an entry that names no node, or whose row is malformed, gets the
 // layout's "bad entry" id (the walker will stay in place and flag it).
@@ -83,7 +74,7 @@ constexpr int kRecordItems = 4;  // entries of a thread, all their look-ups in f
 template <int kRec, bool kGroups>
 __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n_nodes,
-    int64_t n_edges, int id_bits, int lo_bits, const uint4* __restrict__ groups,
+    int64_t n_edges, int id_bits, int lo_bits, int id_bytes, const uint4* __restrict__ groups,
     void* __restrict__ rec) {
     const int64_t e0 = (int64_t)blockIdx.x * (kRecordThreads * kRecordItems) + threadIdx.x;
     uint32_t t[kRecordItems];
@@ -136,6 +127,12 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
         if (kRec == kRecWide) {
             static_cast<int4*>(rec)[e] =
                 ok ? make_int4((int)t[u], lo[u], hi[u] - lo[u], 0) : make_int4(-1, 0, 0, 0);
+        } else if (kRec == kRecShort) {
+            const uint32_t r = ok ? t[u] : (uint32_t)n_nodes;
+            uint8_t* to = static_cast<uint8_t*>(rec) + e * id_bytes;
+            to[0] = (uint8_t)r;
+            to[1] = (uint8_t)(r >> 8);
+            if (id_bytes == 3) to[2] = (uint8_t)(r >> 16);
         } else {
             const uint32_t deg_big = (1u << rec_degree_bits(id_bits, lo_bits)) - 1u;
             unsigned long long r = (unsigned long long)(uint32_t)n_nodes;  // bad entry
@@ -152,7 +149,7 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
 template <bool kCount, int kRec>
 __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const void* __restrict__ rec, int id_bits, int lo_bits, int32_t n_nodes, int64_t n_edges,
+    const void* __restrict__ rec, int id_bits, int lo_bits, int id_bytes, int32_t n_nodes, int64_t n_edges,
     const int32_t* __restrict__ seeds, int64_t n_seeds, int32_t M, int32_t m, uint32_t key0,
     uint32_t key1, int32_t* __restrict__ walks, int32_t* __restrict__ set_sizes, int32_t slots,
     uint32_t* __restrict__ err) {
@@ -186,7 +183,7 @@ __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
         n_distinct = distinct_insert(table, slots, (uint32_t)u, lane == 0);
     }
 
-    const WalkGraph g{row_ptr, col_idx, rec, id_bits, lo_bits, n_nodes, n_edges};
+    const WalkGraph g{row_ptr, col_idx, rec, id_bits, lo_bits, id_bytes, n_nodes, n_edges};
     int32_t u_lo, u_deg;
     bool bad_graph = seed_row(g, u, &u_lo, &u_deg);
     for (int w0 = 0; w0 < M; w0 += kWalkChains * kWave) {
@@ -225,6 +222,22 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
     return b;
 }
 
+// Whether records are the ids alone: where row_ptr, a quarter of a 4 MB L2 at most, leaves the L2 to
+// them and packed records are at least twice as large as it.  Walks + RPE (M = 100, m = 4 where nothing
+// else is said), us, packed / short:
+//    30,000 nodes   0.6 M entries, M = 200   193 /   195     1.2 M            130 /   114
+//    60,000 nodes   0.6 M, M = 200           302 /   307     4.8 M, M = 200   671 /   485
+//   100,000 nodes   1.2 M                    326 /   324     1.6 M, m = 9     742 /   562
+//                   8 M, M = 200           1,154 / 1,034
+//   235,000 nodes   2.6 M, M = 200         1,538 / 1,450     16 M, M = 200  2,721 / 2,668
+//   300,000 nodes   4.8 M, M = 50            711 /   707
+//   350,000 nodes   7 M, M = 50              881 /   903
+//   500,000 nodes   2 M, M = 50              950 /   989     6 M, M = 50    1,108 / 1,198
+// (Entries are addressed with 24 bits.)
+static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges) {
+    return n_nodes <= 1 << 18 && n_edges >= 1 << 20 && n_edges < 1 << 24;
+}
+
 EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     EdgeRecords plan;
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
@@ -232,8 +245,12 @@ EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
     // small graphs the packed array fits more of its lines into the L2s.)
     plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
+    if (rows_beside_short_records(n_nodes, n_edges)) {
+        plan.format = kRecShort;
+        plan.id_bytes = plan.id_bits <= 16 ? 2 : 3;
+    }
     // the degree lies in the word's upper half
-    if (plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
+    if (plan.format == kRecPacked && plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
     return plan;
 }
 
@@ -255,7 +272,10 @@ static bool rows_in_groups(int32_t n_nodes, int64_t n_edges) {
 }
 
 static size_t record_array_bytes(const EdgeRecords& plan, int64_t n_edges) {
-    return ((size_t)n_edges * (plan.format == kRecPacked ? 8 : 16) + 15) & ~(size_t)15;
+    const size_t bytes = plan.format == kRecShort ? plan.id_bytes : plan.format == kRecPacked ? 8 : 16;
+    // short records are read as words: the last one's word may end behind it
+    const size_t behind = plan.format == kRecShort ? 2 : 0;
+    return ((size_t)n_edges * bytes + behind + 15) & ~(size_t)15;
 }
 
 size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges) {
@@ -280,7 +300,7 @@ static hipError_t launch_walks_cfg(hipStream_t stream, const int32_t* row_ptr,
     }
     hipLaunchKernelGGL((walk_kernel<kCount, kRec>), dim3((unsigned)blocks),
                        dim3(kWalkWavesPerBlock * kWave), lds_bytes, stream, row_ptr, col_idx,
-                       rec.data, rec.id_bits, rec.lo_bits, n_nodes, n_edges, seeds, n_seeds, M, m,
+                       rec.data, rec.id_bits, rec.lo_bits, rec.id_bytes, n_nodes, n_edges, seeds, n_seeds, M, m,
                        (uint32_t)(rng_seed & 0xFFFFFFFFull), (uint32_t)(rng_seed >> 32), walks,
                        set_sizes, slots, err);
     return hipGetLastError();
@@ -299,11 +319,13 @@ hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const
         row_group_kernel<<<dim3((unsigned)((n_groups + 63) / 64)), dim3(64), 0, stream>>>(
             row_ptr, n_nodes, n_edges, groups);
     }
-    const auto kernel = rec.format == kRecPacked
+    const auto kernel = rec.format == kRecShort
+                            ? (groups ? edge_record_kernel<kRecShort, true> : edge_record_kernel<kRecShort, false>)
+                        : rec.format == kRecPacked
                             ? (groups ? edge_record_kernel<kRecPacked, true> : edge_record_kernel<kRecPacked, false>)
                             : (groups ? edge_record_kernel<kRecWide, true> : edge_record_kernel<kRecWide, false>);
     kernel<<<grid, block, 0, stream>>>(row_ptr, col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits,
-                                       groups, data);
+                                       rec.id_bytes, groups, data);
     return hipGetLastError();
 }
 
@@ -317,6 +339,7 @@ static hipError_t launch_walks_c(hipStream_t stream, const int32_t* row_ptr, con
     stream, row_ptr, col_idx, rec, n_nodes, n_edges, seeds, n_seeds, M, m, rng_seed, walks, set_sizes, err
     if (rec.data == nullptr) return launch_walks_cfg<kCount, kRecNone>(SUREL_WALK_ARGS);
     if (rec.format == kRecPacked) return launch_walks_cfg<kCount, kRecPacked>(SUREL_WALK_ARGS);
+    if (rec.format == kRecShort) return launch_walks_cfg<kCount, kRecShort>(SUREL_WALK_ARGS);
     return launch_walks_cfg<kCount, kRecWide>(SUREL_WALK_ARGS);
 }
 

@@ -8,15 +8,20 @@ namespace surel {
 
 // Per-edge neighbour records: one record per CSR entry e with the neighbour col_idx[e], the start
 // of that neighbour's row and its degree, so that a step is one gather instead of two dependent
-// ones.  Two layouts:
+// ones.  Three layouts:
 //   kRecPacked  one 64-bit word, id in the low id_bits, row start in the next lo_bits, degree in
 //               the rest; id = n_nodes marks a bad entry, a degree field of all ones means "does
 //               not fit, it is row_ptr[id + 1] - row start".  id_bits + lo_bits >= 32: the degree
 //               lies in the upper half of the word;
 //   kRecWide    int4 (id, row start, degree, 0); id -1 for an entry that names no node or whose
 //               row is malformed: for graphs whose ids and row starts leave the packed degree too
-//               few bits.
-constexpr int kRecNone = 0, kRecWide = 1, kRecPacked = 2;
+//               few bits;
+//   kRecShort   the id alone, in id_bytes = 2 or 3 bytes, n_nodes marking a bad entry; the row is
+//               looked up in row_ptr after all, except behind the last step.  For graphs of so few
+//               nodes that row_ptr lies in every L2, and so many entries that packed records do not:
+//               a line from memory carries 43 or 64 neighbours instead of 16, and a larger part of
+//               the array stays in the L2 (see edge_record_plan).
+constexpr int kRecNone = 0, kRecWide = 1, kRecPacked = 2, kRecShort = 3;
 
 // Bits of the degree field of a packed record: what the two other fields leave, 31 at most.
 __host__ __device__ constexpr int rec_degree_bits(int id_bits, int lo_bits) {
@@ -28,10 +33,20 @@ struct WalkGraph {
     const int32_t* __restrict__ row_ptr;
     const int32_t* __restrict__ col_idx;
     const void* __restrict__ rec;
-    int id_bits, lo_bits;  // kRecPacked only
+    int id_bits, lo_bits;  // kRecPacked; kRecShort: id_bits only
+    int id_bytes;          // kRecShort
     int32_t n_nodes;
     int64_t n_edges;
 };
+
+// Both ends of node t's row in one load.
+__device__ __forceinline__ void row_ends(const int32_t* __restrict__ row_ptr, uint32_t t, int32_t* lo,
+                                         int32_t* hi) {
+    typedef int ends_t __attribute__((ext_vector_type(2), aligned(4)));
+    const ends_t ends = *reinterpret_cast<const ends_t*>(row_ptr + t);
+    *lo = ends.x;
+    *hi = ends.y;
+}
 
 // Row of the seed (wave-uniform loads); a malformed row counts as degree 0.
 __device__ __forceinline__ bool seed_row(const WalkGraph& g, int32_t u, int32_t* lo, int32_t* deg) {
@@ -99,6 +114,28 @@ __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t
                             id[c] = (uint32_t)nb[c].x;  // -1: not below n_nodes
                             lo[c] = (uint32_t)nb[c].y;
                             deg[c] = (uint32_t)nb[c].z;
+                        }
+                    } else if (kRec == kRecShort) {
+                        const char* rec = static_cast<const char*>(g.rec);
+                        const uint32_t id_mask = (1u << g.id_bits) - 1u;
+                        struct __attribute__((packed)) word_t { uint32_t v; };
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const uint32_t at = (uint32_t)__umul24(e[c], (uint32_t)g.id_bytes);
+                            id[c] = reinterpret_cast<const word_t*>(rec + at)->v & id_mask;
+                        }
+#pragma unroll
+                        for (int c = 0; c < C; ++c) lo[c] = deg[c] = 0u;
+                        if (s < m) {  // nobody steps on from the last node
+                            int32_t first[C], end[C];
+#pragma unroll
+                            for (int c = 0; c < C; ++c)
+                                row_ends(g.row_ptr, min(id[c], (uint32_t)g.n_nodes - 1u), &first[c], &end[c]);
+#pragma unroll
+                            for (int c = 0; c < C; ++c) {
+                                lo[c] = (uint32_t)first[c];
+                                deg[c] = (uint32_t)(end[c] - first[c]);
+                            }
                         }
                     } else {
                         const uint2* rec = static_cast<const uint2*>(g.rec);

@@ -179,6 +179,7 @@ static hipError_t launch_walk_rpe_e(hipStream_t stream, int max_lds_bytes, int n
                : launch_walk_rpe_erc<E, REC_, false>(stream, max_lds_bytes, n_cu, f, lb, code, set)
     if (f.g.rec == nullptr) SUREL_WR_CASE(kRecNone);
     if (rec_format == kRecPacked) SUREL_WR_CASE(kRecPacked);
+    if (rec_format == kRecShort) SUREL_WR_CASE(kRecShort);
     SUREL_WR_CASE(kRecWide);
 #undef SUREL_WR_CASE
 }

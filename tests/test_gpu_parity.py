@@ -1269,6 +1269,49 @@ def test_one_call_rpe_ids_capacity(ctx):
     assert rc == binding.OK and rows == 0 and got_T == 0 and int(off[0]) == 0
 
 
+@pytest.mark.parametrize("n_nodes, n_edges, malformed", [
+    (65_535, 1 << 20, False), (65_536, 1 << 20, False), (1 << 18, (1 << 20) + 5, False),
+    ((1 << 18) + 1, 1 << 20, False), (65_535, (1 << 20) - 1, False), (1500, (1 << 20) + 3, False),
+    (65_535, 1 << 20, True), (200_000, 1 << 20, True), (30_000, (1 << 24) - 1, False),
+    (30_000, 1 << 24, False)])
+def test_short_edge_records(ctx, n_nodes, n_edges, malformed):
+    # records that are ids of 2 or 3 bytes, on both sides of every line between them and the packed
+    # ones: uneven degrees, empty rows, a hub, entries and rows that are malformed
+    rng = np.random.default_rng(n_nodes + n_edges)
+    cuts = np.sort((rng.random(n_nodes - 1) ** 2 * (n_edges + 1)).astype(np.int64))
+    rp = np.concatenate([[0], cuts, [n_edges]]).astype(np.int32)
+    ci = rng.integers(0, n_nodes, size=n_edges).astype(np.int32)
+    ci[-3:] = n_nodes - 1  # the last entries, whose words end behind the array
+    M, m = 120, 5
+    n_seeds = 9000 if n_edges < 1 << 23 else 34_953 * 4
+    seeds = rng.integers(0, n_nodes, size=n_seeds).astype(np.int32)
+    seeds[:9] = n_nodes - 1
+    assert n_seeds * M * (m - 1) >= 4 * n_edges  # enough steps to make the records
+    d_rp, d_ci, d_seeds = dev(rp), dev(ci), dev(seeds)
+    if malformed:
+        rp, ci = rp.copy(), ci.copy()
+        rp[n_nodes // 3] = -5
+        ci[::101] = n_nodes + rng.integers(0, 1000, size=ci[::101].size)
+        ci[1::101] = n_nodes // 3
+        d_rp, d_ci = dev(rp), dev(ci)
+        w = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 3)
+        assert ctx.check() == binding.DEV_BAD_GRAPH
+        f = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 3)[0]
+        assert ctx.check() == binding.DEV_BAD_GRAPH
+        assert torch.equal(f, w) and bool(((w >= 0) & (w < n_nodes)).all())
+        # a malformed row is never followed
+        walks, lo, hi = w.cpu().numpy(), rp[:-1], rp[1:]
+        at, moved = walks[:, :, :-1], walks[:, :, 1:] != walks[:, :, :-1]
+        assert moved.any() and not (moved & ((lo[at] < 0) | (hi[at] < lo[at]))).any()
+        return
+    w = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 3)
+    f = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 3)[0]
+    assert ctx.check() == 0
+    n = 4000
+    assert torch.equal(f, w)
+    assert np.array_equal(w[:n].cpu().numpy(), oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
+
+
 @pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
                                            ((1 << 18) + 11, False), (1 << 18, True),
                                            ((5 << 18) - 1, False), (5 << 18, False),
