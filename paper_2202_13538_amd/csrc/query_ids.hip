@@ -15,8 +15,9 @@
 // no directory.
 // What bounds it: LDS reads at random places (a wavefront's 64 lanes hit some banks four or five
 // times) and the instructions around them, so that waves in flight are what counts: 65,536 pairs of
-// M = 200, m = 4 with codes take 0.44 ms (4.9 TB/s of the bytes in and out) with eight waves per
-// SIMD, 0.50 with five; twice as many parts, 0.55; a wave per query with bisection, 1.22.
+// M = 200, m = 4 with codes take 0.43 ms (5.0 TB/s of the bytes in and out; 0.46 when the results
+// went through the caches) with eight waves per SIMD, 0.50 with five; twice as many parts, 0.55; a
+// wave per query with bisection, 1.22.
 // (Per-query hash dictionaries in LDS were measured too and lost: their probe loops diverge.)
 #include "device_util.h"
 #include "kernels.h"
@@ -25,8 +26,8 @@ namespace surel {
 
 // The K row indices of one walk entry (4-byte aligned, written with one store).
 template <int K>
-struct __attribute__((aligned(4))) RowIds {
-    int32_t v[K];
+struct RowIds {
+    typedef int32_t type __attribute__((ext_vector_type(K), aligned(4)));
 };
 
 constexpr int kCrowd = 8;  // ids in one part of the directory, at most
@@ -237,19 +238,21 @@ __global__ __launch_bounds__(256, 8) void query_ids_kernel(
 #pragma unroll
                 for (int e = 0; e < kQiEntries; ++e) {
                     const int t = t0 + e * T + tid;
-                    RowIds<K> row;
+                    typename RowIds<K>::type row;
 #pragma unroll
                     for (int j2 = 0; j2 < K; ++j2) {
                         const bool found = at[e][j2] == x[e];
                         if constexpr (kCode) {
-                            row.v[j2] = -1;
-                            if (found) row.v[j2] = (int32_t)lds32[lay.codes + j2 * lay.list + pos[e][j2]];
+                            row[j2] = -1;
+                            if (found) row[j2] = (int32_t)lds32[lay.codes + j2 * lay.list + pos[e][j2]];
                         } else {
-                            row.v[j2] = found ? (int32_t)((uint32_t)lo[j2] + pos[e][j2]) : -1;
+                            row[j2] = found ? (int32_t)((uint32_t)lo[j2] + pos[e][j2]) : -1;
                         }
                     }
                     // the K indices of an entry as one 4*K-byte store
-                    if (t < n_key) *reinterpret_cast<RowIds<K>*>(out_j + (int64_t)t * K) = row;
+                    if (t < n_key)
+                        __builtin_nontemporal_store(
+                            row, reinterpret_cast<typename RowIds<K>::type*>(out_j + (int64_t)t * K));
                 }
             }
         }
