@@ -89,12 +89,19 @@ class SurelError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load libsurel.so.  Raises if it is missing: there is no other implementation."""
-    global _lib
+    global _lib, _ptr
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
                 f"{LIB_PATH} is not built; run `python -m paper_2202_13538_amd.build` "
                 "(hipcc cross-compiles for gfx950, no GPU needed)")
+        try:
+            from . import _marshal
+        except ImportError:  # not built, or for another torch: the checks stay in Python
+            pass
+        else:
+            _marshal.otherwise(_ptr_in_python)
+            _ptr = _marshal.ptr
         lib = ctypes.CDLL(LIB_PATH)
         for name, (restype, argtypes) in SIGNATURES.items():
             fn = getattr(lib, name)
@@ -104,7 +111,7 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
-def _ptr(t: torch.Tensor | None, dtype: torch.dtype, what: str) -> int | None:
+def _ptr_in_python(t: torch.Tensor | None, dtype: torch.dtype, what: str) -> int | None:
     if t is None:
         return None
     if t.dtype != dtype:
@@ -114,6 +121,9 @@ def _ptr(t: torch.Tensor | None, dtype: torch.dtype, what: str) -> int | None:
     if not t.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
     return t.data_ptr()
+
+
+_ptr = _ptr_in_python  # load() puts the one of host/marshal.cpp in its place
 
 
 class Context:

@@ -3,7 +3,8 @@
 ``python -m paper_2202_13538_amd.build`` compiles every source under ``csrc/`` and links
 ``paper_2202_13538_amd/libsurel.so``, then the memory-system micro-benchmarks of
 ``membench/`` into ``libsurel_membench.so`` (benchmark tooling that ``bench.py --membench``
-loads; the hot path does not).  hipcc cross-compiles for gfx950, so no GPU is needed to build.
+loads; the hot path does not), and ``_marshal.so``, the binding's argument checks, with the host
+compiler.  hipcc cross-compiles for gfx950, so no GPU is needed to build.
 """
 from __future__ import annotations
 
@@ -17,6 +18,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libsurel.so")
 MEMBENCH_SRC = os.path.join(PKG_DIR, "membench", "membench.hip")
 MEMBENCH_LIB_PATH = os.path.join(PKG_DIR, "libsurel_membench.so")
+MARSHAL_SRC = os.path.join(PKG_DIR, "host", "marshal.cpp")
+MARSHAL_PATH = os.path.join(PKG_DIR, "_marshal.so")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -55,6 +58,26 @@ def _link(objs: list[str], lib_path: str) -> None:
     os.replace(tmp, lib_path)
 
 
+def _build_marshal() -> None:
+    """The binding's argument checks, an extension module against the torch that runs this."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = MARSHAL_PATH + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *(f"-isystem{path}" for path in cpp_extension.include_paths()),
+           "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", tmp, "-L" + torch_lib,
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + torch_lib]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {MARSHAL_SRC}:\n{res.stderr}")
+    os.replace(tmp, MARSHAL_PATH)
+
+
 def build(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
     """Compile and link unconditionally.  Returns the path of libsurel.so."""
     os.makedirs(BUILD_DIR, exist_ok=True)
@@ -66,11 +89,13 @@ def build(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
         if f.endswith(".o") and f not in wanted:
             os.remove(os.path.join(BUILD_DIR, f))
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(all_srcs))) as pool:
+        marshal = pool.submit(_build_marshal)
         objs = list(pool.map(lambda s: _compile(s, extra), all_srcs))
+        marshal.result()
     _link(objs[:-1], LIB_PATH)
     _link(objs[-1:], MEMBENCH_LIB_PATH)
     if verbose:
-        print(f"built {LIB_PATH} from {len(srcs)} sources, {MEMBENCH_LIB_PATH} from 1")
+        print(f"built {LIB_PATH} from {len(srcs)} sources, {MEMBENCH_LIB_PATH} and {MARSHAL_PATH} from 1")
     return LIB_PATH
 
 

@@ -547,6 +547,32 @@ def test_header_is_plain_c_and_links_against_the_library(tmp_path):
                    check=True)
 
 
+def test_tensor_arguments_are_checked_the_same_in_both_languages(lib):
+    # the built module's check of a tensor argument and the one in Python that it stands in for
+    import torch
+
+    class Tensor(torch.Tensor):
+        pass
+
+    cpu = torch.zeros(6, dtype=torch.int32)
+    good = (None, torch.int32, "x")
+    bad = [(cpu, torch.int32), (cpu, torch.int64), (cpu.view(2, 3).t(), torch.int32),
+           (torch.empty(4, device="meta"), torch.float32), (cpu.as_subclass(Tensor), torch.int32),
+           (torch.nn.Parameter(torch.zeros(3)), torch.float32), (5, torch.int32), (cpu, 7),
+           (torch.zeros(3).to_sparse(), torch.float32)]
+    assert binding._ptr is not binding._ptr_in_python, "_marshal.so is not built"
+    assert binding._ptr(*good) is None and binding._ptr_in_python(*good) is None
+    for tensor, dtype in bad:
+        raised = []
+        for check in (binding._ptr, binding._ptr_in_python):
+            with pytest.raises(Exception) as e:
+                check(tensor, dtype, "x")
+            raised.append((type(e.value), str(e.value)))
+        assert raised[0] == raised[1]
+    with pytest.raises(TypeError):
+        binding._ptr(cpu)
+
+
 def test_the_product_never_reaches_for_the_oracle():
     """Only tests, smoke() and the benchmark's cpu_baseline leg may use oracle/: no file of the
     package names it, the benchmark imports it inside cpu_baseline only, and the oracle imports

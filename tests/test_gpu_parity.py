@@ -131,6 +131,18 @@ def full_compare(ctx, rp, ci, seeds, M, m, rng_seed, queries):
 # --------------------------------------------------------------------------- #
 # small and medium inputs, element by element
 # --------------------------------------------------------------------------- #
+def test_tensor_arguments_give_their_addresses(ctx):
+    t = torch.arange(40, dtype=torch.int32, device="cuda")
+    u16 = t.to(torch.int16).view(torch.uint16)
+    for x in (t, t[3:], t.view(8, 5)[2:], t[:0], u16, u16[1:], torch.nn.Parameter(t.float())):
+        assert binding._ptr(x, x.dtype, "x") == binding._ptr_in_python(x, x.dtype, "x") == x.data_ptr()
+    for x in (t.view(8, 5).t(), t[::2]):
+        with pytest.raises(ValueError, match="contiguous"):
+            binding._ptr(x, torch.int32, "x")
+    with pytest.raises(TypeError, match="x must be torch.int64, got torch.int32"):
+        binding._ptr(t, torch.int64, "x")
+
+
 def test_rmat4k_whole_pipeline_bit_exact(ctx):
     wl = synth.WORKLOADS["rmat4k"]
     rp, ci = synth.make_graph(wl)
