@@ -633,7 +633,7 @@ static int join_layout(surel_ctx* ctx, const JoinScratch& ws, const int64_t* d_r
     hipError_t hrc;
     {
         KernelSpan span(ctx, SUREL_K_JOIN_COUNT);
-        hrc = surel::launch_join_count(ctx->stream, ctx->max_lds_bytes, d_rpe_off,
+        hrc = surel::launch_join_count(ctx->stream, ctx->max_lds_bytes, ctx->n_cu, d_rpe_off,
                                        d_rpe_ids, n_blocks, max_set, d_queries, n_queries, k,
                                        ws.counts, ctx->d_err);
     }

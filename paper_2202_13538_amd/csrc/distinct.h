@@ -9,10 +9,13 @@ namespace surel {
 
 constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;  // no node id reaches 2^28
 
-// Slots for a set of at most n_max ids: a power of two, at least twice n_max.
+// Slots for a set of at most n_max ids: a power of two, at least twice n_max, or a third more than
+// n_max where twice were more than 8 KB and left a compute unit four waves of the walk (131,000 seeds
+// of M = 150, m = 9: 4.2 -> 2.8 ms; of M = 120, m = 5, where LDS is not what limits the waves, walks
+// take 5 % longer with half the slots).
 __host__ __device__ constexpr int distinct_slots(int n_max) {
     int s = 128;
-    while (s < 2 * n_max) s *= 2;
+    while (s < 2048 ? s < 2 * n_max : 3 * s < 4 * n_max) s *= 2;
     return s;
 }
 
@@ -22,7 +25,7 @@ __device__ __forceinline__ void distinct_clear(uint32_t* table, int slots, int l
 
 // Inserts `id` for the lanes with `active` set; returns how many of them were new
 // (wave-uniform).  All 64 lanes must call it together.  The table never fills up (it has
-// twice as many slots as ids), so every probe sequence ends.
+// more slots than ids), so every probe sequence ends.
 __device__ __forceinline__ int distinct_insert(uint32_t* table, int slots, uint32_t id,
                                                bool active) {
     const uint32_t mask = (uint32_t)slots - 1u;

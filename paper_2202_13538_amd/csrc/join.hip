@@ -34,6 +34,13 @@ namespace surel {
 // join_off is complete (the caller's, or the scan of a counting launch).  A query whose union
 // does not have the join_off[q+1] - join_off[q] rows that the offsets give it is flagged and
 // writes nothing.
+// Outputs of more bytes go past the caches, from rounds that lie like the output's lines.  What fits the
+// 256 MB memory-side cache is written faster there, whatever the lines.  Fill in us, through / past the
+// caches: 10,000 pairs of M = 60, m = 3 (54 MB) 18 / 21; 60,000 of M = 30, m = 2 (86 MB) 67 / 74;
+// 18,772 triples of M = 66, m = 3 (180 MB) 77 / 87; 20,000 pairs of M = 100, m = 4 (270 MB) 80 / 88;
+// 35,000 of them (470 MB) 156 / 143; 500,000 of M = 30, m = 3 (900 MB) 623 / 501.
+constexpr int64_t kPastBytes = 5 << 26;
+
 template <int K, int LT>
 __global__ __launch_bounds__(kWave) void join_fill_kernel(
     const int64_t* __restrict__ rpe_off, const int32_t* __restrict__ rpe_ids,
@@ -54,7 +61,8 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
         JoinQuery<K> jq;
         const uint32_t problem = join_lookup<K>(q, rpe_off, n_blocks, max_set, queries, jq);
         const int64_t off = join_off[q];
-        const int first_bit = (int)(off & (kRowsAlign - 1));
+        const bool past = join_off[n_queries] * (int64_t)(4 + 2 * K * LT) > kPastBytes;
+        const int first_bit = past ? (int)(off & (kRowsAlign - 1)) : 0;
         int rows = 0;  // an unusable query yields no rows
         if (problem != 0) {
             if (lane == 0) atomicOr(err, problem);
@@ -73,8 +81,12 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
         } else if (rows > 0 && off + rows > cap_rows) {
             if (lane == 0) atomicOr(err, kDevCapacity);
         } else if (rows > 0) {
-            join_write<K, LT, false>(base, lay, jq, first_bit, rows, off, rpe_cnt, max_set, out_ids, out_cnt,
-                                     absent16, team);
+            if (past)
+                join_write<K, LT, false, true>(base, lay, jq, first_bit, rows, off, rpe_cnt, max_set,
+                                               out_ids, out_cnt, absent16, team);
+            else
+                join_write<K, LT, false, false>(base, lay, jq, 0, rows, off, rpe_cnt, max_set, out_ids,
+                                                out_cnt, absent16, team);
         }
         wave_sync();
     }
@@ -175,7 +187,7 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
         if (threadIdx.x == 0) atomicOr(err, kDevCapacity);
         return;
     }
-    join_write<K, LT, true>(base, lay, jq, 0, rows, off, rpe_cnt, max_set, out_ids, out_cnt, absent16,
+    join_write<K, LT, true, false>(base, lay, jq, 0, rows, off, rpe_cnt, max_set, out_ids, out_cnt, absent16,
                             team);
 }
 
@@ -194,8 +206,10 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
 // By merge path, where every lane bisects and then merges its share node after node, it took 446
 // instructions a pair and 0.63 ms, now 0.49; 262,144 triples of m = 3 0.36 -> 0.23; 65,536 pairs of
 // 561 nodes a list 0.105 -> 0.075.
-// Queries to a wave: 4 / 8 / 16 pairs take 0.52 / 0.50 / 0.58 ms, 4 / 8 triples 0.239 / 0.234.
-constexpr int kCountQueries = 8;
+// Queries to a wave, for long lists: 4 / 8 / 16 pairs take 0.52 / 0.50 / 0.58 ms, 4 / 8 triples 0.239 /
+// 0.234.  For shorter lists as few as leave 16 waves a compute unit: 4,694 triples of 500 nodes a list
+// 33 us (eight to a wave 106), 20,000 pairs of 290 nodes 17 (23 where eight waves were enough).
+constexpr int kCountQueries = 8;  // at most; fewer where the waves would not fill the device
 constexpr int kCountStage = 8;  // words of a list a lane holds for the next query (512 ids)
 
 // LDS of a counting wave, in 32-bit words: the bit map, the lists that are looked up in, and the
@@ -229,11 +243,11 @@ template <int K>
 __global__ __launch_bounds__(kWave) void join_count_kernel(
     const int64_t* __restrict__ rpe_off, const int32_t* __restrict__ rpe_ids, int64_t n_blocks,
     int32_t max_set, const int32_t* __restrict__ queries, int64_t n_queries,
-    int32_t* __restrict__ counts, uint32_t* __restrict__ err) {
+    int per_wave, int32_t* __restrict__ counts, uint32_t* __restrict__ err) {
     extern __shared__ __align__(16) uint32_t base[];
     const CountLds lay = count_lds_layout(K, max_set);
     const int lane = lane_id();
-    const int64_t q_first = (int64_t)blockIdx.x * kCountQueries;
+    const int64_t q_first = (int64_t)blockIdx.x * per_wave;
 
     // lane l < kCountQueries looks up the blocks of query q_first + l
     int64_t my_lo[K];
@@ -244,7 +258,7 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
         my_lo[j] = 0;
         my_n[j] = 0;
     }
-    if (lane < kCountQueries && q_first + lane < n_queries) {
+    if (lane < per_wave && q_first + lane < n_queries) {
         int32_t b[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) b[j] = queries[(q_first + lane) * K + j];
@@ -341,7 +355,7 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
 #pragma unroll
     for (int j = 0; j < K; ++j) fetch(staged[j], lo[j], 0, n[j]);
 #pragma unroll 1
-    for (int i = 0; i < kCountQueries; ++i) {
+    for (int i = 0; i < per_wave; ++i) {
         const int64_t q = q_first + i;
         if (q >= n_queries) break;
         int64_t lo_now[K];
@@ -383,7 +397,7 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
                     fetch(x, lo_now[j], t0, n_now[j]);
                     insert(x, t0, n_now[j], list);
                 }
-            } else if (i + 1 < kCountQueries && q + 1 < n_queries) {
+            } else if (i + 1 < per_wave && q + 1 < n_queries) {
                 // the registers are free: the next query's lists
                 blocks_of(i + 1, lo, n);
 #pragma unroll
@@ -497,19 +511,21 @@ static hipError_t launch_join_count_k(const JoinJob& j) {
     if (lds_bytes > (size_t)j.max_lds_bytes) return hipErrorInvalidValue;
     hipError_t rc = allow_lds(reinterpret_cast<const void*>(join_count_kernel<K>), lds_bytes);
     if (rc != hipSuccess) return rc;
-    const int64_t blocks = (j.n_queries + kCountQueries - 1) / kCountQueries;
+    int per_wave = (int)(j.n_queries / ((int64_t)j.n_cu * 16));
+    per_wave = per_wave < 1 ? 1 : per_wave > kCountQueries ? kCountQueries : per_wave;
+    const int64_t blocks = (j.n_queries + per_wave - 1) / per_wave;
     hipLaunchKernelGGL((join_count_kernel<K>), dim3((unsigned)blocks), dim3(kWave), lds_bytes,
                        j.stream, j.rpe_off, j.rpe_ids, j.n_blocks, j.max_set, j.queries,
-                       j.n_queries, j.counts, j.err);
+                       j.n_queries, per_wave, j.counts, j.err);
     return hipGetLastError();
 }
 
-hipError_t launch_join_count(hipStream_t stream, int max_lds_bytes, const int64_t* rpe_off,
+hipError_t launch_join_count(hipStream_t stream, int max_lds_bytes, int n_cu, const int64_t* rpe_off,
                              const int32_t* rpe_ids, int64_t n_blocks, int32_t max_set,
                              const int32_t* queries, int64_t n_queries, int32_t k, int32_t* counts,
                              uint32_t* err) {
     JoinJob j{};
-    j.stream = stream, j.max_lds_bytes = max_lds_bytes;
+    j.stream = stream, j.max_lds_bytes = max_lds_bytes, j.n_cu = n_cu;
     j.rpe_off = rpe_off, j.rpe_ids = rpe_ids, j.n_blocks = n_blocks, j.m = 1, j.max_set = max_set;
     j.queries = queries, j.n_queries = n_queries, j.counts = counts, j.err = err;
     if (n_queries == 0) return hipSuccess;

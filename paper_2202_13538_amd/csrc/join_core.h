@@ -20,8 +20,8 @@
 // the table (zeros where the node is absent) as the aligned words that cover them, packs them into
 // the row's words in registers, and the row goes out either straight from the registers (rows of
 // whole words that one store takes) or through an LDS tile that is laid out like the output and
-// streamed out 16 bytes per lane (join_tiled).  In the filling launch a query's rounds of 64 rows
-// lie like the output's groups of 32 (the masks start that many bits in), so that all lines of the
+// streamed out 16 bytes per lane (join_tiled).  In a filling launch with a large output (kPastBytes in
+// join.hip) a query's rounds of 64 rows lie like the output's groups of 32 (the masks start that many bits in), so that all lines of the
 // output but a query's first and last are written whole by one instruction, and the stores go past
 // the caches: the 1,048,576 pairs of the 2.9M-node graph 5.11 ms, 4.98 with the rounds in place, 4.46
 // past the caches as well; 262,144 triples 1.33 -> 1.18, 262,144 pairs of codes 0.80 -> 0.64.  (Rounds
@@ -40,11 +40,11 @@ __host__ __device__ constexpr int join_cover(int LT) { return LT % 2 == 0 ? LT /
 // Rounds of 64 union rows whose gathers a wave has in flight together.  More rounds shorten a
 // wave's chain of memory round trips but cost registers, i.e. waves per compute unit; the measure is
 // the words a lane holds.  Pairs of m = 4: 4.59 ms with four rounds (24 words), 4.46 with six, 4.44
-// with eight; triples of m = 3: 1.22 ms with three (18 words), 1.21 with four, 1.18 with five, 1.21
-// with six; pairs of codes: 0.65 ms with four (8 words), 0.64 with eight and ten.
-__host__ __device__ constexpr int join_rounds(int K, int LT) {
-    const int most = 8;
-    const int fit = (K == 2 ? 36 : 33) / (K * join_cover(LT));
+// with eight; triples of m = 3: 1.22 ms with three (18 words), 1.19 with four, 1.18 with five, of m = 2
+// 0.87 with four, 1.02 with five; pairs of codes: 0.65 ms with four (8 words), 0.64 with eight and ten.
+__host__ __device__ constexpr int join_rounds(int K, int LT, bool past) {
+    const int most = K == 3 ? 4 : past && join_cover(LT) == 1 ? 8 : 6;
+    const int fit = (K == 2 ? 36 : 27) / (K * join_cover(LT));
     return fit < 1 ? 1 : (fit < most ? fit : most);
 }
 
@@ -367,21 +367,20 @@ __device__ __forceinline__ int join_unite(uint32_t* base, const JoinLds& lay, in
     }
 }
 
-// Stores rows of a long query list past the caches (see the file's head); a short list's may be
-// wanted there by whoever reads them next, and their lines come in pieces from several waves.
-template <bool kMulti, typename T>
+// Stores past the caches or through them.
+template <bool kPast, typename T>
 __device__ __forceinline__ void join_store(T* to, T value) {
-    if constexpr (kMulti) {
-        *to = value;
-    } else {
+    if constexpr (kPast) {
         __builtin_nontemporal_store(value, to);
+    } else {
+        *to = value;
     }
 }
 
 // Writes the n_out > 0 union rows of a query that join_unite left in LDS (first_bit as
 // there) to rows [off, off + n_out) of the output; wave w of the team takes a contiguous share of
-// the rounds.
-template <int K, int LT, bool kMulti>
+// the rounds.  kPast: they go past the caches (see the file's head).
+template <int K, int LT, bool kMulti, bool kPast>
 __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                                            const JoinQuery<K>& jq, int first_bit, int n_out,
                                            int64_t off, const uint16_t* __restrict__ rpe_cnt, int max_set,
@@ -392,7 +391,7 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
     constexpr int kWords = (kCounts + 1) / 2;   // words of a row, packed from its first count
     constexpr int kHalf = LT / 2;               // whole words of a vector
     constexpr int kCover = join_cover(LT);
-    constexpr int kRounds = join_rounds(K, LT);
+    constexpr int kRounds = join_rounds(K, LT, kPast);
     const int lane = team.lane;
     const uint32_t* mask = base + lay.mask;
     const uint32_t* mask01 = base + lay.mask01;
@@ -493,14 +492,16 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                 raw[g][j][kCover] = 0u;
             }
         }
-        // all of them are waited for here: in the middle of the stores, every wait for a load would
-        // wait for stores as well (pairs of codes 0.80 -> 0.72 ms)
+        // All of them are waited for here: in the middle of stores past the caches, every wait for a load
+        // would wait for stores as well (pairs of codes 0.80 -> 0.72 ms).  Stores that the caches take
+        // are soon done, and the rounds better go out as their vectors come (20,000 pairs 98 -> 80 us).
 #pragma unroll
         for (int g = 0; g < kRounds; ++g)
 #pragma unroll
             for (int j = 0; j < K; ++j)
 #pragma unroll
-                for (int t = 0; t < kCover; ++t) asm volatile("" : "+v"(raw[g][j][t]));
+                for (int t = 0; t < kCover; ++t)
+                    if constexpr (kPast) asm volatile("" : "+v"(raw[g][j][t]));
 #pragma unroll
         for (int g = 0; g < kRounds; ++g) {
             if (r0 + g * kWave >= r_last) break;
@@ -532,8 +533,8 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
             }
             const int r1 = r0 + g * kWave;
             const int r = r1 + lane;
-            const bool live = (kMulti || r >= first_bit) && r < r_last;
-            if (live) join_store<kMulti>(out_ids + r, (int32_t)id[g]);
+            const bool live = (!kPast || r >= first_bit) && r < r_last;
+            if (live) join_store<kPast>(out_ids + r, (int32_t)id[g]);
             if constexpr (!join_tiled(K, LT)) {
                 // a lane's row is stored from its registers, in one instruction: the rows of
                 // neighbouring lanes adjoin, so a wave's store is contiguous
@@ -544,10 +545,10 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                     for (int d = 0; d < kWords; ++d) row[d] = w[d];
                     uint32_t* row_words = reinterpret_cast<uint32_t*>(out_cnt) + (int64_t)r * kWords;
                     row_t* to = reinterpret_cast<row_t*>(row_words);
-                    if constexpr (kMulti) {
-                        *to = row;
-                    } else {
+                    if constexpr (kPast) {
                         __builtin_nontemporal_store(row, to);
+                    } else {
+                        *to = row;
                     }
                 }
             } else {
@@ -575,7 +576,7 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                 constexpr int kUnit = kCounts % 2 == 0 ? 2 : 1;  // counts moved at a time at the ends
                 // counts [first, last) of the tile are rows; the 16-byte pieces that lie in there
                 // are [lead, tail)
-                const int first = kMulti ? 0 : max(first_bit - r1, 0) * kCounts;
+                const int first = kPast ? max(first_bit - r1, 0) * kCounts : 0;
                 const int last = min(r_last - r1, kWave) * kCounts;
                 const int lead = min(((head + first + 7) & ~7) - head, last);
                 const int n_quads = (last - lead) >> 3;
@@ -588,12 +589,12 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
                     uint32_t* d32 = reinterpret_cast<uint32_t*>(dst);
                     if (lane < (lead - first) / 2) d32[first / 2 + lane] = t32[first / 2 + lane];
                     for (int t = lane; t < n_quads; t += kWave)
-                        join_store<kMulti>(dst_quads + t, tile_quads[t]);
+                        join_store<kPast>(dst_quads + t, tile_quads[t]);
                     if (lane < (last - tail) / 2) d32[tail / 2 + lane] = t32[tail / 2 + lane];
                 } else {
                     if (lane < lead - first) dst[first + lane] = tile16[head + first + lane];
                     for (int t = lane; t < n_quads; t += kWave)
-                        join_store<kMulti>(dst_quads + t, tile_quads[t]);
+                        join_store<kPast>(dst_quads + t, tile_quads[t]);
                     if (lane < last - tail) dst[tail + lane] = tile16[head + tail + lane];
                 }
                 wave_sync();

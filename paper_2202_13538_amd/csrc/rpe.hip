@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kWaves* kWave) void rpe_fill_kernel(
     const int32_t* __restrict__ walks, int64_t n_seeds, int32_t M, int32_t m, int32_t n_nodes,
     uint32_t magic_L, const int64_t* __restrict__ rpe_off, int64_t cap_rows,
     int32_t* __restrict__ ids, uint16_t* __restrict__ cnt, int32_t lds_words_per_wave,
-    int32_t lds_rows, uint32_t* __restrict__ err) {
+    int32_t lds_rows, bool past, uint32_t* __restrict__ err) {
     extern __shared__ __align__(16) uint32_t lds32[];
 
     const int lane = lane_id();
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kWaves* kWave) void rpe_fill_kernel(
         if (lane == 0) atomicOr(err, kDevCapacity);
         return;
     }
-    rpe_write_rows<E, true>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt,
+    rpe_write_rows<E>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt, past,
                       [](int, int, const uint16_t*, uint32_t*) {});
 }
 
@@ -139,7 +139,7 @@ static hipError_t launch_rpe_fill_e(hipStream_t stream, const int32_t* walks, in
     const uint32_t magic_L = 65536u / (uint32_t)L + 1u;
     hipLaunchKernelGGL((rpe_fill_kernel<E, kRpeWaves>), dim3((unsigned)blocks),
                        dim3(kRpeWaves * kWave), lds_bytes, stream, walks, n_seeds, M, m, n_nodes,
-                       magic_L, rpe_off, cap_rows, ids, cnt, words, lds_rows, err);
+                       magic_L, rpe_off, cap_rows, ids, cnt, words, lds_rows, table_goes_past(n_seeds, M, m), err);
     return hipGetLastError();
 }
 

@@ -97,13 +97,10 @@ __device__ __forceinline__ void rpe_assemble_rows(const uint32_t (&x)[E], const 
 }
 
 // Moves n 32-bit words, or 16-bit counts, from LDS to global memory, 16 bytes per
-// lane where it can: src lies at the same place inside a 16-byte piece as dst.  Large jobs write
-// past the caches, which walks keep their records in (walks + table of 235,000 seeds of M = 200, m = 4:
-// 1.58 -> 1.55 ms; 500,009 tables of M = 50, m = 4 from finished walks: 423 -> 403 us; through the
-// caches at the lines that a block shares with its neighbours: 1.55 ms and 427 us).  What a small job writes
-// is read from there by the next call (join of 1,024 pairs behind it: 12.4 us, 13.1 past the caches).
-template <bool kPastCaches, typename T>
-__device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst, int n, int lane) {
+// lane where it can: src lies at the same place inside a 16-byte piece as dst.  past: past the caches.
+template <typename T>
+__device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst, int n, int lane,
+                                               bool past) {
     constexpr int kPer = 16 / (int)sizeof(T);
     const int head = (int)((reinterpret_cast<uintptr_t>(dst) / sizeof(T)) & (kPer - 1));
     const int lead = min((kPer - head) & (kPer - 1), n);
@@ -113,14 +110,21 @@ __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst
     typedef uint32_t quad_t __attribute__((ext_vector_type(4)));
     const quad_t* s4 = reinterpret_cast<const quad_t*>(src + lead);
     quad_t* d4 = reinterpret_cast<quad_t*>(dst + lead);
-    for (int t = lane; t < n_quads; t += kWave) {
-        if constexpr (kPastCaches) {
-            __builtin_nontemporal_store(s4[t], d4 + t);
-        } else {
-            d4[t] = s4[t];
-        }
+    if (past) {
+        for (int t = lane; t < n_quads; t += kWave) __builtin_nontemporal_store(s4[t], d4 + t);
+    } else {
+        for (int t = lane; t < n_quads; t += kWave) d4[t] = s4[t];
     }
     if (lane < n - tail) dst[tail + lane] = src[tail + lane];
+}
+
+// Whether a table's rows go past the caches: where it may take twice the 256 MB memory-side cache, of
+// which a half to two thirds come out.  Then the rows only push the records out of the L2s that walks
+// keep there (walks + table of 235,000 seeds of M = 200, m = 4: 1.58 -> 1.55 ms; 500,009 tables of
+// M = 50, m = 4 from finished walks: 423 -> 403 us).  A smaller table is still there when a join reads
+// it (20,000 pairs of M = 100, m = 4 on 30,000 nodes 83 us, 100 when the table went past the caches).
+inline bool table_goes_past(int64_t n_seeds, int32_t M, int32_t m) {
+    return n_seeds * (1 + (int64_t)M * m) * (4 + 2 * (m + 1)) > (int64_t)512 << 20;
 }
 
 // Writes the block's rows to rows [off, off + sc.n_rows) of the table, at most lds_rows of them
@@ -128,12 +132,12 @@ __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst
 // one turn are rare, the LDS of a wave decides how many waves a compute unit holds).  cnt may be
 // null: a table that carries RPE-IDs only.  each(row0, n, cnt16, free_words) is called for every
 // turn while its counts lie in LDS (from cnt16 on), with n words of LDS that are free again.
-template <int E, bool kPastCaches, typename Each>
+template <int E, typename Each>
 __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const RpeRowScan& sc,
                                                int lane, int L, uint32_t start_weight,
                                                uint32_t* lds, int lds_rows, int64_t off,
                                                int32_t* __restrict__ ids,
-                                               uint16_t* __restrict__ cnt, Each&& each) {
+                                               uint16_t* __restrict__ cnt, bool past, Each&& each) {
     uint32_t* cnt_words = lds + rpe_id_words(lds_rows);
     for (int row0 = 0; row0 < sc.n_rows; row0 += lds_rows) {
         const int n = min(lds_rows, sc.n_rows - row0);
@@ -143,10 +147,10 @@ __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const Rpe
         const int head = (int)((reinterpret_cast<uintptr_t>(dst_cnt) >> 1) & 7u);
         rpe_assemble_rows<E>(x, sc, lane, L, row0, n, start_weight, lds_ids, cnt_words, head);
         const uint16_t* cnt16 = reinterpret_cast<const uint16_t*>(cnt_words) + head;
-        stream_aligned<kPastCaches>(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane);
+        stream_aligned(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane, past);
         wave_sync();
         each(row0, n, cnt16, lds_ids);
-        if (cnt != nullptr) stream_aligned<kPastCaches>(cnt16, dst_cnt, n * L, lane);
+        if (cnt != nullptr) stream_aligned(cnt16, dst_cnt, n * L, lane, past);
         wave_sync();  // the LDS words are free again
     }
 }

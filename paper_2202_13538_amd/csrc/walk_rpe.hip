@@ -102,8 +102,8 @@ __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob
                 if (off + sc.n_rows > f.cap_rows) {
                     if (lane == 0) atomicOr(f.err, kDevCapacity);
                 } else {
-                    rpe_write_rows<E, true>(
-                        x, sc, lane, L, (uint32_t)f.M, wave_lds, f.lds_rows, off, f.ids, f.cnt,
+                    rpe_write_rows<E>(
+                        x, sc, lane, L, (uint32_t)f.M, wave_lds, f.lds_rows, off, f.ids, f.cnt, f.past,
                         [&](int row0, int n, const uint16_t* cnt16, uint32_t* free_words) {
                             // every row's number in the set of distinct vectors
                             if constexpr (kCodes)

@@ -36,6 +36,7 @@ struct FusedJob {
     uint16_t* __restrict__ cnt;
     int32_t lds_words_per_wave;
     int32_t lds_rows;     // rows of a block that fit there at a time
+    bool past;            // the table's rows go past the caches
     uint32_t spin_limit;
     int64_t* h_total;     // host memory that gets the row total too, or null
     uint32_t* __restrict__ err;
@@ -61,7 +62,7 @@ inline FusedJob fused_job(const int32_t* row_ptr, const int32_t* col_idx, int32_
     return FusedJob{{row_ptr, col_idx, rec.data, rec.id_bits, rec.lo_bits, rec.id_bytes, n_nodes, n_edges},
                     seeds, n_seeds, M, m, (uint32_t)(rng_seed & 0xFFFFFFFFull),
                     (uint32_t)(rng_seed >> 32), 65536u / (uint32_t)m + 1u, walks, cap_rows, rpe_off,
-                    ids, cnt, 0, 0, spin_limit, h_total, err};
+                    ids, cnt, 0, 0, table_goes_past(n_seeds, M, m), spin_limit, h_total, err};
 }
 
 // Writes -1 for all walks of seed number i, which is not a node.
@@ -108,7 +109,7 @@ __device__ __forceinline__ void fused_walk_and_sort(const FusedJob& f, int64_t i
     raise_error(f.err, bad_graph, kDevBadGraph);
     wave_sync();
     // the block goes out as it lies in LDS
-    stream_aligned<true>(block, out, M * L, lane);
+    stream_aligned(block, out, M * L, lane, true);
     // Keys: entry idx of the steps is step 1 + idx mod m of walk idx / m.  A register's entries lie
     // 64 behind those of the register before it.  (Worked out anew for every seed, which the asm
     // makes the compiler believe: kept over the seeds, the places of all E registers are 2E

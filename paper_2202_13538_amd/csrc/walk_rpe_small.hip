@@ -108,7 +108,7 @@ __global__ __launch_bounds__(small_walk_waves(E) * kWave) void walk_rpe_small_ke
         if (lane == 0) atomicOr(f.err, kDevCapacity);
         return;
     }
-    rpe_write_rows<E, false>(x, sc, lane, L, (uint32_t)f.M, wave_lds, f.lds_rows, off, f.ids, f.cnt,
+    rpe_write_rows<E>(x, sc, lane, L, (uint32_t)f.M, wave_lds, f.lds_rows, off, f.ids, f.cnt, false,
                       [](int, int, const uint16_t*, uint32_t*) {});
 }
 
