@@ -234,18 +234,23 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
 //   350,000 nodes   7 M, M = 50              881 /   903
 //   500,000 nodes   2 M, M = 50              950 /   989     6 M, M = 50    1,108 / 1,198
 // (Entries are addressed with 24 bits.)
-static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges) {
-    return n_nodes <= 1 << 18 && n_edges >= 1 << 20 && n_edges < 1 << 24;
+// few_waves: the launch has a dozen waves a compute unit or fewer (walks that count sets of more than 640
+// nodes in LDS), and the second trip of a step shows: 235,000 seeds of M = 200, m = 4 without the table
+// 1,372 / 1,460 us, 131,000 891 / 860, 212,449 of M = 147, m = 9 3,897 / 4,124.
+constexpr int kManySteps = 640;
+bool walks_have_few_waves(int32_t M, int32_t m, bool set_sizes) { return set_sizes && M * m > kManySteps; }
+static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges, bool few_waves) {
+    return n_nodes <= (few_waves ? 1 << 17 : 1 << 18) && n_edges >= 1 << 20 && n_edges < 1 << 24;
 }
 
-EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
+EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves) {
     EdgeRecords plan;
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
     plan.lo_bits = bits_for((uint64_t)n_edges);   // 31 at most
     // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
     // small graphs the packed array fits more of its lines into the L2s.)
     plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
-    if (rows_beside_short_records(n_nodes, n_edges)) {
+    if (rows_beside_short_records(n_nodes, n_edges, few_waves)) {
         plan.format = kRecShort;
         plan.id_bytes = plan.id_bits <= 16 ? 2 : 3;
     }

@@ -1324,6 +1324,28 @@ def test_short_edge_records(ctx, n_nodes, n_edges, malformed):
     assert np.array_equal(w[:n].cpu().numpy(), oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
 
 
+@pytest.mark.parametrize("n_nodes", [1 << 17, (1 << 17) + 1])
+@pytest.mark.parametrize("M", [128, 129])
+def test_edge_records_of_walks_that_count_their_sets(ctx, n_nodes, M):
+    # sets of up to and of more than 640 nodes, whose records are short up to 2^18 and up to 2^17
+    # nodes: the walks are those that are made without sizes, the sizes those of the walks
+    m, n_edges, n_seeds = 5, 1 << 20, 9000
+    rng = np.random.default_rng(n_nodes + M)
+    cuts = np.sort((rng.random(n_nodes - 1) ** 2 * (n_edges + 1)).astype(np.int64))
+    rp = np.concatenate([[0], cuts, [n_edges]]).astype(np.int32)
+    ci = rng.integers(0, n_nodes, size=n_edges).astype(np.int32)
+    seeds = rng.integers(0, n_nodes, size=n_seeds).astype(np.int32)
+    sizes = torch.empty(n_seeds, dtype=torch.int32, device="cuda")
+    w = binding.sample_walks(ctx, dev(rp), dev(ci), dev(seeds), M, m, 3, set_sizes=sizes)
+    plain = binding.sample_walks(ctx, dev(rp), dev(ci), dev(seeds), M, m, 3)
+    assert ctx.check() == 0
+    assert torch.equal(w, plain)
+    n = 500
+    walks = w[:n].cpu().numpy()
+    assert np.array_equal(walks, oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
+    assert [len(np.unique(x)) for x in walks] == sizes[:n].cpu().tolist()
+
+
 @pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
                                            ((1 << 18) + 11, False), (1 << 18, True),
                                            ((5 << 18) - 1, False), (5 << 18, False),
