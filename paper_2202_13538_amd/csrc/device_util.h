@@ -31,6 +31,11 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Waits until every load and store that this wavefront has issued to memory is done, and keeps the
+// compiler from moving memory accesses across this point: what is read behind it was not read before it,
+// and whoever sees a store behind it sees the (write-through) stores before it.
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Raise bits of the error word: one atomic per wave at most, none in the common case.
 __device__ __forceinline__ void raise_error(uint32_t* err, bool cond, uint32_t bit) {
     if (__ballot(cond) != 0ull) {

@@ -69,7 +69,6 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
             // address are served one after the other)
             const uint64_t* words = reinterpret_cast<const uint64_t*>(slot);
             const uint64_t a = __hip_atomic_load(words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t b = __hip_atomic_load(words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             st = (uint32_t)a;
             if (st == kSlotEmpty && atomicCAS(slot, kSlotEmpty, kSlotLocked) == kSlotEmpty) {
                 // this lane owns the slot: is there still room in T?
@@ -88,10 +87,11 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                 for (int k = 0; k < NW; ++k)
                     __hip_atomic_store(slot + kSlotVector + k, w[k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
-                // The vector is written past the caches, so "full" may follow as soon as that is
-                // done.  (A release here writes back what the die's L2 holds, for every new vector:
-                // 97 M rows with 15,609 vectors took 0.79 ms, 0.37 without it.)
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                // The vector is written past the caches, so "full" may follow as soon as that is done:
+                // every word of a slot that others read in this launch has to be stored like that.  (A
+                // release here writes back what the die's L2 holds, for every new vector: 97 M rows with
+                // 15,609 vectors took 0.79 ms, 0.37 without it.)
+                wait_memory();
                 __hip_atomic_store(slot, kSlotFull | (uint32_t)number, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
                 return (int32_t)number;
@@ -106,7 +106,15 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
                 __builtin_amdgcn_s_sleep(1);
                 continue;
             }
-            first[0] = (uint32_t)(a >> 32), first[1] = (uint32_t)b, first[2] = (uint32_t)(b >> 32);
+            first[0] = (uint32_t)(a >> 32);
+        }
+        // The slot is full; only words that came with the state, or are read from here on, decide.  (Words
+        // read before it was full are those of the call before: emptying a slot leaves its vector there.)
+        wait_memory();
+        if (NW > 1 && !plain) {
+            const uint64_t b = __hip_atomic_load(reinterpret_cast<const uint64_t*>(slot) + 1, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            first[1] = (uint32_t)b, first[2] = (uint32_t)(b >> 32);
         }
         auto word_past_caches = [&](int k) {
             return __hip_atomic_load(slot + kSlotVector + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -115,9 +123,9 @@ __device__ __forceinline__ int32_t find_or_insert(const uint32_t (&w)[NW], uint3
 #pragma unroll
         for (int k = 0; k < NW; ++k)
             same = same && (k < 3 ? first[k < 3 ? k : 0] : plain ? slot[kSlotVector + k] : word_past_caches(k)) == w[k];
-        // Another vector, or words that were read before they were written: only what is read after the
-        // slot was seen to be full decides.  (Hardly a vector meets another one's slot.)
-        if (!same) {
+        // Another vector, says a line of the caches: what lies behind them decides.  (Hardly a vector meets
+        // another one's slot.)
+        if (!same && plain) {
             same = true;
 #pragma unroll
             for (int k = 0; k < NW; ++k) same = same && word_past_caches(k) == w[k];
