@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
     const uint16_t* __restrict__ rpe_cnt, int64_t n_blocks, int32_t max_set,
     const int32_t* __restrict__ queries, int64_t n_queries,
     const int64_t* __restrict__ join_off, int64_t cap_rows, int32_t* __restrict__ out_ids,
-    uint16_t* __restrict__ out_cnt, uint16_t absent16, uint32_t* __restrict__ err) {
+    uint16_t* __restrict__ out_cnt, int first_place, uint16_t absent16, uint32_t* __restrict__ err) {
     extern __shared__ __align__(16) uint32_t base[];
     const JoinTeam<false> team{lane_id(), 0, 1, nullptr};
     const int lane = team.lane;
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kWave) void join_fill_kernel(
         const uint32_t problem = join_lookup<K>(q, rpe_off, n_blocks, max_set, queries, jq);
         const int64_t off = join_off[q];
         const bool past = join_off[n_queries] * (int64_t)(4 + 2 * K * LT) > kPastBytes;
-        const int first_bit = past ? (int)(off & (kRowsAlign - 1)) : 0;
+        const int first_bit = past ? (int)((off + first_place) & (kRowsAlign - 1)) : 0;
         int rows = 0;  // an unusable query yields no rows
         if (problem != 0) {
             if (lane == 0) atomicOr(err, problem);
@@ -457,10 +457,11 @@ static hipError_t launch_join_fill_cfg(const JoinJob& j) {
     hipError_t rc = allow_lds(reinterpret_cast<const void*>(join_fill_kernel<K, LT>), lds_bytes);
     if (rc != hipSuccess) return rc;
     if (j.n_queries > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    const int first_place = join_first_place(j.out_ids, j.out_cnt, 2 * K * LT);
     hipLaunchKernelGGL((join_fill_kernel<K, LT>), dim3((unsigned)j.n_queries), dim3(kWave),
                        lds_bytes, j.stream, j.rpe_off, j.rpe_ids, j.rpe_cnt, j.n_blocks, j.max_set,
                        j.queries, j.n_queries, j.join_off, j.cap_rows, j.out_ids, j.out_cnt,
-                       j.absent16, j.err);
+                       first_place, j.absent16, j.err);
     return hipGetLastError();
 }
 

@@ -29,6 +29,7 @@
 #pragma once
 
 #include "device_util.h"
+#include "lines.h"
 
 namespace surel {
 
@@ -59,10 +60,6 @@ __host__ __device__ constexpr int join_tile_words(int K, int LT) {
 }
 
 // LDS of one query, in 32-bit words.
-// The filling launch puts a row at the place inside kRowsAlign rows that it has in the output: 32 ids
-// are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
-constexpr int kRowsAlign = 32;
-
 struct JoinLds {
     int ids;         // pairs: lists 0 and 1, max_set words each; triples: the same, later list 2
     int u01;         // triples: the union of lists 0 and 1, [2 * max_set]
