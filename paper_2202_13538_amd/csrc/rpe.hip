@@ -47,14 +47,15 @@ __global__ __launch_bounds__(kRpeWaves* kWave) void rpe_count_kernel(
     if (lane == 0) set_sizes[i] = n_distinct;
 }
 
-// E = keys per lane, kWaves = waves (seeds) per workgroup.
+// E = keys per lane, kWaves = waves (seeds) per workgroup, kPast: the rows go past the caches.  (Asked at
+// run time, that costs tables of small blocks 3 %: 2.9 M of M = 10, m = 2 970 us, 1,002 so.)
 // rpe_off is complete when this kernel starts.
-template <int E, int kWaves>
+template <int E, int kWaves, bool kPast>
 __global__ __launch_bounds__(kWaves* kWave) void rpe_fill_kernel(
     const int32_t* __restrict__ walks, int64_t n_seeds, int32_t M, int32_t m, int32_t n_nodes,
     uint32_t magic_L, const int64_t* __restrict__ rpe_off, int64_t cap_rows,
     int32_t* __restrict__ ids, uint16_t* __restrict__ cnt, int32_t lds_words_per_wave,
-    int32_t lds_rows, bool past, uint32_t* __restrict__ err) {
+    int32_t lds_rows, uint32_t* __restrict__ err) {
     extern __shared__ __align__(16) uint32_t lds32[];
 
     const int lane = lane_id();
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(kWaves* kWave) void rpe_fill_kernel(
         if (lane == 0) atomicOr(err, kDevCapacity);
         return;
     }
-    rpe_write_rows<E>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt, past,
+    rpe_write_rows<E>(x, sc, lane, L, 0u, lds32 + wave * lds_words_per_wave, lds_rows, off, ids, cnt, kPast,
                       [](int, int, const uint16_t*, uint32_t*) {});
 }
 
@@ -137,9 +138,10 @@ static hipError_t launch_rpe_fill_e(hipStream_t stream, const int32_t* walks, in
     if (lds_bytes > 48 * 1024) return hipErrorInvalidValue;
     const int64_t blocks = (n_seeds + kRpeWaves - 1) / kRpeWaves;
     const uint32_t magic_L = 65536u / (uint32_t)L + 1u;
-    hipLaunchKernelGGL((rpe_fill_kernel<E, kRpeWaves>), dim3((unsigned)blocks),
-                       dim3(kRpeWaves * kWave), lds_bytes, stream, walks, n_seeds, M, m, n_nodes,
-                       magic_L, rpe_off, cap_rows, ids, cnt, words, lds_rows, table_goes_past(n_seeds, M, m), err);
+    const auto kernel = table_goes_past(n_seeds, M, m) ? rpe_fill_kernel<E, kRpeWaves, true>
+                                                       : rpe_fill_kernel<E, kRpeWaves, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kRpeWaves * kWave), lds_bytes, stream, walks,
+                       n_seeds, M, m, n_nodes, magic_L, rpe_off, cap_rows, ids, cnt, words, lds_rows, err);
     return hipGetLastError();
 }
 
