@@ -445,6 +445,38 @@ def test_one_pass_captured_in_a_graph_replays_to_the_same_bytes(n_seeds, n_queri
         c.close()
 
 
+@pytest.mark.parametrize("M,m", [(1, 1), (21, 2), (32, 1), (16, 3), (13, 4), (22, 2), (33, 1)])
+def test_blocks_of_about_one_value_a_lane(ctx, M, m):
+    # walk blocks of 2, 63, 64, 65 and 66 values and the rows of as many nodes, in outputs that start
+    # anywhere inside 16 bytes, from the fused kernel and from the separate calls
+    rng = np.random.default_rng(M)
+    n, L = 9000, m + 1
+    rp = (np.arange(n + 1) * 40).astype(np.int32)
+    ci = rng.integers(0, n, size=40 * n).astype(np.int32)
+    seeds = rng.integers(0, n, size=n).astype(np.int32)
+    want = oracle.sample_walks(rp, ci, seeds, M, m, 5)
+    table = oracle.build_rpe(want)
+    R, d_rp, d_ci, d_seeds = table[1].size, dev(rp), dev(ci), dev(seeds)
+    for skip in (0, 2, 4, 6) if L % 2 else (0, 1, 2, 3):  # count vectors start at aligned words
+        walks = torch.full((n * M * L + 8,), -7, dtype=torch.int32, device="cuda")
+        ids = torch.full((R + 8,), -7, dtype=torch.int32, device="cuda")
+        cnt = torch.full((R + 8, L), 9, dtype=torch.int16, device="cuda").view(torch.uint16)
+        off = torch.empty(n + 1, dtype=torch.int64, device="cuda")
+        w = walks[skip:skip + n * M * L].view(n, M, L)
+        rc, rows = binding.sample_walks_rpe_raw(ctx, d_rp, d_ci, d_seeds, M, m, 5, w, R, off,
+                                                ids[skip:skip + R], cnt[skip:skip + R])
+        assert rc == binding.OK and rows == R and ctx.check() == 0
+        assert np.array_equal(w.cpu().numpy(), want)
+        assert_table_equal((off, ids[skip:skip + R], cnt[skip:skip + R]), table, f"fused, from {skip}")
+        ids[skip:skip + R], cnt.view(torch.int16)[skip:skip + R] = -7, 9
+        rc, rows = binding.build_rpe_raw(ctx, w, n, R, off, ids[skip:skip + R], cnt[skip:skip + R])
+        assert rc == binding.OK and rows == R and ctx.check() == 0
+        assert_table_equal((off, ids[skip:skip + R], cnt[skip:skip + R]), table, f"table, from {skip}")
+        for rest, whole in ((-7, walks), (-7, ids), (9, cnt.view(torch.int16))):
+            size = whole.shape[0] - 8
+            assert (whole[:skip] == rest).all() and (whole[skip + size:] == rest).all()
+
+
 def test_fused_kernel_waits_are_bounded(ctx):
     # with a spin limit of zero every wait inside the fused kernel gives up at once: the kernel
     # must still end, say so, and write nothing out of place; the default limit then gives the
