@@ -36,6 +36,14 @@ __device__ __forceinline__ void wave_sync() {
 // and whoever sees a store behind it sees the (write-through) stores before it.
 __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// A register with some value, for a variable that is set on a part of the ways to where it is used and does
+// not matter on the others (an unset one would make that use undefined; to set it takes an instruction).
+__device__ __forceinline__ uint32_t any_value() {
+    uint32_t x;
+    asm volatile("" : "=v"(x));
+    return x;
+}
+
 // Raise bits of the error word: one atomic per wave at most, none in the common case.
 __device__ __forceinline__ void raise_error(uint32_t* err, bool cond, uint32_t bit) {
     if (__ballot(cond) != 0ull) {

@@ -295,9 +295,11 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
             n[j] = __builtin_amdgcn_readlane(my_n[j], i);
         }
     };
-    // ids t0 .. t0 + 511 of a list
+    // ids t0 .. t0 + 511 of a list, in the registers that it has ids for
     auto fetch = [&](uint32_t (&x)[kCountStage], int64_t lo, int t0, int n) {
         const int32_t* list = rpe_ids + lo;
+#pragma unroll
+        for (int u = 0; u < kCountStage; ++u) x[u] = any_value();
 #pragma unroll
         for (int u = 0; u < kCountStage; ++u) {
             const int first = t0 + u * kWave;
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(kWave) void join_count_kernel(
     };
     uint32_t* waiting = base + lay.waiting;
     auto probe = [&](const uint32_t (&x)[kCountStage], int t0, int n, int& n_waiting) {
-        // (registers that hold no ids read some word of the map)
+        // (registers that hold no ids read some word of the map, which is masked out)
         uint32_t word[kCountStage];
         const int n_words = n - t0;
 #pragma unroll

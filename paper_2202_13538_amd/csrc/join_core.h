@@ -444,6 +444,14 @@ __device__ __forceinline__ void join_write(uint32_t* base, const JoinLds& lay,
         uint32_t shift[kRounds][K];
         bool present[kRounds][K];
         uint32_t id[kRounds];
+        if constexpr (kPast) {  // below, rounds past the last row are waited for with the others
+#pragma unroll
+            for (int g = 0; g < kRounds; ++g)
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int t = 0; t < kCover; ++t) raw[g][j][t] = any_value();
+        }
 #pragma unroll
         for (int g = 0; g < kRounds; ++g) {
             if (r0 + g * kWave >= r_last) break;  // wave-uniform: no round past the last row
