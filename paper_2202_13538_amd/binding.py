@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import platform
 
 import torch
 
@@ -95,13 +96,7 @@ def load() -> ctypes.CDLL:
             raise RuntimeError(
                 f"{LIB_PATH} is not built; run `python -m paper_2202_13538_amd.build` "
                 "(hipcc cross-compiles for gfx950, no GPU needed)")
-        try:
-            from . import _marshal
-        except ImportError:  # not built, or for another torch: the checks stay in Python
-            pass
-        else:
-            _marshal.otherwise(_ptr_in_python)
-            _ptr = _marshal.ptr
+        _ptr = _checks_of_arguments()
         lib = ctypes.CDLL(LIB_PATH)
         for name, (restype, argtypes) in SIGNATURES.items():
             fn = getattr(lib, name)
@@ -124,6 +119,19 @@ def _ptr_in_python(t: torch.Tensor | None, dtype: torch.dtype, what: str) -> int
 
 
 _ptr = _ptr_in_python  # load() puts the one of host/marshal.cpp in its place
+
+
+def _checks_of_arguments():
+    """_ptr in native code, or in Python where _marshal.so is not built or is one for another torch or
+    Python (which need not fail to load, but reads tensors through other headers)."""
+    try:
+        from . import _marshal
+    except ImportError:
+        return _ptr_in_python
+    if getattr(_marshal, "built_for", None) != f"{torch.__version__} {platform.python_version()}":
+        return _ptr_in_python
+    _marshal.otherwise(_ptr_in_python)
+    return _marshal.ptr
 
 
 class Context:

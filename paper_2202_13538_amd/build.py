@@ -4,7 +4,8 @@
 ``paper_2202_13538_amd/libsurel.so``, then the memory-system micro-benchmarks of
 ``membench/`` into ``libsurel_membench.so`` (benchmark tooling that ``bench.py --membench``
 loads; the hot path does not), and ``_marshal.so``, the binding's argument checks, with the host
-compiler.  hipcc cross-compiles for gfx950, so no GPU is needed to build.
+compiler.  Without a host compiler or torch's headers there is no ``_marshal.so``, and the binding checks
+in Python.  hipcc cross-compiles for gfx950, so no GPU is needed to build.
 """
 from __future__ import annotations
 
@@ -58,24 +59,32 @@ def _link(objs: list[str], lib_path: str) -> None:
     os.replace(tmp, lib_path)
 
 
-def _build_marshal() -> None:
-    """The binding's argument checks, an extension module against the torch that runs this."""
-    import sysconfig
+def _build_marshal() -> str | None:
+    """The binding's argument checks, an extension module against the torch and Python that run this.
+    Returns None, or why there is none (one of an earlier build is removed then)."""
+    try:
+        import sysconfig
 
-    import torch
-    from torch.utils import cpp_extension
+        import torch
+        from torch.utils import cpp_extension
 
-    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    tmp = MARSHAL_PATH + f".tmp{os.getpid()}"
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-           *(f"-isystem{path}" for path in cpp_extension.include_paths()),
-           "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", tmp, "-L" + torch_lib,
-           "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + torch_lib]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"{cmd[0]} failed on {MARSHAL_SRC}:\n{res.stderr}")
-    os.replace(tmp, MARSHAL_PATH)
+        torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+        tmp = MARSHAL_PATH + f".tmp{os.getpid()}"
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+               f'-DSUREL_TORCH_VERSION="{torch.__version__}"',
+               *(f"-isystem{path}" for path in cpp_extension.include_paths()),
+               "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", tmp, "-L" + torch_lib,
+               "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + torch_lib]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        why = None if res.returncode == 0 else f"{cmd[0]} failed on {MARSHAL_SRC}:\n{res.stderr}"
+    except (ImportError, OSError) as e:
+        why = str(e)
+    if why is None:
+        os.replace(tmp, MARSHAL_PATH)
+    elif os.path.exists(MARSHAL_PATH):
+        os.remove(MARSHAL_PATH)
+    return why
 
 
 def build(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
@@ -91,11 +100,14 @@ def build(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(all_srcs))) as pool:
         marshal = pool.submit(_build_marshal)
         objs = list(pool.map(lambda s: _compile(s, extra), all_srcs))
-        marshal.result()
+        no_marshal = marshal.result()
     _link(objs[:-1], LIB_PATH)
     _link(objs[-1:], MEMBENCH_LIB_PATH)
+    if no_marshal is not None:
+        sys.stderr.write(f"{MARSHAL_PATH} is not built, the binding checks its arguments in Python: {no_marshal}\n")
     if verbose:
-        print(f"built {LIB_PATH} from {len(srcs)} sources, {MEMBENCH_LIB_PATH} and {MARSHAL_PATH} from 1")
+        print(f"built {LIB_PATH} from {len(srcs)} sources, {MEMBENCH_LIB_PATH}"
+              + ("" if no_marshal is not None else f" and {MARSHAL_PATH}") + " from 1")
     return LIB_PATH
 
 

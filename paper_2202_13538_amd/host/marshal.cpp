@@ -52,4 +52,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// built_for: the torch and the Python whose headers this was compiled with; with others it must not be used.
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject* m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", SUREL_TORCH_VERSION " " PY_VERSION) != 0)
+        Py_CLEAR(m);
+    return m;
+}

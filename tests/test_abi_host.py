@@ -573,6 +573,39 @@ def test_tensor_arguments_are_checked_the_same_in_both_languages(lib):
         binding._ptr(cpu)
 
 
+def test_without_a_host_compiler_the_checks_of_arguments_stay_in_python(tmp_path, monkeypatch, capsys):
+    # no host compiler, one that fails, no headers: the library is built all the same, and a module of an
+    # earlier build does not stay behind
+    from paper_2202_13538_amd import build as hip_build
+
+    for name in ("BUILD_DIR", "LIB_PATH", "MEMBENCH_LIB_PATH", "MARSHAL_PATH"):
+        monkeypatch.setattr(hip_build, name, str(tmp_path / name))
+    monkeypatch.setattr(hip_build, "_compile", lambda src, extra: src)
+    monkeypatch.setattr(hip_build, "_link", lambda objs, path: open(path, "w").close())
+    for compiler in ("false", str(tmp_path / "none")):
+        (tmp_path / "MARSHAL_PATH").write_text("old")
+        (tmp_path / "LIB_PATH").unlink(missing_ok=True)
+        monkeypatch.setenv("CXX", compiler)
+        assert hip_build.build() == str(tmp_path / "LIB_PATH") and (tmp_path / "LIB_PATH").exists()
+        assert not (tmp_path / "MARSHAL_PATH").exists()
+        assert "checks its arguments in Python" in capsys.readouterr().err
+
+
+def test_a_module_for_another_torch_is_not_used(lib, monkeypatch):
+    import types
+
+    import paper_2202_13538_amd
+    from paper_2202_13538_amd import _marshal
+
+    import torch
+
+    assert binding._checks_of_arguments() is _marshal.ptr
+    for built_for in ("2.1.0 3.10.12", torch.__version__ + " 3.9.1", None):
+        other = types.SimpleNamespace(ptr=print, otherwise=print, built_for=built_for)
+        monkeypatch.setattr(paper_2202_13538_amd, "_marshal", other)
+        assert binding._checks_of_arguments() is binding._ptr_in_python
+
+
 def test_the_product_never_reaches_for_the_oracle():
     """Only tests, smoke() and the benchmark's cpu_baseline leg may use oracle/: no file of the
     package names it, the benchmark imports it inside cpu_baseline only, and the oracle imports
