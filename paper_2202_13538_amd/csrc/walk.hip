@@ -61,10 +61,11 @@ __global__ void row_group_kernel(const int32_t* __restrict__ row_ptr, int32_t n_
 // of its row and its degree; an entry that names no node, or whose row is malformed, gets the
 // layout's "bad entry" id (the walker will stay in place and flag it).
 // kGroups: the rows are looked up in groups (above) instead of row_ptr, see rows_in_groups.  Entries
-// and records go past the caches, which a pass's outputs have filled by then: 20 M entries on 1M
+// and packed records go past the caches, which a pass's outputs have filled by then: 20 M entries on 1M
 // nodes 137 us, 161 through the caches, 2.6 M on 235,000 22 and 24, 42 M on 524,288 249 and 286.
 // (Only where nothing else had been written since the launch before were they faster through the
-// caches, up to 24 M entries.)
+// caches, up to 24 M entries.)  The bytes of short records, two or three stores an entry, are put
+// together in the caches.
 // What bounds this kernel is the random look-up: a 128-byte line each, 56 G/s from memory where it
 // misses the L2 and 260 G/s from an L2 with nothing else to do.  The 11.6 MB of row_ptr of a
 // 2.9M-node graph miss a 4 MB L2 most of the time, its groups are 3.9 MB: 60 M entries in 508 us,
@@ -239,8 +240,9 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
 // 1,372 / 1,460 us, 131,000 891 / 860, 212,449 of M = 147, m = 9 3,897 / 4,124.
 constexpr int kManySteps = 640;
 bool walks_have_few_waves(int32_t M, int32_t m, bool set_sizes) { return set_sizes && M * m > kManySteps; }
+constexpr int32_t kShortNodes = 1 << 18;
 static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges, bool few_waves) {
-    return n_nodes <= (few_waves ? 1 << 17 : 1 << 18) && n_edges >= 1 << 20 && n_edges < 1 << 24;
+    return n_nodes <= (few_waves ? kShortNodes / 2 : kShortNodes) && n_edges >= 1 << 20 && n_edges < 1 << 24;
 }
 
 EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves) {
@@ -272,6 +274,7 @@ EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves) {
 //   2,000,000     75 /  63      327 / 342      369 / 291      491 / 459
 //   2,900,000    133 /  94      596 / 540      682 / 465      916 / 730      717 / 392
 constexpr int32_t kGroupNodes = 5 << 18;
+static_assert(kGroupNodes > kShortNodes, "short records are not made from groups");
 static bool rows_in_groups(int32_t n_nodes, int64_t n_edges) {
     return n_nodes >= kGroupNodes && n_edges <= 32 * (int64_t)n_nodes;
 }
@@ -325,7 +328,7 @@ hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const
             row_ptr, n_nodes, n_edges, groups);
     }
     const auto kernel = rec.format == kRecShort
-                            ? (groups ? edge_record_kernel<kRecShort, true> : edge_record_kernel<kRecShort, false>)
+                            ? edge_record_kernel<kRecShort, false>  // of graphs too small for groups
                         : rec.format == kRecPacked
                             ? (groups ? edge_record_kernel<kRecPacked, true> : edge_record_kernel<kRecPacked, false>)
                             : (groups ? edge_record_kernel<kRecWide, true> : edge_record_kernel<kRecWide, false>);
