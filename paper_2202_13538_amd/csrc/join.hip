@@ -34,13 +34,6 @@ namespace surel {
 // join_off is complete (the caller's, or the scan of a counting launch).  A query whose union
 // does not have the join_off[q+1] - join_off[q] rows that the offsets give it is flagged and
 // writes nothing.
-// Outputs of more bytes go past the caches, from rounds that lie like the output's lines.  What fits the
-// 256 MB memory-side cache is written faster there, whatever the lines.  Fill in us, through / past the
-// caches: 10,000 pairs of M = 60, m = 3 (54 MB) 18 / 21; 60,000 of M = 30, m = 2 (86 MB) 67 / 74;
-// 18,772 triples of M = 66, m = 3 (180 MB) 77 / 87; 20,000 pairs of M = 100, m = 4 (270 MB) 80 / 88;
-// 35,000 of them (470 MB) 156 / 143; 500,000 of M = 30, m = 3 (900 MB) 623 / 501.
-constexpr int64_t kPastBytes = 5 << 26;
-
 template <int K, int LT>
 __global__ __launch_bounds__(kWave) void join_fill_kernel(
     const int64_t* __restrict__ rpe_off, const int32_t* __restrict__ rpe_ids,

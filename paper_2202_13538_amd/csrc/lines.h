@@ -5,6 +5,13 @@
 
 namespace surel {
 
+// Joined rows of more bytes go past the caches, from rounds that lie like the output's lines.  What fits the
+// 256 MB memory-side cache is written faster there, whatever the lines.  Fill in us, through / past the
+// caches: 10,000 pairs of M = 60, m = 3 (54 MB) 18 / 21; 60,000 of M = 30, m = 2 (86 MB) 67 / 74;
+// 18,772 triples of M = 66, m = 3 (180 MB) 77 / 87; 20,000 pairs of M = 100, m = 4 (270 MB) 80 / 88;
+// 35,000 of them (470 MB) 156 / 143; 500,000 of M = 30, m = 3 (900 MB) 623 / 501.
+constexpr int64_t kPastBytes = 5 << 26;
+
 // The join's filling launch puts a row at the place inside kRowsAlign rows that it has in the output's
 // lines: 32 ids are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
 constexpr int kRowsAlign = 32;

@@ -4,7 +4,9 @@ Bit-exact comparison of walks, RPE tables and joins, element by element, on smal
 medium inputs (several tiles, ragged tails, the degenerate cases) and of the device-detected
 problems.  The workloads at their full sizes are in test_gpu_full_size.py.
 """
+import itertools
 import os
+import re
 
 import numpy as np
 import pytest
@@ -925,8 +927,8 @@ def test_join_vector_lengths_in_one_and_in_two_launches(ctx, L, k):
 @pytest.mark.parametrize("k", [2, 3])
 @pytest.mark.parametrize("L", [2, 4, 5, 10])
 def test_join_fill_at_every_place_of_a_line(ctx, L, k):
-    # the filling launch counts a query's rows from their place inside 32 rows of the output: blocks
-    # of sizes that put queries at every such place, and outputs that start anywhere in a line
+    # blocks of sizes that put queries at every place inside 32 rows of the output, and outputs that
+    # start anywhere in a line: small ones, which are written through the caches
     rng = np.random.default_rng(100 * L + k)
     sizes = [0, 1, 2, 15, 16, 31, 32, 33, 47, 63, 64, 65, 95, 96]
     blocks = [np.sort(rng.choice(300, size, replace=False)) for size in sizes]
@@ -945,6 +947,47 @@ def test_join_fill_at_every_place_of_a_line(ctx, L, k):
         assert_table_equal((d_off, ids[part], cnt[part]), want, f"rows from place {skip} on")
         for rest in (slice(0, skip), slice(skip + J, None)):
             assert (ids[rest] == -7).all() and (cnt.view(torch.int16)[rest] == 9).all()
+
+
+@pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("L", range(2, 17))
+def test_join_fill_past_the_caches_at_every_place_of_a_line(ctx, L, k):
+    # an output of so many bytes is written past the caches, a query's rows from their place inside 32
+    # rows of the lines on: queries at every such place, for every length of vector, in outputs that
+    # start anywhere in a line, ids and vectors at the same row and at different ones
+    lines = open(os.path.join(os.path.dirname(binding.LIB_PATH), "csrc", "lines.h")).read()
+    a, shift = re.search(r"kPastBytes = (\d+) << (\d+);", lines).groups()
+    past = int(a) << int(shift)
+    rng = np.random.default_rng(100 * L + k)
+    sizes = [0, 1, 2, 15, 16, 31, 32, 33, 47, 63, 64, 65, 95, 96, 400]
+    blocks = [np.sort(rng.choice(900, size, replace=False)) for size in sizes]
+    table = hand_made_table(blocks, L, rng)
+    d_table = (dev(table[0]), dev(table[1]), dev(table[2].view(np.int16)).view(torch.uint16))
+    queries = rng.integers(0, len(blocks), size=(2500, k)).astype(np.int32)
+    want = oracle.join_queries(*table, queries)
+    J, row_bytes = want[1].size, 4 + 2 * k * L
+    times = past // (J * row_bytes) + 1  # the list of queries over and over
+    assert times * J * row_bytes > past
+    d_q = dev(queries).repeat(times, 1)
+    d_off = dev(want[0])
+    starts = (torch.arange(times, device="cuda") * J).view(-1, 1) + d_off[:-1]
+    d_off = torch.cat([starts.flatten(), torch.tensor([times * J], device="cuda")])
+    assert (d_off[:-1] % 32).unique().numel() == 32
+    w_ids, w_cnt = dev(want[1]), dev(want[2].view(np.int16)).view(J, k, L)
+    rows = times * J
+    ids = torch.empty(rows + 64, dtype=torch.int32, device="cuda")
+    cnt = torch.empty((rows + 64, k, L), dtype=torch.int16, device="cuda")
+    even = k * L % 2 == 0  # vectors of an output start at aligned words
+    for at_ids, at_cnt in ((0, 0), (1, 1) if even else (2, 2), (38, 38), (0, 6), (5, 0)):
+        ids.fill_(-7), cnt.fill_(9)
+        in_ids, in_cnt = ids[at_ids:at_ids + rows], cnt[at_cnt:at_cnt + rows]
+        assert binding.join_fill(ctx, *d_table, d_q, 400, d_off, rows, in_ids,
+                                 in_cnt.view(torch.uint16)) == binding.OK
+        assert ctx.check() == 0
+        assert bool((in_ids.view(times, J) == w_ids).all()), f"ids from place {at_ids} on"
+        assert bool((in_cnt.view(times, J, k, L) == w_cnt).all()), f"vectors from place {at_cnt} on"
+        assert (ids[:at_ids] == -7).all() and (ids[at_ids + rows:] == -7).all()
+        assert (cnt[:at_cnt] == 9).all() and (cnt[at_cnt + rows:] == 9).all()
 
 
 @pytest.mark.parametrize("k", [2, 3])
@@ -971,6 +1014,20 @@ def test_join_counts_of_lists_whose_ids_share_bits(ctx, stride, k):
     rc, J = binding.join_count(ctx, dev(table[0]), dev(table[1]), dev(queries), 2048, off)
     assert rc == binding.OK and ctx.check() == 0 and J == want[1].size
     assert np.array_equal(off.cpu().numpy(), want[0])
+    # lists of so many queries that a wavefront has several of them, up to its eight and with a rest,
+    # the next one's ids on their way while one is counted: the sizes are those of the unions
+    of = {tuple(q): n for q, n in zip(queries.tolist(), np.diff(want[0]).tolist())}
+    for q in itertools.product(range(len(blocks)), repeat=k):
+        if q not in of:
+            of[q] = np.unique(np.concatenate([blocks[b] for b in q])).size
+    per_cu = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    for n in (2 * per_cu + 1, 5 * per_cu + 3, 8 * per_cu, 9 * per_cu + 5):
+        queries = rng.integers(0, len(blocks), size=(n, k)).astype(np.int32)
+        off = torch.empty(n + 1, dtype=torch.int64, device="cuda")
+        rc, J = binding.join_count(ctx, dev(table[0]), dev(table[1]), dev(queries), 2048, off)
+        sizes = np.array([of[tuple(q)] for q in queries.tolist()])
+        assert rc == binding.OK and ctx.check() == 0 and J == sizes.sum()
+        assert np.array_equal(np.diff(off.cpu().numpy()), sizes)
 
 
 @pytest.mark.parametrize("k", [2, 3])
