@@ -24,6 +24,7 @@
 
 #include "device_util.h"
 #include "kernels.h"
+#include "lines.h"
 #include "prune_set.h"
 
 namespace surel {
@@ -97,7 +98,7 @@ struct LateList {
 // (With all rows that the direct table does not have on the late list, two in a hundred went out a
 // second time to a line that had left the caches: 2.6 M more writes beside 9.1 M, a fifth of the time.
 // With none on it, tables with many vectors waited for the global table in every tile.)
-template <int LT>
+template <int LT, bool kPast>
 __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t first, uint16_t* misses,
                                              LateList<LT>& late, uint32_t* cache, const VectorSet& set,
                                              int32_t* __restrict__ code) {
@@ -181,7 +182,11 @@ __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t 
     for (int g = 0; g < kTurns; ++g) {
         two_t* to = reinterpret_cast<two_t*>(code + (g * kWave + lane) * 2);
         const two_t both = {number[g][0], number[g][1]};
-        __builtin_nontemporal_store(both, to);
+        if constexpr (kPast) {
+            __builtin_nontemporal_store(both, to);
+        } else {
+            *to = both;
+        }
     }
 }
 
@@ -191,7 +196,8 @@ __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t 
 // vectors 0.45 ms = 4.5 TB/s (0.53 with fix-ups in place of whole lines), 0.38 with no row looked up
 // anywhere but in the direct table; 97 M rows with 15,609 vectors 0.35 ms (0.81).  The tile's loads and
 // the codes' stores are in one straight line, so that a wait for the next tile is not one for the codes.
-template <int LT>
+// kPast: the codes go past the caches (codes_go_past).
+template <int LT, bool kPast>
 __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(
     const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
     VectorSet set) {
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
                 if (turn == 0)
                     rows_numbers<LT, CollectTables>(kWarmRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
                                                      misses, cache, set, out);
-                tile_numbers<LT>(tile, lane, first, misses, late, cache, set, out);
+                tile_numbers<LT, kPast>(tile, lane, first, misses, late, cache, set, out);
                 if (late.n >= kWave) late.resolve(lane, cache, set, place);
             } else {
                 rows_numbers<0, CollectTables>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
@@ -501,14 +507,16 @@ static hipError_t launch_collect(hipStream_t stream, int n_cu, const uint16_t* c
                                  int L, int32_t* code, const VectorSet& set) {
     using C = Collect<LT>;
     const size_t lds_bytes = (size_t)(kTableWords + C::kWaves * C::kWaveWords) * 4;
-    hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(prune_collect_kernel<LT>),
+    const auto kernel = LT > 0 && codes_go_past(n_rows) ? prune_collect_kernel<LT, (LT > 0)>
+                                                        : prune_collect_kernel<LT, false>;
+    hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (rc != hipSuccess) return rc;
     // a workgroup fills its LDS tables once and keeps them
     int64_t blocks = (n_rows / C::kRows + C::kWaves) / C::kWaves;
     if (blocks > n_cu) blocks = n_cu;
-    hipLaunchKernelGGL((prune_collect_kernel<LT>), dim3((unsigned)blocks), dim3(C::kWaves * kWave),
-                       lds_bytes, stream, cnt, n_rows, L, code, set);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(C::kWaves * kWave), lds_bytes, stream, cnt,
+                       n_rows, L, code, set);
     return hipGetLastError();
 }
 

@@ -612,11 +612,13 @@ def test_prune_of_many_distinct_vectors(ctx, L, n_T):
 @pytest.mark.parametrize("L", [2, 3, 5, 6, 10])
 @pytest.mark.parametrize("n_rows,n_T,most", [(1, 1, 3), (127, 9, 3), (512, 512, 200), (513, 40, 3),
                                              (3_000_003, 300, 7), (3_000_003, 1500, 90),
-                                             (2_200_000, 40_000, 300)])
+                                             (2_200_000, 40_000, 300), (1 << 25, 1500, 90),
+                                             ((1 << 25) + 1, 1500, 90), ((1 << 25) + 513, 40_000, 300)])
 def test_prune_lists_of_rows_that_wait_for_a_look_up(ctx, L, n_rows, n_T, most):
     # around a tile of 512 rows and the rows looked up first; tables whose rows the direct table knows,
     # the hashed cache knows, or neither, so that the list of late rows fills, is emptied over several
-    # tiles, and has no room: T is sorted and distinct, and every row's code names its vector
+    # tiles, and has no room; codes that go through the caches and (from more than 2^25 rows on) past
+    # them: T is sorted and distinct, and every row's code names its vector
     g = torch.Generator(device="cuda").manual_seed(n_rows + L)
     vectors = torch.randint(0, most + 1, (4 * n_T, L), device="cuda", generator=g)
     vectors[::2, 0] = 0

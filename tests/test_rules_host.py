@@ -43,3 +43,11 @@ def test_rounds_of_the_join_lie_in_the_lines_of_outputs_that_start_anywhere(tmp_
             assert place == ids // 4 % rows
         else:
             assert place in fits
+
+
+def test_codes_that_the_memory_side_cache_holds_stay_in_the_caches(tmp_path):
+    # pruning reads them back; half of the 256 MB are theirs
+    half = (128 << 20) // 4
+    rows = [0, 1, 8_400_000, half, half + 1, 146_000_000, 1 << 31]
+    past = evaluate(tmp_path, ["lines.h"], [f"codes_go_past({n}ll)" for n in rows])
+    assert past == [0, 0, 0, 0, 1, 1, 1]
