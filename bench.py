@@ -90,6 +90,21 @@ def read_membench():
     return out
 
 
+def passes_of_case(torch, args) -> float:
+    """Microseconds of a pass of a case of perf/cases.py among others."""
+    from perf import cases
+
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == args.case), 1)
+    for _ in range(args.warmup):
+        cases.run(state)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(args.steps):
+        cases.run(state)
+    torch.cuda.synchronize()
+    return round((time.perf_counter() - t0) / args.steps * 1e6, 1)
+
+
 def membench(torch) -> dict:
     """Streaming, gather and scatter rates of this GPU (libsurel_membench.so)."""
     import ctypes
@@ -261,6 +276,9 @@ def main() -> int:
                          "(streaming, dependent random gathers by table size, scatters) and print "
                          "them as one JSON line: the measured ceilings of this GPU that the "
                          "roofline.as_moved figures are compared with")
+    ap.add_argument("--case",
+                    help="instead of the pipeline, run W + K passes of this case of perf/cases.py and "
+                         "print the time of one of the K (what the traces of the cases were made with)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="after the timed region, run three plain 1 GiB read + 1 GiB write "
                          "elementwise kernels (the known-size reference for rocprofv3 FETCH_SIZE "
@@ -288,6 +306,12 @@ def main() -> int:
         torch.cuda.set_device(0)
         print(json.dumps({"membench": membench(torch), "unit": "TB/s for stream_*, G gathers or "
                           "rows per second for *_Gs", "data": "synthetic"}))
+        return 0
+
+    if args.case is not None:
+        torch.cuda.set_device(0)
+        print(json.dumps({"case": args.case, "us_per_pass": passes_of_case(torch, args), "steps": args.steps,
+                          "warmup": args.warmup, "data": "synthetic"}))
         return 0
 
     wl = synth.WORKLOADS[args.workload]
