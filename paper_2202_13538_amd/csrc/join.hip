@@ -184,20 +184,21 @@ __global__ __launch_bounds__(1024) void join_small_kernel(
                             team);
 }
 
-// Counting.  A wavefront takes kCountQueries consecutive queries.  Their
+// Counting.  A wavefront takes up to kCountQueries consecutive queries.  Their
 // blocks are looked up by one lane each (block numbers, then the blocks' offsets: two round
 // trips to memory for all of them), and while one query is counted in LDS the lists of the next one
 // are already on their way into registers.
 //
 // Nothing is merged: the union has the rows of all lists less those of nodes that an earlier list
 // holds.  A list's nodes set their bits in a hashed bit map; of the next list's nodes only those that
-// find their bit set, true repetitions and a false one or two in a hundred, are put on a list and
-// looked up in the earlier ones by bisection, 64 at a time.
+// find their bit set are put on a list and looked up in the earlier ones by bisection, 64 at a time:
+// true repetitions and false ones, as many of a list as the map has bits set (276 ids in 8,192 bits 3.3
+// in a hundred, 561 6.4; triples of 181 2.2 of the second list, 4.3 of the third).
 // What bounds it: the lists' way from memory.  1,048,576 pairs of the 2.9M-node graph move 6.2 TB/s
 // (23.7 M lines of 128 bytes, a tenth of them for the blocks' offsets) with 222 vector instructions
-// a pair; triples of 181 nodes a list the vector instructions (400 a triple, 0.7 of the time).
+// a pair; triples of 181 nodes a list the vector instructions (0.74 of the time).
 // By merge path, where every lane bisects and then merges its share node after node, it took 446
-// instructions a pair and 0.63 ms, now 0.49; 262,144 triples of m = 3 0.36 -> 0.23; 65,536 pairs of
+// instructions a pair and 0.63 ms, now 0.49; 262,144 triples of m = 3 0.36 -> 0.21; 65,536 pairs of
 // 561 nodes a list 0.105 -> 0.075.
 // Queries to a wave, for long lists: 4 / 8 / 16 pairs take 0.52 / 0.50 / 0.58 ms, 4 / 8 triples 0.239 /
 // 0.234.  For shorter lists as few as leave 16 waves a compute unit: 4,694 triples of 500 nodes a list
@@ -208,7 +209,8 @@ constexpr int kCountStage = 8;  // words of a list a lane holds for the next que
 // LDS of a counting wave, in 32-bit words: the bit map, the lists that are looked up in, and the
 // nodes that wait for their look-up.
 struct CountLds {
-    int map_bits;  // log2 of the words of the bit map: max_set ids set one bit in eight at most
+    int map_bits;  // log2 of the words of the bit map: max_set ids set one bit in eight at most (the
+                   // third list of a triple finds two lists' bits, one in four at most)
     int lists, waiting;
     int total;
 };

@@ -15,7 +15,7 @@ constexpr int64_t kPastBytes = 5 << 26;
 // Whether the codes of a table's rows go past the caches while the distinct vectors are collected.  The
 // renumbering reads them back at once, from the 256 MB memory-side cache if they are there.  Pruning in us,
 // through / past the caches, codes in the same buffer each time and in several in turn: 8.4 M rows (m = 4,
-// 34 MB of codes) 83 / 88 and 87 / 91, 17 M 113 / 117 and 122 / 129, 29 M 169 / 166 and 170 / 176,
+// 34 MB of codes) 85 / 88 and 88 / 92, 17 M 114 / 117 and 122 / 129, 29 M 168 / 166 and 170 / 176,
 // 58 M (234 MB) 306 / 304, 146 M 716 / 691.
 inline bool codes_go_past(int64_t n_rows) { return n_rows > (int64_t)1 << 25; }
 

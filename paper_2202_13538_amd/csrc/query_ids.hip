@@ -249,7 +249,12 @@ __global__ __launch_bounds__(256, 8) void query_ids_kernel(
                             row[j2] = found ? (int32_t)((uint32_t)lo[j2] + pos[e][j2]) : -1;
                         }
                     }
-                    // the K indices of an entry as one 4*K-byte store
+                    // The K indices of an entry as one 4*K-byte store, past the caches for results of any
+                    // size.  Through / past them, us: 64 pairs of M = 200, m = 4 (1 MB) 9.3 / 9.3, 2,048
+                    // (33 MB) 20.4 / 17.3, 8,192 (131 MB) 58.9 / 58.8, 16,384 112 / 108, 65,536 412 / 398;
+                    // triples of M = 61, m = 3, 8,192 of them (72 MB) 46.8 / 47.4, 65,536 289 / 273; 1,024
+                    // pairs of M = 25, m = 2 6.2 / 6.5.  Whoever reads the results next takes as long, but
+                    // for the 72 MB in buffers used in turn: 69.9 / 74.2 with a pass over them behind it.
                     if (t < n_key)
                         __builtin_nontemporal_store(
                             row, reinterpret_cast<typename RowIds<K>::type*>(out_j + (int64_t)t * K));
