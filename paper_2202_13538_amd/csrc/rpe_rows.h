@@ -98,14 +98,16 @@ __device__ __forceinline__ void rpe_assemble_rows(const uint32_t (&x)[E], const 
 
 // Moves n 32-bit words, or 16-bit counts, from LDS to global memory, 16 bytes per
 // lane where it can: src lies at the same place inside a 16-byte piece as dst.  past: past the caches.
-// What one instruction takes goes out a value a lane: a piece and its two ends would be three (walks +
-// RPE of 2 M seeds of M = 5, m = 4 3,396 -> 3,333 us, 2.9 M tables of M = 20, m = 2 1,023 -> 955).
-template <typename T>
+// kFew: what one instruction takes goes out a value a lane: a piece and its two ends would be three (walks +
+// RPE of 2 M seeds of M = 5, m = 4 3,396 -> 3,333 us, 2.9 M tables of M = 20, m = 2 1,023 -> 955).  Blocks of
+// that kind have up to 128 keys; longer ones are not asked for it.
+constexpr bool few_values(int E) { return E <= 2; }  // E: sort keys per lane
+template <bool kFew, typename T>
 __device__ __forceinline__ void stream_aligned(const T* src, T* __restrict__ dst, int n, int lane,
                                                bool past) {
     constexpr int kPer = 16 / (int)sizeof(T);
     const int head = (int)((reinterpret_cast<uintptr_t>(dst) / sizeof(T)) & (kPer - 1));
-    const int lead = n <= kWave ? n : (kPer - head) & (kPer - 1);
+    const int lead = kFew && n <= kWave ? n : min((kPer - head) & (kPer - 1), n);
     const int n_quads = (n - lead) / kPer;
     const int tail = lead + n_quads * kPer;
     if (lane < lead) dst[lane] = src[lane];
@@ -149,10 +151,10 @@ __device__ __forceinline__ void rpe_write_rows(const uint32_t (&x)[E], const Rpe
         const int head = (int)((reinterpret_cast<uintptr_t>(dst_cnt) >> 1) & 7u);
         rpe_assemble_rows<E>(x, sc, lane, L, row0, n, start_weight, lds_ids, cnt_words, head);
         const uint16_t* cnt16 = reinterpret_cast<const uint16_t*>(cnt_words) + head;
-        stream_aligned(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane, past);
+        stream_aligned<few_values(E)>(reinterpret_cast<const int32_t*>(lds_ids), dst_ids, n, lane, past);
         wave_sync();
         each(row0, n, cnt16, lds_ids);
-        if (cnt != nullptr) stream_aligned(cnt16, dst_cnt, n * L, lane, past);
+        if (cnt != nullptr) stream_aligned<few_values(E)>(cnt16, dst_cnt, n * L, lane, past);
         wave_sync();  // the LDS words are free again
     }
 }

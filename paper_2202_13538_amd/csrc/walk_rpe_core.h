@@ -109,7 +109,7 @@ __device__ __forceinline__ void fused_walk_and_sort(const FusedJob& f, int64_t i
     raise_error(f.err, bad_graph, kDevBadGraph);
     wave_sync();
     // the block goes out as it lies in LDS
-    stream_aligned(block, out, M * L, lane, true);
+    stream_aligned<few_values(E)>(block, out, M * L, lane, true);
     // Keys: entry idx of the steps is step 1 + idx mod m of walk idx / m.  A register's entries lie
     // 64 behind those of the register before it.  (Worked out anew for every seed, which the asm
     // makes the compiler believe: kept over the seeds, the places of all E registers are 2E
