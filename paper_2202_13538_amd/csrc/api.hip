@@ -890,7 +890,7 @@ int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_qu
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return SUREL_E_HIP;
     if (int rc = grow_buffer(ctx, &ctx->d_batch, &ctx->batch_bytes,
-                             surel::incidence_scratch_bytes(n_queries * k)))
+                             surel::incidence_scratch_bytes(n_queries, k, n_nodes)))
         return rc;
     KernelSpan span(ctx, SUREL_K_BATCH);
     if (surel::launch_query_incidence(ctx->stream, d_queries, n_queries, k, n_nodes, d_inc_off,

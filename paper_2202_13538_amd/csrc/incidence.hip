@@ -4,13 +4,19 @@
 // the indices of the queries that name the node, ascending; inc_off[x] .. inc_off[x+1] is
 // node x's part.
 //
-// The sort takes 8 bits a pass, least significant first, in three launches: digit counts of every
-// tile, places (column sums over the tiles and over the digits), and the scatter, which puts a
-// tile's pairs in order in LDS first, so that they leave as runs of a digit.  The first pass reads
-// the query list itself.
-// What bounds it: the memory round trips of the launches one after the other, at these sizes.
-// A million two-node queries on 2.9M nodes: 86 us (three passes of 5 + 6 + 14, offsets 12); with
-// a wavefront per tile of 1,024 pairs, a bisection per node and five launches a pass it was 290.
+// One pass puts the pairs into buckets of consecutive nodes (the node's upper bits, at most 1,024
+// buckets), in three launches: digit counts of every tile, places (column sums over the tiles and
+// over the digits), and the scatter, which puts a tile's pairs in order in LDS first, so that they
+// leave as runs of a bucket.  Then a workgroup per bucket sorts its pairs by the node's lower bits in
+// LDS, and writes the nodes' offsets and the queries: they go through memory once.  Buckets with more
+// pairs than LDS holds (queries crowd on neighbouring nodes) are taken in chunks by workgroups of
+// their own, behind a launch that counts each chunk's nodes.
+// What bounds it: the memory round trips of the launches one after the other, at these sizes: a million
+// two-node queries on 2.9M nodes 42 us (4.8 + 6.5 + 12.3 + 3.5 + 14.5), with three passes of 8 bits and the
+// offsets behind them 87.
+// Graphs of 2^23 nodes and more, whose buckets would have more nodes than LDS has room for, are
+// sorted 8 bits a pass, least significant first, the same three launches a pass, and the offsets by a
+// launch of their own.
 #include "device_util.h"
 #include "kernels.h"
 #include "small_scan.h"
@@ -22,6 +28,8 @@ namespace {
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortBins = 256;                    // 8 bits a pass
+constexpr int kBucketBits = 10;                   // at most 2^10 buckets
+constexpr int kBuckets = 1 << kBucketBits;
 constexpr int kSortMostItems = 8;                 // pairs per thread of a tile
 constexpr int kSortFewItems = 2;                  // for short lists: more tiles than compute units
 constexpr int64_t kSortFew = 1 << 19;
@@ -39,17 +47,46 @@ struct SortSource {
         const uint32_t x = (uint32_t)queries[t];
         const bool out = x >= (uint32_t)n_nodes;
         *bad = *bad || out;
-        return make_uint2(out ? (uint32_t)n_nodes : x, (uint32_t)(t / k));
+        const uint32_t at = (uint32_t)t;  // t / k for k = 1, 2, 3
+        const uint32_t query = k == 1 ? at : k == 2 ? at >> 1 : __umulhi(at, 0xAAAAAAABu) >> 1;
+        return make_uint2(out ? (uint32_t)n_nodes : x, query);
+    }
+};
+
+// Where the scatter puts a pair: whole, or (last pass) apart, or as an item of a bucket, the lower
+// bits of the node above the query's number, in as few bytes as hold both.
+struct SortTarget {
+    uint2* pairs;
+    uint32_t* keys;
+    int32_t* vals;
+    void* items;
+    int low_bits, query_bits;
+    __device__ __forceinline__ void put(uint32_t to, uint2 p) const {
+        if (items != nullptr) {
+            const uint32_t low = p.x & ((1u << low_bits) - 1u);
+            if (low_bits + query_bits <= 32) {
+                static_cast<uint32_t*>(items)[to] = low << query_bits | p.y;
+            } else {
+                static_cast<uint64_t*>(items)[to] = (uint64_t)low << query_bits | p.y;
+            }
+        } else if (keys == nullptr) {
+            pairs[to] = p;
+        } else {
+            keys[to] = p.x;
+            vals[to] = (int32_t)p.y;
+        }
     }
 };
 
 // hist[tile][d] = pairs of the tile whose key has digit d.
-template <int kItems>
+template <int kItems, int kBins>
 __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortSource src, int64_t n, int shift,
-                                                                uint32_t* __restrict__ hist) {
-    __shared__ uint32_t bins[kSortBins];
+                                                                uint32_t* __restrict__ hist,
+                                                                uint32_t* __restrict__ any_large) {
+    __shared__ uint32_t bins[kBins];
     const int tid = (int)threadIdx.x;
-    if (tid < kSortBins) bins[tid] = 0u;
+    if (any_large != nullptr && blockIdx.x == 0 && tid == 0) *any_large = 0u;
+    if (tid < kBins) bins[tid] = 0u;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kSortThreads * kItems;
     uint2 pair[kItems];
@@ -62,21 +99,24 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortSource src,
 #pragma unroll
     for (int r = 0; r < kItems; ++r)
         if (base + r * kSortThreads + tid < n)
-            atomicAdd(&bins[(pair[r].x >> shift) & (kSortBins - 1)], 1u);
+            atomicAdd(&bins[(pair[r].x >> shift) & (kBins - 1)], 1u);
     __syncthreads();
-    if (tid < kSortBins) hist[(int64_t)blockIdx.x * kSortBins + tid] = bins[tid];
+    if (tid < kBins) hist[(int64_t)blockIdx.x * kBins + tid] = bins[tid];
     raise_error(src.err, bad, kDevBadQuery);
 }
 
 // places[tile][d] = place of the tile's first pair with digit d.  A workgroup takes 64 digits, its
 // 16 waves a share of the tiles each; the digits of the workgroups before it come in through
 // small_scan.h (whose helpers read the counts at any time: the places are an array of their own).
-constexpr int kPlaceGroups = kSortBins / kWave;
+// any_large (optional; the counting launch has cleared it): set where a digit has more than `large` pairs.
+constexpr int kPlaceTiles = 16;
+template <int kBins>
 __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_t* __restrict__ hist,
                                                                   int64_t n_tiles,
                                                                   uint32_t* __restrict__ places,
                                                                   SmallScan* __restrict__ ss,
-                                                                  uint32_t spin_limit) {
+                                                                  uint32_t spin_limit, uint32_t large,
+                                                                  uint32_t* __restrict__ any_large) {
     __shared__ uint32_t share[kSortWaves][kWave];
     __shared__ int64_t s_base;
     const int lane = lane_id();
@@ -87,13 +127,17 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
     uint32_t* to = places + (int64_t)blockIdx.x * kWave + lane;
     uint32_t tag = 0;
     if (wave == 0) tag = small_scan_tag(ss);
-    uint32_t sum = 0;
-    for (int64_t t = t0; t < t1; t += 8) {
-        uint32_t v[8];
+    uint32_t first[kPlaceTiles], sum = 0;  // the wave's first tiles stay in registers
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = t + u < t1 ? column[(t + u) * kSortBins] : 0u;
+    for (int u = 0; u < kPlaceTiles; ++u) first[u] = t0 + u < t1 ? column[(t0 + u) * kBins] : 0u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
+    for (int u = 0; u < kPlaceTiles; ++u) sum += first[u];
+    for (int64_t t = t0 + kPlaceTiles; t < t1; t += 4) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = t + u < t1 ? column[(t + u) * kBins] : 0u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum += v[u];
     }
     share[wave][lane] = sum;
     __syncthreads();
@@ -105,12 +149,13 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
     }
     const uint32_t incl = wave_incl_sum(total);
     if (wave == 0) {
+        if (any_large != nullptr && total > large) *any_large = 1u;
         if (lane == kWave - 1) small_scan_publish(ss, (int)blockIdx.x, tag, incl);
         const int64_t base =
             small_scan_before(ss, (int)blockIdx.x, tag, spin_limit, lane, [&](int j) {
                 uint32_t pairs = 0;  // of another workgroup's digits
 #pragma unroll 1
-                for (int64_t t = 0; t < n_tiles; ++t) pairs += hist[t * kSortBins + j * kWave + lane];
+                for (int64_t t = 0; t < n_tiles; ++t) pairs += hist[t * kBins + j * kWave + lane];
                 return wave_bcast_u32(wave_incl_sum(pairs), kWave - 1);
             });
         if (lane == 0) {
@@ -120,13 +165,18 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
     }
     __syncthreads();
     uint32_t at = (uint32_t)s_base + incl - total + before;
-    for (int64_t t = t0; t < t1; t += 8) {
-        uint32_t v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = t + u < t1 ? column[(t + u) * kSortBins] : 0u;
+    for (int u = 0; u < kPlaceTiles; ++u) {
+        if (t0 + u < t1) to[(t0 + u) * kBins] = at;
+        at += first[u];
+    }
+    for (int64_t t = t0 + kPlaceTiles; t < t1; t += 4) {
+        uint32_t v[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (t + u < t1) to[(t + u) * kSortBins] = at;
+        for (int u = 0; u < 4; ++u) v[u] = t + u < t1 ? column[(t + u) * kBins] : 0u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (t + u < t1) to[(t + u) * kBins] = at;
             at += v[u];
         }
     }
@@ -134,96 +184,118 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
 
 // Moves a tile's pairs to their places.  Wave w owns the tile's pairs [w * 64 * kItems, ..) in
 // rounds of 64, in index order: a pair's rank among the earlier ones of its digit is that of its
-// wave so far, plus the lanes before it with the same digit (found by eight ballots).  keys / vals
-// null: the pairs go to out_pairs, else (last pass) apart.
-template <int kItems>
+// wave so far, plus the lanes before it with the same digit.
+// kFast: one addition in LDS that returns the count before it gives both, if it takes the lanes one after
+// the other (as LDS does).  Whether it did shows in the sorted tile, whose pairs' queries ascend inside a
+// digit; else, and where pairs come in another order than that of the queries, ballots tell, one a bit.
+// 2.1 M pairs to 708 buckets 12.3 us, with ballots 15.
+template <int kItems, int kBins, bool kFast>
 __global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(
-    SortSource src, int64_t n, int shift, const uint32_t* __restrict__ places,
-    uint2* __restrict__ out_pairs, uint32_t* __restrict__ keys, int32_t* __restrict__ vals) {
-    __shared__ uint16_t count[kSortWaves][kSortBins];  // pairs of a digit in a wave, then before it
-    __shared__ uint32_t start[kSortBins];              // first place of a digit inside the tile
-    __shared__ uint32_t shift_to[kSortBins];           // its place in the output minus that
-    __shared__ uint32_t wave_sum[kSortBins / kWave];
+    SortSource src, int64_t n, int shift, const uint32_t* __restrict__ places, SortTarget target) {
+    // pairs of a digit in a wave, then before it: 16 bits each
+    __shared__ __align__(16) uint32_t count_words[kSortWaves][kBins / 2];
+    __shared__ uint32_t start[kBins];              // first place of a digit inside the tile
+    __shared__ uint32_t shift_to[kBins];           // its place in the output minus that
+    __shared__ uint32_t wave_sum[kBins / kWave];
     extern __shared__ __align__(16) uint2 sorted[];    // the tile's pairs, in order
     const int tid = (int)threadIdx.x;
     const int lane = lane_id();
     const int wave = tid >> 6;
-    for (int d = lane; d < kSortBins; d += kWave) count[wave][d] = 0;
+    uint16_t* count = reinterpret_cast<uint16_t*>(&count_words[0][0]);  // [wave][digit]
+    uint16_t* own = count + wave * kBins;
     const int64_t tile = (int64_t)blockIdx.x * kSortThreads * kItems;
     const int64_t base = tile + wave * (kWave * kItems);
     uint2 pair[kItems];
-    uint32_t rank[kItems];
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
         const int64_t t = base + r * kWave + lane;
         pair[r] = t < n ? src.get(t, &bad) : make_uint2(0u, 0u);
     }
-    wave_sync();
     const uint64_t below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-        const bool valid = base + r * kWave + lane < n;
-        const uint32_t d = (pair[r].x >> shift) & (kSortBins - 1);
-        uint64_t same = __ballot(valid);  // lanes whose pair has this lane's digit
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t has = __ballot((d >> b) & 1u);
-            same &= ((d >> b) & 1u) ? has : ~has;
-        }
-        const uint32_t in_round = (uint32_t)__popcll(same & below);
-        const uint32_t group = (uint32_t)__popcll(same);
-        const uint32_t so_far = count[wave][d];
-        rank[r] = so_far + in_round;
-        wave_sync();  // every lane has read the count before the group's last lane moves it on
-        if (valid && in_round + 1 == group) count[wave][d] = (uint16_t)(so_far + group);
-        wave_sync();
-    }
-    __syncthreads();
-    uint32_t total = 0;
-    if (tid < kSortBins) {
-#pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) {
-            const uint32_t c = count[w][tid];
-            count[w][tid] = (uint16_t)total;
-            total += c;
-        }
-    }
-    uint32_t incl = 0;
-    if (wave < kSortBins / kWave) {
-        incl = wave_incl_sum(total);
-        if (lane == kWave - 1) wave_sum[wave] = incl;
-    }
-    __syncthreads();
-    if (tid < kSortBins) {
-        uint32_t first = incl - total;
-        for (int w = 0; w < wave; ++w) first += wave_sum[w];
-        start[tid] = first;
-        shift_to[tid] = places[(int64_t)blockIdx.x * kSortBins + tid] - first;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-        if (base + r * kWave + lane < n) {
-            const uint32_t d = (pair[r].x >> shift) & (kSortBins - 1);
-            sorted[start[d] + count[wave][d] + rank[r]] = pair[r];
-        }
-    }
-    __syncthreads();
     const int n_here = (int)min((int64_t)kSortThreads * kItems, n - tile);
+#pragma unroll 1
+    for (bool fast = kFast;; fast = false) {
+        for (int d = lane; d < kBins / 8; d += kWave)
+            reinterpret_cast<uint4*>(own)[d] = make_uint4(0u, 0u, 0u, 0u);
+        wave_sync();
+        uint32_t rank[kItems];
+        if (fast) {
 #pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-        const int i = r * kSortThreads + tid;
-        if (i < n_here) {
-            const uint2 p = sorted[i];
-            const uint32_t to = shift_to[(p.x >> shift) & (kSortBins - 1)] + (uint32_t)i;
-            if (keys == nullptr) {
-                out_pairs[to] = p;
-            } else {
-                keys[to] = p.x;
-                vals[to] = (int32_t)p.y;
+            for (int r = 0; r < kItems; ++r) {
+                const uint32_t d = (pair[r].x >> shift) & (kBins - 1);
+                if (base + r * kWave + lane < n)
+                    rank[r] = atomicAdd(&count_words[wave][d >> 1], 1u << (d & 1u) * 16u) >> (d & 1u) * 16u & 0xFFFFu;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                const bool valid = base + r * kWave + lane < n;
+                uint32_t d = (pair[r].x >> shift) & (kBins - 1);
+                if (kFast) asm volatile("" : "+v"(d));  // (its bits are not looked at before they are needed)
+                uint64_t same = __ballot(valid);  // lanes whose pair has this lane's digit
+#pragma unroll
+                for (int b = 0; (1 << b) < kBins; ++b) {
+                    const uint64_t has = __ballot((d >> b) & 1u);
+                    same &= ((d >> b) & 1u) ? has : ~has;
+                }
+                const uint32_t in_round = (uint32_t)__popcll(same & below);
+                const uint32_t group = (uint32_t)__popcll(same);
+                const uint32_t so_far = own[d];
+                rank[r] = so_far + in_round;
+                wave_sync();  // every lane has read the count before the group's last lane moves it on
+                if (valid && in_round + 1 == group) own[d] = (uint16_t)(so_far + group);
+                wave_sync();
             }
         }
+        __syncthreads();
+        uint32_t total = 0;
+        if (tid < kBins) {
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const uint32_t c = count[w * kBins + tid];
+                count[w * kBins + tid] = (uint16_t)total;
+                total += c;
+            }
+        }
+        uint32_t incl = 0;
+        if (wave < kBins / kWave) {
+            incl = wave_incl_sum(total);
+            if (lane == kWave - 1) wave_sum[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < kBins) {
+            uint32_t first = incl - total;
+            for (int w = 0; w < wave; ++w) first += wave_sum[w];
+            start[tid] = first;
+            shift_to[tid] = places[(int64_t)blockIdx.x * kBins + tid] - first;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            if (base + r * kWave + lane < n) {
+                const uint32_t d = (pair[r].x >> shift) & (kBins - 1);
+                sorted[start[d] + own[d] + rank[r]] = pair[r];
+            }
+        }
+        __syncthreads();
+        bool wrong = false;
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const int i = r * kSortThreads + tid;
+            if (i < n_here) {
+                const uint2 p = sorted[i];
+                const uint32_t d = (p.x >> shift) & (kBins - 1);
+                if (fast) {
+                    const uint2 next = sorted[min(i + 1, n_here - 1)];
+                    wrong = wrong || (next.y < p.y && ((next.x >> shift) & (kBins - 1)) == d);
+                }
+                const uint32_t to = shift_to[d] + (uint32_t)i;
+                // (a place is one of the output unless the list changes while it is sorted)
+                if (to < (uint32_t)n) target.put(to, p);
+            }
+        }
+        if (!fast || __syncthreads_or(wrong) == 0) break;
     }
 }
 
@@ -338,6 +410,462 @@ __global__ __launch_bounds__(kOffsetsThreads) void incidence_offsets_kernel(
         if (x0 + t <= n_nodes) inc_off[x0 + t] = first + behind[t];
 }
 
+// The buckets' lists.  A workgroup takes the pairs of its bucket in order, a share of consecutive ones a
+// wave: they are counted for every wave and node, sums over both give each node's place and, within it,
+// each wave's, and counting once more puts the pairs there.
+// What bounds it: a third each the way there (launch, the bucket's place, its pairs), instructions, and
+// 8 bytes a node and 4 a pair on their way out.  708 buckets of 3,000 pairs and 4,096 nodes 14.5 us; with
+// pairs read twice and the offsets last 18.5, sorted in two passes of six bits 27.
+constexpr int kListThreads = 256;
+constexpr int kListWaves = kListThreads / kWave;
+static_assert(kListWaves == 4, "a node's four counts are the bytes of four words");
+constexpr int kListRounds = 26;                // pairs of a thread, at most
+constexpr int kListPairs = kListRounds * kListThreads;  // LDS takes them, of three workgroups a CU
+constexpr int kListBits = 13;                  // lower bits of a node, at most
+constexpr int kListBins = 1 << (kListBits + 1) / 2;
+constexpr int kListFlight = 16;   // rows of chunk counts in flight
+constexpr int kListChunks = 256;  // workgroups for chunks; about as many chunks where pairs crowd most
+
+// Nodes of a bucket, rounded up to whole 16-byte pieces of their counts.
+__host__ __device__ constexpr int list_nodes(int low_bits) { return low_bits < 4 ? 16 : 1 << low_bits; }
+
+struct ListJob {
+    const uint32_t* any_large;     // not zero: a bucket has more than kListPairs pairs
+    const uint32_t* bucket_start;  // of every bucket, in items
+    int n_buckets;
+    int64_t n;
+    const void* items;
+    int low_bits, query_bits;
+    int32_t n_nodes;
+    uint32_t chunk_pairs;          // of a bucket with more than kListPairs, a multiple of that
+    uint16_t* chunk_counts;        // [chunk][list_nodes(low_bits)]
+    int64_t* inc_off;
+    int32_t* inc_q;
+    // (inside the array also where the query list changes while it is sorted)
+    __device__ __forceinline__ uint32_t start_of(int b) const {
+        return min(b < n_buckets ? bucket_start[b] : (uint32_t)n, (uint32_t)n);
+    }
+    template <typename Item>
+    __device__ __forceinline__ uint32_t low_of(Item item) const {
+        return (uint32_t)(item >> query_bits) & ((1u << low_bits) - 1u);
+    }
+    __device__ __forceinline__ uint32_t size_of(int b) const {
+        const uint32_t first = start_of(b), end = start_of(b + 1);
+        return end > first ? end - first : 0u;
+    }
+};
+
+// Chunk number `id` of the large buckets; bucket -1: there are no more.
+struct ListChunk {
+    int bucket;
+    uint32_t first, n;             // pairs of the chunk, as places among the items
+    int at, bucket_chunk, n_bucket_chunks;  // its row of chunk_counts, its bucket's first row, and rows
+};
+__device__ __forceinline__ ListChunk list_chunk(const ListJob& job, int id, ListChunk* shared,
+                                                uint32_t* wave_sum) {
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    if (*job.any_large == 0u) return ListChunk{-1, 0, 0, 0, 0, 0};
+    constexpr int kPer = kBuckets / kListThreads;
+    uint32_t chunks[kPer], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int b = tid * kPer + u;
+        const uint32_t size = b < job.n_buckets ? job.size_of(b) : 0u;
+        chunks[u] = size > (uint32_t)kListPairs ? (size + job.chunk_pairs - 1) / job.chunk_pairs : 0u;
+        sum += chunks[u];
+    }
+    __syncthreads();
+    if (tid == 0) shared->bucket = -1;
+    const uint32_t incl = wave_incl_sum(sum);
+    if (lane == kWave - 1) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t first = incl - sum;
+    for (int w = 0; w < wave; ++w) first += wave_sum[w];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if ((uint32_t)id >= first && (uint32_t)id < first + chunks[u]) {
+            const int b = tid * kPer + u;
+            const uint32_t before = ((uint32_t)id - first) * job.chunk_pairs;
+            *shared = ListChunk{b, job.start_of(b) + before, min(job.size_of(b) - before, job.chunk_pairs),
+                                id, (int)first, (int)chunks[u]};
+        }
+        first += chunks[u];
+    }
+    __syncthreads();
+    return *shared;
+}
+
+// Pairs of every node of a chunk of a large bucket.
+template <typename Item>
+__global__ __launch_bounds__(kListThreads) void list_chunk_counts_kernel(ListJob job) {
+    __shared__ uint32_t counts[1 << kListBits];
+    __shared__ ListChunk shared;
+    __shared__ uint32_t wave_sum[kListWaves];
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
+    const Item* items = static_cast<const Item*>(job.items);
+    for (int id = (int)blockIdx.x;; id += (int)gridDim.x) {
+        const ListChunk c = list_chunk(job, id, &shared, wave_sum);
+        if (c.bucket < 0) return;
+        for (int x = tid; x < list_nodes(job.low_bits); x += kListThreads) counts[x] = 0u;
+        __syncthreads();
+        for (uint32_t t0 = 0; t0 < c.n; t0 += 8 * kListThreads) {
+            uint32_t low[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t t = t0 + u * kListThreads + tid;
+                low[u] = job.low_of(items[c.first + min(t, c.n - 1)]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool valid = t0 + u * kListThreads + tid < c.n;
+                // a node that holds most of a bucket: one addition for a wave of its pairs
+                const uint32_t one = wave_bcast_u32(low[u], 0);
+                const uint64_t all = __ballot(valid);
+                if (__ballot(valid && low[u] == one) == all) {
+                    if (lane == 0 && all != 0ull) atomicAdd(&counts[one], (uint32_t)__popcll(all));
+                } else if (valid) {
+                    atomicAdd(&counts[low[u]], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        uint16_t* to = job.chunk_counts + (int64_t)c.at * list_nodes(job.low_bits);
+        for (int x = tid; x < list_nodes(job.low_bits); x += kListThreads) to[x] = (uint16_t)counts[x];
+        __syncthreads();
+    }
+}
+
+// LDS of a workgroup: the pairs, then for every node of the bucket its place, and a word.
+template <typename Item>
+size_t list_lds_bytes(int low_bits) {
+    static_assert(kListPairs * sizeof(Item) + (2 << kListBits) >= 4 << kListBits, "room for list_chunk_places");
+    return kListPairs * sizeof(Item) + (size_t)list_nodes(low_bits) * 6;
+}
+
+struct ListLds {
+    uint32_t count[kListWaves][kListBins];
+    uint32_t wave_word[kListWaves];
+    ListChunk chunk;
+};
+
+// Adds 1 to counts[d] for every lane that counts, and returns what was there before the lane's own: the
+// lanes in order, if LDS takes them so.  (A wave of one digit, which is what a list with few nodes is made
+// of, adds once: 64 additions to a word of LDS take 50 ns, one after the other.)
+__device__ __forceinline__ uint32_t count_in_order(uint32_t* counts, uint32_t d, bool valid, int lane) {
+    const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+    const uint64_t all = __ballot(valid);
+    if (__ballot(valid && d == one) == all) {
+        uint32_t before = 0;
+        if (lane == 0) before = atomicAdd(&counts[one], (uint32_t)__popcll(all));
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)before) + (uint32_t)lane;
+    }
+    return valid ? atomicAdd(&counts[d], 1u) : 0u;
+}
+
+// Sorts n pairs (n <= kListPairs, in the order of their queries) from `items` on by the lower bits of their
+// node, into sorted[0 .. n): in two passes of half the bits each, with ranks as in the fast scatter above.
+// Did the pairs not come out in order, each would count the pairs before it.
+template <typename Item>
+__device__ __forceinline__ void list_sort(const Item* __restrict__ items, int n, int low_bits,
+                                          int query_bits, Item* sorted, ListLds& lds) {
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int rounds = (n + kListThreads - 1) / kListThreads;
+    const int half = max((low_bits + 1) / 2, 1);
+#pragma unroll 1
+    for (int done = 0; done < max(low_bits, 1); done += half) {
+        int base = wave * rounds * kWave + lane;
+        asm volatile("" : "+v"(base));  // (no comparison of a pass is kept for the next one)
+        Item x[kListRounds];
+        const Item* from = done == 0 ? items : sorted;
+#pragma unroll
+        for (int r = 0; r < kListRounds; ++r)
+            if (r < rounds) x[r] = from[min(base + r * kWave, n - 1)];
+        const int shift = query_bits + done;
+        const uint32_t mask = (1u << min(half, low_bits - done)) - 1u;
+        for (int d = lane; d < kListBins; d += kWave) lds.count[wave][d] = 0;
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < kListRounds; ++r)
+            if (r < rounds)
+                (void)count_in_order(lds.count[wave], (uint32_t)(x[r] >> shift) & mask, base + r * kWave < n, lane);
+        __syncthreads();
+        uint32_t total = 0, incl = 0;
+        if (tid < kListBins) {
+            for (int w = 0; w < kListWaves; ++w) total += lds.count[w][tid];
+            incl = wave_incl_sum(total);
+            if (lane == kWave - 1) lds.wave_word[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < kListBins) {
+            uint32_t at = incl - total;
+            for (int w = 0; w < wave; ++w) at += lds.wave_word[w];
+            for (int w = 0; w < kListWaves; ++w) {
+                const uint32_t c = lds.count[w][tid];
+                lds.count[w][tid] = at;
+                at += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kListRounds; ++r) {
+            if (r < rounds) {
+                const bool valid = base + r * kWave < n;
+                const uint32_t at = count_in_order(lds.count[wave], (uint32_t)(x[r] >> shift) & mask, valid, lane);
+                if (valid) sorted[at] = x[r];
+            }
+        }
+        __syncthreads();
+    }
+    bool wrong = false;
+    for (int i = tid; i < n - 1; i += kListThreads) wrong = wrong || sorted[i] > sorted[i + 1];
+    if (__syncthreads_or(wrong) != 0) {
+#pragma unroll 1
+        for (int i = tid; i < n; i += kListThreads) {
+            const Item x = items[i];
+            int at = 0;
+            for (int j = 0; j < n; ++j) at += items[j] < x || (items[j] == x && j < i) ? 1 : 0;
+            sorted[at] = x;
+        }
+        __syncthreads();
+    }
+}
+
+// A bucket's pairs.  counts: a byte for every wave (kListNodes words apart) and node, cleared; places: 16
+// bits for every node.  Where a node has more pairs than a byte holds, or the pairs have not come out in
+// order (those of one instruction do if LDS takes its lanes one after the other), they are sorted.
+template <typename Item>
+__device__ __forceinline__ void list_bucket(const ListJob& job, int bucket, uint32_t first, int n,
+                                            const Item* __restrict__ items, Item* sorted, uint16_t* places, uint32_t* counts,
+                                            ListLds& lds) {
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int n_here = 1 << job.low_bits;
+    const int words = list_nodes(job.low_bits) / 4;  // of a wave's counts
+    const uint32_t query_mask = (1u << job.query_bits) - 1u;
+    const int rounds = (n + kListThreads - 1) / kListThreads;
+    const int base = wave * rounds * kWave + lane;
+    uint32_t* own = counts + wave * words;
+    auto offsets_out = [&]() {
+        const int64_t node0 = (int64_t)bucket << job.low_bits;
+        for (int low = tid; low < n_here; low += kListThreads)
+            if (node0 + low <= job.n_nodes) job.inc_off[node0 + low] = (int64_t)first + places[low];
+    };
+    Item x[kListRounds];
+#pragma unroll
+    for (int r = 0; r < kListRounds; ++r)
+        if (r < rounds) x[r] = items[min(base + r * kWave, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kListRounds; ++r) {
+        if (r < rounds) {
+            const uint32_t low = job.low_of(x[r]);
+            if (base + r * kWave < n) atomicAdd(&own[low >> 2], 1u << ((low & 3u) * 8u));
+        }
+    }
+    __syncthreads();
+    // four nodes at a time: sums over the waves before, and pairs of all waves
+    uint32_t sum = 0, most = 0;
+    const int per = (words + kListThreads - 1) / kListThreads;
+    for (int u = 0; u < per; ++u) {
+        const int t = tid * per + u;
+        if (t >= words) break;
+        uint32_t even = 0, odd = 0;  // nodes 0 and 2, 1 and 3, 16 bits each
+#pragma unroll
+        for (int w = 0; w < kListWaves; ++w) {
+            const uint32_t c = counts[w * words + t];
+            counts[w * words + t] = even | odd << 8;
+            even += c & 0x00FF00FFu;
+            odd += c >> 8 & 0x00FF00FFu;
+        }
+        most |= (even | odd) & 0xFF00FF00u;  // more than a byte holds
+        uint16_t* to = places + 4 * t;
+        to[0] = (uint16_t)even;
+        to[1] = (uint16_t)odd;
+        to[2] = (uint16_t)(even >> 16);
+        to[3] = (uint16_t)(odd >> 16);
+        sum += (even & 0xFFFFu) + (even >> 16) + (odd & 0xFFFFu) + (odd >> 16);
+    }
+    const uint32_t incl = wave_incl_sum(sum);
+    if (lane == kWave - 1) lds.wave_word[wave] = incl;
+    bool sort = __syncthreads_or(most != 0u) != 0;
+    uint32_t before = incl - sum, all = 0;
+    for (int w = 0; w < kListWaves; ++w) {
+        if (w < wave) before += lds.wave_word[w];
+        all += lds.wave_word[w];
+    }
+    sort = sort || all != (uint32_t)n;  // a byte ran over into its neighbour: 255 or 256 are missing
+    if (!sort) {
+        for (int u = 0; u < per; ++u) {
+            const int t = tid * per + u;
+            if (t >= words) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t here = places[4 * t + e];
+                places[4 * t + e] = (uint16_t)before;
+                before += here;
+            }
+        }
+        __syncthreads();
+        offsets_out();
+#pragma unroll
+        for (int r = 0; r < kListRounds; ++r) {
+            if (r < rounds) {
+                const uint32_t low = job.low_of(x[r]);
+                if (base + r * kWave < n) {
+                    const uint32_t shift = (low & 3u) * 8u;
+                    const uint32_t rank = atomicAdd(&own[low >> 2], 1u << shift) >> shift & 0xFFu;
+                    sorted[places[low] + rank] = x[r];
+                }
+            }
+        }
+        __syncthreads();
+        bool wrong = false;
+#pragma unroll 4
+        for (int i = tid; i < n; i += kListThreads) {
+            const Item item = sorted[i];
+            wrong = wrong || item > sorted[min(i + 1, n - 1)];
+            job.inc_q[first + i] = (int32_t)((uint32_t)item & query_mask);
+        }
+        sort = __syncthreads_or(wrong) != 0;
+    }
+    if (sort) {
+        list_sort<Item>(items, n, job.low_bits, job.query_bits, sorted, lds);
+        for (int i = tid; i < n; i += kListThreads) {
+            const Item item = sorted[i];
+            const int low = (int)job.low_of(item);
+            job.inc_q[first + i] = (int32_t)((uint32_t)item & query_mask);
+            // places of the nodes that have pairs, and of those without in front of them
+            const int last = i > 0 ? (int)job.low_of(sorted[i - 1]) : -1;
+            for (int y = last + 1; y <= low; ++y) places[y] = (uint16_t)i;
+            if (i + 1 == n)
+                for (int y = low + 1; y < n_here; ++y) places[y] = (uint16_t)n;
+        }
+        __syncthreads();
+        offsets_out();
+    }
+}
+
+// words[x]: where the first pair of node x in chunk c of a large bucket goes.  The bucket's first chunk
+// also writes the nodes' offsets.  spare: as many words again, where the pairs and places will be.
+__device__ __forceinline__ void list_chunk_places(const ListJob& job, const ListChunk& c, uint32_t* words,
+                                                  uint32_t* spare, ListLds& lds) {
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int n_here = 1 << job.low_bits;
+    const int turns = (n_here + kListThreads - 1) / kListThreads;
+    // rows of 8 nodes in 16 bytes; the sums over the chunks go to the bucket's words first
+    const int pieces = list_nodes(job.low_bits) / 8;
+    const uint4* counts = reinterpret_cast<const uint4*>(job.chunk_counts) + (int64_t)c.bucket_chunk * pieces;
+    const int mine = c.at - c.bucket_chunk;
+#pragma unroll 1
+    for (int p = tid; p < pieces; p += kListThreads) {
+        uint32_t all[8] = {}, before_mine[8] = {};
+#pragma unroll 1
+        for (int k0 = 0; k0 < c.n_bucket_chunks; k0 += kListFlight) {
+            uint4 v[kListFlight];
+#pragma unroll
+            for (int k = 0; k < kListFlight; ++k)
+                v[k] = counts[(int64_t)min(k0 + k, c.n_bucket_chunks - 1) * pieces + p];
+#pragma unroll
+            for (int k = 0; k < kListFlight; ++k) {
+                const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+                const bool there = k0 + k < c.n_bucket_chunks, first = k0 + k < mine;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t one = there ? w[e / 2] >> (e & 1) * 16 & 0xFFFFu : 0u;
+                    all[e] += one;
+                    before_mine[e] += first ? one : 0u;
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            words[p * 8 + e] = all[e];
+            spare[p * 8 + e] = before_mine[e];
+        }
+    }
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll 1
+    for (int u = 0; u < turns; ++u) {
+        const int x = (wave * turns + u) * kWave + lane;
+        sum += x < n_here ? words[x] : 0u;
+    }
+    sum = wave_bcast_u32(wave_incl_sum(sum), kWave - 1);
+    __syncthreads();
+    if (lane == 0) lds.wave_word[wave] = sum;
+    __syncthreads();
+    uint32_t before = job.start_of(c.bucket);
+    for (int w = 0; w < wave; ++w) before += lds.wave_word[w];
+#pragma unroll 1
+    for (int u = 0; u < turns; ++u) {
+        const int x = (wave * turns + u) * kWave + lane;
+        const uint32_t all = x < n_here ? words[x] : 0u;
+        const uint32_t incl = wave_incl_sum(all);
+        const uint32_t to = before + incl - all;
+        const int64_t node = ((int64_t)c.bucket << job.low_bits) + x;
+        if (x < n_here) {
+            words[x] = to + spare[x];
+            if (mine == 0 && node <= job.n_nodes) job.inc_off[node] = (int64_t)to;
+        }
+        before += wave_bcast_u32(incl, kWave - 1);
+    }
+}
+
+// Sorted pairs of a part of a chunk go out; words[x] moves on to where the node's next pair goes.
+template <typename Item>
+__device__ __forceinline__ void list_chunk_out(const ListJob& job, int n, const Item* sorted, uint32_t* words) {
+    const int tid = (int)threadIdx.x;
+    const uint32_t query_mask = (1u << job.query_bits) - 1u;
+    auto low_of = [&](int i) { return job.low_of(sorted[i]); };
+#pragma unroll 4
+    for (int i = tid; i < n; i += kListThreads)  // less the place of its first pair here
+        if (i == 0 || low_of(i - 1) != low_of(i)) words[low_of(i)] -= (uint32_t)i;
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < n; i += kListThreads) {
+        const uint32_t to = words[low_of(i)] + (uint32_t)i;
+        if (to < (uint32_t)job.n) job.inc_q[to] = (int32_t)((uint32_t)sorted[i] & query_mask);
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < n; i += kListThreads)
+        if (i + 1 == n || low_of(i + 1) != low_of(i)) words[low_of(i)] += (uint32_t)i + 1u;
+    __syncthreads();
+}
+
+// Workgroups below n_buckets: a bucket each.  Those behind them: the chunks of the large buckets.
+template <typename Item>
+__global__ __launch_bounds__(kListThreads) void incidence_lists_kernel(ListJob job) {
+    extern __shared__ __align__(16) unsigned char dynamic[];
+    __shared__ ListLds lds;
+    const int n_nodes = list_nodes(job.low_bits);
+    Item* sorted = reinterpret_cast<Item*>(dynamic);
+    uint16_t* places = reinterpret_cast<uint16_t*>(dynamic + kListPairs * sizeof(Item));
+    uint32_t* words = reinterpret_cast<uint32_t*>(places + n_nodes);
+    const Item* items = static_cast<const Item*>(job.items);
+    if ((int)blockIdx.x < job.n_buckets) {
+        const int b = (int)blockIdx.x;
+        const uint32_t first = job.start_of(b), n = job.size_of(b);
+        if (n > (uint32_t)kListPairs) return;
+        uint4* clear = reinterpret_cast<uint4*>(words);
+        for (int x = (int)threadIdx.x; x < n_nodes / 4; x += kListThreads) clear[x] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        list_bucket(job, b, first, (int)n, items + first, sorted, places, words, lds);
+        return;
+    }
+#pragma unroll 1
+    for (int id = (int)blockIdx.x - job.n_buckets;; id += (int)gridDim.x - job.n_buckets) {
+        const ListChunk c = list_chunk(job, id, &lds.chunk, lds.wave_word);
+        if (c.bucket < 0) return;
+        list_chunk_places(job, c, words, reinterpret_cast<uint32_t*>(dynamic), lds);
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t t0 = 0; t0 < c.n; t0 += kListPairs) {
+            const int n = (int)min((uint32_t)kListPairs, c.n - t0);
+            list_sort<Item>(items + c.first + t0, n, job.low_bits, job.query_bits, sorted, lds);
+            list_chunk_out(job, n, sorted, words);
+        }
+    }
+}
+
 int sort_items(int64_t n) { return n <= kSortFew ? kSortFewItems : kSortMostItems; }
 int64_t sort_tiles(int64_t n) {
     const int64_t tile = (int64_t)kSortThreads * sort_items(n);
@@ -345,12 +873,101 @@ int64_t sort_tiles(int64_t n) {
 }
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
+// Bits that hold 0 .. most.
+int bits_of(uint64_t most) {
+    int bits = 1;
+    while (bits < 64 && (most >> bits) != 0) ++bits;
+    return bits;
+}
+
+// Pairs of a bucket on average, at most: of more, not all buckets of a list that names all nodes alike
+// would fit LDS.  In us, by buckets / 8 bits a pass: 3.1 M pairs on 2.9M nodes (4,443 a bucket) 52 / 108, on
+// 600,000 50 / 106, 8.4 M on 2.9M (11,848) 387 / 205; 2.1 M on 10M nodes (8 bits only) 100, on 8M 80 / 100.
+// Lists that crowd, 2.1 M pairs on 2.9M nodes: half of them with one node 131 / 127, 1,048 nodes named
+// 1,000 times 97 / 97, ids by descending degree 106 / 133, 3,000 neighbouring nodes 146 / 138.
+constexpr int64_t kBucketMean = 5500;
+static_assert(kBuckets * kBucketMean / kListPairs / kListChunks * kListPairs + kListPairs < 1 << 16,
+              "16 bits count a chunk's pairs");
+
+// How a query list is sorted, and where its arrays lie in the scratch memory.
+struct SortPlan {
+    bool buckets;              // by buckets, or 8 bits a pass
+    int64_t n_tiles;
+    int items;                 // pairs of a thread of a tile
+    int low_bits, query_bits;  // of an item of a bucket
+    uint32_t chunk_pairs;
+    size_t pairs[2], keys, item_at, hist, places, any_large, chunk_counts, bytes;
+};
+SortPlan sort_plan(int64_t n, int32_t k, int32_t n_nodes) {
+    SortPlan p{};
+    if (n < 1) n = 1;
+    p.n_tiles = sort_tiles(n);
+    p.items = sort_items(n);
+    const int key_bits = bits_of((uint64_t)n_nodes);  // keys are 0..n_nodes
+    p.low_bits = key_bits > kBucketBits ? key_bits - kBucketBits : 0;
+    const int64_t n_buckets = (n_nodes >> p.low_bits) + 1;
+    p.buckets = key_bits <= kBucketBits + kListBits && n <= n_buckets * kBucketMean;
+    auto part = [&](size_t bytes) {
+        const size_t at = p.bytes;
+        p.bytes += padded(bytes);
+        return at;
+    };
+    if (p.buckets) {
+        p.query_bits = bits_of((uint64_t)((n - 1) / k));
+        p.chunk_pairs = (uint32_t)((n / kListPairs / kListChunks + 1) * kListPairs);
+        p.any_large = part(sizeof(uint32_t));
+        p.item_at = part((size_t)n * (p.low_bits + p.query_bits <= 32 ? 4 : 8));
+        // a large bucket has more than kListPairs pairs, and one chunk at most that is not full
+        const int64_t large = n / kListPairs < kBuckets ? n / kListPairs : kBuckets;
+        p.chunk_counts = part((size_t)(n / p.chunk_pairs + large) * list_nodes(p.low_bits) * sizeof(uint16_t));
+    } else {
+        p.pairs[0] = part((size_t)n * sizeof(uint2));
+        p.pairs[1] = part((size_t)n * sizeof(uint2));
+        p.keys = part((size_t)n * sizeof(uint32_t));
+    }
+    const size_t counts = (size_t)p.n_tiles * (p.buckets ? kBuckets : kSortBins) * sizeof(uint32_t);
+    p.hist = part(counts);
+    p.places = part(counts);
+    return p;
+}
+
+// One pass: the pairs of `src` by kBins digits, to where `target` says.
+template <int kItems, int kBins>
+hipError_t sort_pass(hipStream_t stream, const SortPlan& p, const SortSource& src, int64_t n, int shift,
+                     uint32_t* hist, uint32_t* places, const SortTarget& target, SmallScan* ss,
+                     uint32_t spin_limit, uint32_t* any_large) {
+    const dim3 grid((unsigned)p.n_tiles), block(kSortThreads);
+    const size_t lds_bytes = (size_t)kSortThreads * kItems * sizeof(uint2);
+    if (lds_bytes > 48 * 1024) {
+        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(sort_scatter_kernel<kItems, kBins, kBins == kBuckets>),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (rc != hipSuccess) return rc;
+    }
+    sort_hist_kernel<kItems, kBins><<<grid, block, 0, stream>>>(src, n, shift, hist, any_large);
+    sort_places_kernel<kBins><<<dim3(kBins / kWave), block, 0, stream>>>(
+        hist, p.n_tiles, places, ss, spin_limit, (uint32_t)kListPairs, any_large);
+    sort_scatter_kernel<kItems, kBins, kBins == kBuckets><<<grid, block, lds_bytes, stream>>>(src, n, shift, places, target);
+    return hipGetLastError();
+}
+
+template <typename Item>
+hipError_t launch_lists(hipStream_t stream, const ListJob& job) {
+    const size_t lds_bytes = list_lds_bytes<Item>(job.low_bits);
+    hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(incidence_lists_kernel<Item>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (rc != hipSuccess) return rc;
+    const int chunk_groups = job.n > kListPairs ? kListChunks : 0;
+    if (chunk_groups > 0)
+        list_chunk_counts_kernel<Item><<<dim3(chunk_groups), dim3(kListThreads), 0, stream>>>(job);
+    incidence_lists_kernel<Item><<<dim3((unsigned)(job.n_buckets + chunk_groups)), dim3(kListThreads),
+                                   lds_bytes, stream>>>(job);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-size_t incidence_scratch_bytes(int64_t n_entries) {
-    const int64_t n = n_entries > 0 ? n_entries : 1;
-    return 2 * padded((size_t)n * sizeof(uint2)) + padded((size_t)n * sizeof(uint32_t)) +
-           2 * padded((size_t)sort_tiles(n) * kSortBins * sizeof(uint32_t));
+size_t incidence_scratch_bytes(int64_t n_queries, int32_t k, int32_t n_nodes) {
+    return sort_plan(n_queries * k, k, n_nodes).bytes;
 }
 
 hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, int64_t n_queries,
@@ -365,45 +982,40 @@ hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, in
             nullptr, 0, n_nodes, offset_items, inc_off);
         return hipGetLastError();
     }
-    const int64_t n_tiles = sort_tiles(n);
-    const int items = sort_items(n);
-    char* p = static_cast<char*>(scratch);
-    uint2* pairs[2] = {reinterpret_cast<uint2*>(p), reinterpret_cast<uint2*>(p + padded((size_t)n * sizeof(uint2)))};
-    p += 2 * padded((size_t)n * sizeof(uint2));
-    uint32_t* keys = reinterpret_cast<uint32_t*>(p);
-    p += padded((size_t)n * sizeof(uint32_t));
-    uint32_t* hist = reinterpret_cast<uint32_t*>(p);
-    p += padded((size_t)n_tiles * kSortBins * sizeof(uint32_t));
-    uint32_t* places = reinterpret_cast<uint32_t*>(p);
-
-    int bits = 1;  // keys are 0..n_nodes
-    while (bits < 32 && ((uint32_t)n_nodes >> bits) != 0u) ++bits;
-    const dim3 grid((unsigned)n_tiles), block(kSortThreads);
-    const size_t lds_bytes = (size_t)kSortThreads * items * sizeof(uint2);
-    if (items == kSortMostItems) {
-        hipError_t rc = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(sort_scatter_kernel<kSortMostItems>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    const SortPlan p = sort_plan(n, k, n_nodes);
+    char* base = static_cast<char*>(scratch);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(base + p.hist);
+    uint32_t* places = reinterpret_cast<uint32_t*>(base + p.places);
+    SmallScan* ss = static_cast<SmallScan*>(small_scan);
+    const bool few = p.items == kSortFewItems;
+    if (p.buckets) {
+        const SortSource src{queries, k, n_nodes, nullptr, err};
+        const SortTarget target{nullptr, nullptr, nullptr, base + p.item_at, p.low_bits, p.query_bits};
+        uint32_t* any_large = reinterpret_cast<uint32_t*>(base + p.any_large);
+        hipError_t rc = few ? sort_pass<kSortFewItems, kBuckets>(stream, p, src, n, p.low_bits, hist, places,
+                                                                 target, ss, spin_limit, any_large)
+                            : sort_pass<kSortMostItems, kBuckets>(stream, p, src, n, p.low_bits, hist, places,
+                                                                  target, ss, spin_limit, any_large);
         if (rc != hipSuccess) return rc;
+        // the first tile's places are the buckets' starts
+        const ListJob job{any_large, places, (n_nodes >> p.low_bits) + 1, n, target.items, p.low_bits, p.query_bits,
+                          n_nodes, p.chunk_pairs, reinterpret_cast<uint16_t*>(base + p.chunk_counts),
+                          inc_off, inc_q};
+        return p.low_bits + p.query_bits <= 32 ? launch_lists<uint32_t>(stream, job)
+                                               : launch_lists<uint64_t>(stream, job);
     }
-    for (int shift = 0, pass = 0; shift < bits; shift += 8, ++pass) {
-        const bool last = shift + 8 >= bits;  // the last pass puts the queries where they belong
+    uint2* pairs[2] = {reinterpret_cast<uint2*>(base + p.pairs[0]), reinterpret_cast<uint2*>(base + p.pairs[1])};
+    uint32_t* keys = reinterpret_cast<uint32_t*>(base + p.keys);
+    const int key_bits = bits_of((uint64_t)n_nodes);
+    for (int shift = 0, pass = 0; shift < key_bits; shift += 8, ++pass) {
+        const bool last = shift + 8 >= key_bits;  // the last pass puts the queries where they belong
         const SortSource src{pass == 0 ? queries : nullptr, k, n_nodes, pairs[(pass + 1) & 1], err};
-        uint2* to = pairs[pass & 1];
-        if (items == kSortMostItems) {
-            sort_hist_kernel<kSortMostItems><<<grid, block, 0, stream>>>(src, n, shift, hist);
-        } else {
-            sort_hist_kernel<kSortFewItems><<<grid, block, 0, stream>>>(src, n, shift, hist);
-        }
-        sort_places_kernel<<<dim3(kPlaceGroups), block, 0, stream>>>(
-            hist, n_tiles, places, static_cast<SmallScan*>(small_scan), spin_limit);
-        if (items == kSortMostItems) {
-            sort_scatter_kernel<kSortMostItems><<<grid, block, lds_bytes, stream>>>(
-                src, n, shift, places, to, last ? keys : nullptr, inc_q);
-        } else {
-            sort_scatter_kernel<kSortFewItems><<<grid, block, lds_bytes, stream>>>(
-                src, n, shift, places, to, last ? keys : nullptr, inc_q);
-        }
+        const SortTarget target{pairs[pass & 1], last ? keys : nullptr, inc_q, nullptr, 0, 0};
+        hipError_t rc = few ? sort_pass<kSortFewItems, kSortBins>(stream, p, src, n, shift, hist, places,
+                                                                  target, ss, spin_limit, nullptr)
+                            : sort_pass<kSortMostItems, kSortBins>(stream, p, src, n, shift, hist, places,
+                                                                   target, ss, spin_limit, nullptr);
+        if (rc != hipSuccess) return rc;
     }
     incidence_offsets_kernel<<<offset_grid, dim3(kOffsetsThreads), 0, stream>>>(
         keys, n, n_nodes, offset_items, inc_off);

@@ -162,9 +162,9 @@ hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScra
 
 // incidence.hip.  The queries of every node: inc_q[inc_off[x] .. inc_off[x+1]) = indices of the
 // queries that name node x, ascending (a query that names x twice is listed twice).  Entries
-// outside [0, n_nodes) are flagged and left out.  scratch: incidence_scratch_bytes(n_queries*k);
+// outside [0, n_nodes) are flagged and left out.  scratch: incidence_scratch_bytes(...);
 // small_scan, spin_limit: as for launch_join_small.
-size_t incidence_scratch_bytes(int64_t n_entries);
+size_t incidence_scratch_bytes(int64_t n_queries, int32_t k, int32_t n_nodes);
 hipError_t launch_query_incidence(hipStream_t stream, const int32_t* queries, int64_t n_queries,
                                   int32_t k, int32_t n_nodes, int64_t* inc_off, int32_t* inc_q,
                                   void* scratch, void* small_scan, uint32_t spin_limit,

@@ -74,6 +74,30 @@ def test_query_incidence_offsets_around_group_sizes(ctx, n_nodes, spread):
     assert np.array_equal(inc_q.cpu().numpy(), want_q)
 
 
+@pytest.mark.parametrize("n_nodes", [1, 7, 1023, 1024, 4100, (1 << 23) - 1, 1 << 23])
+@pytest.mark.parametrize("n_queries,k", [(255, 1), (6656, 1), (6657, 1), (262_145, 2), (600_000, 3)])
+@pytest.mark.parametrize("shape", ["spread", "neighbours", "one"])
+def test_query_incidence_by_buckets(ctx, n_nodes, n_queries, k, shape):
+    # buckets of one node and of 8,192, empty ones, ones that LDS just holds and just not (6,656 pairs),
+    # nodes with more pairs of one wave than a byte counts, items of 32 and of 64 bits, queries that name
+    # a node twice, short lists and long ones, and graphs that are sorted 8 bits a pass
+    rng = np.random.default_rng(n_nodes + n_queries)
+    if shape == "one":
+        queries = np.full((n_queries, k), n_nodes // 2)
+        queries[::97, 0] = rng.integers(0, n_nodes, size=queries[::97, 0].shape)
+    else:
+        width = n_nodes if shape == "spread" else min(n_nodes, 3000)
+        start = rng.integers(0, n_nodes - width + 1)
+        queries = rng.integers(start, start + width, size=(n_queries, k))
+        queries[rng.random(n_queries) < 0.1, k - 1] = start  # a tenth of them name one node
+    queries = queries.astype(np.int32)
+    inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
+    assert ctx.check() == 0
+    want_off, want_q = numpy_incidence(queries, n_nodes)
+    assert np.array_equal(inc_off.cpu().numpy(), want_off)
+    assert np.array_equal(inc_q.cpu().numpy(), want_q)
+
+
 def test_query_incidence_of_an_empty_list_and_bad_ids(ctx):
     empty = torch.empty((0, 2), dtype=torch.int32, device="cuda")
     inc_off, inc_q = binding.query_incidence(ctx, empty, 17)
