@@ -11,8 +11,7 @@ constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;  // no node id reaches 2^28
 
 // Slots for a set of at most n_max ids: a power of two, at least twice n_max, or a third more than
 // n_max where twice were more than 8 KB and left a compute unit four waves of the walk (131,000 seeds
-// of M = 150, m = 9: 4.2 -> 2.8 ms; of M = 120, m = 5, where LDS is not what limits the waves, walks
-// take 5 % longer with half the slots).
+// of M = 150, m = 9: 4.2 -> 2.8 ms).  Any multiple of 64 above n_max, up to 4,096, does.
 __host__ __device__ constexpr int distinct_slots(int n_max) {
     int s = 128;
     while (s < 2048 ? s < 2 * n_max : 3 * s < 4 * n_max) s *= 2;
@@ -28,8 +27,10 @@ __device__ __forceinline__ void distinct_clear(uint32_t* table, int slots, int l
 // more slots than ids), so every probe sequence ends.
 __device__ __forceinline__ int distinct_insert(uint32_t* table, int slots, uint32_t id,
                                                bool active) {
-    const uint32_t mask = (uint32_t)slots - 1u;
-    uint32_t slot = (id * 0x9E3779B1u) >> 7 & mask;
+    uint32_t slot = __umulhi(id * 0x9E3779B1u, (uint32_t)slots);
+    // Ids that meet in a slot go on from it in steps of their own: 67, 71, 73 or 79, primes that `slots`, 64
+    // times at most 64, has no factor in common with, so that every slot is reached.
+    const uint32_t step = 0x4F494743u >> (id & 3u) * 8u & 0xFFu;
     bool is_new = false;
     bool pending = active;
     for (int probe = 0; probe < slots; ++probe) {
@@ -42,7 +43,8 @@ __device__ __forceinline__ int distinct_insert(uint32_t* table, int slots, uint3
             } else if (old == id) {
                 pending = false;
             } else {
-                slot = (slot + 1u) & mask;
+                slot += step;
+                slot = min(slot, slot - (uint32_t)slots);
             }
         }
     }

@@ -26,12 +26,10 @@ inline void launch_and_mark(Kernel kernel, dim3 grid, dim3 block, size_t lds_byt
 struct EdgeRecords {
     const void* data = nullptr;  // null: no records, the walk reads the CSR
     int format = 0;
-    int id_bits = 0, lo_bits = 0;  // field widths of the packed layout
-    int id_bytes = 0;              // of the short layout
+    int id_bits = 0, lo_bits = 0;  // field widths of the packed layout; of the short one id_bits
 };
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m);
-bool walks_have_few_waves(int32_t M, int32_t m, bool set_sizes);  // launch_walks
-EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves);
+EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges);
 size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges);
 hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const int32_t* col_idx,
                                int32_t n_nodes, int64_t n_edges, const EdgeRecords& rec);

@@ -64,8 +64,7 @@ __global__ void row_group_kernel(const int32_t* __restrict__ row_ptr, int32_t n_
 // and packed records go past the caches, which a pass's outputs have filled by then: 20 M entries on 1M
 // nodes 137 us, 161 through the caches, 2.6 M on 235,000 22 and 24, 42 M on 524,288 249 and 286.
 // (Only where nothing else had been written since the launch before were they faster through the
-// caches, up to 24 M entries.)  The bytes of short records, two or three stores an entry, are put
-// together in the caches.
+// caches, up to 24 M entries.)  Short records of a workgroup are whole words, put together from LDS.
 // What bounds this kernel is the random look-up: a 128-byte line each, 56 G/s from memory where it
 // misses the L2 and 260 G/s from an L2 with nothing else to do.  The 11.6 MB of row_ptr of a
 // 2.9M-node graph miss a 4 MB L2 most of the time, its groups are 3.9 MB: 60 M entries in 508 us,
@@ -75,7 +74,7 @@ constexpr int kRecordItems = 4;  // entries of a thread, all their look-ups in f
 template <int kRec, bool kGroups>
 __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int32_t n_nodes,
-    int64_t n_edges, int id_bits, int lo_bits, int id_bytes, const uint4* __restrict__ groups,
+    int64_t n_edges, int id_bits, int lo_bits, const uint4* __restrict__ groups,
     void* __restrict__ rec) {
     const int64_t e0 = (int64_t)blockIdx.x * (kRecordThreads * kRecordItems) + threadIdx.x;
     uint32_t t[kRecordItems];
@@ -120,6 +119,30 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
 #pragma unroll
         for (int u = 0; u < kRecordItems; ++u) row_ends(row_ptr, node[u] ? t[u] : 0u, &lo[u], &hi[u]);
     }
+    if constexpr (kRec == kRecShort) {
+        constexpr int kTile = kRecordThreads * kRecordItems;
+        __shared__ uint32_t ids[kTile + 1];
+        const int tid = (int)threadIdx.x;
+        const int64_t first = (int64_t)blockIdx.x * kTile;
+        const int n = (int)min((int64_t)kTile, n_edges - first);
+#pragma unroll
+        for (int u = 0; u < kRecordItems; ++u) {
+            const bool ok = node[u] && lo[u] >= 0 && hi[u] >= lo[u] && (int64_t)hi[u] <= n_edges;
+            const int i = u * kRecordThreads + tid;
+            ids[i] = i >= n ? 0u : ok ? t[u] : (uint32_t)n_nodes;
+        }
+        __syncthreads();
+        // a tile is 32 * id_bits words, and begins with a word of its own
+        uint32_t* to = static_cast<uint32_t*>(rec) + (int64_t)blockIdx.x * (kTile / 32 * id_bits);
+        const int n_words = (n * id_bits + 31) / 32;
+        for (int j = tid; j < n_words; j += kRecordThreads) {
+            int i = j * 32 / id_bits, at = i * id_bits - j * 32;  // the first id of word j, and its place there
+            uint32_t word = ids[i] >> -at;
+            for (at += id_bits; at < 32; at += id_bits) word |= ids[++i] << at;
+            to[j] = word;
+        }
+        return;
+    }
 #pragma unroll
     for (int u = 0; u < kRecordItems; ++u) {
         const int64_t e = e0 + u * kRecordThreads;
@@ -128,12 +151,6 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
         if (kRec == kRecWide) {
             static_cast<int4*>(rec)[e] =
                 ok ? make_int4((int)t[u], lo[u], hi[u] - lo[u], 0) : make_int4(-1, 0, 0, 0);
-        } else if (kRec == kRecShort) {
-            const uint32_t r = ok ? t[u] : (uint32_t)n_nodes;
-            uint8_t* to = static_cast<uint8_t*>(rec) + e * id_bytes;
-            to[0] = (uint8_t)r;
-            to[1] = (uint8_t)(r >> 8);
-            if (id_bytes == 3) to[2] = (uint8_t)(r >> 16);
         } else {
             const uint32_t deg_big = (1u << rec_degree_bits(id_bits, lo_bits)) - 1u;
             unsigned long long r = (unsigned long long)(uint32_t)n_nodes;  // bad entry
@@ -150,7 +167,7 @@ __global__ __launch_bounds__(kRecordThreads) void edge_record_kernel(
 template <bool kCount, int kRec>
 __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const void* __restrict__ rec, int id_bits, int lo_bits, int id_bytes, int32_t n_nodes, int64_t n_edges,
+    const void* __restrict__ rec, int id_bits, int lo_bits, int32_t n_nodes, int64_t n_edges,
     const int32_t* __restrict__ seeds, int64_t n_seeds, int32_t M, int32_t m, uint32_t key0,
     uint32_t key1, int32_t* __restrict__ walks, int32_t* __restrict__ set_sizes, int32_t slots,
     uint32_t* __restrict__ err) {
@@ -184,7 +201,7 @@ __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
         n_distinct = distinct_insert(table, slots, (uint32_t)u, lane == 0);
     }
 
-    const WalkGraph g{row_ptr, col_idx, rec, id_bits, lo_bits, id_bytes, n_nodes, n_edges};
+    const WalkGraph g{row_ptr, col_idx, rec, id_bits, lo_bits, n_nodes, n_edges};
     int32_t u_lo, u_deg;
     bool bad_graph = seed_row(g, u, &u_lo, &u_deg);
     for (int w0 = 0; w0 < M; w0 += kWalkChains * kWave) {
@@ -211,6 +228,31 @@ __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
     raise_error(err, bad_graph, kDevBadGraph);
 }
 
+// LDS for the set of a seed's nodes while walks are made from short records, whose second trip wants waves
+// to hide behind: as many workgroups a compute unit as half as many slots again as nodes allow, and then as
+// many slots as they have room for.  235,000 seeds of M = 150, m = 4 1,290 -> 880 us (12 -> 24 waves), of
+// M = 200 1,380 -> 1,067 (20 waves), 120,000 of M = 200, m = 9 4,930 -> 2,635 (8 waves).  From packed
+// records, where lines from memory are what bounds the walks, they are faster with fewer waves
+// (1,000,000 seeds of M = 120, m = 5 5,790, with 20 waves 6,000; 400,000 of M = 200, m = 4 3,290 and 3,390).
+// (At six workgroups free slots are worth more than waves: 235,000 seeds of M = 100, m = 4 with 832 slots
+// 569 us, with 576, which eight have room for, 627.)
+constexpr int kWalkMostGroups = 6;
+struct WalkTable {
+    int groups, slots;
+};
+static WalkTable walk_table(int32_t M, int32_t m) {
+    constexpr int kLds = 160 * 1024 / 4, kLdsPart = kLds / 128;  // words of a compute unit, given out in parts
+    const int n = 1 + M * m;
+    const int stage = kWalkChains * kWave * (m + 1);
+    WalkTable t{kLds / (kWalkWavesPerBlock * (stage + n + n / 2)), 0};
+    t.groups = t.groups < 1 ? 1 : t.groups > kWalkMostGroups ? kWalkMostGroups : t.groups;
+    const int room = kLds / t.groups / kLdsPart * kLdsPart / kWalkWavesPerBlock - stage;
+    t.slots = (room < 5 * n / 2 ? room : 5 * n / 2) / 64 * 64;
+    if (t.slots <= n) t.slots = (n + 64) / 64 * 64;
+    if (t.slots < 128) t.slots = 128;  // (more than distinct_insert goes on by)
+    return t;
+}
+
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m) {
     // the expansion reads every edge entry once; it pays off when the steps after the first
     // outnumber the edge entries several times
@@ -223,38 +265,34 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
     return b;
 }
 
-// Whether records are the ids alone: where row_ptr, a quarter of a 4 MB L2 at most, leaves the L2 to
-// them and packed records are at least twice as large as it.  Walks + RPE (M = 100, m = 4 where nothing
-// else is said), us, packed / short:
-//    30,000 nodes   0.6 M entries, M = 200   193 /   195     1.2 M            130 /   114
-//    60,000 nodes   0.6 M, M = 200           302 /   307     4.8 M, M = 200   671 /   485
-//   100,000 nodes   1.2 M                    326 /   324     1.6 M, m = 9     742 /   562
-//                   8 M, M = 200           1,154 / 1,034
-//   235,000 nodes   2.6 M, M = 200         1,538 / 1,450     16 M, M = 200  2,721 / 2,668
-//   300,000 nodes   4.8 M, M = 50            711 /   707
-//   350,000 nodes   7 M, M = 50              881 /   903
-//   500,000 nodes   2 M, M = 50              950 /   989     6 M, M = 50    1,108 / 1,198
+// Whether records are the ids alone: where row_ptr leaves the larger part of a 4 MB L2 to them and packed
+// records are at least twice as large as it.  Walks + RPE (M = 100, m = 4 where nothing else is said), us,
+// packed / short (up to 235,000 nodes short ones of whole bytes, then / of whole bits):
+//    30,000 nodes   0.6 M entries, M = 200   193 /   195     1.2 M            130 /   114 /   114
+//    60,000 nodes   0.6 M, M = 200           302 /   307     4.8 M, M = 200   671 /   485 /   485
+//   100,000 nodes   1.2 M                    326 /   324     1.6 M, m = 9     742 /   562 /   520
+//                   8 M, M = 200           1,154 / 1,034 / 955
+//   235,000 nodes   2.6 M, M = 200         1,538 / 1,450 / 1,430   16 M, M = 200  2,721 / 2,668 / 2,570
+//   300,000 nodes   4.8 M, M = 50            749 /   721
+//   350,000 nodes   7 M, M = 50              940 /   923     3 M            1,138 / 1,086
+//   500,000 nodes   2 M, M = 50              977 / 1,012     6 M, M = 50    1,152 / 1,206
+// Walks alone, counting their sets: 320,000 nodes, 3 M, M = 150 1,540 / 1,147, 5 M, M = 150, m = 9 5,539 /
+// 5,377, 14 M 6,600 / 6,632; 390,000, 8 M, M = 150 2,408 / 2,496.
 // (Entries are addressed with 24 bits.)
-// few_waves: the launch has a dozen waves a compute unit or fewer (walks that count sets of more than 640
-// nodes in LDS), and the second trip of a step shows: 235,000 seeds of M = 200, m = 4 without the table
-// 1,372 / 1,460 us, 131,000 891 / 860, 212,449 of M = 147, m = 9 3,897 / 4,124.
-constexpr int kManySteps = 640;
-bool walks_have_few_waves(int32_t M, int32_t m, bool set_sizes) { return set_sizes && M * m > kManySteps; }
-constexpr int32_t kShortNodes = 1 << 18;
-static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges, bool few_waves) {
-    return n_nodes <= (few_waves ? kShortNodes / 2 : kShortNodes) && n_edges >= 1 << 20 && n_edges < 1 << 24;
+constexpr int32_t kShortNodes = 5 << 16;
+static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges) {
+    return n_nodes <= kShortNodes && n_edges >= 1 << 20 && n_edges < 1 << 24;
 }
 
-EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves) {
+EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
     EdgeRecords plan;
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
     plan.lo_bits = bits_for((uint64_t)n_edges);   // 31 at most
     // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
     // small graphs the packed array fits more of its lines into the L2s.)
     plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
-    if (rows_beside_short_records(n_nodes, n_edges, few_waves)) {
+    if (rows_beside_short_records(n_nodes, n_edges)) {
         plan.format = kRecShort;
-        plan.id_bytes = plan.id_bits <= 16 ? 2 : 3;
     }
     // the degree lies in the word's upper half
     if (plan.format == kRecPacked && plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
@@ -280,10 +318,10 @@ static bool rows_in_groups(int32_t n_nodes, int64_t n_edges) {
 }
 
 static size_t record_array_bytes(const EdgeRecords& plan, int64_t n_edges) {
-    const size_t bytes = plan.format == kRecShort ? plan.id_bytes : plan.format == kRecPacked ? 8 : 16;
-    // short records are read as words: the last one's word may end behind it
-    const size_t behind = plan.format == kRecShort ? 2 : 0;
-    return ((size_t)n_edges * bytes + behind + 15) & ~(size_t)15;
+    const size_t bits = plan.format == kRecShort ? plan.id_bits : plan.format == kRecPacked ? 64 : 128;
+    // short records are read as the four bytes from where one begins: the last one's may end behind it
+    const size_t behind = plan.format == kRecShort ? 4 : 0;
+    return (((size_t)n_edges * bits + 7) / 8 + behind + 15) & ~(size_t)15;
 }
 
 size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges) {
@@ -298,7 +336,7 @@ static hipError_t launch_walks_cfg(hipStream_t stream, const int32_t* row_ptr,
                                    int32_t M, int32_t m, uint64_t rng_seed, int32_t* walks,
                                    int32_t* set_sizes, uint32_t* err) {
     const int64_t blocks = (n_seeds + kWalkWavesPerBlock - 1) / kWalkWavesPerBlock;
-    const int slots = kCount ? distinct_slots(1 + M * m) : 0;
+    const int slots = !kCount ? 0 : kRec == kRecShort ? walk_table(M, m).slots : distinct_slots(1 + M * m);
     const size_t lds_bytes = (size_t)kWalkWavesPerBlock * (kWalkChains * kWave * (m + 1) + slots) * 4;
     if (lds_bytes > 48 * 1024) {
         hipError_t rc = hipFuncSetAttribute(
@@ -308,7 +346,7 @@ static hipError_t launch_walks_cfg(hipStream_t stream, const int32_t* row_ptr,
     }
     hipLaunchKernelGGL((walk_kernel<kCount, kRec>), dim3((unsigned)blocks),
                        dim3(kWalkWavesPerBlock * kWave), lds_bytes, stream, row_ptr, col_idx,
-                       rec.data, rec.id_bits, rec.lo_bits, rec.id_bytes, n_nodes, n_edges, seeds, n_seeds, M, m,
+                       rec.data, rec.id_bits, rec.lo_bits, n_nodes, n_edges, seeds, n_seeds, M, m,
                        (uint32_t)(rng_seed & 0xFFFFFFFFull), (uint32_t)(rng_seed >> 32), walks,
                        set_sizes, slots, err);
     return hipGetLastError();
@@ -332,8 +370,8 @@ hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const
                         : rec.format == kRecPacked
                             ? (groups ? edge_record_kernel<kRecPacked, true> : edge_record_kernel<kRecPacked, false>)
                             : (groups ? edge_record_kernel<kRecWide, true> : edge_record_kernel<kRecWide, false>);
-    kernel<<<grid, block, 0, stream>>>(row_ptr, col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits,
-                                       rec.id_bytes, groups, data);
+    kernel<<<grid, block, 0, stream>>>(row_ptr, col_idx, n_nodes, n_edges, rec.id_bits, rec.lo_bits, groups,
+                                       data);
     return hipGetLastError();
 }
 

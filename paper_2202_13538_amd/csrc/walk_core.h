@@ -16,10 +16,10 @@ namespace surel {
 //   kRecWide    int4 (id, row start, degree, 0); id -1 for an entry that names no node or whose
 //               row is malformed: for graphs whose ids and row starts leave the packed degree too
 //               few bits;
-//   kRecShort   the id alone, in id_bytes = 2 or 3 bytes, n_nodes marking a bad entry; the row is
-//               looked up in row_ptr after all, except behind the last step.  For graphs of so few
+//   kRecShort   the id alone, id_bits <= 19 bits after id_bits bits, n_nodes marking a bad entry; the row
+//               is looked up in row_ptr after all, except behind the last step.  For graphs of so few
 //               nodes that row_ptr lies in every L2, and so many entries that packed records do not:
-//               a line from memory carries 43 or 64 neighbours instead of 16, and a larger part of
+//               a line from memory carries 54 neighbours and more instead of 16, and a larger part of
 //               the array stays in the L2 (see edge_record_plan).
 constexpr int kRecNone = 0, kRecWide = 1, kRecPacked = 2, kRecShort = 3;
 
@@ -34,7 +34,6 @@ struct WalkGraph {
     const int32_t* __restrict__ col_idx;
     const void* __restrict__ rec;
     int id_bits, lo_bits;  // kRecPacked; kRecShort: id_bits only
-    int id_bytes;          // kRecShort
     int32_t n_nodes;
     int64_t n_edges;
 };
@@ -117,12 +116,12 @@ __device__ __forceinline__ bool walk_many(const WalkGraph& g, int32_t u, int32_t
                         }
                     } else if (kRec == kRecShort) {
                         const char* rec = static_cast<const char*>(g.rec);
-                        const uint32_t id_mask = (1u << g.id_bits) - 1u;
                         struct __attribute__((packed)) word_t { uint32_t v; };
 #pragma unroll
-                        for (int c = 0; c < C; ++c) {
-                            const uint32_t at = (uint32_t)__umul24(e[c], (uint32_t)g.id_bytes);
-                            id[c] = reinterpret_cast<const word_t*>(rec + at)->v & id_mask;
+                        for (int c = 0; c < C; ++c) {  // a record ends within four bytes of where it begins
+                            const uint32_t bit = (uint32_t)__umul24(e[c], (uint32_t)g.id_bits);
+                            const uint32_t word = reinterpret_cast<const word_t*>(rec + (bit >> 3))->v;
+                            id[c] = __builtin_amdgcn_ubfe(word, bit & 7u, (uint32_t)g.id_bits);
                         }
 #pragma unroll
                         for (int c = 0; c < C; ++c) lo[c] = deg[c] = 0u;

@@ -59,7 +59,7 @@ inline FusedJob fused_job(const int32_t* row_ptr, const int32_t* col_idx, int32_
                           int32_t m, uint64_t rng_seed, int32_t* walks, int64_t cap_rows,
                           int64_t* rpe_off, int32_t* ids, uint16_t* cnt, const EdgeRecords& rec,
                           uint32_t spin_limit, int64_t* h_total, uint32_t* err) {
-    return FusedJob{{row_ptr, col_idx, rec.data, rec.id_bits, rec.lo_bits, rec.id_bytes, n_nodes, n_edges},
+    return FusedJob{{row_ptr, col_idx, rec.data, rec.id_bits, rec.lo_bits, n_nodes, n_edges},
                     seeds, n_seeds, M, m, (uint32_t)(rng_seed & 0xFFFFFFFFull),
                     (uint32_t)(rng_seed >> 32), 65536u / (uint32_t)m + 1u, walks, cap_rows, rpe_off,
                     ids, cnt, 0, 0, table_goes_past(n_seeds, M, m), spin_limit, h_total, err};

@@ -1374,11 +1374,12 @@ def test_one_call_rpe_ids_capacity(ctx):
 
 @pytest.mark.parametrize("n_nodes, n_edges, malformed", [
     (65_535, 1 << 20, False), (65_536, 1 << 20, False), (1 << 18, (1 << 20) + 5, False),
-    ((1 << 18) + 1, 1 << 20, False), (65_535, (1 << 20) - 1, False), (1500, (1 << 20) + 3, False),
+    ((1 << 18) + 1, 1 << 20, False), (5 << 16, (1 << 20) + 1023, False), ((5 << 16) + 1, 1 << 20, False),
+    (1, 1 << 20, False), (65_535, (1 << 20) - 1, False), (1500, (1 << 20) + 3, False),
     (65_535, 1 << 20, True), (200_000, 1 << 20, True), (30_000, (1 << 24) - 1, False),
     (30_000, 1 << 24, False)])
 def test_short_edge_records(ctx, n_nodes, n_edges, malformed):
-    # records that are ids of 2 or 3 bytes, on both sides of every line between them and the packed
+    # records that are ids of 1 to 19 bits, on both sides of every line between them and the packed
     # ones: uneven degrees, empty rows, a hub, entries and rows that are malformed
     rng = np.random.default_rng(n_nodes + n_edges)
     cuts = np.sort((rng.random(n_nodes - 1) ** 2 * (n_edges + 1)).astype(np.int64))
@@ -1418,8 +1419,7 @@ def test_short_edge_records(ctx, n_nodes, n_edges, malformed):
 @pytest.mark.parametrize("n_nodes", [1 << 17, (1 << 17) + 1])
 @pytest.mark.parametrize("M", [128, 129])
 def test_edge_records_of_walks_that_count_their_sets(ctx, n_nodes, M):
-    # sets of up to and of more than 640 nodes, whose records are short up to 2^18 and up to 2^17
-    # nodes: the walks are those that are made without sizes, the sizes those of the walks
+    # sets of about 640 nodes: the walks are those that are made without sizes, the sizes those of the walks
     m, n_edges, n_seeds = 5, 1 << 20, 9000
     rng = np.random.default_rng(n_nodes + M)
     cuts = np.sort((rng.random(n_nodes - 1) ** 2 * (n_edges + 1)).astype(np.int64))
@@ -1435,6 +1435,29 @@ def test_edge_records_of_walks_that_count_their_sets(ctx, n_nodes, M):
     walks = w[:n].cpu().numpy()
     assert np.array_equal(walks, oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
     assert [len(np.unique(x)) for x in walks] == sizes[:n].cpu().tolist()
+
+
+@pytest.mark.parametrize("M, m, n_seeds, n_nodes", [(1, 2, 4_200_000, 70_000), (4, 2, 1_100_000, 70_000),
+                                                    (50, 4, 30_000, 3), (61, 9, 9000, 70_000),
+                                                    (150, 4, 9400, 70_000), (200, 9, 3000, 70_000),
+                                                    (200, 9, 3000, 330_000), (128, 15, 2400, 70_000),
+                                                    (682, 2, 6200, 70_000), (1024, 1, 3000, 70_000)])
+def test_set_sizes_of_tables_that_fill_lds(ctx, M, m, n_seeds, n_nodes):
+    # hash tables of any multiple of 64 slots, the smallest, the largest and the fullest among them (and of
+    # powers of two where records are not short): every size against the sorted walks
+    n_edges = 1 << 20
+    rng = np.random.default_rng(M + m)
+    cuts = np.sort(rng.integers(0, n_edges + 1, size=n_nodes - 1))
+    rp = np.concatenate([[0], cuts, [n_edges]]).astype(np.int32)
+    ci = rng.integers(0, n_nodes, size=n_edges).astype(np.int32)
+    seeds = rng.integers(0, n_nodes, size=n_seeds).astype(np.int32)
+    sizes = torch.empty(n_seeds, dtype=torch.int32, device="cuda")
+    w = binding.sample_walks(ctx, dev(rp), dev(ci), dev(seeds), M, m, 3, set_sizes=sizes)
+    assert ctx.check() == 0
+    nodes = w.view(n_seeds, -1).sort(dim=1).values
+    assert torch.equal(1 + (nodes[:, 1:] != nodes[:, :-1]).sum(dim=1).int(), sizes)
+    n = 200
+    assert np.array_equal(w[:n].cpu().numpy(), oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
 
 
 @pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
