@@ -548,29 +548,32 @@ static int prune_scratch(surel_ctx* ctx, int64_t cap_T, surel::PruneScratch* ps)
 
 // The end of the pruning calls: T and the codes, the number of distinct vectors and (h_rows, if the
 // call's kernel reports it in the pinned words) the row total, with one wait.
-// n_rows, d_rows: the number of rows, or where it stands on the device.
+// n_rows, d_rows: the number of rows, or where it stands on the device.  d_cnt: see launch_prune_order.
 static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m, int64_t n_rows,
-                        const int64_t* d_rows, int64_t cap_rows, uint16_t* d_T, int32_t* d_code,
-                        int64_t* h_rows, int64_t* h_n_T) {
+                        const int64_t* d_rows, int64_t cap_rows, const uint16_t* d_cnt, uint16_t* d_T,
+                        int32_t* d_code, int64_t* h_rows, int64_t* h_n_T) {
     KernelSpan span(ctx, SUREL_K_PRUNE);
-    if (surel::launch_prune_order(ctx->stream, ctx->n_cu, ps, m, n_rows, d_rows, cap_rows, d_T, d_code,
-                                  ctx->h_pinned + 2, ctx->h_pinned + 1) != hipSuccess)
+    if (surel::launch_prune_order(ctx->stream, ctx->n_cu, ps, m, n_rows, d_rows, cap_rows, d_cnt, d_T,
+                                  d_code, ctx->h_pinned + 2, ctx->h_pinned + 1) != hipSuccess)
         return SUREL_E_HIP;
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
     const int64_t n_T = ctx->h_pinned[2];
     *h_n_T = n_T;
-    // with more than cap_T vectors the set's list is not complete, and its slots are not all empty
-    if (n_T <= ps.cap_T) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
+    // with more than cap_T vectors the set's list is not complete, and its slots are not all empty; with
+    // more than are ranked at once they are emptied behind the sort
+    const bool many = n_T > surel::prune_rank_most(ps.cap_T, m);
+    if (!many) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
     if (h_rows) {
         *h_rows = n_rows = pinned_total(ctx);
         if (int rc = judge_total(true, cap_rows, n_rows)) return rc;  // not all rows have codes
     }
     if (n_T > ps.cap_T) return SUREL_E_CAPACITY;
-    if (n_T > surel::prune_rank_most(ps.cap_T, m)) {
-        if (surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_T, d_code) !=
+    if (many) {
+        if (surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_cnt, d_T, d_code) !=
             hipSuccess)
             return SUREL_E_HIP;
         if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+        ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
     }
     return SUREL_OK;
 }
@@ -602,7 +605,7 @@ int surel_sample_walks_rpe_ids(surel_ctx* ctx, const int32_t* d_row_ptr, const i
                               rng_seed, d_walks, cap_rows, d_rpe_off, d_rpe_ids, d_rpe_cnt, d_code,
                               ps, true))
         return rc;
-    return prune_finish(ctx, ps, m, 0, d_rpe_off + n_seeds, cap_rows, d_T, d_code, h_rows, h_n_T);
+    return prune_finish(ctx, ps, m, 0, d_rpe_off + n_seeds, cap_rows, nullptr, d_T, d_code, h_rows, h_n_T);
 }
 
 // The join over vectors of m+1 16-bit entries per table row; absent16 fills the vector of a
@@ -878,7 +881,7 @@ int surel_prune_rpe(surel_ctx* ctx, const uint16_t* d_rpe_cnt, int64_t n_rows, i
                                         ctx->spin_limit, ctx->d_err) != hipSuccess)
             return SUREL_E_HIP;
     }
-    return prune_finish(ctx, ps, m, n_rows, nullptr, n_rows, d_T, d_code, nullptr, h_n_T);
+    return prune_finish(ctx, ps, m, n_rows, nullptr, n_rows, d_rpe_cnt, d_T, d_code, nullptr, h_n_T);
 }
 
 int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_queries, int32_t k,

@@ -12,13 +12,6 @@ namespace surel {
 // 35,000 of them (470 MB) 156 / 143; 500,000 of M = 30, m = 3 (900 MB) 623 / 501.
 constexpr int64_t kPastBytes = 5 << 26;
 
-// Whether the codes of a table's rows go past the caches while the distinct vectors are collected.  The
-// renumbering reads them back at once, from the 256 MB memory-side cache if they are there.  Pruning in us,
-// through / past the caches, codes in the same buffer each time and in several in turn: 8.4 M rows (m = 4,
-// 34 MB of codes) 85 / 88 and 88 / 92, 17 M 114 / 117 and 122 / 129, 29 M 168 / 166 and 170 / 176,
-// 58 M (234 MB) 306 / 304, 146 M 716 / 691.
-inline bool codes_go_past(int64_t n_rows) { return n_rows > (int64_t)1 << 25; }
-
 // The join's filling launch puts a row at the place inside kRowsAlign rows that it has in the output's
 // lines: 32 ids are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
 constexpr int kRowsAlign = 32;

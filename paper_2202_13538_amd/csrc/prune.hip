@@ -6,13 +6,14 @@
 //
 // Steps, all on the device:
 //   collect  every row looks its vector up in a global open-addressing hash set and inserts it if
-//            it is new (prune_set.h); the vector's number in the set goes to code[row].  A slot is
+//            it is new (prune_set.h); the vector's number in the set goes to the codes.  A slot is
 //            64 bytes (state, number, vector), aligned, so one cache line holds all of it; only a
 //            slot that does not look full yet is touched with atomics.
 //   rank     every vector's place in the sorted array: up to prune_rank_most vectors are compared
 //            all with all (a few thousand, usually: one short launch that needs no count on the
 //            host), more are sorted with a bitonic network in global memory.  T[place] = vector.
-//   codes    code[row] = place of the row's vector.
+//   codes    code[row] = place of the row's vector, from the numbers (which are 16 bits each where no
+//            larger ones occur, see kNarrowMost).
 //   clean    the slots that were used are emptied again, by the list of the set's members (a
 //            memset of the table, and a pass over it that gathers the full slots, were 95 us of a
 //            call with cap_T = 2^20).
@@ -24,7 +25,6 @@
 
 #include "device_util.h"
 #include "kernels.h"
-#include "lines.h"
 #include "prune_set.h"
 
 namespace surel {
@@ -46,6 +46,22 @@ struct Collect {
     static constexpr int kWaves = kFit < 16 ? kFit : 16;
 };
 
+// Numbers of a tile on their way to the renumbering.  While a wave has seen no number above kNarrowMost, its
+// tiles' numbers go out in 16 bits, in the first half of the tile's codes: a lane's rows (g * kWave + lane) * 2
+// and the one behind, g = 0 .. 3, are the 16 bytes at lane * 16, and kNarrowMost + 1 is a row whose vector the
+// renumbering looks up once more (one that was on the late list and has a larger number).  From then on a tile
+// is its codes as they stand, with kWide set in each, so that any word of a tile tells which of both it is.
+// (Numbers are handed out in the order of insertion, so the commonest vectors have small ones.)
+// 146 M rows of 1M seeds with 1,500 vectors are pruned in 545 us, 692 with numbers of 32 bits; 60 M with
+// 100,000 vectors, nearly all of them wide, in 1.90 ms, 1.98.
+constexpr int32_t kNarrowMost = 0x7FFE;
+constexpr uint32_t kNarrowUnknown = (uint32_t)kNarrowMost + 1u;
+constexpr uint32_t kWide = 0x80000000u;
+// place of a row of a tile among the 16-bit numbers
+__device__ __forceinline__ int narrow_place(int t) {
+    return ((t >> 1) & (kWave - 1)) * 8 + (t / (2 * kWave)) * 2 + (t & 1);
+}
+
 // Rows whose vectors no LDS table has, with their vectors (as pairs of counts, see row_pairs): looked
 // up in the global table together once there are 64 of them, for the look-up is a chain of trips to
 // memory behind the counts on their way.
@@ -55,6 +71,7 @@ struct LateList {
     static constexpr int kRoom = Collect<LT>::kLate;
     uint4* items;  // pairs 0 .. NW-1, row
     int n;
+    uint32_t wide_from;  // the first row of the wave's that went out wide (~0: none yet)
     __device__ __forceinline__ void append(uint64_t all, bool mine, const uint32_t (&pair)[NW], uint32_t row) {
         const int before = (int)__builtin_amdgcn_mbcnt_hi(
             (uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
@@ -63,10 +80,12 @@ struct LateList {
                                            NW > 2 ? pair[NW > 2 ? 2 : 0] : 0u, row);
         n += __popcll(all);
     }
-    // place(row): where the row's code goes
-    template <typename Place>
-    __device__ __forceinline__ void resolve(int lane, uint32_t* cache, const VectorSet& set,
-                                            Place&& place) {
+    // tile(row): the codes of the row's tile.  next: the first row that has not gone out yet.
+    template <typename Tile>
+    __device__ __forceinline__ void resolve(int lane, uint32_t next, uint32_t* cache,
+                                            const VectorSet& set, Tile&& tile) {
+        constexpr uint32_t kRows = Collect<LT>::kRows;
+        const uint32_t wide_before = wide_from;
         wave_sync();
         for (int u0 = 0; u0 < n; u0 += kWave) {
             const bool valid = u0 + lane < n;
@@ -82,7 +101,16 @@ struct LateList {
             const int32_t number = lookup_hashed<NW, CollectTables>(w, hash_vector<NW>(w), valid,
                                                                      cache + kDirectWords, set, lane);
             if (valid && small && number >= 0) cache[at] = (uint32_t)number + 1u;
-            if (valid) *place(item.w) = number;
+            if (wide_from == ~0u && __ballot(valid && number > kNarrowMost) != 0ull) wide_from = next;
+            if (valid) {
+                int32_t* codes = tile(item.w);
+                const int t = (int)(item.w % kRows);
+                if (item.w >= wide_before) {
+                    codes[t] = (int32_t)((uint32_t)number | kWide);
+                } else if ((uint32_t)number < kNarrowUnknown) {
+                    reinterpret_cast<uint16_t*>(codes)[narrow_place(t)] = (uint16_t)number;
+                }
+            }
         }
         n = 0;
         wave_sync();
@@ -98,7 +126,7 @@ struct LateList {
 // (With all rows that the direct table does not have on the late list, two in a hundred went out a
 // second time to a line that had left the caches: 2.6 M more writes beside 9.1 M, a fifth of the time.
 // With none on it, tables with many vectors waited for the global table in every tile.)
-template <int LT, bool kPast>
+template <int LT>
 __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t first, uint16_t* misses,
                                              LateList<LT>& late, uint32_t* cache, const VectorSet& set,
                                              int32_t* __restrict__ code) {
@@ -177,27 +205,39 @@ __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t 
             }
         }
     }
-    typedef int32_t two_t __attribute__((ext_vector_type(2), aligned(4)));
+    if (late.wide_from == ~0u) {
+        bool large = false;
+#pragma unroll
+        for (int g = 0; g < kTurns; ++g) large = large || max(number[g][0], number[g][1]) > kNarrowMost;
+        if (__ballot(large) != 0ull) late.wide_from = first;
+    }
+    if (late.wide_from == ~0u) {
+        static_assert(kTurns == 4, "a lane's rows are 16 bytes");
+        typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));
+        quad_t all;
+#pragma unroll
+        for (int g = 0; g < kTurns; ++g)
+            all[g] = min((uint32_t)number[g][0], kNarrowUnknown) | min((uint32_t)number[g][1], kNarrowUnknown) << 16;
+        reinterpret_cast<quad_t*>(code)[lane] = all;
+        return;
+    }
+    typedef uint32_t two_t __attribute__((ext_vector_type(2), aligned(4)));
 #pragma unroll
     for (int g = 0; g < kTurns; ++g) {
-        two_t* to = reinterpret_cast<two_t*>(code + (g * kWave + lane) * 2);
-        const two_t both = {number[g][0], number[g][1]};
-        if constexpr (kPast) {
-            __builtin_nontemporal_store(both, to);
-        } else {
-            *to = both;
-        }
+        const two_t both = {(uint32_t)number[g][0] | kWide, (uint32_t)number[g][1] | kWide};
+        reinterpret_cast<two_t*>(code)[g * kWave + lane] = both;
     }
 }
 
 // A wavefront takes tiles of consecutive rows: they come in as contiguous 16-byte pieces (the next
 // tile's are on their way while one is looked up) and are read row by row from LDS.
-// What bounds it: the stream of counts in and codes out.  146 M rows of 1M seeds with some 1,500
-// vectors 0.45 ms = 4.5 TB/s (0.53 with fix-ups in place of whole lines), 0.38 with no row looked up
-// anywhere but in the direct table; 97 M rows with 15,609 vectors 0.35 ms (0.81).  The tile's loads and
-// the codes' stores are in one straight line, so that a wait for the next tile is not one for the codes.
-// kPast: the codes go past the caches (codes_go_past).
-template <int LT, bool kPast>
+// What bounds it: the stream of counts in and numbers out, and the chain of a tile through LDS.  146 M rows
+// of 1M seeds with some 1,500 vectors 344 us = 5.1 TB/s.  The counts go past the caches and the numbers do not
+// (both past them 378 us, counts through them 386; the renumbering then finds more of the numbers: 146 us, 166
+// where they went past; 60 M rows pruned in 578 us, 586 where they went past, 700 M 6.09 ms and 6.07).  Two
+// tiles ahead: 401 us where one took 387.  The tile's loads and the numbers' stores are in one straight
+// line, so that a wait for the next tile is not one for the numbers.
+template <int LT>
 __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(
     const uint16_t* __restrict__ cnt, int64_t n_rows, int L, int32_t* __restrict__ code,
     VectorSet set) {
@@ -211,7 +251,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t* tile = lds32 + kTableWords + wave * C::kWaveWords;
     const int n_quads = kRows * L / 8;  // whole 16-byte pieces
-    struct __attribute__((packed, aligned(4))) quad_t { uint32_t v[4]; };  // the array is 4-byte aligned
+    typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));  // the array is 4-byte aligned
     const int64_t stride = (int64_t)gridDim.x * C::kWaves;
     const int64_t n_whole = n_rows / kRows;
     int64_t at = (int64_t)blockIdx.x * C::kWaves + wave;
@@ -220,23 +260,23 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
         const quad_t* from = reinterpret_cast<const quad_t*>(cnt + t * kRows * L);
 #pragma unroll
         for (int u = 0; u < kQuads; ++u)
-            if (LT > 0 || u * kWave + lane < n_quads) next[u] = from[u * kWave + lane];
+            if (LT > 0 || u * kWave + lane < n_quads) next[u] = __builtin_nontemporal_load(from + u * kWave + lane);
     };
     auto to_lds = [&]() {
         uint4* to = reinterpret_cast<uint4*>(tile);
 #pragma unroll
         for (int u = 0; u < kQuads; ++u)
             if (LT > 0 || u * kWave + lane < n_quads)
-                to[u * kWave + lane] = make_uint4(next[u].v[0], next[u].v[1], next[u].v[2], next[u].v[3]);
+                to[u * kWave + lane] = make_uint4(next[u][0], next[u][1], next[u][2], next[u][3]);
         wave_sync();
     };
     uint16_t* misses = reinterpret_cast<uint16_t*>(tile + C::kTileWords);
-    LateList<LT == 0 ? 2 : LT> late{reinterpret_cast<uint4*>(tile + C::kTileWords + C::kMisses / 2), 0};
+    LateList<LT == 0 ? 2 : LT> late{reinterpret_cast<uint4*>(tile + C::kTileWords + C::kMisses / 2), 0, ~0u};
     // a wave's rows are numbered along its own tiles, so that 32 bits do for a table of any size
     const int64_t at0 = at;
     uint32_t first = 0;
-    auto place = [&](uint32_t row) -> int32_t* {
-        return code + (at0 + (int64_t)(row / kRows) * stride) * kRows + row % kRows;
+    auto tile_of = [&](uint32_t row) -> int32_t* {
+        return code + (at0 + (int64_t)(row / kRows) * stride) * kRows;
     };
     if (at < n_whole) {
         fetch(at);
@@ -252,12 +292,14 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
             if (at < n_whole) fetch(at);
             if constexpr (LT > 0) {
                 // before anything is known all rows of a tile would go on the list: a few make most
-                // of the others known
-                if (turn == 0)
+                // of the others known (what they leave in the tile's codes is written over)
+                if (turn == 0) {
                     rows_numbers<LT, CollectTables>(kWarmRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
                                                      misses, cache, set, out);
-                tile_numbers<LT, kPast>(tile, lane, first, misses, late, cache, set, out);
-                if (late.n >= kWave) late.resolve(lane, cache, set, place);
+                    wait_memory();
+                }
+                tile_numbers<LT>(tile, lane, first, misses, late, cache, set, out);
+                if (late.n >= kWave) late.resolve(lane, first + kRows, cache, set, tile_of);
             } else {
                 rows_numbers<0, CollectTables>(kRows, lane, L, reinterpret_cast<const uint16_t*>(tile),
                                                 nullptr, cache, set, out);
@@ -267,7 +309,7 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
             if (at < n_whole) to_lds();
             if (turn == 0) break;
         }
-        if constexpr (LT > 0) late.resolve(lane, cache, set, place);
+        if constexpr (LT > 0) late.resolve(lane, first, cache, set, tile_of);
     }
     // the rows behind the last whole tile
     const int rest = (int)(n_rows - n_whole * kRows);
@@ -349,14 +391,17 @@ __global__ __launch_bounds__(256) void prune_place_kernel(
     }
 }
 
-// Empties the slots of the set's members and its counter.
+// Empties the slots of the set's members and its counters, unless there are more than `most` and the set
+// holds all of them: then they are ranked by the sort, whose renumbering looks into the slots.
 __global__ __launch_bounds__(256) void prune_clean_kernel(const uint32_t* __restrict__ members,
-                                                          int64_t cap_T,
+                                                          int64_t most, int64_t cap_T,
                                                           uint32_t* __restrict__ slots,
                                                           unsigned long long* __restrict__ counters) {
     // counters[0]: vectors inserted; counters[1]: workgroups of this launch that have read it;
     // counters[2]: whether a wait ran out
-    const int64_t n = min((int64_t)counters[0], cap_T);
+    const int64_t n_all = (int64_t)counters[0];
+    if (n_all > most && n_all <= cap_T) return;
+    const int64_t n = min(n_all, cap_T);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         slots[(size_t)members[i * kItemWords + kMaxVecWords] * kSlotWords] = kSlotEmpty;
@@ -475,6 +520,117 @@ __global__ __launch_bounds__(256) void prune_codes_kernel(
     }
 }
 
+// The same for numbers as the collecting launch leaves them (Collect<LT>, LT > 0): whole tiles narrow or
+// wide, then plain numbers.  A wave takes tiles, kCodesUnroll of them in flight; with no more vectors than
+// narrow numbers no tile is wide and only the first half of its codes is read.  The first kHotRanks places,
+// which nearly all rows have, are in LDS.
+// What bounds it: the stream of numbers in and codes out, 0.88 GB of 146 M rows in 146 us = 6 TB/s (from
+// numbers of 32 bits 210 us); 8 M rows are bound by the trips before it.
+constexpr int kHotRanks = 4096;
+template <int LT>
+__global__ __launch_bounds__(256) void prune_tile_codes_kernel(
+    const uint32_t* __restrict__ ranks, const unsigned long long* __restrict__ n_inserted,
+    int64_t n_known, int64_t most, int64_t n_rows, const uint16_t* __restrict__ cnt,
+    const uint32_t* __restrict__ slots, uint32_t slot_mask, int32_t* __restrict__ code) {
+    constexpr int kRows = Collect<LT>::kRows, NW = (LT + 1) / 2;
+    typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t two_t __attribute__((ext_vector_type(2), aligned(4)));
+    __shared__ uint32_t hot[kHotRanks];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t n_whole = n_rows / kRows;
+    const int64_t stride = (int64_t)gridDim.x * 4;
+    int64_t t0 = (int64_t)blockIdx.x * 4 + wave;
+    quad_t low[kCodesUnroll], high[kCodesUnroll];
+    auto part = [&](int u) {
+        return reinterpret_cast<const quad_t*>(code + min(t0 + u * stride, n_whole - 1) * kRows) + lane;
+    };
+    auto load_low = [&]() {
+#pragma unroll
+        for (int u = 0; u < kCodesUnroll; ++u) low[u] = __builtin_nontemporal_load(part(u));
+    };
+    if (t0 < n_whole) load_low();  // before the trips for the number of vectors and their places
+    const int64_t n = n_known >= 0 ? n_known : (int64_t)*n_inserted;
+    if (n > most) return;
+    // (a wave with one tile would wait for this table longer than for its places: 2 M rows 86 -> 85 us)
+    const uint32_t n_hot = n_whole > stride ? (uint32_t)min(n, (int64_t)kHotRanks) : 0u;
+    if (n_hot != 0u) {
+        uint32_t mine[kHotRanks / 256];  // their loads are one trip
+#pragma unroll
+        for (int u = 0; u < kHotRanks / 256; ++u) {
+            const uint32_t t = u * 256 + threadIdx.x;
+            mine[u] = t < n_hot ? ranks[t] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kHotRanks / 256; ++u) hot[u * 256 + threadIdx.x] = mine[u];
+        __syncthreads();
+    }
+    auto rank_of = [&](uint32_t c) -> uint32_t {
+        return c < n_hot ? hot[c] : c < (uint32_t)n ? ranks[c] : ~0u;
+    };
+    // a row whose number did not fit: its vector's slot is full and behind no empty one
+    auto number_of = [&](int64_t row) -> uint32_t {
+        uint32_t w[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k)
+            w[k] = (uint32_t)cnt[row * LT + 2 * k] << 16 | (2 * k + 1 < LT ? (uint32_t)cnt[row * LT + min(2 * k + 1, LT - 1)] : 0u);
+        uint32_t h = hash_vector<NW>(w) & slot_mask;
+        for (uint32_t probe = 0; probe <= slot_mask; ++probe) {
+            const uint32_t* slot = slots + (size_t)h * kSlotWords;
+            const uint32_t st = slot[0];
+            if ((st & kSlotFull) == 0u) break;
+            bool same = true;
+#pragma unroll
+            for (int k = 0; k < NW; ++k) same = same && slot[kSlotVector + k] == w[k];
+            if (same) return st & ~kSlotFull;
+            h = (h + 1u) & slot_mask;
+        }
+        return ~0u;
+    };
+    const bool none_wide = n <= (int64_t)kNarrowMost + 1;
+    while (t0 < n_whole) {
+        if (!none_wide) {
+#pragma unroll
+            for (int u = 0; u < kCodesUnroll; ++u) high[u] = __builtin_nontemporal_load(part(u) + kWave);
+        }
+#pragma unroll
+        for (int u = 0; u < kCodesUnroll; ++u) {
+            const int64_t t = t0 + u * stride;
+            if (t >= n_whole) break;
+            int32_t* to = code + t * kRows;
+            if (!none_wide && (__builtin_amdgcn_readfirstlane((int)low[u][0]) < 0)) {
+                quad_t a, b;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    a[k] = rank_of(low[u][k] & ~kWide);
+                    b[k] = rank_of(high[u][k] & ~kWide);
+                }
+                __builtin_nontemporal_store(a, reinterpret_cast<quad_t*>(to) + lane);
+                __builtin_nontemporal_store(b, reinterpret_cast<quad_t*>(to) + kWave + lane);
+                continue;
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                uint32_t c[2] = {low[u][g] & 0xFFFFu, low[u][g] >> 16};
+                if (!none_wide) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        if (c[h] == kNarrowUnknown) c[h] = number_of(t * kRows + (g * kWave + lane) * 2 + h);
+                }
+                const two_t both = {rank_of(c[0]), rank_of(c[1])};
+                __builtin_nontemporal_store(both, reinterpret_cast<two_t*>(to) + g * kWave + lane);
+            }
+        }
+        t0 += stride * kCodesUnroll;
+        if (t0 < n_whole) load_low();
+    }
+    // rows behind the last whole tile: fewer than a tile's
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int64_t row = n_whole * kRows + threadIdx.x; row < n_rows; row += blockDim.x)
+            code[row] = (int32_t)rank_of((uint32_t)code[row]);
+    }
+}
+
 int64_t prune_slots(int64_t cap_T) {
     int64_t s = 1024;
     while (s < 4 * cap_T) s *= 2;
@@ -507,8 +663,7 @@ static hipError_t launch_collect(hipStream_t stream, int n_cu, const uint16_t* c
                                  int L, int32_t* code, const VectorSet& set) {
     using C = Collect<LT>;
     const size_t lds_bytes = (size_t)(kTableWords + C::kWaves * C::kWaveWords) * 4;
-    const auto kernel = LT > 0 && codes_go_past(n_rows) ? prune_collect_kernel<LT, (LT > 0)>
-                                                        : prune_collect_kernel<LT, false>;
+    const auto kernel = prune_collect_kernel<LT>;
     hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (rc != hipSuccess) return rc;
@@ -536,13 +691,39 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
     }
 }
 
-static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int64_t n_known,
+template <int LT>
+static void launch_tile_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int64_t n_known,
+                              int64_t most, int64_t n_rows, const uint16_t* cnt, int32_t* code) {
+    int64_t blocks = n_rows / Collect<LT>::kRows / 4 + 1;
+    if (blocks > (int64_t)n_cu * 8) blocks = (int64_t)n_cu * 8;
+    hipLaunchKernelGGL(prune_tile_codes_kernel<LT>, dim3((unsigned)blocks), dim3(256), 0, stream, ps.ranks,
+                       ps.counters, n_known, most, n_rows, cnt, ps.slots,
+                       (uint32_t)(prune_slots(ps.cap_T) - 1), code);
+}
+
+// cnt: the rows' vectors where the numbers come from launch_prune_collect, else null.
+static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m, int64_t n_known,
                          int64_t most, int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
-                         int32_t* code) {
+                         const uint16_t* cnt, int32_t* code) {
+    if (cnt != nullptr) {
+        switch (m + 1) {
+            case 2: return launch_tile_codes<2>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
+            case 3: return launch_tile_codes<3>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
+            case 4: return launch_tile_codes<4>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
+            case 5: return launch_tile_codes<5>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
+            case 6: return launch_tile_codes<6>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
+            default: break;
+        }
+    }
     int64_t blocks = ((d_rows ? cap_rows : n_rows) / 4 + 256) / 256;
     if (blocks > (int64_t)n_cu * 32) blocks = (int64_t)n_cu * 32;
     hipLaunchKernelGGL(prune_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, ps.ranks,
                        ps.counters, n_known, most, n_rows, d_rows, cap_rows, code);
+}
+
+static void launch_clean(hipStream_t stream, const PruneScratch& ps, int64_t most) {
+    hipLaunchKernelGGL(prune_clean_kernel, dim3(64), dim3(256), 0, stream, ps.members, most, ps.cap_T,
+                       ps.slots, ps.counters);
 }
 
 int64_t prune_rank_most(int64_t cap_T, int32_t m) {
@@ -553,8 +734,9 @@ int64_t prune_rank_most(int64_t cap_T, int32_t m) {
 }
 
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
-                              int64_t n_rows, const int64_t* d_rows, int64_t cap_rows, uint16_t* T,
-                              int32_t* code, int64_t* h_n_T, int64_t* h_stalled) {
+                              int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
+                              const uint16_t* cnt, uint16_t* T, int32_t* code, int64_t* h_n_T,
+                              int64_t* h_stalled) {
     const int64_t most = prune_rank_most(ps.cap_T, m);
     const int L = m + 1;
     switch ((L + 1) / 2) {
@@ -576,14 +758,14 @@ hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& 
     }
     hipLaunchKernelGGL(prune_place_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.counters,
                        most, L, ps.ranks, T, h_n_T, h_stalled);
-    launch_codes(stream, n_cu, ps, -1, most, n_rows, d_rows, cap_rows, code);
-    hipLaunchKernelGGL(prune_clean_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.cap_T,
-                       ps.slots, ps.counters);
+    launch_codes(stream, n_cu, ps, m, -1, most, n_rows, d_rows, cap_rows, cnt, code);
+    launch_clean(stream, ps, most);
     return hipGetLastError();
 }
 
 hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
-                                   int64_t n_rows, int64_t n_T, uint16_t* T, int32_t* code) {
+                                   int64_t n_rows, int64_t n_T, const uint16_t* cnt, uint16_t* T,
+                                   int32_t* code) {
     int64_t len = 1;
     while (len < n_T) len *= 2;  // <= prune_list_len(cap_T) because n_T <= cap_T
     if (len > n_T)
@@ -595,7 +777,8 @@ hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScra
                                dim3(256), 0, stream, ps.members, len, j, k);
     hipLaunchKernelGGL(prune_rank_kernel, dim3((unsigned)((n_T + 255) / 256)), dim3(256), 0, stream,
                        ps.members, n_T, m + 1, ps.slots, ps.ranks, T);
-    launch_codes(stream, n_cu, ps, n_T, n_T, n_rows, nullptr, n_rows, code);
+    launch_codes(stream, n_cu, ps, m, n_T, n_T, n_rows, nullptr, n_rows, cnt, code);
+    launch_clean(stream, ps, ps.cap_T);
     return hipGetLastError();
 }
 

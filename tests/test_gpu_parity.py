@@ -617,8 +617,8 @@ def test_prune_of_many_distinct_vectors(ctx, L, n_T):
 def test_prune_lists_of_rows_that_wait_for_a_look_up(ctx, L, n_rows, n_T, most):
     # around a tile of 512 rows and the rows looked up first; tables whose rows the direct table knows,
     # the hashed cache knows, or neither, so that the list of late rows fills, is emptied over several
-    # tiles, and has no room; codes that go through the caches and (from more than 2^25 rows on) past
-    # them: T is sorted and distinct, and every row's code names its vector
+    # tiles, and has no room; few rows and many (more than 2^25): T is sorted and distinct, and every row's
+    # code names its vector
     g = torch.Generator(device="cuda").manual_seed(n_rows + L)
     vectors = torch.randint(0, most + 1, (4 * n_T, L), device="cuda", generator=g)
     vectors[::2, 0] = 0
@@ -632,6 +632,34 @@ def test_prune_lists_of_rows_that_wait_for_a_look_up(ctx, L, n_rows, n_T, most):
     want = torch.unique(vectors[torch.unique(pick)], dim=0)  # sorted entry by entry
     assert torch.equal(T.view(torch.int16).long(), want)
     assert torch.equal(T.view(torch.int16)[code.long()], cnt.view(torch.int16))
+
+
+@pytest.mark.parametrize("L", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("n_T", [32_766, 32_767, 32_768, 42_000])
+def test_prune_numbers_of_16_bits(ctx, L, n_T):
+    # on both sides of the number of vectors whose numbers fit 16 bits; most rows have common vectors and
+    # every tile some rare ones, so that rows whose numbers do not fit lie in tiles that went out in 16 bits,
+    # in ones that did not, and behind the last whole tile; ranked all with all and (the last) by the sort
+    n_rows = 6_000_000 + 77
+    g = torch.Generator(device="cuda").manual_seed(n_T + L)
+    number = torch.randperm(n_T, device="cuda", generator=g)
+    vectors = torch.randint(0, 4, (n_T, L), device="cuda", generator=g)
+    vectors[:, 0], vectors[:, -1] = number % 256, number // 256
+    pick = (torch.rand(n_rows, device="cuda", generator=g) * 40).long()
+    rare = torch.rand(n_rows, device="cuda", generator=g) < 0.02
+    pick[rare] = torch.randint(0, n_T, (int(rare.sum()),), device="cuda", generator=g)
+    pick[torch.randperm(n_rows, device="cuda", generator=g)[:n_T]] = torch.arange(n_T, device="cuda")
+    cnt = vectors[pick].to(torch.int16).contiguous().view(torch.uint16)
+    want = torch.unique(vectors, dim=0)
+    assert want.shape[0] == n_T
+    T = torch.zeros((1 << 17, L), dtype=torch.int16, device="cuda").view(torch.uint16)
+    codes = torch.zeros(n_rows + 3, dtype=torch.int32, device="cuda")
+    for place in range(4):  # codes that start anywhere; later calls find the set empty again
+        code = codes[place:place + n_rows]
+        rc, got = binding.prune_rpe_raw(ctx, cnt, 1 << 17, T, code)
+        assert rc == binding.OK and got == n_T and ctx.check() == 0
+        assert torch.equal(T.view(torch.int16)[:n_T].long(), want)
+        assert torch.equal(T.view(torch.int16)[code.long()], cnt.view(torch.int16))
 
 
 def test_one_call_rpe_ids_of_many_distinct_vectors(ctx):
