@@ -41,7 +41,7 @@ hipError_t launch_walks(hipStream_t stream, const int32_t* row_ptr, const int32_
                         int32_t M, int32_t m, uint64_t rng_seed, int32_t* walks,
                         int32_t* set_sizes, const EdgeRecords& rec, uint32_t* err);
 
-// walk_rpe.hip.  Walks and the RPE table in one persistent kernel: writes walks,
+// walk_rpe_kernel.h.  Walks and the RPE table in one persistent kernel: writes walks,
 // rpe_off[0..n_seeds] and (unless ids is null) the rows.  lb: device scratch of
 // lookback_words(n_seeds) 64-bit words (cleared by the launch itself).  n_cu: compute
 // units of the device.  spin_limit bounds every wait inside the kernel (kDevStall when one runs

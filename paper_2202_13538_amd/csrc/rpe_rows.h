@@ -14,9 +14,13 @@ namespace surel {
 constexpr uint32_t kPadKeys = 0xFFFFFFF0u;
 __device__ __forceinline__ uint32_t pad_key(int lane) { return kPadKeys | ((uint32_t)lane & 15u); }
 
-// Walk keys of a wave: the sort is compiled for these numbers of keys per lane.
+// Walk keys of a wave: the sort is compiled for these numbers of keys per lane.  (Vector instructions of a
+// sort, wave_sort.h: 482 with 7, 518 with 8, 670 with 9, 734 with 10, 874 with 12, 1,050 with 13, 1,090 with
+// 14, 1,182 with 16; 15 and 11 take no fewer than 16 and 12.  Walks + RPE of 235,000 seeds of M = 200, m = 4,
+// 801 keys: 1,361 us with 16, 1,298 with 13; of 99,991 of M = 61, m = 9, 550 keys: 493 with 10, 483 with 9;
+// walks of 2.9M-node graphs wait for memory and take the same time.)
 #define SUREL_FOR_SORT_SIZES(X) \
-    X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32)
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(12) X(13) X(14) X(16) X(20) X(24) X(32)
 
 template <int E>
 __device__ __forceinline__ void copy_keys(uint32_t (&to)[E], const uint32_t (&from)[E]) {

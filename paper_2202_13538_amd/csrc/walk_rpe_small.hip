@@ -1,7 +1,7 @@
 // Walks and RPE of few seeds (Sec. 3.2) in one launch, a wavefront per seed, as many seeds as the
 // device has room for at a time.
 //
-// The kernel for many seeds (walk_rpe.hip) has waves that draw seeds, a scanner wave, and scratch
+// The kernel for many seeds (walk_rpe_kernel.h) has waves that draw seeds, a scanner wave, and scratch
 // that a launch of its own clears; on large graphs it reads neighbour records that another launch
 // makes.  With a seed or less per wave of the chip none of that pays: the time is the chain of one
 // seed (its walks' dependent gathers, the sort, the offset, the rows) plus every launch around it.

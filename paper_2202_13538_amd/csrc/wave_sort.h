@@ -56,18 +56,21 @@ struct SortNetwork {
             }
         }
     }
-    // A bitonic run (rotated in any way) of `count` places.  Even: its even and its odd places
-    // are bitonic runs whose numbers of zeros (in the sense of the 0-1 principle) differ by one
-    // at most; once both are sorted, neighbours are compared.  Odd: sorted from scratch.
+    // A bitonic run (rotated in any way) of `count` places: its even and its odd places are bitonic
+    // runs.  In the sense of the 0-1 principle its zeros are neighbours on the circle of its places, so
+    // where the count is even the two differ by one zero at most; once both are sorted, every even place
+    // is compared with the one behind it.  Where it is odd the circle's last place and its first are both
+    // even, so the even places have between one zero less and two zeros more than the odd ones; with two
+    // more it is the odd places that are compared with the ones behind them, and where one of the two
+    // rounds of comparisons has something to do the other has not.  (Odd counts sorted from scratch: 48
+    // comparators instead of 34 at 13, 26 instead of 20 at 9, 16 instead of 13 at 7.)
     constexpr void add_bitonic(int first, int stride, int count) {
         if (count < 2) return;
-        if (count % 2 != 0) {
-            add_sort(first, stride, count);
-            return;
-        }
-        add_bitonic(first, 2 * stride, count / 2);
+        add_bitonic(first, 2 * stride, (count + 1) / 2);
         add_bitonic(first + stride, 2 * stride, count / 2);
-        for (int i = 0; i < count; i += 2) add(first + i * stride, first + (i + 1) * stride);
+        for (int i = 0; i + 1 < count; i += 2) add(first + i * stride, first + (i + 1) * stride);
+        if (count % 2 == 0) return;
+        for (int i = 1; i + 1 < count; i += 2) add(first + i * stride, first + (i + 1) * stride);
     }
 };
 template <int E>

@@ -634,6 +634,28 @@ def test_prune_lists_of_rows_that_wait_for_a_look_up(ctx, L, n_rows, n_T, most):
     assert torch.equal(T.view(torch.int16)[code.long()], cnt.view(torch.int16))
 
 
+@pytest.mark.parametrize("M,m", [(149, 3), (112, 4), (112, 3), (115, 5), (144, 4), (144, 3), (277, 3),
+                                 (208, 4), (208, 3), (179, 5), (224, 4), (224, 3)])
+def test_sorts_of_odd_numbers_of_keys_a_lane(ctx, M, m):
+    # the last number of keys of a sort and the first of the next one, for 7, 9, 13 and 14 keys a lane, of
+    # M*m + 1 keys (walks + RPE, for many seeds and for few) and of M*(m+1) (RPE of finished walks)
+    wl = synth.Workload("t", "rmat", 4096, 60_000, 0.0, M, m, 0, 2, "uniform", graph_seed=M)
+    rp, ci = synth.make_graph(wl)
+    seeds = np.concatenate([np.arange(4096), np.arange(1500)]).astype(np.int32)
+    w = oracle.sample_walks(rp, ci, seeds, M, m, 5)
+    t_off, t_ids, t_cnt = oracle.build_rpe(w)
+    for n in (seeds.size, 600):
+        rows = int(t_off[n])
+        walks, off, ids, cnt = binding.sample_walks_rpe(ctx, dev(rp), dev(ci), dev(seeds[:n]), M, m, 5)
+        assert np.array_equal(walks.cpu().numpy(), w[:n])
+        b_off, b_ids, b_cnt = binding.build_rpe(ctx, walks, wl.n_nodes)
+        assert ctx.check() == 0
+        for o, i, c in ((off, ids, cnt), (b_off, b_ids, b_cnt)):
+            assert np.array_equal(o.cpu().numpy(), t_off[:n + 1])
+            assert np.array_equal(i.cpu().numpy(), t_ids[:rows])
+            assert np.array_equal(host_u16(c).reshape(-1, m + 1), t_cnt[:rows])
+
+
 @pytest.mark.parametrize("L", [2, 3, 4, 5, 6])
 @pytest.mark.parametrize("n_T", [32_766, 32_767, 32_768, 42_000])
 def test_prune_numbers_of_16_bits(ctx, L, n_T):
