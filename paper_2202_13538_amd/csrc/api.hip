@@ -29,6 +29,7 @@ struct surel_ctx {
     size_t lb_bytes = 0;
     void* d_prune = nullptr;      // grow-only workspace: hash slots, sort list, counters of prune
     size_t prune_bytes = 0;
+    int prune_turn = 0;           // which of two sets of counters the next of these calls takes
     size_t prune_clean = 0;       // bytes of the hash slots in it that are known to be empty
     void* d_batch = nullptr;      // grow-only workspace: sort arrays of the incidence lists, hash
     size_t batch_bytes = 0;       // tables of the mini-batch search
@@ -535,7 +536,10 @@ static int prune_scratch(surel_ctx* ctx, int64_t cap_T, surel::PruneScratch* ps)
     if (need > ctx->prune_bytes) ctx->prune_clean = 0;
     if (int rc = grow_buffer(ctx, &ctx->d_prune, &ctx->prune_bytes, need)) return rc;
     char* ws = static_cast<char*>(ctx->d_prune);
-    ps->counters = reinterpret_cast<unsigned long long*>(ws);
+    // two calls take turns with two sets of counters
+    ps->counters = reinterpret_cast<unsigned long long*>(ws + 128 * ctx->prune_turn);
+    ctx->prune_turn ^= 1;
+    ps->next_counters = reinterpret_cast<unsigned long long*>(ws + 128 * ctx->prune_turn);
     ps->slots = reinterpret_cast<uint32_t*>(ws + 256);
     ps->members = reinterpret_cast<uint32_t*>(ws + 256 + slot_bytes);
     ps->ranks = reinterpret_cast<uint32_t*>(ws + 256 + slot_bytes + member_bytes);
@@ -559,21 +563,24 @@ static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m
     if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
     const int64_t n_T = ctx->h_pinned[2];
     *h_n_T = n_T;
-    // with more than cap_T vectors the set's list is not complete, and its slots are not all empty; with
-    // more than are ranked at once they are emptied behind the sort
-    const bool many = n_T > surel::prune_rank_most(ps.cap_T, m);
-    if (!many) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
+    // with more than cap_T vectors the set's list is not complete; with more than are ranked at once, or
+    // than the renumbering can do without the slots for, they are emptied behind it
+    const bool late_clean = n_T > surel::prune_clean_most(ps.cap_T, m, d_cnt);
+    if (!late_clean) ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
     if (h_rows) {
         *h_rows = n_rows = pinned_total(ctx);
         if (int rc = judge_total(true, cap_rows, n_rows)) return rc;  // not all rows have codes
     }
     if (n_T > ps.cap_T) return SUREL_E_CAPACITY;
-    if (many) {
-        if (surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_cnt, d_T, d_code) !=
-            hipSuccess)
+    if (late_clean) {
+        const bool many = n_T > surel::prune_rank_most(ps.cap_T, m);
+        if (many && surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_cnt, d_T,
+                                                   d_code) != hipSuccess)
             return SUREL_E_HIP;
-        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
+        // (nobody outside waits for empty slots: the context's next call is on the same stream)
+        if (surel::launch_prune_clean(ctx->stream, ps, n_T) != hipSuccess) return SUREL_E_HIP;
         ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
+        if (many && hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
     }
     return SUREL_OK;
 }

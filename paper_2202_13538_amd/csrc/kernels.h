@@ -58,6 +58,7 @@ struct PruneScratch {
     uint32_t* members = nullptr;
     uint32_t* ranks = nullptr;
     unsigned long long* counters = nullptr;
+    unsigned long long* next_counters = nullptr;  // of the next call
     int64_t cap_T = 0;
 };
 hipError_t launch_walk_rpe(hipStream_t stream, int max_lds_bytes, int n_cu, const int32_t* row_ptr,
@@ -134,9 +135,10 @@ hipError_t launch_query_ids(hipStream_t stream, int max_lds_bytes, const int32_t
 
 // prune.hip.  Distinct count vectors of the table, sorted, and every row's index among them.
 // PruneScratch: device scratch of prune_slot_bytes, prune_member_bytes and prune_rank_bytes(cap_T)
-// bytes and three 64-bit counters.  slots and counters are zero before a call (launch_prune_clear)
-// and are left zero by launch_prune_order, or launch_prune_order_many where that has to be called,
-// unless there were more than cap_T distinct vectors.
+// bytes, three 64-bit counters, and three of the next call.  slots and counters are zero before a call
+// (launch_prune_clear); launch_prune_order clears the next call's counters and, with up to prune_clean_most
+// vectors, leaves the slots zero; with more, up to cap_T, launch_prune_clean has to be called after it (and
+// after launch_prune_order_many).
 size_t prune_slot_bytes(int64_t cap_T);
 size_t prune_member_bytes(int64_t cap_T);
 size_t prune_rank_bytes(int64_t cap_T);
@@ -148,12 +150,14 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
                                 uint32_t spin_limit, uint32_t* err);
 // T = the set's vectors, sorted; code[row] = place of the row's vector there; *h_n_T (host memory)
 // = their number; *h_stalled (host memory) = 1 if a wait ran out while they were collected (else it
-// stays); then empties the set.  d_rows (optional): where the number of rows stands on
+// stays).  d_rows (optional): where the number of rows stands on
 // the device; with more than cap_rows of them the codes stay as they are.  cnt: the rows' vectors, if
 // code comes from launch_prune_collect; null if code[row] is the number of the row's vector.  With more
 // than prune_rank_most(cap_T, m) distinct vectors T, code and set stay as they are, and
 // launch_prune_order_many has to be called with the number.
 int64_t prune_rank_most(int64_t cap_T, int32_t m);
+int64_t prune_clean_most(int64_t cap_T, int32_t m, const uint16_t* cnt);
+hipError_t launch_prune_clean(hipStream_t stream, const PruneScratch& ps, int64_t n_T);
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
                               int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
                               const uint16_t* cnt, uint16_t* T, int32_t* code, int64_t* h_n_T,

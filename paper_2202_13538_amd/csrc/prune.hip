@@ -11,12 +11,13 @@
 //            slot that does not look full yet is touched with atomics.
 //   rank     every vector's place in the sorted array: up to prune_rank_most vectors are compared
 //            all with all (a few thousand, usually: one short launch that needs no count on the
-//            host), more are sorted with a bitonic network in global memory.  T[place] = vector.
+//            host), more are sorted with a bitonic network in global memory.
 //   codes    code[row] = place of the row's vector, from the numbers (which are 16 bits each where no
 //            larger ones occur, see kNarrowMost).
-//   clean    the slots that were used are emptied again, by the list of the set's members (a
-//            memset of the table, and a pass over it that gathers the full slots, were 95 us of a
-//            call with cap_T = 2^20).
+//            The launch stores T as well, and empties the slots that were used again, by the list of the
+//            set's members (a memset of the table, and a pass over it that gathers the full slots,
+//            were 95 us of a call with cap_T = 2^20).  With so many vectors that the slots are still
+//            asked then, they are emptied behind it.
 // Waiting.  A lane that finds a slot locked (another lane is writing its vector) polls it
 // again; the writer needs nothing from the poller (inside one wavefront the writer's branch
 // runs to its end before the next poll), so the poll ends; it is bounded by the spin limit
@@ -52,8 +53,8 @@ struct Collect {
 // renumbering looks up once more (one that was on the late list and has a larger number).  From then on a tile
 // is its codes as they stand, with kWide set in each, so that any word of a tile tells which of both it is.
 // (Numbers are handed out in the order of insertion, so the commonest vectors have small ones.)
-// 146 M rows of 1M seeds with 1,500 vectors are pruned in 545 us, 692 with numbers of 32 bits; 60 M with
-// 100,000 vectors, nearly all of them wide, in 1.90 ms, 1.98.
+// 146 M rows of 1M seeds with 1,500 vectors are pruned in 522 us, 692 with numbers of 32 bits and other
+// ways to the caches; 60 M with 100,000 vectors, nearly all of them wide, in 1.90 ms, 1.98.
 constexpr int32_t kNarrowMost = 0x7FFE;
 constexpr uint32_t kNarrowUnknown = (uint32_t)kNarrowMost + 1u;
 constexpr uint32_t kWide = 0x80000000u;
@@ -333,6 +334,9 @@ __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kern
 constexpr int64_t kRankWords = 5'000'000'000;
 constexpr int kRankTile = 256;
 constexpr int kRankBlocks = 1024;
+// Up to so many vectors a tile is compared with a quarter of another at a time: still a workgroup each, and
+// the launch takes as long as one workgroup's loop (1,500 vectors of three words 11.7 -> 5.0 us).
+constexpr int kRankFew = 4096;
 
 // ranks[i] += vectors of one tile that are smaller than vector i of another, for all pairs of
 // tiles.  The number of vectors is read on the device, so that the launch does not wait for the
@@ -345,9 +349,11 @@ __global__ __launch_bounds__(kRankTile) void prune_rank_pairs_kernel(
     const int64_t n = (int64_t)*n_inserted;
     if (n > most) return;
     const int64_t tiles = (n + kRankTile - 1) / kRankTile;
-    for (int64_t p = blockIdx.x; p < tiles * tiles; p += gridDim.x) {
-        const int64_t i = (p / tiles) * kRankTile + threadIdx.x;
-        const int64_t j0 = (p % tiles) * kRankTile;
+    const int width = n <= kRankFew ? kRankTile / 4 : kRankTile;
+    const int64_t parts = (n + width - 1) / width;
+    for (int64_t p = blockIdx.x; p < tiles * parts; p += gridDim.x) {
+        const int64_t i = (p / parts) * kRankTile + threadIdx.x;
+        const int64_t j0 = (p % parts) * width;
         uint32_t mine[NW];
 #pragma unroll
         for (int k = 0; k < NW; ++k) mine[k] = i < n ? members[i * kItemWords + k] : 0u;
@@ -356,7 +362,7 @@ __global__ __launch_bounds__(kRankTile) void prune_rank_pairs_kernel(
         for (int k = 0; k < NW; ++k)
             other[k][threadIdx.x] = j0 + threadIdx.x < n ? members[(j0 + threadIdx.x) * kItemWords + k] : ~0u;
         __syncthreads();
-        const int m = (int)min((int64_t)kRankTile, n - j0);
+        const int m = (int)min((int64_t)width, n - j0);
         uint32_t smaller = 0;
         for (int j = 0; j < m; ++j) {
             bool less = false;
@@ -369,48 +375,50 @@ __global__ __launch_bounds__(kRankTile) void prune_rank_pairs_kernel(
     }
 }
 
-// T[ranks[i]] = vector i; the number of vectors also goes to host memory, and whether a wait ran out.
-__global__ __launch_bounds__(256) void prune_place_kernel(
-    const uint32_t* __restrict__ members, const unsigned long long* __restrict__ counters,
-    int64_t most, int L, const uint32_t* __restrict__ ranks, uint16_t* __restrict__ T,
-    int64_t* h_n_T, int64_t* h_stalled) {
-    const int64_t n = (int64_t)counters[0];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        *h_n_T = n;
-        if (counters[2] != 0ull) *h_stalled = 1;
-    }
-    if (n > most) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t* item = members + i * kItemWords;
-        const int64_t place = ranks[i];
-        for (int e = 0; e < L; ++e) {
-            const uint32_t word = item[e >> 1];
-            T[place * L + e] = (uint16_t)((e & 1) ? (word & 0xFFFFu) : (word >> 16));
+// What the launch that renumbers the codes does besides (RankedSet::finish, called by all its threads with
+// the number of vectors): T[ranks[i]] = vector i; with up to clean_most vectors the slots of the set's
+// members are emptied; the counters of the call after this one are cleared (two calls take turns with two
+// sets of them, so nobody has to know who reads the present ones last); the number of vectors also goes to
+// host memory, and whether a wait ran out.  (As launches of their own, with a clearing of the counters by
+// their last workgroup, T and the slots took 5 + 4 us and the gaps before them; with the ranks, above,
+// 250,000 rows with 1,500 vectors are pruned in 74 us instead of 85.)
+struct RankedSet {
+    const uint32_t* __restrict__ members;
+    const unsigned long long* __restrict__ counters;
+    unsigned long long* next_counters;
+    const uint32_t* __restrict__ ranks;
+    uint32_t* slots;
+    uint16_t* T;
+    int64_t most, clean_most;
+    int L;
+    int64_t* h_n_T;
+    int64_t* h_stalled;
+    __device__ __forceinline__ void finish(int64_t n) const {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            *h_n_T = n;
+            if (counters[2] != 0ull) *h_stalled = 1;
+            next_counters[0] = 0ull;
+            next_counters[2] = 0ull;
+        }
+        if (n > most) return;
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+             i += (int64_t)gridDim.x * blockDim.x) {
+            const uint32_t* item = members + i * kItemWords;
+            const int64_t place = ranks[i];
+            for (int e = 0; e < L; ++e) {
+                const uint32_t word = item[e >> 1];
+                T[place * L + e] = (uint16_t)((e & 1) ? (word & 0xFFFFu) : (word >> 16));
+            }
+            if (n <= clean_most) slots[(size_t)item[kMaxVecWords] * kSlotWords] = kSlotEmpty;
         }
     }
-}
+};
 
-// Empties the slots of the set's members and its counters, unless there are more than `most` and the set
-// holds all of them: then they are ranked by the sort, whose renumbering looks into the slots.
+// Empties the slots of the set's members.
 __global__ __launch_bounds__(256) void prune_clean_kernel(const uint32_t* __restrict__ members,
-                                                          int64_t most, int64_t cap_T,
-                                                          uint32_t* __restrict__ slots,
-                                                          unsigned long long* __restrict__ counters) {
-    // counters[0]: vectors inserted; counters[1]: workgroups of this launch that have read it;
-    // counters[2]: whether a wait ran out
-    const int64_t n_all = (int64_t)counters[0];
-    if (n_all > most && n_all <= cap_T) return;
-    const int64_t n = min(n_all, cap_T);
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        slots[(size_t)members[i * kItemWords + kMaxVecWords] * kSlotWords] = kSlotEmpty;
-    __syncthreads();
-    if (threadIdx.x == 0 && atomicAdd(&counters[1], 1ull) + 1ull == gridDim.x) {
-        counters[0] = 0ull;
-        counters[1] = 0ull;
-        counters[2] = 0ull;
-    }
+                                                          int64_t n, uint32_t* __restrict__ slots) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) slots[(size_t)members[i * kItemWords + kMaxVecWords] * kSlotWords] = kSlotEmpty;
 }
 
 // Entries from `first` on become padding that sorts behind every vector.
@@ -474,15 +482,16 @@ __global__ __launch_bounds__(256) void prune_rank_kernel(const uint32_t* __restr
 // Four rows a lane, moved as 16-byte words where the array's alignment allows (the pass is a
 // plain stream over the codes; the places come from a few thousand words).
 // rows (optional): where the number of rows stands on the device (more than cap_rows of them: the
-// codes are not all there, nothing is done); n_known < 0: the number of vectors stands in
-// *n_inserted, and with more than `most` nothing is done.
+// codes are not all there and stay as they are); n_known < 0: the number of vectors stands in the set's
+// counters, with more than set.most the codes stay as they are, and set.finish is called.
 constexpr int kCodesUnroll = 4;
 __global__ __launch_bounds__(256) void prune_codes_kernel(
-    const uint32_t* __restrict__ ranks, const unsigned long long* __restrict__ n_inserted,
-    int64_t n_known, int64_t most, int64_t n_rows, const int64_t* __restrict__ rows,
+    RankedSet set, int64_t n_known, int64_t n_rows, const int64_t* __restrict__ rows,
     int64_t cap_rows, int32_t* __restrict__ code) {
-    const int64_t n = n_known >= 0 ? n_known : (int64_t)*n_inserted;
-    if (n > most) return;
+    const uint32_t* __restrict__ ranks = set.ranks;
+    const int64_t n = n_known >= 0 ? n_known : (int64_t)set.counters[0];
+    if (n_known < 0) set.finish(n);
+    if (n > set.most) return;
     if (rows != nullptr) n_rows = *rows;
     if (n_rows > cap_rows) return;
     auto rank_of = [&](int32_t c) -> int32_t {
@@ -529,9 +538,10 @@ __global__ __launch_bounds__(256) void prune_codes_kernel(
 constexpr int kHotRanks = 4096;
 template <int LT>
 __global__ __launch_bounds__(256) void prune_tile_codes_kernel(
-    const uint32_t* __restrict__ ranks, const unsigned long long* __restrict__ n_inserted,
-    int64_t n_known, int64_t most, int64_t n_rows, const uint16_t* __restrict__ cnt,
-    const uint32_t* __restrict__ slots, uint32_t slot_mask, int32_t* __restrict__ code) {
+    RankedSet set, int64_t n_known, int64_t n_rows, const uint16_t* __restrict__ cnt,
+    uint32_t slot_mask, int32_t* __restrict__ code) {
+    const uint32_t* __restrict__ ranks = set.ranks;
+    const uint32_t* slots = set.slots;
     constexpr int kRows = Collect<LT>::kRows, NW = (LT + 1) / 2;
     typedef uint32_t quad_t __attribute__((ext_vector_type(4), aligned(4)));
     typedef uint32_t two_t __attribute__((ext_vector_type(2), aligned(4)));
@@ -550,8 +560,9 @@ __global__ __launch_bounds__(256) void prune_tile_codes_kernel(
         for (int u = 0; u < kCodesUnroll; ++u) low[u] = __builtin_nontemporal_load(part(u));
     };
     if (t0 < n_whole) load_low();  // before the trips for the number of vectors and their places
-    const int64_t n = n_known >= 0 ? n_known : (int64_t)*n_inserted;
-    if (n > most) return;
+    const int64_t n = n_known >= 0 ? n_known : (int64_t)set.counters[0];
+    if (n_known < 0) set.finish(n);
+    if (n > set.most) return;
     // (a wave with one tile would wait for this table longer than for its places: 2 M rows 86 -> 85 us)
     const uint32_t n_hot = n_whole > stride ? (uint32_t)min(n, (int64_t)kHotRanks) : 0u;
     if (n_hot != 0u) {
@@ -655,7 +666,9 @@ hipError_t launch_prune_clear(hipStream_t stream, const PruneScratch& ps) {
     // graph, and plain memsets do)
     hipError_t rc = hipMemsetAsync(ps.slots, 0, prune_slot_bytes(ps.cap_T), stream);
     if (rc != hipSuccess) return rc;
-    return hipMemsetAsync(ps.counters, 0, 3 * sizeof(unsigned long long), stream);
+    rc = hipMemsetAsync(ps.counters, 0, 3 * sizeof(unsigned long long), stream);
+    if (rc != hipSuccess) return rc;
+    return hipMemsetAsync(ps.next_counters, 0, 3 * sizeof(unsigned long long), stream);
 }
 
 template <int LT>
@@ -692,38 +705,34 @@ hipError_t launch_prune_collect(hipStream_t stream, int n_cu, const uint16_t* cn
 }
 
 template <int LT>
-static void launch_tile_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int64_t n_known,
-                              int64_t most, int64_t n_rows, const uint16_t* cnt, int32_t* code) {
+static void launch_tile_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, const RankedSet& set,
+                              int64_t n_known, int64_t n_rows, const uint16_t* cnt, int32_t* code) {
     int64_t blocks = n_rows / Collect<LT>::kRows / 4 + 1;
     if (blocks > (int64_t)n_cu * 8) blocks = (int64_t)n_cu * 8;
-    hipLaunchKernelGGL(prune_tile_codes_kernel<LT>, dim3((unsigned)blocks), dim3(256), 0, stream, ps.ranks,
-                       ps.counters, n_known, most, n_rows, cnt, ps.slots,
-                       (uint32_t)(prune_slots(ps.cap_T) - 1), code);
+    hipLaunchKernelGGL(prune_tile_codes_kernel<LT>, dim3((unsigned)blocks), dim3(256), 0, stream, set,
+                       n_known, n_rows, cnt, (uint32_t)(prune_slots(ps.cap_T) - 1), code);
 }
 
+// Whether the numbers of the collecting launch are tiles of the two forms (Collect<LT>, LT > 0).
+static bool numbers_in_tiles(const uint16_t* cnt, int32_t m) { return cnt != nullptr && m <= 5; }
+
 // cnt: the rows' vectors where the numbers come from launch_prune_collect, else null.
-static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m, int64_t n_known,
-                         int64_t most, int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
+static void launch_codes(hipStream_t stream, int n_cu, const PruneScratch& ps, const RankedSet& set,
+                         int64_t n_known, int64_t n_rows, const int64_t* d_rows, int64_t cap_rows,
                          const uint16_t* cnt, int32_t* code) {
-    if (cnt != nullptr) {
-        switch (m + 1) {
-            case 2: return launch_tile_codes<2>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
-            case 3: return launch_tile_codes<3>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
-            case 4: return launch_tile_codes<4>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
-            case 5: return launch_tile_codes<5>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
-            case 6: return launch_tile_codes<6>(stream, n_cu, ps, n_known, most, n_rows, cnt, code);
-            default: break;
+    if (numbers_in_tiles(cnt, set.L - 1)) {
+        switch (set.L) {
+            case 2: return launch_tile_codes<2>(stream, n_cu, ps, set, n_known, n_rows, cnt, code);
+            case 3: return launch_tile_codes<3>(stream, n_cu, ps, set, n_known, n_rows, cnt, code);
+            case 4: return launch_tile_codes<4>(stream, n_cu, ps, set, n_known, n_rows, cnt, code);
+            case 5: return launch_tile_codes<5>(stream, n_cu, ps, set, n_known, n_rows, cnt, code);
+            default: return launch_tile_codes<6>(stream, n_cu, ps, set, n_known, n_rows, cnt, code);
         }
     }
     int64_t blocks = ((d_rows ? cap_rows : n_rows) / 4 + 256) / 256;
     if (blocks > (int64_t)n_cu * 32) blocks = (int64_t)n_cu * 32;
-    hipLaunchKernelGGL(prune_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, ps.ranks,
-                       ps.counters, n_known, most, n_rows, d_rows, cap_rows, code);
-}
-
-static void launch_clean(hipStream_t stream, const PruneScratch& ps, int64_t most) {
-    hipLaunchKernelGGL(prune_clean_kernel, dim3(64), dim3(256), 0, stream, ps.members, most, ps.cap_T,
-                       ps.slots, ps.counters);
+    hipLaunchKernelGGL(prune_codes_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, set, n_known,
+                       n_rows, d_rows, cap_rows, code);
 }
 
 int64_t prune_rank_most(int64_t cap_T, int32_t m) {
@@ -731,6 +740,12 @@ int64_t prune_rank_most(int64_t cap_T, int32_t m) {
     int64_t n = (int64_t)std::sqrt((double)kRankWords / (double)words);
     while (n * n * words > kRankWords) --n;
     return cap_T < n ? cap_T : n;
+}
+
+int64_t prune_clean_most(int64_t cap_T, int32_t m, const uint16_t* cnt) {
+    // wide tiles' renumbering looks into the slots
+    const int64_t most = prune_rank_most(cap_T, m);
+    return numbers_in_tiles(cnt, m) && most > (int64_t)kNarrowMost + 1 ? (int64_t)kNarrowMost + 1 : most;
 }
 
 hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& ps, int32_t m,
@@ -756,10 +771,15 @@ hipError_t launch_prune_order(hipStream_t stream, int n_cu, const PruneScratch& 
 #undef SUREL_RANK_CASE
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(prune_place_kernel, dim3(64), dim3(256), 0, stream, ps.members, ps.counters,
-                       most, L, ps.ranks, T, h_n_T, h_stalled);
-    launch_codes(stream, n_cu, ps, m, -1, most, n_rows, d_rows, cap_rows, cnt, code);
-    launch_clean(stream, ps, most);
+    const RankedSet set{ps.members, ps.counters, ps.next_counters, ps.ranks, ps.slots, T, most,
+                        prune_clean_most(ps.cap_T, m, cnt), L, h_n_T, h_stalled};
+    launch_codes(stream, n_cu, ps, set, -1, n_rows, d_rows, cap_rows, cnt, code);
+    return hipGetLastError();
+}
+
+hipError_t launch_prune_clean(hipStream_t stream, const PruneScratch& ps, int64_t n_T) {
+    hipLaunchKernelGGL(prune_clean_kernel, dim3((unsigned)((n_T + 255) / 256)), dim3(256), 0, stream,
+                       ps.members, n_T, ps.slots);
     return hipGetLastError();
 }
 
@@ -777,8 +797,9 @@ hipError_t launch_prune_order_many(hipStream_t stream, int n_cu, const PruneScra
                                dim3(256), 0, stream, ps.members, len, j, k);
     hipLaunchKernelGGL(prune_rank_kernel, dim3((unsigned)((n_T + 255) / 256)), dim3(256), 0, stream,
                        ps.members, n_T, m + 1, ps.slots, ps.ranks, T);
-    launch_codes(stream, n_cu, ps, m, n_T, n_T, n_rows, nullptr, n_rows, cnt, code);
-    launch_clean(stream, ps, ps.cap_T);
+    const RankedSet set{ps.members, ps.counters, ps.next_counters, ps.ranks, ps.slots, T, n_T, 0, m + 1,
+                        nullptr, nullptr};
+    launch_codes(stream, n_cu, ps, set, n_T, n_rows, nullptr, n_rows, cnt, code);
     return hipGetLastError();
 }
 
