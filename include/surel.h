@@ -400,8 +400,8 @@ int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_qu
  *                block x.
  *   d_counts     int32[n_batches][2] (device, written): (nodes in V̄, queries in the batch).
  * Limits: 1 <= n_start, B1, B2 <= SUREL_MAX_BATCH.  Searches whose tables and queue fit 79 KB of
- * LDS (the default limits among them) need no workspace.  For others the context's workspace grows
- * by 8 bytes times (2 (B2 + c) + 2 (n_start + k B2)), c = 4 B2 rounded up to a power of two within
+ * LDS (156 KB where B2 > 64; the default limits are among them) need no workspace.  For others the
+ * context's workspace grows by 8 bytes times (2 (B2 + c) + 2 (n_start + k B2)), c = 4 B2 rounded up to a power of two within
  * [64, 1024], both terms rounded up to powers of two, for each search in flight (4 per compute
  * unit, 16 where B2 <= 64; fewer where that would pass 4 GiB).  Asynchronous.
  * Device-detected: BAD_QUERY (a start node or query entry outside [0, n_nodes): skipped),

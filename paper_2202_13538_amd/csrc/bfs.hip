@@ -23,13 +23,19 @@ namespace {
 constexpr int kBfsPer = 4;        // candidates (or new queries) per thread, at most
 constexpr int kBfsMaxThreads = 256;  // a workgroup has 256 threads, or 64 for small batches
 constexpr int kBfsMaxChunk = kBfsMaxThreads * kBfsPer;  // candidates settled at a time, at most
-// Searches whose tables fit into this much LDS keep them there (two workgroups per compute unit, or
-// more): an insertion is a few LDS round trips instead of atomics that travel to memory.  8,192
-// searches of 32 queries: 71 us, with the tables in global memory 524.  Of a chunk's new queries only
-// those that the batch has room for get their nodes entered: the tables and lists of such a search
-// are then 4.9 KB, not 9.5, 32 searches of a compute unit run at a time instead of 16, and with the
-// entries of a chunk spread over all threads (bfs_share) the launch takes 35 us.
-constexpr size_t kBfsLdsMost = 79 * 1024;
+// Searches whose tables fit into this much LDS keep them there: an insertion is a few LDS round trips instead
+// of atomics that travel to memory.  8,192 searches of 32 queries: 71 us, with the tables in global memory
+// 524.  Of a chunk's new queries only those that the batch has room for get their nodes entered, and what a
+// thread alone needs of a chunk is in its registers: such a search's LDS is then 4.7 KB with the static
+// part, four of the 128 parts that a compute unit's LDS is given out in, and 32 searches of a compute unit
+// run at a time (which also takes no more scalar registers than eight waves of a SIMD have): 27 us (34 with
+// 25 searches, lists of candidates in LDS and two loads of a query's nodes and of a list's place).
+// Searches of more than 64 queries may have a compute unit's LDS for one of them: 1,024 queries of two
+// nodes, 16 / 256 / 4,096 searches 40 / 48 / 551 us, with tables in global memory 90 / 176 / 2,087; 2,000
+// queries 65 / 80 / 930 and 146 / 277 / 3,506.
+constexpr size_t kBfsLdsMost = 79 * 1024;       // of a search of one wavefront
+constexpr size_t kBfsLdsMostWide = 156 * 1024;  // of one of four, which has 3.1 KB that are not dynamic
+constexpr size_t kBfsLdsEight = 16 * 1024;      // of one of four, eight of which a compute unit then holds
 constexpr int kBfsMaxK = 3;
 constexpr uint32_t kBfsEmpty = 0xFFFFFFFFu;
 
@@ -76,6 +82,10 @@ __device__ __forceinline__ uint32_t bfs_block_scan(uint32_t v, uint32_t* total, 
     const int lane = lane_id();
     const int wave = threadIdx.x >> 6;
     const uint32_t incl = wave_incl_sum(v);
+    if constexpr (T == kWave) {
+        *total = wave_bcast_u32(incl, kWave - 1);
+        return incl - v;
+    }
     __syncthreads();  // wave_sums may still be read from the previous scan
     if (lane == kWave - 1) wave_sums[wave] = incl;
     __syncthreads();
@@ -122,14 +132,11 @@ struct BfsArgs {
 // Dynamic LDS of a workgroup, in 32-bit words: the lists of a chunk and, with kLds, the queue of
 // nodes and both tables.
 struct BfsLds {
-    uint32_t cand_q, cand_slot, new_q, node_slot, queue, tables, total;
+    uint32_t new_q, node_slot, queue, tables, total;
 };
-__host__ __device__ inline BfsLds bfs_lds(uint32_t chunk, uint32_t most_new, uint32_t queue,
-                                          uint32_t slots, bool in_lds) {
+__host__ __device__ inline BfsLds bfs_lds(uint32_t most_new, uint32_t queue, uint32_t slots, bool in_lds) {
     BfsLds o;
-    o.cand_q = 0;                        // query of each candidate
-    o.cand_slot = o.cand_q + chunk;      // its slot in the query table
-    o.new_q = o.cand_slot + chunk;       // newly reached queries, in order
+    o.new_q = 0;                           // newly reached queries, in order
     o.node_slot = o.new_q + most_new;      // slots of their nodes
     o.queue = (o.node_slot + most_new * kBfsMaxK + 3) / 4 * 4;
     o.tables = o.queue + (in_lds ? (queue + 3) / 4 * 4 : 0);
@@ -137,15 +144,16 @@ __host__ __device__ inline BfsLds bfs_lds(uint32_t chunk, uint32_t most_new, uin
     return o;
 }
 
-template <int T, bool kLds>
-__global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
+// kPerSimd: waves of a SIMD that the registers leave room for.  Eight take more of the scalar ones out to
+// lanes of vector ones, and are taken where LDS has room for as many searches: 2,048 of 128 queries 39 us,
+// with four 45 (which are seven, as it comes out); 436 of 600 queries 62 and 60.
+template <int T, bool kLds, int kPerSimd>
+__global__ __launch_bounds__(T, kPerSimd) void bfs_batch_kernel(BfsArgs a) {
     __shared__ uint32_t wave_sums[T / kWave];
     __shared__ uint32_t pre[T + 1];              // candidates before each node of the stretch
-    __shared__ uint32_t s_take;
+    __shared__ int64_t list_at[T];               // where its list begins
     extern __shared__ __align__(16) uint32_t lds32[];
-    const BfsLds lay = bfs_lds(a.chunk, a.most_new, a.queue, a.slots_q + a.slots_v, kLds);
-    uint32_t* const cand_q = lds32 + lay.cand_q;
-    uint32_t* const cand_slot = lds32 + lay.cand_slot;
+    const BfsLds lay = bfs_lds(a.most_new, a.queue, a.slots_q + a.slots_v, kLds);
     uint32_t* const new_q = lds32 + lay.new_q;
     uint32_t* const node_slot = lds32 + lay.node_slot;
     uint32_t* const queue = lds32 + lay.queue;   // kLds only
@@ -231,7 +239,8 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             uint32_t deg = 0;
             if ((uint32_t)tid < nf) {
                 const int32_t u = kLds ? (int32_t)queue[head + tid] : vbar[head + tid];
-                const int64_t len = a.inc_off[u + 1] - a.inc_off[u] - (tid == 0 ? (int64_t)j_cur : 0);
+                list_at[tid] = a.inc_off[u];
+                const int64_t len = a.inc_off[u + 1] - list_at[tid] - (tid == 0 ? (int64_t)j_cur : 0);
                 bad_lists |= len < 0;
                 // a list longer than a chunk is taken in pieces; how much longer does not matter
                 deg = (uint32_t)max((int64_t)0, min(len, (int64_t)a.chunk + 1));
@@ -240,23 +249,27 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             const uint32_t excl = bfs_block_scan<T>(deg, &total, wave_sums);
             pre[tid] = excl;
             if (tid == T - 1) pre[T] = total;
-            if (tid == 0) s_take = 0;
-            __syncthreads();
             // nodes taken whole: the longest prefix of the stretch with at most a.chunk entries
-            if ((uint32_t)tid < nf && pre[tid + 1] <= a.chunk &&
-                ((uint32_t)tid + 1 == nf || pre[tid + 2] > a.chunk))
-                s_take = (uint32_t)tid + 1;
-            __syncthreads();
-            const uint32_t take = s_take;
+            const bool whole = (uint32_t)tid < nf && excl + deg <= a.chunk;
+            uint32_t take;
+            if constexpr (T == kWave) {
+                __syncthreads();
+                take = (uint32_t)__popcll(__ballot(whole));
+            } else {
+                take = (uint32_t)__syncthreads_count(whole);
+            }
             const bool partial = take == 0;  // the first node's list alone is longer than a chunk
             const uint32_t n_c = partial ? a.chunk : pre[take];
             const uint32_t n_src = partial ? 1u : take;
             const int per_c = bfs_share<T>((int32_t)n_c);
 
             // candidates: entry j of node t' of the stretch, numbered cand_base + c
+            uint32_t cand_q[kBfsPer], cand_slot[kBfsPer];  // query of each, and its slot in the query table
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
                 const uint32_t c = (uint32_t)(tid * per_c + r);
+                cand_q[r] = 0u;
+                cand_slot[r] = kBfsEmpty;
                 if (r < per_c && c < n_c) {
                     uint32_t lo = 0, hi = n_src;  // last node with pre[node] <= c
                     while (hi - lo > 1) {
@@ -267,18 +280,14 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
                             hi = mid;
                         }
                     }
-                    const int32_t u = kLds ? (int32_t)queue[head + lo] : vbar[head + lo];
-                    const int64_t e = a.inc_off[u] + (lo == 0 ? (int64_t)j_cur : 0) + (c - pre[lo]);
-                    uint32_t q = 0, slot = kBfsEmpty;
-                    if (e >= 0 && e < n_entries) q = (uint32_t)a.inc_q[e];
-                    if (e >= 0 && e < n_entries && (int64_t)q < a.n_queries) {
-                        slot = insert_min(q_tab, q_mask, q, cand_base + c);
-                        table_full |= slot == kBfsEmpty;
+                    const int64_t e = list_at[lo] + (lo == 0 ? (int64_t)j_cur : 0) + (c - pre[lo]);
+                    if (e >= 0 && e < n_entries) cand_q[r] = (uint32_t)a.inc_q[e];
+                    if (e >= 0 && e < n_entries && (int64_t)cand_q[r] < a.n_queries) {
+                        cand_slot[r] = insert_min(q_tab, q_mask, cand_q[r], cand_base + c);
+                        table_full |= cand_slot[r] == kBfsEmpty;
                     } else {
                         bad_lists = true;
                     }
-                    cand_q[c] = q;
-                    cand_slot[c] = slot;
                 }
             }
             __syncthreads();
@@ -287,8 +296,7 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
                 const uint32_t c = (uint32_t)(tid * per_c + r);
-                if (r < per_c && c < n_c && cand_slot[c] != kBfsEmpty &&
-                    table_load<kLds>(&q_tab[2 * cand_slot[c] + 1]) == cand_base + c)
+                if (cand_slot[r] != kBfsEmpty && table_load<kLds>(&q_tab[2 * cand_slot[r] + 1]) == cand_base + c)
                     own |= 1u << r;
             }
             uint32_t n_new;
@@ -299,7 +307,7 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r)
                 if (own & (1u << r)) {
-                    const uint32_t q = cand_q[tid * per_c + r];
+                    const uint32_t q = cand_q[r];
                     if (at < n_look) {
                         new_q[at] = q;
                     } else {  // B2 queries come before it: only its node ids are checked
@@ -311,13 +319,18 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
             __syncthreads();
 
             // their nodes: node (i, j) is numbered n_start + (n_b + i) * k + j
+            int32_t nodes[kBfsPer][kBfsMaxK];
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
                 const uint32_t i = (uint32_t)(tid * per_q + r);
                 if (r < per_q && i < n_look) {
                     const int64_t q = new_q[i];
-                    for (int j = 0; j < k; ++j) {
-                        const int32_t x = a.queries[q * k + j];
+#pragma unroll
+                    for (int j = 0; j < kBfsMaxK; ++j) nodes[r][j] = j < k ? a.queries[q * k + j] : 0;
+#pragma unroll
+                    for (int j = 0; j < kBfsMaxK; ++j) {
+                        if (j >= k) break;
+                        const int32_t x = nodes[r][j];
                         uint32_t slot = kBfsEmpty;
                         if ((uint32_t)x < (uint32_t)a.n_nodes) {
                             slot = insert_min(v_tab, v_mask, (uint32_t)x,
@@ -369,9 +382,11 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
                 }
                 before += mine;
             }
-            uint32_t took, took_nodes;
-            (void)bfs_block_scan<T>(n_ok, &took, wave_sums);
-            (void)bfs_block_scan<T>(nodes_ok, &took_nodes, wave_sums);
+            // (at most kBfsMaxChunk queries of three nodes: both sums in one word)
+            static_assert(kBfsMaxChunk * kBfsMaxK < 1 << 16, "halves of a word");
+            uint32_t both;
+            (void)bfs_block_scan<T>(nodes_ok << 16 | n_ok, &both, wave_sums);
+            const uint32_t took = both & 0xFFFFu, took_nodes = both >> 16;
 #pragma unroll
             for (int r = 0; r < kBfsPer; ++r) {
                 const uint32_t i = (uint32_t)(tid * per_q + r);
@@ -379,8 +394,10 @@ __global__ __launch_bounds__(T) void bfs_batch_kernel(BfsArgs a) {
                     const int64_t q = new_q[i];
                     batch[n_b + i] = (int32_t)q;
                     uint32_t at_v = first_at[r];
-                    for (int j = 0; j < k; ++j) {
-                        const int32_t x = a.queries[q * k + j];
+#pragma unroll
+                    for (int j = 0; j < kBfsMaxK; ++j) {
+                        if (j >= k) break;
+                        const int32_t x = nodes[r][j];
                         if (tuples) tuples[(int64_t)(n_b + i) * k + j] = x;
                         if (fresh[r] & (1u << j)) {
                             vbar[at_v] = x;
@@ -454,14 +471,14 @@ static uint32_t bfs_most_new(int32_t B2) {
 }
 static size_t bfs_lds_bytes(int32_t n_start, int32_t B1, int32_t B2, int32_t k, bool in_lds) {
     const BfsTables t = bfs_tables(n_start, B1, B2, k, in_lds);
-    return sizeof(uint32_t) * (size_t)bfs_lds(bfs_chunk(B2), bfs_most_new(B2),
-                                              (uint32_t)bfs_nodes(n_start, B1, B2, k),
+    return sizeof(uint32_t) * (size_t)bfs_lds(bfs_most_new(B2), (uint32_t)bfs_nodes(n_start, B1, B2, k),
                                               t.slots_q + t.slots_v, in_lds).total;
 }
 static bool bfs_in_lds(int32_t n_start, int32_t B1, int32_t B2, int32_t k) {
     // (the sizes first: the words of large tables need not fit 32 bits)
-    return bfs_tables(n_start, B1, B2, k, true).bytes() <= kBfsLdsMost &&
-           bfs_lds_bytes(n_start, B1, B2, k, true) <= kBfsLdsMost;
+    const size_t most = bfs_threads(B2) == kWave ? kBfsLdsMost : kBfsLdsMostWide;
+    return bfs_tables(n_start, B1, B2, k, true).bytes() <= most &&
+           bfs_lds_bytes(n_start, B1, B2, k, true) <= most;
 }
 
 // Searches in flight with tables in global memory: 16 waves a compute unit, fewer if their tables
@@ -480,14 +497,14 @@ size_t bfs_scratch_bytes(int n_cu, int64_t n_batches, int32_t n_start, int32_t B
     return (size_t)bfs_grid(n_cu, n_batches, per, bfs_threads(B2)) * per;
 }
 
-template <int T, bool kLds>
+template <int T, bool kLds, int kPerSimd>
 static hipError_t launch_bfs_cfg(hipStream_t stream, int64_t grid, size_t lds_bytes, const BfsArgs& a) {
     if (lds_bytes > 48 * 1024) {
-        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_batch_kernel<T, kLds>),
+        hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(bfs_batch_kernel<T, kLds, kPerSimd>),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (rc != hipSuccess) return rc;
     }
-    hipLaunchKernelGGL((bfs_batch_kernel<T, kLds>), dim3((unsigned)grid), dim3(T), lds_bytes, stream, a);
+    hipLaunchKernelGGL((bfs_batch_kernel<T, kLds, kPerSimd>), dim3((unsigned)grid), dim3(T), lds_bytes, stream, a);
     return hipGetLastError();
 }
 
@@ -526,12 +543,13 @@ hipError_t launch_bfs_batches(hipStream_t stream, int n_cu, const int32_t* queri
     const size_t lds_bytes = bfs_lds_bytes(n_start, B1, B2, k, in_lds);
     if (in_lds) {  // a workgroup per search, the hardware hands them out
         const int64_t grid = n_batches < 0x7FFFFF ? n_batches : 0x7FFFFF;
-        if (threads == kWave) return launch_bfs_cfg<kWave, true>(stream, grid, lds_bytes, a);
-        return launch_bfs_cfg<kBfsMaxThreads, true>(stream, grid, lds_bytes, a);
+        if (threads == kWave) return launch_bfs_cfg<kWave, true, 8>(stream, grid, lds_bytes, a);
+        if (lds_bytes <= kBfsLdsEight) return launch_bfs_cfg<kBfsMaxThreads, true, 8>(stream, grid, lds_bytes, a);
+        return launch_bfs_cfg<kBfsMaxThreads, true, 4>(stream, grid, lds_bytes, a);
     }
     const int grid = bfs_grid(n_cu, n_batches, tables.bytes(), threads);
-    if (threads == kWave) return launch_bfs_cfg<kWave, false>(stream, grid, lds_bytes, a);
-    return launch_bfs_cfg<kBfsMaxThreads, false>(stream, grid, lds_bytes, a);
+    if (threads == kWave) return launch_bfs_cfg<kWave, false, 4>(stream, grid, lds_bytes, a);
+    return launch_bfs_cfg<kBfsMaxThreads, false, 4>(stream, grid, lds_bytes, a);
 }
 
 }  // namespace surel

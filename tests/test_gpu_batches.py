@@ -144,6 +144,19 @@ def test_bfs_batches_equal_the_queue_search(ctx, k, B1, B2):
     print(f"k={k} B1={B1} B2={B2}: nodes {counts[:, 0].tolist()[:6]} queries {counts[:, 1].tolist()[:6]}")
 
 
+@pytest.mark.parametrize("k,B2", [(2, 128), (2, 129), (2, 768), (2, 1024), (2, 2252), (2, 2253), (3, 256),
+                                  (3, 768), (3, 2179), (3, 2180), (1, 2252), (1, 2253), (2, 4096)])
+def test_bfs_batches_whose_tables_fill_lds(ctx, k, B2):
+    # a compute unit's LDS for eight searches, for a few and for one, and tables in global memory, on both
+    # sides of each line; searches that find fewer and more queries than B2
+    rng = np.random.default_rng(B2 + k)
+    n_nodes, n_queries = 30_000, 60_000
+    queries = random_queries(rng, n_nodes, n_queries, k, hubs=3, hub_share=0.05)
+    start = rng.integers(0, n_nodes, size=(300, 16)).astype(np.int32)
+    for B1 in (10 ** 6, B2):
+        compare_batches(ctx, queries, n_nodes, start, B1, B2, which=range(0, 300, 60))
+
+
 @pytest.mark.parametrize("n_start", [1, 16, 64, 65, 128, 257, 1025])
 @pytest.mark.parametrize("B2", [1, 16, 31, 32, 63, 64, 65, 256, 257])
 def test_bfs_batches_around_the_sizes_of_a_share(ctx, n_start, B2):
