@@ -12,6 +12,12 @@ namespace surel {
 // 35,000 of them (470 MB) 156 / 143; 500,000 of M = 30, m = 3 (900 MB) 623 / 501.
 constexpr int64_t kPastBytes = 5 << 26;
 
+// Whether the codes of a table's rows go past the caches when walks + RPE-IDs renumber them.  Where half of the
+// 256 MB memory-side cache holds them, they stay there for the join, in us with its time, past / through the
+// caches: 5.4 M rows and 20,000 pairs 229 / 229, 14.6 M and 200,000 pairs 672 / 660, 18 M and 20,000 433 / 430,
+// 27 M and 20,000 583 / 578.
+constexpr bool codes_go_past(int64_t n_rows) { return n_rows > (int64_t)1 << 25; }
+
 // The join's filling launch puts a row at the place inside kRowsAlign rows that it has in the output's
 // lines: 32 ids are a line, 32 vectors one or more.  (64 took as long, 16 and 1 % more.)
 constexpr int kRowsAlign = 32;
