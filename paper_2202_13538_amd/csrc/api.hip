@@ -551,7 +551,8 @@ static int prune_scratch(surel_ctx* ctx, int64_t cap_T, surel::PruneScratch* ps)
 }
 
 // The end of the pruning calls: T and the codes, the number of distinct vectors and (h_rows, if the
-// call's kernel reports it in the pinned words) the row total, with one wait.
+// call's kernel reports it in the pinned words) the row total, with one wait, and a second one where
+// launches depend on the number of vectors.
 // n_rows, d_rows: the number of rows, or where it stands on the device.  d_cnt: see launch_prune_order.
 static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m, int64_t n_rows,
                         const int64_t* d_rows, int64_t cap_rows, const uint16_t* d_cnt, uint16_t* d_T,
@@ -577,10 +578,9 @@ static int prune_finish(surel_ctx* ctx, const surel::PruneScratch& ps, int32_t m
         if (many && surel::launch_prune_order_many(ctx->stream, ctx->n_cu, ps, m, n_rows, n_T, d_cnt, d_T,
                                                    d_code) != hipSuccess)
             return SUREL_E_HIP;
-        // (nobody outside waits for empty slots: the context's next call is on the same stream)
         if (surel::launch_prune_clean(ctx->stream, ps, n_T) != hipSuccess) return SUREL_E_HIP;
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
         ctx->prune_clean = surel::prune_slot_bytes(ps.cap_T);
-        if (many && hipStreamSynchronize(ctx->stream) != hipSuccess) return SUREL_E_HIP;
     }
     return SUREL_OK;
 }

@@ -684,6 +684,25 @@ def test_prune_numbers_of_16_bits(ctx, L, n_T):
         assert torch.equal(T.view(torch.int16)[code.long()], cnt.view(torch.int16))
 
 
+@pytest.mark.parametrize("L", [2, 4, 5])
+@pytest.mark.parametrize("n_T", [32_767, 32_768, 40_001])
+def test_pruning_has_done_its_work_when_it_returns(ctx, L, n_T):
+    # the call waits for its own work, also where the hash set is emptied by a launch of its own (more vectors
+    # than 16-bit numbers, fewer than are sorted): nothing of it is still under way on the stream
+    number = torch.arange(n_T, device="cuda")
+    vectors = torch.zeros((n_T, L), dtype=torch.int64, device="cuda")
+    vectors[:, 0], vectors[:, -1] = number % 256, number // 256
+    cnt = vectors.to(torch.int16).contiguous().view(torch.uint16)
+    T = torch.zeros((1 << 17, L), dtype=torch.int16, device="cuda").view(torch.uint16)
+    code = torch.zeros(n_T, dtype=torch.int32, device="cuda")
+    busy = 0
+    for _ in range(40):
+        rc, got = binding.prune_rpe_raw(ctx, cnt, 1 << 17, T, code)
+        busy += not ctx.stream.query()
+        assert rc == binding.OK and got == n_T
+    assert busy == 0 and ctx.check() == 0
+
+
 def test_one_call_rpe_ids_of_many_distinct_vectors(ctx):
     # every node is visited several times at every step, so hardly two rows are the same
     wl = synth.Workload("t", "rmat", 256, 5000, 0.0, 128, 15, 0, 2, "uniform", graph_seed=3)
