@@ -4,6 +4,7 @@
 #pragma once
 
 #include "device_util.h"
+#include "walk_table.h"
 
 namespace surel {
 
@@ -11,7 +12,8 @@ constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;  // no node id reaches 2^28
 
 // Slots for a set of at most n_max ids: a power of two, at least twice n_max, or a third more than
 // n_max where twice were more than 8 KB and left a compute unit four waves of the walk (131,000 seeds
-// of M = 150, m = 9: 4.2 -> 2.8 ms).  Any multiple of 64 above n_max, up to 4,096, does.
+// of M = 150, m = 9: 4.2 -> 2.8 ms).  Any multiple of 64 above n_max from
+// kDistinctSlotsLeast to kDistinctSlotsMost does.
 __host__ __device__ constexpr int distinct_slots(int n_max) {
     int s = 128;
     while (s < 2048 ? s < 2 * n_max : 3 * s < 4 * n_max) s *= 2;
@@ -28,9 +30,7 @@ __device__ __forceinline__ void distinct_clear(uint32_t* table, int slots, int l
 __device__ __forceinline__ int distinct_insert(uint32_t* table, int slots, uint32_t id,
                                                bool active) {
     uint32_t slot = __umulhi(id * 0x9E3779B1u, (uint32_t)slots);
-    // Ids that meet in a slot go on from it in steps of their own: 67, 71, 73 or 79, primes that `slots`, 64
-    // times at most 64, has no factor in common with, so that every slot is reached.
-    const uint32_t step = 0x4F494743u >> (id & 3u) * 8u & 0xFFu;
+    const uint32_t step = kDistinctSteps >> (id & 3u) * 8u & 0xFFu;
     bool is_new = false;
     bool pending = active;
     for (int probe = 0; probe < slots; ++probe) {

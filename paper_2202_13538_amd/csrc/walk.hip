@@ -23,11 +23,9 @@
 #include "distinct.h"
 #include "kernels.h"
 #include "walk_core.h"
+#include "walk_table.h"
 
 namespace surel {
-
-constexpr int kWalkWavesPerBlock = 4;
-constexpr int kWalkChains = 2;  // walks a lane moves at a time
 
 // Rows of 12 consecutive nodes in 16 bytes: the start of the first row, then the degrees, a byte
 // each.  A byte of 255 says "ask row_ptr": a degree that does not fit, a malformed row, and every
@@ -226,31 +224,6 @@ __global__ __launch_bounds__(kWalkWavesPerBlock* kWave) void walk_kernel(
     }
     if (kCount && lane == 0) set_sizes[i] = n_distinct;
     raise_error(err, bad_graph, kDevBadGraph);
-}
-
-// LDS for the set of a seed's nodes while walks are made from short records, whose second trip wants waves
-// to hide behind: as many workgroups a compute unit as half as many slots again as nodes allow, and then as
-// many slots as they have room for.  235,000 seeds of M = 150, m = 4 1,290 -> 880 us (12 -> 24 waves), of
-// M = 200 1,380 -> 1,067 (20 waves), 120,000 of M = 200, m = 9 4,930 -> 2,635 (8 waves).  From packed
-// records, where lines from memory are what bounds the walks, they are faster with fewer waves
-// (1,000,000 seeds of M = 120, m = 5 5,790, with 20 waves 6,000; 400,000 of M = 200, m = 4 3,290 and 3,390).
-// (At six workgroups free slots are worth more than waves: 235,000 seeds of M = 100, m = 4 with 832 slots
-// 569 us, with 576, which eight have room for, 627.)
-constexpr int kWalkMostGroups = 6;
-struct WalkTable {
-    int groups, slots;
-};
-static WalkTable walk_table(int32_t M, int32_t m) {
-    constexpr int kLds = 160 * 1024 / 4, kLdsPart = kLds / 128;  // words of a compute unit, given out in parts
-    const int n = 1 + M * m;
-    const int stage = kWalkChains * kWave * (m + 1);
-    WalkTable t{kLds / (kWalkWavesPerBlock * (stage + n + n / 2)), 0};
-    t.groups = t.groups < 1 ? 1 : t.groups > kWalkMostGroups ? kWalkMostGroups : t.groups;
-    const int room = kLds / t.groups / kLdsPart * kLdsPart / kWalkWavesPerBlock - stage;
-    t.slots = (room < 5 * n / 2 ? room : 5 * n / 2) / 64 * 64;
-    if (t.slots <= n) t.slots = (n + 64) / 64 * 64;
-    if (t.slots < 128) t.slots = 128;  // (more than distinct_insert goes on by)
-    return t;
 }
 
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m) {

@@ -1,4 +1,5 @@
 """Rules of the kernels' launches that are plain functions, compiled for the host."""
+import math
 import os
 import shutil
 import subprocess
@@ -20,6 +21,19 @@ def evaluate(tmp_path, includes, expressions):
     subprocess.run(["g++", "-O0", "-std=c++17", "-I" + CSRC, "-o", str(tmp_path / "main"),
                     str(tmp_path / "main.cpp")], check=True)
     out = subprocess.run([str(tmp_path / "main")], capture_output=True, text=True, check=True).stdout
+    return [int(x) for x in out.split()]
+
+
+def evaluate_list(tmp_path, includes, expression, values):
+    """The values of one C++ expression for every tuple x of `values`."""
+    rows = ", ".join("{" + ", ".join(map(str, v)) + "}" for v in values)
+    source = "".join(f'#include "{name}"\n' for name in includes)
+    source += f"#include <cstdio>\nusing namespace surel;\nstatic const int all[][{len(values[0])}] = {{{rows}}};\n"
+    source += f'int main() {{ for (auto& x : all) printf("%lld\\n", (long long)({expression})); }}\n'
+    (tmp_path / "list.cpp").write_text(source)
+    subprocess.run(["g++", "-O0", "-std=c++17", "-I" + CSRC, "-o", str(tmp_path / "list"),
+                    str(tmp_path / "list.cpp")], check=True)
+    out = subprocess.run([str(tmp_path / "list")], capture_output=True, text=True, check=True).stdout
     return [int(x) for x in out.split()]
 
 
@@ -51,3 +65,16 @@ def test_codes_that_the_memory_side_cache_holds_stay_in_the_caches(tmp_path):
     rows = [0, 1, 8_400_000, half, half + 1, 146_000_000, 1 << 31]
     past = evaluate(tmp_path, ["lines.h"], [f"codes_go_past({n}ll)" for n in rows])
     assert past == [0, 0, 0, 0, 1, 1, 1]
+
+
+def test_every_slot_of_a_set_is_reached_from_every_other(tmp_path):
+    # ids that meet go on in steps that no number of slots may have a factor in common with; the set holds all
+    # nodes of a seed's walks, and a workgroup's four fit a compute unit's LDS
+    sizes = [(M, m) for m in range(1, 16) for M in range(1, 2048 // (m + 1) + 1)]
+    steps = evaluate(tmp_path, ["walk_table.h"], [f"kDistinctSteps >> {8 * i} & 0xFF" for i in range(4)])
+    slots = evaluate_list(tmp_path, ["walk_table.h"], "walk_table(x[0], x[1]).slots", sizes)
+    for (M, m), s in zip(sizes, slots, strict=True):
+        assert s % 64 == 0 and 1 + M * m < s and max(steps) < s
+        assert s <= 64 * 64, (M, m)
+        assert all(math.gcd(s, step) == 1 for step in steps)
+        assert 4 * (2 * 64 * (m + 1) + s) * 4 <= 160 * 1024
