@@ -9,11 +9,11 @@
 // over the digits), and the scatter, which puts a tile's pairs in order in LDS first, so that they
 // leave as runs of a bucket.  Then a workgroup per bucket sorts its pairs by the node's lower bits in
 // LDS, and writes the nodes' offsets and the queries: they go through memory once.  Buckets with more
-// pairs than LDS holds (queries crowd on neighbouring nodes) are taken in chunks by workgroups of
-// their own, behind a launch that counts each chunk's nodes.
+// pairs than LDS holds (queries crowd on neighbouring nodes) are cut into chunks; the same launch counts
+// each chunk's nodes, and another one puts the chunks in order.
 // What bounds it: the memory round trips of the launches one after the other, at these sizes: a million
-// two-node queries on 2.9M nodes 42 us (4.8 + 6.5 + 12.3 + 3.5 + 14.5), with three passes of 8 bits and the
-// offsets behind them 87.
+// two-node queries on 2.9M nodes 39 us (5 + 6.5 + 12.5 + 14 + 4, of which the last finds that there are no
+// chunks), with three passes of 8 bits and the offsets behind them 85.
 // Graphs of 2^23 nodes and more, whose buckets would have more nodes than LDS has room for, are
 // sorted 8 bits a pass, least significant first, the same three launches a pass, and the offsets by a
 // launch of their own.
@@ -109,7 +109,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortSource src,
 // 16 waves a share of the tiles each; the digits of the workgroups before it come in through
 // small_scan.h (whose helpers read the counts at any time: the places are an array of their own).
 // any_large (optional; the counting launch has cleared it): set where a digit has more than `large` pairs.
-constexpr int kPlaceTiles = 16;
 template <int kBins>
 __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_t* __restrict__ hist,
                                                                   int64_t n_tiles,
@@ -127,6 +126,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
     uint32_t* to = places + (int64_t)blockIdx.x * kWave + lane;
     uint32_t tag = 0;
     if (wave == 0) tag = small_scan_tag(ss);
+    constexpr int kPlaceTiles = 16;
     uint32_t first[kPlaceTiles], sum = 0;  // the wave's first tiles stay in registers
 #pragma unroll
     for (int u = 0; u < kPlaceTiles; ++u) first[u] = t0 + u < t1 ? column[(t0 + u) * kBins] : 0u;
@@ -414,17 +414,33 @@ __global__ __launch_bounds__(kOffsetsThreads) void incidence_offsets_kernel(
 // wave: they are counted for every wave and node, sums over both give each node's place and, within it,
 // each wave's, and counting once more puts the pairs there.
 // What bounds it: a third each the way there (launch, the bucket's place, its pairs), instructions, and
-// 8 bytes a node and 4 a pair on their way out.  708 buckets of 3,000 pairs and 4,096 nodes 14.5 us; with
+// 8 bytes a node and 4 a pair on their way out.  708 buckets of 3,000 pairs and 4,096 nodes 14 us; with
 // pairs read twice and the offsets last 18.5, sorted in two passes of six bits 27.
+//
+// Lists that crowd.  Where a byte does not count a node's pairs of a wave, and in the chunks of large buckets,
+// ballots tell a round's pairs of a node apart, and the waves take turns to add theirs to the nodes' words.
+// What bounds the chunks is that every one reads the counts of all chunks of its bucket: 2.1 M pairs on 3,000
+// neighbours of 2.9M nodes, 205 chunks of 4,096 counts, 55 us, 26 of them the counts (16 the turns, 5 the way
+// out through LDS, 24 without it).  The whole call in us, 8 bits a pass / chunks of 6,656 pairs sorted in two
+// passes by 256 threads of the launch for the buckets / as it is, 2.1 M pairs on 2.9M nodes and on 235,000:
+//    half of them with one node      122 / 127 /  84     99 / 110 /  60
+//    all with one node               117 / 155 / 102     97 / 125 /  71
+//    3,000 neighbours                132 / 160 / 107     98 / 105 /  60
+//    1,048 nodes, 2,000 times each    96 / 100 /  83     92 /  95 /  71
+//    ids by descending degree        133 / 106 /  73     96 / 103 /  55
 constexpr int kListThreads = 256;
 constexpr int kListWaves = kListThreads / kWave;
 static_assert(kListWaves == 4, "a node's four counts are the bytes of four words");
 constexpr int kListRounds = 26;                // pairs of a thread, at most
-constexpr int kListPairs = kListRounds * kListThreads;  // LDS takes them, of three workgroups a CU
+// of a bucket that LDS takes: with 32-bit items and up to 12 lower bits, of three workgroups a CU
+constexpr int kListPairs = kListRounds * kListThreads;
 constexpr int kListBits = 13;                  // lower bits of a node, at most
-constexpr int kListBins = 1 << (kListBits + 1) / 2;
-constexpr int kListFlight = 16;   // rows of chunk counts in flight
-constexpr int kListChunks = 256;  // workgroups for chunks; about as many chunks where pairs crowd most
+constexpr int kListFlight = 8;    // rows of chunk counts in flight, and a wave's rounds of pairs
+constexpr int kListChunks = 256;  // workgroups that count chunks' nodes, and that put chunks in order
+constexpr int kChunkThreads = 1024;
+constexpr int kChunkWaves = kChunkThreads / kWave;
+constexpr int kPartRounds = 10;
+constexpr int kPartPairs = kPartRounds * kChunkThreads;  // of a chunk that LDS takes at a time
 
 // Nodes of a bucket, rounded up to whole 16-byte pieces of their counts.
 __host__ __device__ constexpr int list_nodes(int low_bits) { return low_bits < 4 ? 16 : 1 << low_bits; }
@@ -437,7 +453,7 @@ struct ListJob {
     const void* items;
     int low_bits, query_bits;
     int32_t n_nodes;
-    uint32_t chunk_pairs;          // of a bucket with more than kListPairs, a multiple of that
+    uint32_t chunk_pairs;          // of a bucket with more than kListPairs
     uint16_t* chunk_counts;        // [chunk][list_nodes(low_bits)]
     int64_t* inc_off;
     int32_t* inc_q;
@@ -461,11 +477,12 @@ struct ListChunk {
     uint32_t first, n;             // pairs of the chunk, as places among the items
     int at, bucket_chunk, n_bucket_chunks;  // its row of chunk_counts, its bucket's first row, and rows
 };
+template <int kThreads>
 __device__ __forceinline__ ListChunk list_chunk(const ListJob& job, int id, ListChunk* shared,
                                                 uint32_t* wave_sum) {
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     if (*job.any_large == 0u) return ListChunk{-1, 0, 0, 0, 0, 0};
-    constexpr int kPer = kBuckets / kListThreads;
+    constexpr int kPer = kBuckets / kThreads;
     uint32_t chunks[kPer], sum = 0;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -495,16 +512,15 @@ __device__ __forceinline__ ListChunk list_chunk(const ListJob& job, int id, List
     return *shared;
 }
 
-// Pairs of every node of a chunk of a large bucket.
+// Pairs of every node of the chunks of large buckets, workgroup `group` of n_groups.  counts: a word a node.
 template <typename Item>
-__global__ __launch_bounds__(kListThreads) void list_chunk_counts_kernel(ListJob job) {
-    __shared__ uint32_t counts[1 << kListBits];
-    __shared__ ListChunk shared;
-    __shared__ uint32_t wave_sum[kListWaves];
+__device__ __forceinline__ void list_chunk_counts(const ListJob& job, int group, int n_groups, uint32_t* counts,
+                                                  ListChunk* shared, uint32_t* wave_sum) {
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const Item* items = static_cast<const Item*>(job.items);
-    for (int id = (int)blockIdx.x;; id += (int)gridDim.x) {
-        const ListChunk c = list_chunk(job, id, &shared, wave_sum);
+#pragma unroll 1
+    for (int id = group;; id += n_groups) {
+        const ListChunk c = list_chunk<kListThreads>(job, id, shared, wave_sum);
         if (c.bucket < 0) return;
         for (int x = tid; x < list_nodes(job.low_bits); x += kListThreads) counts[x] = 0u;
         __syncthreads();
@@ -535,108 +551,139 @@ __global__ __launch_bounds__(kListThreads) void list_chunk_counts_kernel(ListJob
     }
 }
 
+// What a lane does with its pair in a round of 64, in a word: a place among the nodes' words and what it adds
+// there (the first lane of a node the number of its pairs, the others nothing, somewhere), the lane's rank
+// among the lanes of its node, and the first of them.
+constexpr int kRankAt = kListBits, kLeaderAt = kRankAt + 6, kAddAt = kLeaderAt + 6;
+static_assert(kAddAt + 7 <= 32, "a word");
+
+// Rounds of 64 pairs of a wave that has some, of n in all: no fewer than four, for a wave's turn (list_turns)
+// takes longer than its rounds.
+template <int kThreads>
+__device__ __forceinline__ int list_rounds(int n) { return max((n + kThreads - 1) / kThreads, 4); }
+
+// word[r] of round r of the wave's pairs, a share of consecutive ones of n, found by ballots, one a bit.
+// totals (or null): a word a node, to which the node's pairs are added.
+template <typename Item, int kThreads, int kRounds>
+__device__ __forceinline__ void list_ranks(const ListJob& job, const Item* __restrict__ items, int n,
+                                           uint32_t (&word)[kRounds], uint32_t* totals) {
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int rounds = list_rounds<kThreads>(n);
+    int base = wave * rounds * kWave + lane;
+    asm volatile("" : "+v"(base));  // (no comparison is kept from one loop for the next)
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r0 = 0; r0 < kRounds; r0 += kListFlight) {
+        uint32_t low[kListFlight];
+        uint64_t same[kListFlight];
+        if (r0 < rounds) {
+#pragma unroll
+            for (int u = 0; u < kListFlight && r0 + u < kRounds; ++u) {
+                low[u] = job.low_of(items[min(base + (r0 + u) * kWave, n - 1)]);
+                same[u] = __ballot(r0 + u < rounds && base + (r0 + u) * kWave < n);
+            }
+#pragma unroll 1
+            for (int b = 0; b < job.low_bits; ++b) {
+#pragma unroll
+                for (int u = 0; u < kListFlight && r0 + u < kRounds; ++u) {
+                    const bool one = (low[u] >> b & 1u) != 0u;
+                    const uint64_t has = __ballot(one);
+                    same[u] &= one ? has : ~has;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kListFlight && r0 + u < kRounds; ++u) {
+            word[r0 + u] = (uint32_t)lane & 15u;
+            if (r0 + u < rounds && base + (r0 + u) * kWave < n) {
+                const uint32_t rank = (uint32_t)__popcll(same[u] & below), all = (uint32_t)__popcll(same[u]);
+                const uint32_t leader = (uint32_t)__ffsll((unsigned long long)same[u]) - 1u;
+                word[r0 + u] = (rank == 0u ? low[u] | all << kAddAt : (uint32_t)lane & 15u) | rank << kRankAt | leader << kLeaderAt;
+                if (totals != nullptr && rank == 0u) atomicAdd(&totals[low[u]], all);
+            }
+        }
+    }
+}
+
+// place[r] of the pairs of list_ranks, in order of their nodes and queries: words[x] is the place of node x's
+// first one and becomes the one behind its last.  The waves take turns, so that a wave's pairs come behind
+// those of the waves before; a turn's additions follow one another in LDS, which takes a wave's instructions
+// in order.
+template <int kThreads, int kRounds>
+__device__ __forceinline__ void list_turns(int n, const uint32_t (&word)[kRounds], uint32_t* words,
+                                           uint32_t (&place)[kRounds]) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int rounds = list_rounds<kThreads>(n);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) place[r] = 0u;
+    __syncthreads();
+#pragma unroll 1
+    for (int turn = 0; turn * rounds * kWave < n; ++turn) {
+        if (wave == turn) {
+#pragma unroll
+            for (int r0 = 0; r0 < kRounds; r0 += kListFlight) {
+                if (r0 < rounds) {
+#pragma unroll
+                    for (int r = r0; r < r0 + kListFlight && r < kRounds; ++r)
+                        place[r] = atomicAdd(&words[word[r] & ((1u << kListBits) - 1u)], word[r] >> kAddAt);
+                }
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r)
+        place[r] = (uint32_t)__shfl((int)place[r], (int)(word[r] >> kLeaderAt & 63u), kWave) + (word[r] >> kRankAt & 63u);
+}
+
+// words[x], pairs of node x, becomes the place of its first one, `first` being that of the bucket's.
+// each(x, place): called for every node, before its word changes.
+template <int kThreads, typename Each>
+__device__ __forceinline__ void list_node_places(int n_here, uint32_t first, uint32_t* words, uint32_t* wave_word,
+                                                 Each&& each) {
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int turns = (n_here + kThreads - 1) / kThreads;
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll 1
+    for (int u = 0; u < turns; ++u) {
+        const int x = (wave * turns + u) * kWave + lane;
+        sum += x < n_here ? words[x] : 0u;
+    }
+    sum = wave_bcast_u32(wave_incl_sum(sum), kWave - 1);
+    if (lane == 0) wave_word[wave] = sum;
+    __syncthreads();
+    uint32_t before = first;
+    for (int w = 0; w < wave; ++w) before += wave_word[w];
+#pragma unroll 1
+    for (int u = 0; u < turns; ++u) {
+        const int x = (wave * turns + u) * kWave + lane;
+        const uint32_t here = x < n_here ? words[x] : 0u;
+        const uint32_t incl = wave_incl_sum(here);
+        const uint32_t place = before + incl - here;
+        if (x < n_here) {
+            each(x, place);
+            words[x] = place;
+        }
+        before += wave_bcast_u32(incl, kWave - 1);
+    }
+    __syncthreads();
+}
+
 // LDS of a workgroup: the pairs, then for every node of the bucket its place, and a word.
 template <typename Item>
 size_t list_lds_bytes(int low_bits) {
-    static_assert(kListPairs * sizeof(Item) + (2 << kListBits) >= 4 << kListBits, "room for list_chunk_places");
     return kListPairs * sizeof(Item) + (size_t)list_nodes(low_bits) * 6;
 }
 
-struct ListLds {
-    uint32_t count[kListWaves][kListBins];
-    uint32_t wave_word[kListWaves];
-    ListChunk chunk;
-};
-
-// Adds 1 to counts[d] for every lane that counts, and returns what was there before the lane's own: the
-// lanes in order, if LDS takes them so.  (A wave of one digit, which is what a list with few nodes is made
-// of, adds once: 64 additions to a word of LDS take 50 ns, one after the other.)
-__device__ __forceinline__ uint32_t count_in_order(uint32_t* counts, uint32_t d, bool valid, int lane) {
-    const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
-    const uint64_t all = __ballot(valid);
-    if (__ballot(valid && d == one) == all) {
-        uint32_t before = 0;
-        if (lane == 0) before = atomicAdd(&counts[one], (uint32_t)__popcll(all));
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)before) + (uint32_t)lane;
-    }
-    return valid ? atomicAdd(&counts[d], 1u) : 0u;
-}
-
-// Sorts n pairs (n <= kListPairs, in the order of their queries) from `items` on by the lower bits of their
-// node, into sorted[0 .. n): in two passes of half the bits each, with ranks as in the fast scatter above.
-// Did the pairs not come out in order, each would count the pairs before it.
-template <typename Item>
-__device__ __forceinline__ void list_sort(const Item* __restrict__ items, int n, int low_bits,
-                                          int query_bits, Item* sorted, ListLds& lds) {
-    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int rounds = (n + kListThreads - 1) / kListThreads;
-    const int half = max((low_bits + 1) / 2, 1);
-#pragma unroll 1
-    for (int done = 0; done < max(low_bits, 1); done += half) {
-        int base = wave * rounds * kWave + lane;
-        asm volatile("" : "+v"(base));  // (no comparison of a pass is kept for the next one)
-        Item x[kListRounds];
-        const Item* from = done == 0 ? items : sorted;
-#pragma unroll
-        for (int r = 0; r < kListRounds; ++r)
-            if (r < rounds) x[r] = from[min(base + r * kWave, n - 1)];
-        const int shift = query_bits + done;
-        const uint32_t mask = (1u << min(half, low_bits - done)) - 1u;
-        for (int d = lane; d < kListBins; d += kWave) lds.count[wave][d] = 0;
-        wave_sync();
-#pragma unroll
-        for (int r = 0; r < kListRounds; ++r)
-            if (r < rounds)
-                (void)count_in_order(lds.count[wave], (uint32_t)(x[r] >> shift) & mask, base + r * kWave < n, lane);
-        __syncthreads();
-        uint32_t total = 0, incl = 0;
-        if (tid < kListBins) {
-            for (int w = 0; w < kListWaves; ++w) total += lds.count[w][tid];
-            incl = wave_incl_sum(total);
-            if (lane == kWave - 1) lds.wave_word[wave] = incl;
-        }
-        __syncthreads();
-        if (tid < kListBins) {
-            uint32_t at = incl - total;
-            for (int w = 0; w < wave; ++w) at += lds.wave_word[w];
-            for (int w = 0; w < kListWaves; ++w) {
-                const uint32_t c = lds.count[w][tid];
-                lds.count[w][tid] = at;
-                at += c;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kListRounds; ++r) {
-            if (r < rounds) {
-                const bool valid = base + r * kWave < n;
-                const uint32_t at = count_in_order(lds.count[wave], (uint32_t)(x[r] >> shift) & mask, valid, lane);
-                if (valid) sorted[at] = x[r];
-            }
-        }
-        __syncthreads();
-    }
-    bool wrong = false;
-    for (int i = tid; i < n - 1; i += kListThreads) wrong = wrong || sorted[i] > sorted[i + 1];
-    if (__syncthreads_or(wrong) != 0) {
-#pragma unroll 1
-        for (int i = tid; i < n; i += kListThreads) {
-            const Item x = items[i];
-            int at = 0;
-            for (int j = 0; j < n; ++j) at += items[j] < x || (items[j] == x && j < i) ? 1 : 0;
-            sorted[at] = x;
-        }
-        __syncthreads();
-    }
-}
-
-// A bucket's pairs.  counts: a byte for every wave (kListNodes words apart) and node, cleared; places: 16
+// A bucket's pairs.  counts: a byte for every wave (list_nodes / 4 words apart) and node, cleared; places: 16
 // bits for every node.  Where a node has more pairs than a byte holds, or the pairs have not come out in
-// order (those of one instruction do if LDS takes its lanes one after the other), they are sorted.
+// order (those of one instruction do if LDS takes its lanes one after the other), the waves take turns.
 template <typename Item>
 __device__ __forceinline__ void list_bucket(const ListJob& job, int bucket, uint32_t first, int n,
                                             const Item* __restrict__ items, Item* sorted, uint16_t* places, uint32_t* counts,
-                                            ListLds& lds) {
+                                            uint32_t* wave_word) {
     const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int n_here = 1 << job.low_bits;
     const int words = list_nodes(job.low_bits) / 4;  // of a wave's counts
@@ -684,15 +731,15 @@ __device__ __forceinline__ void list_bucket(const ListJob& job, int bucket, uint
         sum += (even & 0xFFFFu) + (even >> 16) + (odd & 0xFFFFu) + (odd >> 16);
     }
     const uint32_t incl = wave_incl_sum(sum);
-    if (lane == kWave - 1) lds.wave_word[wave] = incl;
-    bool sort = __syncthreads_or(most != 0u) != 0;
+    if (lane == kWave - 1) wave_word[wave] = incl;
+    bool in_turns = __syncthreads_or(most != 0u) != 0;
     uint32_t before = incl - sum, all = 0;
     for (int w = 0; w < kListWaves; ++w) {
-        if (w < wave) before += lds.wave_word[w];
-        all += lds.wave_word[w];
+        if (w < wave) before += wave_word[w];
+        all += wave_word[w];
     }
-    sort = sort || all != (uint32_t)n;  // a byte ran over into its neighbour: 255 or 256 are missing
-    if (!sort) {
+    in_turns = in_turns || all != (uint32_t)n;  // a byte ran over into its neighbour: 255 or 256 are missing
+    if (!in_turns) {
         for (int u = 0; u < per; ++u) {
             const int t = tid * per + u;
             if (t >= words) break;
@@ -724,144 +771,149 @@ __device__ __forceinline__ void list_bucket(const ListJob& job, int bucket, uint
             wrong = wrong || item > sorted[min(i + 1, n - 1)];
             job.inc_q[first + i] = (int32_t)((uint32_t)item & query_mask);
         }
-        sort = __syncthreads_or(wrong) != 0;
+        in_turns = __syncthreads_or(wrong) != 0;
     }
-    if (sort) {
-        list_sort<Item>(items, n, job.low_bits, job.query_bits, sorted, lds);
-        for (int i = tid; i < n; i += kListThreads) {
-            const Item item = sorted[i];
-            const int low = (int)job.low_of(item);
-            job.inc_q[first + i] = (int32_t)((uint32_t)item & query_mask);
-            // places of the nodes that have pairs, and of those without in front of them
-            const int last = i > 0 ? (int)job.low_of(sorted[i - 1]) : -1;
-            for (int y = last + 1; y <= low; ++y) places[y] = (uint16_t)i;
-            if (i + 1 == n)
-                for (int y = low + 1; y < n_here; ++y) places[y] = (uint16_t)n;
-        }
+    if (in_turns) {
+        uint32_t word[kListRounds], place[kListRounds];
+        __syncthreads();  // the words in front may still be read
+        for (int t = tid; t < list_nodes(job.low_bits); t += kListThreads) counts[t] = 0u;
         __syncthreads();
-        offsets_out();
+        list_ranks<Item, kListThreads, kListRounds>(job, items, n, word, counts);
+        list_node_places<kListThreads>(n_here, 0u, counts, wave_word, [&](int x, uint32_t place) {
+            const int64_t node = ((int64_t)bucket << job.low_bits) + x;
+            if (node <= job.n_nodes) job.inc_off[node] = (int64_t)first + place;
+        });
+        list_turns<kListThreads, kListRounds>(n, word, counts, place);
+        uint32_t* queries = reinterpret_cast<uint32_t*>(sorted);
+        const int shares = list_rounds<kListThreads>(n);
+        int at = wave * shares * kWave + lane;
+        asm volatile("" : "+v"(at));  // (no comparison of the loops above is kept for this one)
+#pragma unroll
+        for (int r = 0; r < kListRounds; ++r)
+            if (r < shares && at + r * kWave < n) queries[place[r]] = (uint32_t)items[at + r * kWave] & query_mask;
+        __syncthreads();
+#pragma unroll 4
+        for (int i = tid; i < n; i += kListThreads) job.inc_q[first + i] = (int32_t)queries[i];
     }
 }
 
-// words[x]: where the first pair of node x in chunk c of a large bucket goes.  The bucket's first chunk
-// also writes the nodes' offsets.  spare: as many words again, where the pairs and places will be.
-__device__ __forceinline__ void list_chunk_places(const ListJob& job, const ListChunk& c, uint32_t* words,
-                                                  uint32_t* spare, ListLds& lds) {
-    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int n_here = 1 << job.low_bits;
-    const int turns = (n_here + kListThreads - 1) / kListThreads;
-    // rows of 8 nodes in 16 bytes; the sums over the chunks go to the bucket's words first
-    const int pieces = list_nodes(job.low_bits) / 8;
-    const uint4* counts = reinterpret_cast<const uint4*>(job.chunk_counts) + (int64_t)c.bucket_chunk * pieces;
-    const int mine = c.at - c.bucket_chunk;
-#pragma unroll 1
-    for (int p = tid; p < pieces; p += kListThreads) {
-        uint32_t all[8] = {}, before_mine[8] = {};
-#pragma unroll 1
-        for (int k0 = 0; k0 < c.n_bucket_chunks; k0 += kListFlight) {
-            uint4 v[kListFlight];
-#pragma unroll
-            for (int k = 0; k < kListFlight; ++k)
-                v[k] = counts[(int64_t)min(k0 + k, c.n_bucket_chunks - 1) * pieces + p];
-#pragma unroll
-            for (int k = 0; k < kListFlight; ++k) {
-                const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
-                const bool there = k0 + k < c.n_bucket_chunks, first = k0 + k < mine;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const uint32_t one = there ? w[e / 2] >> (e & 1) * 16 & 0xFFFFu : 0u;
-                    all[e] += one;
-                    before_mine[e] += first ? one : 0u;
-                }
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            words[p * 8 + e] = all[e];
-            spare[p * 8 + e] = before_mine[e];
-        }
-    }
-    __syncthreads();
-    uint32_t sum = 0;
-#pragma unroll 1
-    for (int u = 0; u < turns; ++u) {
-        const int x = (wave * turns + u) * kWave + lane;
-        sum += x < n_here ? words[x] : 0u;
-    }
-    sum = wave_bcast_u32(wave_incl_sum(sum), kWave - 1);
-    __syncthreads();
-    if (lane == 0) lds.wave_word[wave] = sum;
-    __syncthreads();
-    uint32_t before = job.start_of(c.bucket);
-    for (int w = 0; w < wave; ++w) before += lds.wave_word[w];
-#pragma unroll 1
-    for (int u = 0; u < turns; ++u) {
-        const int x = (wave * turns + u) * kWave + lane;
-        const uint32_t all = x < n_here ? words[x] : 0u;
-        const uint32_t incl = wave_incl_sum(all);
-        const uint32_t to = before + incl - all;
-        const int64_t node = ((int64_t)c.bucket << job.low_bits) + x;
-        if (x < n_here) {
-            words[x] = to + spare[x];
-            if (mine == 0 && node <= job.n_nodes) job.inc_off[node] = (int64_t)to;
-        }
-        before += wave_bcast_u32(incl, kWave - 1);
-    }
-}
-
-// Sorted pairs of a part of a chunk go out; words[x] moves on to where the node's next pair goes.
-template <typename Item>
-__device__ __forceinline__ void list_chunk_out(const ListJob& job, int n, const Item* sorted, uint32_t* words) {
-    const int tid = (int)threadIdx.x;
-    const uint32_t query_mask = (1u << job.query_bits) - 1u;
-    auto low_of = [&](int i) { return job.low_of(sorted[i]); };
-#pragma unroll 4
-    for (int i = tid; i < n; i += kListThreads)  // less the place of its first pair here
-        if (i == 0 || low_of(i - 1) != low_of(i)) words[low_of(i)] -= (uint32_t)i;
-    __syncthreads();
-#pragma unroll 4
-    for (int i = tid; i < n; i += kListThreads) {
-        const uint32_t to = words[low_of(i)] + (uint32_t)i;
-        if (to < (uint32_t)job.n) job.inc_q[to] = (int32_t)((uint32_t)sorted[i] & query_mask);
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int i = tid; i < n; i += kListThreads)
-        if (i + 1 == n || low_of(i + 1) != low_of(i)) words[low_of(i)] += (uint32_t)i + 1u;
-    __syncthreads();
-}
-
-// Workgroups below n_buckets: a bucket each.  Those behind them: the chunks of the large buckets.
+// Workgroups below n_buckets: a bucket each.  Those behind them: the nodes of the large buckets' chunks.
 template <typename Item>
 __global__ __launch_bounds__(kListThreads) void incidence_lists_kernel(ListJob job) {
     extern __shared__ __align__(16) unsigned char dynamic[];
-    __shared__ ListLds lds;
+    __shared__ uint32_t wave_word[kListWaves];
+    __shared__ ListChunk chunk;
     const int n_nodes = list_nodes(job.low_bits);
     Item* sorted = reinterpret_cast<Item*>(dynamic);
     uint16_t* places = reinterpret_cast<uint16_t*>(dynamic + kListPairs * sizeof(Item));
     uint32_t* words = reinterpret_cast<uint32_t*>(places + n_nodes);
     const Item* items = static_cast<const Item*>(job.items);
-    if ((int)blockIdx.x < job.n_buckets) {
-        const int b = (int)blockIdx.x;
-        const uint32_t first = job.start_of(b), n = job.size_of(b);
-        if (n > (uint32_t)kListPairs) return;
-        uint4* clear = reinterpret_cast<uint4*>(words);
-        for (int x = (int)threadIdx.x; x < n_nodes / 4; x += kListThreads) clear[x] = make_uint4(0u, 0u, 0u, 0u);
-        __syncthreads();
-        list_bucket(job, b, first, (int)n, items + first, sorted, places, words, lds);
+    if ((int)blockIdx.x >= job.n_buckets) {
+        list_chunk_counts<Item>(job, (int)blockIdx.x - job.n_buckets, (int)gridDim.x - job.n_buckets, words, &chunk,
+                                wave_word);
         return;
     }
+    const int b = (int)blockIdx.x;
+    const uint32_t first = job.start_of(b), n = job.size_of(b);
+    if (n > (uint32_t)kListPairs) return;
+    uint4* clear = reinterpret_cast<uint4*>(words);
+    for (int x = (int)threadIdx.x; x < n_nodes / 4; x += kListThreads) clear[x] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    list_bucket(job, b, first, (int)n, items + first, sorted, places, words, wave_word);
+}
+
+// LDS of a workgroup that puts chunks in order: two words a pair of a part (before that, two a node) and two a
+// node.
+size_t chunk_lds_bytes(int low_bits) {
+    static_assert(kPartPairs >= 1 << kListBits, "room for the nodes' words");
+    return 2 * (kPartPairs + (size_t)list_nodes(low_bits)) * sizeof(uint32_t);
+}
+
+// Puts the chunks of large buckets in order, a part that LDS holds at a time.  A chunk's places come from the
+// counts of all chunks of its bucket; the bucket's first chunk also writes the nodes' offsets.
+template <typename Item>
+__global__ __launch_bounds__(kChunkThreads) void incidence_chunks_kernel(ListJob job) {
+    extern __shared__ __align__(16) uint32_t chunk_words[];
+    __shared__ uint32_t wave_word[kChunkWaves];
+    __shared__ ListChunk shared;
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int n_nodes = list_nodes(job.low_bits), n_here = 1 << job.low_bits;
+    const uint32_t query_mask = (1u << job.query_bits) - 1u;
+    uint32_t* queries = chunk_words;
+    uint32_t* targets = queries + kPartPairs;
+    uint32_t* all = queries;     // pairs of the bucket's nodes
+    uint32_t* before = targets;  // of them, those in front of the chunk
+    uint32_t* words = targets + kPartPairs;
+    uint32_t* next = words + n_nodes;  // where a node's next pair goes in the output; less its place in the part
 #pragma unroll 1
-    for (int id = (int)blockIdx.x - job.n_buckets;; id += (int)gridDim.x - job.n_buckets) {
-        const ListChunk c = list_chunk(job, id, &lds.chunk, lds.wave_word);
+    for (int id = (int)blockIdx.x;; id += (int)gridDim.x) {
+        const ListChunk c = list_chunk<kChunkThreads>(job, id, &shared, wave_word);
         if (c.bucket < 0) return;
-        list_chunk_places(job, c, words, reinterpret_cast<uint32_t*>(dynamic), lds);
+        for (int x = tid; x < n_nodes; x += kChunkThreads) all[x] = before[x] = 0u;
         __syncthreads();
+        // rows of 8 nodes in 16 bytes, as many rows at a time as there are threads for (with no more than
+        // kListFlight a thread: a word takes its additions one after the other)
+        const int pieces = n_nodes / 8, mine = c.at - c.bucket_chunk;
+        const int groups = min(kChunkThreads / pieces, (c.n_bucket_chunks + kListFlight - 1) / kListFlight);
+        const int group = tid / pieces, piece = tid & (pieces - 1);
+        const uint4* counts = reinterpret_cast<const uint4*>(job.chunk_counts) + (int64_t)c.bucket_chunk * pieces + piece;
+        uint32_t sum[8] = {}, in_front[8] = {};
 #pragma unroll 1
-        for (uint32_t t0 = 0; t0 < c.n; t0 += kListPairs) {
-            const int n = (int)min((uint32_t)kListPairs, c.n - t0);
-            list_sort<Item>(items + c.first + t0, n, job.low_bits, job.query_bits, sorted, lds);
-            list_chunk_out(job, n, sorted, words);
+        for (int k0 = group < groups ? group : c.n_bucket_chunks; k0 < c.n_bucket_chunks; k0 += groups * kListFlight) {
+            uint4 v[kListFlight];
+#pragma unroll
+            for (int k = 0; k < kListFlight; ++k)
+                v[k] = counts[(int64_t)min(k0 + k * groups, c.n_bucket_chunks - 1) * pieces];
+#pragma unroll
+            for (int k = 0; k < kListFlight; ++k) {
+                const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+                const bool there = k0 + k * groups < c.n_bucket_chunks, first = k0 + k * groups < mine;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t one = there ? w[e / 2] >> (e & 1) * 16 & 0xFFFFu : 0u;
+                    sum[e] += one;
+                    in_front[e] += first ? one : 0u;
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (sum[e] != 0u) atomicAdd(&all[piece * 8 + e], sum[e]);
+            if (in_front[e] != 0u) atomicAdd(&before[piece * 8 + e], in_front[e]);
+        }
+        list_node_places<kChunkThreads>(n_here, job.start_of(c.bucket), all, wave_word, [&](int x, uint32_t place) {
+            const int64_t node = ((int64_t)c.bucket << job.low_bits) + x;
+            if (mine == 0 && node <= job.n_nodes) job.inc_off[node] = (int64_t)place;
+            next[x] = place + before[x];
+        });
+#pragma unroll 1
+        for (uint32_t part = 0; part < c.n; part += kPartPairs) {
+            const Item* items = static_cast<const Item*>(job.items) + c.first + part;
+            const int n = (int)min((uint32_t)kPartPairs, c.n - part), rounds = list_rounds<kChunkThreads>(n);
+            const int base = wave * rounds * kWave + lane;
+            for (int x = tid; x < n_nodes; x += kChunkThreads) words[x] = 0u;
+            __syncthreads();
+            uint32_t word[kPartRounds], place[kPartRounds];
+            list_ranks<Item, kChunkThreads, kPartRounds>(job, items, n, word, words);
+            list_node_places<kChunkThreads>(n_here, 0u, words, wave_word, [&](int x, uint32_t at) { next[x] -= at; });
+            list_turns<kChunkThreads, kPartRounds>(n, word, words, place);
+#pragma unroll
+            for (int r = 0; r < kPartRounds; ++r) {
+                if (r < rounds && base + r * kWave < n) {
+                    const Item x = items[base + r * kWave];
+                    queries[place[r]] = (uint32_t)x & query_mask;
+                    targets[place[r]] = place[r] + next[job.low_of(x)];
+                }
+            }
+            __syncthreads();
+            for (int x = tid; x < n_here; x += kChunkThreads) next[x] += words[x];
+#pragma unroll 4
+            for (int i = tid; i < n; i += kChunkThreads) {
+                const uint32_t to = targets[i];
+                // (inside the output unless the list changes while it is sorted)
+                if (to < (uint32_t)job.n) job.inc_q[to] = (int32_t)queries[i];
+            }
+            __syncthreads();
         }
     }
 }
@@ -883,11 +935,22 @@ int bits_of(uint64_t most) {
 // Pairs of a bucket on average, at most: of more, not all buckets of a list that names all nodes alike
 // would fit LDS.  In us, by buckets / 8 bits a pass: 3.1 M pairs on 2.9M nodes (4,443 a bucket) 52 / 108, on
 // 600,000 50 / 106, 8.4 M on 2.9M (11,848) 387 / 205; 2.1 M on 10M nodes (8 bits only) 100, on 8M 80 / 100.
-// Lists that crowd, 2.1 M pairs on 2.9M nodes: half of them with one node 131 / 127, 1,048 nodes named
-// 1,000 times 97 / 97, ids by descending degree 106 / 133, 3,000 neighbouring nodes 146 / 138.
+// (Lists that crowd, by buckets / 8 bits a pass: above.  Only where hardly another node is named, on graphs whose
+// buckets have 8,192 nodes, or in short lists on small ones, do they take longer by buckets: 2.1 M pairs on 8M
+// nodes, all with one node 159 / 127, half of them 133 / 136; 100,000 on 30,000 nodes, all with one 37 / 32, half 34 / 40;
+// 2 M on 3,000 neighbours of 30,000 nodes 73 / 66.)
 constexpr int64_t kBucketMean = 5500;
-static_assert(kBuckets * kBucketMean / kListPairs / kListChunks * kListPairs + kListPairs < 1 << 16,
-              "16 bits count a chunk's pairs");
+
+// Pairs of a chunk: where all pairs crowd in a few buckets there is a chunk a compute unit, or not quite (a
+// bucket's last one is not full), and no fewer pairs than nodes that they are counted by (524,288 pairs with one
+// of 2.9M nodes: 67 us with 4,096, 73 with 3,072); more than LDS takes at a time in whole parts (3.8 M pairs with
+// one of 2.9M nodes 145 us, in chunks of a part 221).
+uint32_t list_chunk_pairs(int64_t n, int low_bits) {
+    const int64_t whole = n > (int64_t)kListChunks * 7 / 8 * kPartPairs ? kPartPairs : kChunkThreads;
+    const int64_t pairs = (n / (kListChunks * 7 / 8) + whole) / whole * whole;
+    return (uint32_t)(pairs < list_nodes(low_bits) ? list_nodes(low_bits) : pairs);
+}
+static_assert(kBuckets * kBucketMean / (kListChunks * 7 / 8) + kPartPairs < 1 << 16, "16 bits count a chunk's pairs");
 
 // How a query list is sorted, and where its arrays lie in the scratch memory.
 struct SortPlan {
@@ -914,7 +977,7 @@ SortPlan sort_plan(int64_t n, int32_t k, int32_t n_nodes) {
     };
     if (p.buckets) {
         p.query_bits = bits_of((uint64_t)((n - 1) / k));
-        p.chunk_pairs = (uint32_t)((n / kListPairs / kListChunks + 1) * kListPairs);
+        p.chunk_pairs = list_chunk_pairs(n, p.low_bits);
         p.any_large = part(sizeof(uint32_t));
         p.item_at = part((size_t)n * (p.low_bits + p.query_bits <= 32 ? 4 : 8));
         // a large bucket has more than kListPairs pairs, and one chunk at most that is not full
@@ -956,11 +1019,16 @@ hipError_t launch_lists(hipStream_t stream, const ListJob& job) {
     hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(incidence_lists_kernel<Item>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (rc != hipSuccess) return rc;
-    const int chunk_groups = job.n > kListPairs ? kListChunks : 0;
-    if (chunk_groups > 0)
-        list_chunk_counts_kernel<Item><<<dim3(chunk_groups), dim3(kListThreads), 0, stream>>>(job);
-    incidence_lists_kernel<Item><<<dim3((unsigned)(job.n_buckets + chunk_groups)), dim3(kListThreads),
+    // no bucket of a shorter list is a large one
+    const bool chunks = job.n > kListPairs;
+    incidence_lists_kernel<Item><<<dim3((unsigned)(job.n_buckets + (chunks ? kListChunks : 0))), dim3(kListThreads),
                                    lds_bytes, stream>>>(job);
+    if (!chunks) return hipGetLastError();
+    const size_t chunk_bytes = chunk_lds_bytes(job.low_bits);
+    rc = hipFuncSetAttribute(reinterpret_cast<const void*>(incidence_chunks_kernel<Item>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)chunk_bytes);
+    if (rc != hipSuccess) return rc;
+    incidence_chunks_kernel<Item><<<dim3(kListChunks), dim3(kChunkThreads), chunk_bytes, stream>>>(job);
     return hipGetLastError();
 }
 

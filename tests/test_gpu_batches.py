@@ -98,6 +98,29 @@ def test_query_incidence_by_buckets(ctx, n_nodes, n_queries, k, shape):
     assert np.array_equal(inc_q.cpu().numpy(), want_q)
 
 
+@pytest.mark.parametrize("n_nodes,n_queries,k,named", [
+    (2_900_000, 1_200_001, 2, 3000), (2_900_000, 1_200_001, 2, 1), (8_000_000, 400_000, 3, 9000),
+    (60_000, 1_048_576, 2, 3000), (300, 150_001, 2, 2), (2_900_000, 1_048_576, 2, -1048),
+    (8_000_000, 600_000, 2, -500), (2_900_000, 5100, 2, 1), (2_900_000, 5121, 2, 1), (2_900_000, 20_000, 1, 40)])
+def test_query_incidence_of_crowded_lists(ctx, n_nodes, n_queries, k, named):
+    # all but a few queries name some neighbours, or (below zero) so many nodes anywhere: chunks of one part
+    # and of two, full and not, more of them than workgroups, several buckets that are cut, chunks that start
+    # inside a node's pairs, and buckets in which nodes have more pairs than a byte counts
+    rng = np.random.default_rng(n_nodes + n_queries)
+    if named < 0:
+        nodes = rng.choice(n_nodes, size=-named, replace=False)
+    else:
+        nodes = n_nodes // 3 + np.arange(named)
+    queries = nodes[rng.integers(0, nodes.size, size=(n_queries, k))].astype(np.int32)
+    queries[::1013, 0] = rng.integers(0, n_nodes, size=queries[::1013, 0].shape)
+    for _ in range(2):
+        inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
+    assert ctx.check() == 0
+    want_off, want_q = numpy_incidence(queries, n_nodes)
+    assert np.array_equal(inc_off.cpu().numpy(), want_off)
+    assert np.array_equal(inc_q.cpu().numpy(), want_q)
+
+
 def test_query_incidence_of_an_empty_list_and_bad_ids(ctx):
     empty = torch.empty((0, 2), dtype=torch.int32, device="cuda")
     inc_off, inc_q = binding.query_incidence(ctx, empty, 17)
