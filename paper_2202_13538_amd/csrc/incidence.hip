@@ -14,9 +14,9 @@
 // What bounds it: the memory round trips of the launches one after the other, at these sizes: a million
 // two-node queries on 2.9M nodes 39 us (5 + 6.5 + 12.5 + 14 + 4, of which the last finds that there are no
 // chunks), with three passes of 8 bits and the offsets behind them 85.
-// Graphs of 2^23 nodes and more, whose buckets would have more nodes than LDS has room for, are
-// sorted 8 bits a pass, least significant first, the same three launches a pass, and the offsets by a
-// launch of their own.
+// Graphs of up to 255 nodes, for which one pass of 8 bits does, and graphs of 2^23 nodes and more, whose
+// buckets would have more nodes than LDS has room for, are sorted 8 bits a pass, least significant first, the
+// same three launches a pass, and the offsets by a launch of their own.
 #include "device_util.h"
 #include "kernels.h"
 #include "small_scan.h"
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_places_kernel(const uint32_
     uint32_t* to = places + (int64_t)blockIdx.x * kWave + lane;
     uint32_t tag = 0;
     if (wave == 0) tag = small_scan_tag(ss);
-    constexpr int kPlaceTiles = 16;
+    constexpr int kPlaceTiles = kBins == kBuckets ? 16 : 8;
     uint32_t first[kPlaceTiles], sum = 0;  // the wave's first tiles stay in registers
 #pragma unroll
     for (int u = 0; u < kPlaceTiles; ++u) first[u] = t0 + u < t1 ? column[(t0 + u) * kBins] : 0u;
@@ -969,7 +969,8 @@ SortPlan sort_plan(int64_t n, int32_t k, int32_t n_nodes) {
     const int key_bits = bits_of((uint64_t)n_nodes);  // keys are 0..n_nodes
     p.low_bits = key_bits > kBucketBits ? key_bits - kBucketBits : 0;
     const int64_t n_buckets = (n_nodes >> p.low_bits) + 1;
-    p.buckets = key_bits <= kBucketBits + kListBits && n <= n_buckets * kBucketMean;
+    // (one pass of 8 bits: 64 pairs on 16 nodes 13 us, by buckets 17; 500,000 on 100 nodes 22 and 36)
+    p.buckets = key_bits > 8 && key_bits <= kBucketBits + kListBits && n <= n_buckets * kBucketMean;
     auto part = [&](size_t bytes) {
         const size_t at = p.bytes;
         p.bytes += padded(bytes);
