@@ -10,16 +10,6 @@ namespace surel {
 
 constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;  // no node id reaches 2^28
 
-// Slots for a set of at most n_max ids: a power of two, at least twice n_max, or a third more than
-// n_max where twice were more than 8 KB and left a compute unit four waves of the walk (131,000 seeds
-// of M = 150, m = 9: 4.2 -> 2.8 ms).  Any multiple of 64 above n_max from
-// kDistinctSlotsLeast to kDistinctSlotsMost does.
-__host__ __device__ constexpr int distinct_slots(int n_max) {
-    int s = 128;
-    while (s < 2048 ? s < 2 * n_max : 3 * s < 4 * n_max) s *= 2;
-    return s;
-}
-
 __device__ __forceinline__ void distinct_clear(uint32_t* table, int slots, int lane) {
     for (int t = lane; t < slots; t += kWave) table[t] = kEmptySlot;
 }

@@ -1510,7 +1510,7 @@ def test_edge_records_of_walks_that_count_their_sets(ctx, n_nodes, M):
                                                     (50, 4, 30_000, 3), (61, 9, 9000, 70_000),
                                                     (150, 4, 9400, 70_000), (200, 9, 3000, 70_000),
                                                     (200, 9, 3000, 330_000), (128, 15, 2400, 70_000),
-                                                    (292, 6, 3000, 70_000),
+                                                    (292, 6, 3000, 70_000), (500, 3, 3000, 70_000),
                                                     (682, 2, 6200, 70_000), (1024, 1, 3000, 70_000)])
 def test_set_sizes_of_tables_that_fill_lds(ctx, M, m, n_seeds, n_nodes):
     # hash tables of any multiple of 64 slots, the smallest, the largest and the fullest among them (and of
