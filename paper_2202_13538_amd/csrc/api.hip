@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "walk_table.h"
 
 struct surel_ctx {
     int device = 0;
@@ -189,10 +190,10 @@ int read_total(surel_ctx* ctx, const int64_t* d_off, int64_t n, int64_t* h_rows)
 // error: the walk then reads the CSR directly).
 int make_edge_records(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col_idx,
                       int32_t n_nodes, int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m,
-                      surel::EdgeRecords* records) {
+                      bool few_waves, bool fused, surel::EdgeRecords* records) {
     *records = surel::EdgeRecords{};
     if (!surel::walks_want_records(n_edges, n_seeds, M, m)) return SUREL_OK;
-    surel::EdgeRecords plan = surel::edge_record_plan(n_nodes, n_edges);
+    surel::EdgeRecords plan = surel::edge_record_plan(n_nodes, n_edges, few_waves, fused);
     const size_t need = surel::edge_record_bytes(plan, n_nodes, n_edges);
     (void)grow_buffer(ctx, &ctx->d_rec, &ctx->rec_bytes, need);
     if (ctx->rec_bytes < need) return SUREL_OK;
@@ -313,7 +314,7 @@ int surel_sample_walks(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t* 
     if (!guard.ok) return SUREL_E_HIP;
     surel::EdgeRecords records;
     if (int rc = make_edge_records(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, n_seeds, M, m,
-                                   &records))
+                                   d_set_sizes != nullptr && surel::walk_waves_are_few(M, m), false, &records))
         return rc;
     KernelSpan span(ctx, SUREL_K_WALK);
     hipError_t rc = surel::launch_walks(ctx->stream, d_row_ptr, d_col_idx, n_nodes, n_edges,
@@ -476,7 +477,7 @@ static int fused_launch(surel_ctx* ctx, const int32_t* d_row_ptr, const int32_t*
     }
     surel::EdgeRecords records;
     if (int rc = make_edge_records(ctx, d_row_ptr, d_col_idx, n_nodes, n_edges, n_seeds, M, m,
-                                   &records))
+                                   false, true, &records))
         return rc;
     const size_t lb_need = (size_t)surel::lookback_words(n_seeds) * sizeof(uint64_t);
     if (int rc = grow_buffer(ctx, &ctx->d_lb, &ctx->lb_bytes, lb_need)) return rc;

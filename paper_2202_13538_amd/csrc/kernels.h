@@ -29,7 +29,7 @@ struct EdgeRecords {
     int id_bits = 0, lo_bits = 0;  // field widths of the packed layout; of the short one id_bits
 };
 bool walks_want_records(int64_t n_edges, int64_t n_seeds, int32_t M, int32_t m);
-EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges);
+EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves, bool fused);
 size_t edge_record_bytes(const EdgeRecords& plan, int32_t n_nodes, int64_t n_edges);
 hipError_t launch_edge_records(hipStream_t stream, const int32_t* row_ptr, const int32_t* col_idx,
                                int32_t n_nodes, int64_t n_edges, const EdgeRecords& rec);

@@ -252,21 +252,24 @@ static int bits_for(uint64_t max_value) {  // bits that hold 0 .. max_value
 // Walks alone, counting their sets: 320,000 nodes, 3 M, M = 150 1,540 / 1,147, 5 M, M = 150, m = 9 5,539 /
 // 5,377, 14 M 6,600 / 6,632; 390,000, 8 M, M = 150 2,408 / 2,496.
 // (Entries are addressed with 24 bits.)
-constexpr int32_t kShortNodes = 5 << 16;
-static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges) {
-    return n_nodes <= kShortNodes && n_edges >= 1 << 20 && n_edges < 1 << 24;
+// few_waves (walk_waves_are_few), M = 292, m = 6: 140,000 nodes, 1.4 M 2,371 / 2,166, 200,000, 8 M 4,659 / 4,390,
+// 235,000, 2.6 M 4,151 / 4,428, 327,680, 3.2 M 5,686 / 6,271.  fused, past 2^18 nodes: 300,000, 10 M, M = 100,
+// m = 3 1,054 / 987, M = 64, m = 9 3,201 / 3,227; 327,680, 14 M 1,242 / 1,203 and 3,600 / 3,749, M = 150, m = 5
+// 3,775 / 3,854.
+constexpr int32_t kShortNodes = 5 << 16, kShortNodesFewWaves = 200'000;
+static bool rows_beside_short_records(int32_t n_nodes, int64_t n_edges, bool few_waves, bool fused) {
+    return n_nodes <= (few_waves ? kShortNodesFewWaves : kShortNodes) && n_edges >= 1 << 20 &&
+           n_edges < (fused && n_nodes > 1 << 18 ? 12'000'000 : 1 << 24);
 }
 
-EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges) {
+EdgeRecords edge_record_plan(int32_t n_nodes, int64_t n_edges, bool few_waves, bool fused) {
     EdgeRecords plan;
     plan.id_bits = bits_for((uint64_t)n_nodes);   // n_nodes itself marks a bad entry
     plan.lo_bits = bits_for((uint64_t)n_edges);   // 31 at most
     // packed records where ordinary degrees fit their field, the wide layout otherwise.  (On
     // small graphs the packed array fits more of its lines into the L2s.)
     plan.format = rec_degree_bits(plan.id_bits, plan.lo_bits) >= 12 ? kRecPacked : kRecWide;
-    if (rows_beside_short_records(n_nodes, n_edges)) {
-        plan.format = kRecShort;
-    }
+    if (rows_beside_short_records(n_nodes, n_edges, few_waves, fused)) plan.format = kRecShort;
     // the degree lies in the word's upper half
     if (plan.format == kRecPacked && plan.id_bits + plan.lo_bits < 32) plan.lo_bits = 32 - plan.id_bits;
     return plan;

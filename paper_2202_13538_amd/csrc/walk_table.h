@@ -53,4 +53,12 @@ inline WalkTable walk_table(int32_t M, int32_t m) {
     return t;
 }
 
+// Whether walks that count their sets have so few waves that the second trip of a step from short records shows,
+// and no better a table with them than without.
+inline bool walk_waves_are_few(int32_t M, int32_t m) {
+    const WalkTable t = walk_table(M, m);
+    return t.groups <= 2 && distinct_slots(1 + M * m) >= t.slots &&
+           (kWalkChains * 64 * (m + 1) + distinct_slots(1 + M * m)) * kWalkWavesPerBlock * 4 * t.groups <= 160 * 1024;
+}
+
 }  // namespace surel

@@ -1530,6 +1530,32 @@ def test_set_sizes_of_tables_that_fill_lds(ctx, M, m, n_seeds, n_nodes):
     assert np.array_equal(w[:n].cpu().numpy(), oracle.sample_walks(rp, ci, seeds[:n], M, m, 3))
 
 
+@pytest.mark.parametrize("n_nodes, n_edges, M, m, n_seeds", [
+    (5 << 16, 1 << 20, 150, 4, 9400), ((5 << 16) + 1, 1 << 20, 150, 4, 9400),
+    (200_000, 1 << 20, 292, 6, 3000), (200_001, 1 << 20, 292, 6, 3000),
+    (1 << 18, 12_000_000, 60, 5, 201_000), ((1 << 18) + 1, 11_999_999, 60, 5, 201_000),
+    ((1 << 18) + 1, 12_000_000, 60, 5, 201_000)])
+def test_edge_records_at_the_lines_between_their_forms(ctx, n_nodes, n_edges, M, m, n_seeds):
+    # ids alone up to 5 * 2^16 nodes; up to 200,000 where sets of so many nodes are counted that few waves have
+    # room; past 2^18 in walks + RPE only for fewer than 12,000,000 entries: the same walks in all of them
+    assert n_seeds * M * (m - 1) >= 4 * n_edges  # enough steps to make the records
+    rng = np.random.default_rng(n_nodes + n_edges)
+    cuts = np.sort(rng.integers(0, n_edges + 1, size=n_nodes - 1))
+    rp = np.concatenate([[0], cuts, [n_edges]]).astype(np.int32)
+    ci = rng.integers(0, n_nodes, size=n_edges).astype(np.int32)
+    seeds = rng.integers(0, n_nodes, size=n_seeds).astype(np.int32)
+    d_rp, d_ci, d_seeds = dev(rp), dev(ci), dev(seeds)
+    sizes = torch.empty(n_seeds, dtype=torch.int32, device="cuda")
+    w = binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 3, set_sizes=sizes)
+    assert torch.equal(w, binding.sample_walks(ctx, d_rp, d_ci, d_seeds, M, m, 3))
+    walks, off, _, _ = binding.sample_walks_rpe(ctx, d_rp, d_ci, d_seeds, M, m, 3)
+    assert ctx.check() == 0
+    assert torch.equal(w, walks) and torch.equal(off[1:] - off[:-1], sizes.long())
+    nodes = w.view(n_seeds, -1).sort(dim=1).values
+    assert torch.equal(1 + (nodes[:, 1:] != nodes[:, :-1]).sum(dim=1).int(), sizes)
+    assert np.array_equal(w[:200].cpu().numpy(), oracle.sample_walks(rp, ci, seeds[:200], M, m, 3))
+
+
 @pytest.mark.parametrize("n_nodes, malformed", [((1 << 18) - 1, False), (1 << 18, False),
                                            ((1 << 18) + 11, False), (1 << 18, True),
                                            ((5 << 18) - 1, False), (5 << 18, False),
