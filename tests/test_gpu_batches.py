@@ -59,14 +59,50 @@ def test_query_incidence_equals_a_stable_sort(ctx, n_nodes, n_queries, k):
 @pytest.mark.parametrize("n_nodes", [1023, 1024, 524_287, 524_288, 1_048_575, 4_194_303, 4_300_000])
 @pytest.mark.parametrize("spread", [1.0, 0.002, 0.0])
 def test_query_incidence_offsets_around_group_sizes(ctx, n_nodes, spread):
-    # offsets are laid out 1,024 to 8,192 nodes at a time; lists spread over all nodes, over a few
-    # groups (more keys than a group looks at in LDS) and two nodes that hold nearly all of it
+    # 200,000 pairs, which go to buckets of 1 to 8,192 nodes: lists spread over all nodes, over a few
+    # buckets and two nodes that hold nearly all of it
     rng = np.random.default_rng(n_nodes)
     n_queries = 100_000
     width = max(int(n_nodes * spread), 2)
     start = rng.integers(0, n_nodes - width + 1)
     queries = rng.integers(start, start + width, size=(n_queries, 2)).astype(np.int32)
     queries[0], queries[-1] = (0, n_nodes - 1), (n_nodes - 1, 0)
+    inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
+    assert ctx.check() == 0
+    want_off, want_q = numpy_incidence(queries, n_nodes)
+    assert np.array_equal(inc_off.cpu().numpy(), want_off)
+    assert np.array_equal(inc_q.cpu().numpy(), want_q)
+
+
+def pairs_by_buckets(n_nodes):
+    """The most pairs that go to buckets of nodes (5,500 a bucket); longer lists are sorted 8 bits a pass."""
+    low_bits = max(int(n_nodes).bit_length() - 10, 0)
+    return ((n_nodes >> low_bits) + 1) * 5500
+
+
+@pytest.mark.parametrize("n_nodes", [525_000, 1_048_600, 1_600_000, 2_097_200, 2_700_000, 3_200_000, 4_000_000])
+@pytest.mark.parametrize("spread", [1.0, 0.02, 0.0])
+def test_query_incidence_offsets_of_lists_sorted_8_bits_a_pass(ctx, n_nodes, spread):
+    # offsets are laid out 2,048 to 8,192 nodes at a time, behind the sort; lists spread over all nodes, over a
+    # few groups (more keys than a group looks at in LDS) and two nodes that hold nearly all of it
+    rng = np.random.default_rng(n_nodes)
+    n_queries = pairs_by_buckets(n_nodes) + 1
+    width = max(int(n_nodes * spread), 2)
+    start = rng.integers(0, n_nodes - width + 1)
+    queries = rng.integers(start, start + width, size=(n_queries, 1)).astype(np.int32)
+    queries[0], queries[-1] = 0, n_nodes - 1
+    inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
+    assert ctx.check() == 0
+    want_off, want_q = numpy_incidence(queries, n_nodes)
+    assert np.array_equal(inc_off.cpu().numpy(), want_off)
+    assert np.array_equal(inc_q.cpu().numpy(), want_q)
+
+
+@pytest.mark.parametrize("n_nodes", [255, 256, 3000, 600_000])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_query_incidence_at_the_line_between_the_sorts(ctx, n_nodes, more):
+    rng = np.random.default_rng(n_nodes)
+    queries = rng.integers(0, n_nodes, size=(pairs_by_buckets(n_nodes) + more, 1)).astype(np.int32)
     inc_off, inc_q = binding.query_incidence(ctx, dev(queries), n_nodes)
     assert ctx.check() == 0
     want_off, want_q = numpy_incidence(queries, n_nodes)

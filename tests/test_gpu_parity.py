@@ -657,11 +657,12 @@ def test_sorts_of_odd_numbers_of_keys_a_lane(ctx, M, m):
 
 
 @pytest.mark.parametrize("L", [2, 3, 4, 5, 6])
-@pytest.mark.parametrize("n_T", [32_766, 32_767, 32_768, 42_000])
+@pytest.mark.parametrize("n_T", [32_766, 32_767, 32_768, 42_000, 50_001, 70_711])
 def test_prune_numbers_of_16_bits(ctx, L, n_T):
     # on both sides of the number of vectors whose numbers fit 16 bits; most rows have common vectors and
     # every tile some rare ones, so that rows whose numbers do not fit lie in tiles that went out in 16 bits,
-    # in ones that did not, and behind the last whole tile; ranked all with all and (the last) by the sort
+    # in ones that did not, and behind the last whole tile; ranked all with all and by the sort (from 70,711
+    # vectors of two counts, 50,001 of three or four and 40,825 of five or six)
     n_rows = 6_000_000 + 77
     g = torch.Generator(device="cuda").manual_seed(n_T + L)
     number = torch.randperm(n_T, device="cuda", generator=g)
