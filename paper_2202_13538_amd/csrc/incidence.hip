@@ -12,8 +12,8 @@
 // pairs than LDS holds (queries crowd on neighbouring nodes) are cut into chunks; the same launch counts
 // each chunk's nodes, and another one puts the chunks in order.
 // What bounds it: the memory round trips of the launches one after the other, at these sizes: a million
-// two-node queries on 2.9M nodes 39 us (5 + 6.5 + 12.5 + 14 + 4, of which the last finds that there are no
-// chunks), with three passes of 8 bits and the offsets behind them 85.
+// two-node queries on 2.9M nodes 39 us (4.7 + 5.9 + 12.6 + 15 + 3.8 in a trace, of which the last finds that there
+// are no chunks), with three passes of 8 bits and the offsets behind them 85.
 // Graphs of up to 255 nodes, for which one pass of 8 bits does, and graphs of 2^23 nodes and more, whose
 // buckets would have more nodes than LDS has room for, are sorted 8 bits a pass, least significant first, the
 // same three launches a pass, and the offsets by a launch of their own.
@@ -599,7 +599,8 @@ __device__ __forceinline__ void list_ranks(const ListJob& job, const Item* __res
             if (r0 + u < rounds && base + (r0 + u) * kWave < n) {
                 const uint32_t rank = (uint32_t)__popcll(same[u] & below), all = (uint32_t)__popcll(same[u]);
                 const uint32_t leader = (uint32_t)__ffsll((unsigned long long)same[u]) - 1u;
-                word[r0 + u] = (rank == 0u ? low[u] | all << kAddAt : (uint32_t)lane & 15u) | rank << kRankAt | leader << kLeaderAt;
+                const uint32_t adds = rank == 0u ? low[u] | all << kAddAt : (uint32_t)lane & 15u;
+                word[r0 + u] = adds | rank << kRankAt | leader << kLeaderAt;
                 if (totals != nullptr && rank == 0u) atomicAdd(&totals[low[u]], all);
             }
         }
@@ -634,7 +635,8 @@ __device__ __forceinline__ void list_turns(int n, const uint32_t (&word)[kRounds
     }
 #pragma unroll
     for (int r = 0; r < kRounds; ++r)
-        place[r] = (uint32_t)__shfl((int)place[r], (int)(word[r] >> kLeaderAt & 63u), kWave) + (word[r] >> kRankAt & 63u);
+        place[r] = (word[r] >> kRankAt & 63u) +
+                   (uint32_t)__shfl((int)place[r], (int)(word[r] >> kLeaderAt & 63u), kWave);
 }
 
 // words[x], pairs of node x, becomes the place of its first one, `first` being that of the bucket's.
@@ -856,7 +858,8 @@ __global__ __launch_bounds__(kChunkThreads) void incidence_chunks_kernel(ListJob
         const int pieces = n_nodes / 8, mine = c.at - c.bucket_chunk;
         const int groups = min(kChunkThreads / pieces, (c.n_bucket_chunks + kListFlight - 1) / kListFlight);
         const int group = tid / pieces, piece = tid & (pieces - 1);
-        const uint4* counts = reinterpret_cast<const uint4*>(job.chunk_counts) + (int64_t)c.bucket_chunk * pieces + piece;
+        const uint4* counts =
+            reinterpret_cast<const uint4*>(job.chunk_counts) + (int64_t)c.bucket_chunk * pieces + piece;
         uint32_t sum[8] = {}, in_front[8] = {};
 #pragma unroll 1
         for (int k0 = group < groups ? group : c.n_bucket_chunks; k0 < c.n_bucket_chunks; k0 += groups * kListFlight) {
@@ -937,8 +940,8 @@ int bits_of(uint64_t most) {
 // 600,000 50 / 106, 8.4 M on 2.9M (11,848) 387 / 205; 2.1 M on 10M nodes (8 bits only) 100, on 8M 80 / 100.
 // (Lists that crowd, by buckets / 8 bits a pass: above.  Only where hardly another node is named, on graphs whose
 // buckets have 8,192 nodes, or in short lists on small ones, do they take longer by buckets: 2.1 M pairs on 8M
-// nodes, all with one node 159 / 127, half of them 133 / 136; 100,000 on 30,000 nodes, all with one 37 / 32, half 34 / 40;
-// 2 M on 3,000 neighbours of 30,000 nodes 73 / 66.)
+// nodes, all with one node 159 / 127, half of them 133 / 136; 100,000 on 30,000 nodes, all with one 37 / 32, half
+// 34 / 40; 2 M on 3,000 neighbours of 30,000 nodes 73 / 66.)
 constexpr int64_t kBucketMean = 5500;
 
 // Pairs of a chunk: where all pairs crowd in a few buckets there is a chunk a compute unit, or not quite (a

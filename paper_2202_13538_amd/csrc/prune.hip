@@ -238,7 +238,7 @@ __device__ __forceinline__ void tile_numbers(uint32_t* tile, int lane, uint32_t 
 // of 1M seeds with some 1,500 vectors 344 us = 5.1 TB/s.  The counts go past the caches and the numbers do not
 // (both past them 378 us, counts through them 386; the renumbering then finds more of the numbers: 146 us, 166
 // where they went past; 60 M rows pruned in 578 us, 586 where they went past, 700 M 6.09 ms and 6.07).  Two
-// tiles ahead: 401 us where one took 387.  The tile's loads and the numbers' stores are in one straight
+// tiles ahead: 355 us where one took 343.  The tile's loads and the numbers' stores are in one straight
 // line, so that a wait for the next tile is not one for the numbers.
 template <int LT>
 __global__ __launch_bounds__(Collect<LT>::kWaves* kWave) void prune_collect_kernel(

@@ -154,7 +154,7 @@ constexpr int kDirectWords = 4096;
 // kLonely: see find_or_insert_shared.  Pruning 4 M rows of a table of 4,096 vectors that occur equally
 // often took 0.56 ms at m = 14 and 0.32 at m = 4 with a turn for every vector of a wave, 0.18 and 0.13
 // with 4 lonely ones (of 1,024 vectors 0.43 and 0.22 against 0.17 and 0.12); a walk's own table, 146 M
-// rows with some 1,500 vectors, takes 0.69 ms with both.  The fused kernel has its waves at different
+// rows with some 1,500 vectors, took the same with both.  The fused kernel has its waves at different
 // places and little to gain: 99,991 seeds of M = 61, m = 9 take 0.93 ms with a
 // turn for every vector, 0.94 with 4 lonely ones (1.27 when every new vector wrote an L2 back).
 struct FusedTables {

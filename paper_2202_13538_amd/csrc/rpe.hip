@@ -8,9 +8,9 @@
 // walk entry becomes a 32-bit key (node id << 4 | position); the wave sorts its keys in
 // registers, id changes give the rows and the keys of a row are counted by position.  Rows are
 // assembled in LDS and streamed out contiguously at the seed's offset.
-// What bounds the fill: vector instructions, 0.85 of every SIMD's time with 500,009 tables of M = 50, m = 4
+// What bounds the fill: vector instructions, 0.88 of every SIMD's time with 500,009 tables of M = 50, m = 4
 // (410 a table, 226 of them the sort): 390 to 395 us for 1.63 GB moved, 281 at the rate of a copy, and the
-// same with one, two or four seeds a workgroup; 235,000 of M = 200 987 with 16 keys a lane, 0.70 of the time.
+// same with one, two or four seeds a workgroup; 235,000 of M = 200 995 with 16 keys a lane, 0.69 of the time.
 #include "device_util.h"
 #include "distinct.h"
 #include "rpe_rows.h"

@@ -30,9 +30,9 @@ namespace surel {
 // lies in LDS (Algorithm 1's last step, pruning, done on the fly as well), and its number there
 // goes to code; cnt may then be null.
 // Registers: with fewer than 16 waves on a compute unit the gathers wait longer, so E > 8 with kCodes
-// spills: 6 of 126 vector registers at E = 10, 14 at 12, 30 to 64 at 16 (the plain forms none, 2 in one of
-// E = 16).  Scalar ones go to lanes of a vector register, 48 to 63 in the plain forms and 166 to 182 with
-// kCodes, whose look-up is there for five lengths of vector.
+// spills: 6 of 126 vector registers at E = 9 and 10, 14 of 128 at 12, 17 at 13, 22 at 14, 32 at 16 (the plain
+// forms none, 2 in one of E = 16).  Scalar ones go to lanes of a vector register, 48 to 69 in the plain forms and
+// 166 to 189 with kCodes, whose look-up is there for five lengths of vector.
 template <int E, int kRec, bool kCodes>
 __global__ __launch_bounds__(E <= 16 ? 1024 : 512) void walk_rpe_kernel(FusedJob f,
                                                                         uint64_t* __restrict__ lb,
