@@ -373,8 +373,8 @@ int surel_prune_rpe(surel_ctx* ctx, const uint16_t* d_rpe_cnt, int64_t n_rows, i
  *                twice in x's part.
  * The context's workspace grows to 5 or 9 bytes per entry of d_queries (8 or 12 for up to 2^19 of
  * them), with at most 18 MB beside them for lists that crowd on neighbouring nodes; on graphs of up to
- * 255 nodes or of 2^23 and more, and for lists of some millions of entries (5,500 for each of the 1,024 parts or fewer
- * that the nodes are cut into), to 20.25 (21).
+ * 255 nodes or of 2^23 and more, and for lists of some millions of entries (5,500 for each of the 1,024
+ * parts or fewer that the nodes are cut into), to 20.25 (21).
  * Asynchronous.  Device-detected: BAD_QUERY (an id outside [0, n_nodes); that entry is left out
  * of every part, d_inc_off[n_nodes] is the number of entries kept). */
 int surel_query_incidence(surel_ctx* ctx, const int32_t* d_queries, int64_t n_queries, int32_t k,

@@ -157,6 +157,37 @@ def test_query_incidence_of_crowded_lists(ctx, n_nodes, n_queries, k, named):
     assert np.array_equal(inc_q.cpu().numpy(), want_q)
 
 
+@pytest.mark.parametrize("n_nodes", [200, 300_000])
+def test_query_incidence_captured_in_a_graph(n_nodes):
+    # a captured call sorts whatever list is in its buffer at a replay: spread over all nodes, crowded on a
+    # few (buckets that are cut into chunks, which the replay before had none of, or some of), and spread again
+    rng = np.random.default_rng(n_nodes)
+    spread = rng.integers(0, n_nodes, size=(100_000, 2)).astype(np.int32)
+    crowded = np.where(rng.random((100_000, 2)) < 0.9, n_nodes // 3 + rng.integers(0, 90, size=(100_000, 2)),
+                       spread).astype(np.int32)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        c = binding.Context(stream=stream)
+        d_q = dev(spread)
+        binding.query_incidence(c, d_q, n_nodes)  # the workspace grows
+        assert c.check() == 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+            inc_off, inc_q = binding.query_incidence(c, d_q, n_nodes)
+        for queries in (spread, crowded, spread, crowded[::-1], spread):
+            d_q.copy_(dev(queries))
+            inc_off.fill_(-7)
+            inc_q.fill_(-7)
+            stream.synchronize()
+            graph.replay()
+            stream.synchronize()
+            assert c.check() == 0
+            want_off, want_q = numpy_incidence(queries, n_nodes)
+            assert np.array_equal(inc_off.cpu().numpy(), want_off)
+            assert np.array_equal(inc_q.cpu().numpy(), want_q)
+        c.close()
+
+
 def test_query_incidence_of_an_empty_list_and_bad_ids(ctx):
     empty = torch.empty((0, 2), dtype=torch.int32, device="cuda")
     inc_off, inc_q = binding.query_incidence(ctx, empty, 17)
